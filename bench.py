@@ -257,8 +257,9 @@ def read_profile(L, _lib) -> list:
 
 
 def dominant_sweeps(recs) -> tuple:
-    """(pairs, ms, launches) of the lagged-shift sweeps without offsets."""
-    sel = [r for r in recs if r[0] == 1 and r[1] == 0]
+    """(pairs, ms, launches) of the lagged-shift sweeps without offsets: direct launches
+    (kind 1), or the cell form's moments and values (kinds 51 and 61)."""
+    sel = [r for r in recs if r[0] in (1, 51, 61) and r[1] == 0]
     return sum(r[2] for r in sel), sum(r[3] for r in sel), len(sel)
 
 

@@ -99,7 +99,8 @@ const char* ct_version(void);
                            grid-wide barrier after each half-iteration (f and p, then g and q),
                            instead of one launch per sweep; meant for small problems (short
                            horizons), whose per-iteration launches are bound by launch latency */
-#define CT_UNFUSED 512u /* one launch per sweep (none of CT_FUSED, CT_TINY, CT_MESH) */
+#define CT_UNFUSED 512u /* one direct launch per sweep over every pair (none of CT_FUSED, CT_TINY,
+                           CT_MESH, and not the cell form) */
 #define CT_TINY 2048u   /* run all K iterations in one workgroup with every point and potential
                            in LDS (no synchronisation beyond the workgroup); CT_E_UNSUPPORTED
                            when the problem does not fit in the LDS of one workgroup (about
@@ -115,7 +116,13 @@ const char* ct_version(void);
                            library picks, by the point pairs of one iteration: the
                            one-workgroup solve up to 4e4, the exchange solve up to 1.5e7 where
                            it plans, else the one-workgroup solve up to 1.5e5, the fused
-                           solve up to 1.05e6, and per-sweep launches beyond. */
+                           solve up to 1.05e6, and per-sweep launches beyond.  Above 1.5e7
+                           pairs, from 8 iterations on, those launches take the cell form of
+                           a sweep where it pays (a grid of cells over each point set, sums
+                           over pairs of cells by truncated expansions that leave out less
+                           than 1e-7 of any pair's term; decided on the device), unless
+                           CT_UNFUSED, CT_DIFFERENCE or CT_SAFE_LSE is given or the
+                           workspace lacks its arrays. */
 #define CT_DIFFERENCE 1024u /* per-sweep launches: evaluate the lagged sweeps' exponent in the
                                difference form h_j - |x'_i - y'_j|^2 - shift (d subtractions, d
                                FMAs, one subtraction per pair).  Default: the expanded form
@@ -133,7 +140,10 @@ typedef struct ct_sinkhorn_opts {
     uint32_t flags; /* CT_* flags above */
 } ct_sinkhorn_opts;
 
-/* Workspace bytes needed by ct_sinkhorn_grad for these sizes and options. */
+/* Workspace bytes needed by ct_sinkhorn_grad for these sizes and options.  From 1.5e7 point
+ * pairs per iteration on, most of it holds the cell form's moments (at most 384 MiB for each
+ * of three buffers: 253 MB in all at T = 4096, M = 16384, 1.4 GB at T = 65536, M = 262144).
+ * A smaller workspace that holds the rest is accepted and gets the direct sweeps. */
 size_t ct_sinkhorn_workspace_size(int64_t T, int64_t M, const ct_sinkhorn_opts* o);
 
 /*

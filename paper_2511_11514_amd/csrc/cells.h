@@ -1,0 +1,117 @@
+// Cell form of the soft-min sweep: shared declarations and device code.
+//
+// A sweep is  out_i = -(1/kappa) log2 sum_j 2^(h_j - |x'_i - y'_j|^2)  over scaled
+// points.  Both point sets are split into the cells of a grid of side w.  With
+// x'_i = A + s (A the centre of the query's cell), y'_j = C + u and d = A - C,
+//     h_j - |x'_i - y'_j|^2 = (h_j - |u|^2 + 2 d.u) + (-|d|^2 - 2 d.s - |s|^2) + 2 s.u,
+// so a pair couples the two points only through 2^(2 s.u), and inside a pair of cells
+// |2 s_t u_t| is bounded.  In natural units, on [-1, 1]^2 per axis, that factor is
+// e^(lambda s u) with lambda = ln2 w^2 / 2, and
+//     e^(lambda s u) = I_0(lambda s) + 2 sum_n I_n(lambda s) T_n(u)
+// (T_n Chebyshev polynomials, I_n modified Bessel functions).  The products over the
+// axes with the largest coefficients, 64 of them in 2-D at lambda = 1 and 192 in 3-D at
+// lambda = 0.46, leave out terms that add up to less than 9e-8 of the factor's largest
+// possible value, whatever the points: the rounding of float32.  A sweep becomes
+//     moments   M[a][c][n] = sum_{j in c} 2^(h_j - |u_j|^2 + 2 d.u_j - mu_ac) T_n(u_j)
+//     values    sum_c 2^(mu_ac - |d|^2 - 2 d.s_i - |s_i|^2 - sh_i) sum_n phi_n(s_i) M[a][c][n]
+// for every pair (a, c) of query and key cell, two matrix products of float32 in the
+// matrix cores (v_mfma_f32_32x32x2), with mu_ac the largest exponent of the cell's keys, so
+// that nothing leaves float32's range however far apart the cells are and however much
+// the potentials vary.  Per point and cell it costs 64 (192) multiply-adds; per point
+// pair the direct sweep costs 5 (6) instructions, one of them an exponential.  Measured on
+// an MI355X, d = 2, T = 65536, M = 262144, eps = 0.002, 200 iterations: 1142 ms with direct
+// sweeps (94 % of their issue roof), 96.5 ms in this form; T = 4096, M = 16384, eps = 0.005,
+// 200 iterations: 15.9 against 10.0 ms.
+#pragma once
+
+#include "ct_internal.h"
+
+namespace ct {
+
+template <int D>
+struct CellDim;
+template <>
+struct CellDim<2> {
+    static constexpr int N = 64;     // products kept
+    static constexpr int F = 9;      // one-dimensional functions n = 0..8
+    static constexpr int bits = 5;   // cells per axis: at most 2^bits
+    static constexpr double lambda = 1.0;
+};
+template <>
+struct CellDim<3> {
+    static constexpr int N = 192;
+    static constexpr int F = 8;
+    static constexpr int bits = 4;
+    static constexpr double lambda = 0.46;
+};
+constexpr int kCellIds = 4096;       // most cell codes of either dimension (1024 in 2-D)
+constexpr int kCellTile = 32;        // queries per evaluation tile, cells per moment tile
+constexpr int kCellChunkMax = 1024;  // most keys of one chunk
+
+// One point set's partition, in the workspace.
+struct CellSide {
+    const float* pts;      // [n][d] caller's points
+    int n;
+    int nb, per;           // blocks of `per` points in the counting sort
+    int kc;                // most keys of a chunk
+    int cmax, chmax, tmax; // room for cells, chunks and tiles
+    unsigned* box;         // [8] ordered-integer minima and maxima, [6] unusable points
+    unsigned short* id;    // [n] cell code
+    unsigned* bh;          // [nb][ids] counts, then offsets within the code
+    unsigned* first;       // [ids] first sorted place of the code
+    int* perm;             // [n] sorted place -> caller's index
+    float4* cen;           // [cmax] cell centres (scaled coordinates)
+    int4* chunk;           // [chmax] (first key, end, cell, 0)
+    float4* chcen;         // [chmax] centre of the chunk's cell
+    int4* tile;            // [tmax] (first query, end, cell, 0)
+    int* cnt;              // [4] cells, chunks, tiles, 1: does not fit
+};
+
+struct CellPrep {
+    CellSide side[2];      // x, y
+    const float* w;        // caller's reference weights or null
+    const float* origin;   // [3] subtracted before scaling
+    int d, ids, bits;
+    int need_ref;          // the y-y problem is swept too
+    float sqrt_kappa;
+    float cell;            // side of a cell, scaled
+    size_t mom_cap[3];     // room for moments: cross, x-x, y-y (floats)
+    int* mode;             // out: 1 the cell form pays and fits, 0 the direct sweeps
+    float *xs, *ys, *ws;   // out: points and weights in cell order
+    const float* pot_in;   // [2T+2M] starting potentials or null
+    float* pot_s;          // out: the same in cell order (when pot_in)
+};
+
+// A soft-min job in the cell form, beside its direct form (Job).
+struct CellJob {
+    const int* ncq;        // query cells (device)
+    const float4* qcen;
+    const int4* tile;      // query tiles
+    const int* ntile;
+    const int* nch;        // key chunks
+    const int4* chunk;
+    const float4* chcen;
+    float* mom;            // [ncq][nch][N]
+    float* mu;             // [ncq][nch]  mu_ac - |d|^2
+};
+
+struct CellLaunch {
+    CellJob job[2];
+    const int* mode;
+    int nblocks;           // work units of the direct sweep
+    int R, WS;             // its schedule
+    float inv_cell;        // 1 / w
+};
+
+// Side of a cell in scaled coordinates: lambda = ln2 w^2 / 2.
+double cell_side(int d);
+// Largest number of keys in a chunk for a set of n points.
+int cell_chunk(int n);
+
+hipError_t launch_cell_prep(const CellPrep& P, hipStream_t s);
+// One sweep of one or two jobs: moments then values, or (*mode == 0) the direct sweep
+// then its merge.
+hipError_t launch_cell_sweep(int d, const Schedule& sc, bool lagged, const Launch& L,
+                             const CellLaunch& C, hipStream_t s);
+
+}  // namespace ct

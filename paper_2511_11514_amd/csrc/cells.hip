@@ -1,0 +1,766 @@
+// Kernels of the cell form of the soft-min sweep (see cells.h): the partition of a
+// point set into cells, the moments of the keys, the values at the queries.
+#include <hip/hip_ext.h>
+
+#include <algorithm>
+#include <cmath>
+
+#include "cells.h"
+#include "sweep_device.h"
+
+namespace ct {
+
+namespace {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// Kept products, by decreasing coefficient: one hexadecimal digit per axis (x lowest), the
+// order of that axis's function.
+__device__ constexpr unsigned short kTerms2[CellDim<2>::N] = {
+    0x00, 0x10, 0x01, 0x11, 0x20, 0x02, 0x21, 0x12, 0x22, 0x30, 0x03, 0x31, 0x13, 0x32, 0x23, 0x40,
+    0x04, 0x41, 0x14, 0x33, 0x42, 0x24, 0x50, 0x05, 0x51, 0x15, 0x43, 0x34, 0x52, 0x25, 0x60, 0x06,
+    0x61, 0x16, 0x44, 0x53, 0x35, 0x62, 0x26, 0x70, 0x07, 0x71, 0x17, 0x54, 0x45, 0x63, 0x36, 0x72,
+    0x27, 0x55, 0x80, 0x08, 0x64, 0x46, 0x81, 0x18, 0x73, 0x37, 0x82, 0x28, 0x65, 0x56, 0x74, 0x47,
+};
+__device__ constexpr unsigned short kTerms3[CellDim<3>::N] = {
+    0x000, 0x010, 0x001, 0x100, 0x110, 0x101, 0x011, 0x111, 0x020, 0x002, 0x200, 0x210,
+    0x120, 0x201, 0x021, 0x102, 0x012, 0x211, 0x121, 0x112, 0x300, 0x030, 0x003, 0x022,
+    0x220, 0x202, 0x310, 0x130, 0x301, 0x031, 0x103, 0x013, 0x221, 0x212, 0x122, 0x311,
+    0x131, 0x113, 0x400, 0x040, 0x004, 0x320, 0x230, 0x302, 0x032, 0x203, 0x023, 0x222,
+    0x410, 0x401, 0x140, 0x041, 0x104, 0x014, 0x321, 0x231, 0x312, 0x132, 0x213, 0x123,
+    0x411, 0x141, 0x114, 0x033, 0x330, 0x303, 0x420, 0x402, 0x042, 0x024, 0x240, 0x204,
+    0x050, 0x005, 0x500, 0x322, 0x232, 0x223, 0x133, 0x331, 0x313, 0x421, 0x412, 0x142,
+    0x124, 0x241, 0x214, 0x051, 0x015, 0x510, 0x150, 0x501, 0x105, 0x511, 0x151, 0x115,
+    0x430, 0x340, 0x403, 0x043, 0x304, 0x034, 0x233, 0x332, 0x323, 0x422, 0x242, 0x224,
+    0x520, 0x502, 0x052, 0x025, 0x250, 0x205, 0x060, 0x006, 0x600, 0x431, 0x341, 0x413,
+    0x143, 0x314, 0x134, 0x521, 0x251, 0x512, 0x152, 0x215, 0x125, 0x160, 0x106, 0x610,
+    0x601, 0x061, 0x016, 0x611, 0x161, 0x116, 0x333, 0x440, 0x404, 0x044, 0x432, 0x342,
+    0x423, 0x243, 0x324, 0x234, 0x530, 0x350, 0x503, 0x053, 0x305, 0x035, 0x522, 0x252,
+    0x225, 0x441, 0x414, 0x144, 0x620, 0x260, 0x602, 0x062, 0x206, 0x026, 0x531, 0x351,
+    0x513, 0x153, 0x315, 0x135, 0x700, 0x070, 0x007, 0x621, 0x261, 0x612, 0x162, 0x216,
+    0x126, 0x710, 0x170, 0x701, 0x071, 0x107, 0x017, 0x433, 0x343, 0x334, 0x711, 0x171,
+};
+template <int D>
+__device__ __forceinline__ constexpr int term(int i, int axis) {
+    return ((D == 2 ? kTerms2[i] : kTerms3[i]) >> (4 * axis)) & 15;
+}
+
+// ------------------------------------------------------------------ partition
+
+// Floats as unsigned integers in the same order.
+__device__ __forceinline__ unsigned ordered(float v) {
+    const unsigned u = __float_as_uint(v);
+    return (u & 0x80000000u) ? ~u : u | 0x80000000u;
+}
+__device__ __forceinline__ float from_ordered(unsigned u) {
+    return __uint_as_float((u & 0x80000000u) ? u & 0x7fffffffu : ~u);
+}
+
+__global__ __launch_bounds__(64) void k_cell_init(CellPrep P) {
+    const int i = (int)threadIdx.x;
+    if (i < 16) {
+        CellSide& S = P.side[i >> 3];
+        S.box[i & 7] = (i & 7) < 3 ? 0xffffffffu : 0u;
+    }
+}
+
+// Bounding box of the scaled points (minima and maxima do not depend on the order of the
+// atomics), and the number of points that no cell can take: non-finite coordinates, or
+// weights that are not positive and finite.
+__global__ __launch_bounds__(256) void k_cell_box(CellPrep P) {
+    const CellSide& S = P.side[blockIdx.y];
+    const int d = P.d;
+    unsigned lo[3] = {0xffffffffu, 0xffffffffu, 0xffffffffu}, hi[3] = {0u, 0u, 0u}, bad = 0u;
+    for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < S.n; i += (int)gridDim.x * 256) {
+        bool ok = true;
+        for (int t = 0; t < d; ++t) {
+            const float c = (S.pts[(size_t)i * d + t] - P.origin[t]) * P.sqrt_kappa;
+            ok = ok && isfinite(c);
+            if (isfinite(c)) {
+                lo[t] = min(lo[t], ordered(c));
+                hi[t] = max(hi[t], ordered(c));
+            }
+        }
+        if (blockIdx.y == 1 && P.w) {
+            const float w = P.w[i];
+            ok = ok && w > 0.f && isfinite(w);
+        }
+        bad += ok ? 0u : 1u;
+    }
+    for (int m = 1; m < 64; m <<= 1) {
+        for (int t = 0; t < 3; ++t) {
+            lo[t] = min(lo[t], __shfl_xor(lo[t], m));
+            hi[t] = max(hi[t], __shfl_xor(hi[t], m));
+        }
+        bad += __shfl_xor(bad, m);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        for (int t = 0; t < d; ++t) {
+            atomicMin(&S.box[t], lo[t]);
+            atomicMax(&S.box[3 + t], hi[t]);
+        }
+        if (bad) atomicAdd(&S.box[6], bad);
+    }
+}
+
+// Cell code of a point: its cell's coordinates, bits interleaved, so that cells of
+// neighbouring codes are neighbours.  Points outside the coded box take its border cells
+// (the partition is then marked as not fitting, see k_cell_lists).
+__device__ __forceinline__ int cell_code(const float* c, const float* lo, float inv, int d,
+                                         int bits) {
+    int code = 0;
+    for (int t = 0; t < d; ++t) {
+        const float v = (c[t] - lo[t]) * inv;
+        int k = v > 0.f ? (int)fminf(v, 65535.f) : 0;   // NaN: 0
+        k = min(k, (1 << bits) - 1);
+        for (int b = 0; b < bits; ++b) code |= ((k >> b) & 1) << (b * d + t);
+    }
+    return code;
+}
+
+// Counts per block of `per` points and code.
+__global__ __launch_bounds__(256) void k_cell_hist(CellPrep P) {
+    __shared__ unsigned h[kCellIds];
+    const CellSide& S = P.side[blockIdx.y];
+    const int b = (int)blockIdx.x;
+    if (b >= S.nb) return;
+    for (int i = (int)threadIdx.x; i < P.ids; i += 256) h[i] = 0u;
+    __syncthreads();
+    float lo[3];
+    for (int t = 0; t < 3; ++t) lo[t] = from_ordered(S.box[t]);
+    const int i1 = min(S.n, (b + 1) * S.per);
+    for (int i = b * S.per + (int)threadIdx.x; i < i1; i += 256) {
+        float c[3];
+        for (int t = 0; t < P.d; ++t)
+            c[t] = (S.pts[(size_t)i * P.d + t] - P.origin[t]) * P.sqrt_kappa;
+        const int id = cell_code(c, lo, 1.f / P.cell, P.d, P.bits);
+        S.id[i] = (unsigned short)id;
+        atomicAdd(&h[id], 1u);
+    }
+    __syncthreads();
+    for (int i = (int)threadIdx.x; i < P.ids; i += 256) S.bh[(size_t)b * P.ids + i] = h[i];
+}
+
+// Per code: exclusive sums of its counts over the blocks, and its total.
+__global__ __launch_bounds__(256) void k_cell_scan(CellPrep P) {
+    const CellSide& S = P.side[blockIdx.y];
+    const int id = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (id >= P.ids) return;
+    unsigned run = 0u;
+#pragma unroll 8
+    for (int b = 0; b < S.nb; ++b) {
+        const size_t at = (size_t)b * P.ids + id;
+        const unsigned v = S.bh[at];
+        S.bh[at] = run;
+        run += v;
+    }
+    S.first[id] = run;   // the total; k_cell_lists turns it into the first place
+}
+
+// Inclusive block scan of one int per thread (1024 threads); returns the exclusive sum
+// and the total.
+__device__ __forceinline__ int block_scan(int v, int* sh, int* total) {
+    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+    int s = v;
+    for (int m = 1; m < 64; m <<= 1) {
+        const int o = __shfl_up(s, m);
+        if (lane >= m) s += o;
+    }
+    __syncthreads();
+    if (lane == 63) sh[wave] = s;
+    __syncthreads();
+    int before = 0, all = 0;
+    for (int w = 0; w < 16; ++w) {
+        if (w < wave) before += sh[w];
+        all += sh[w];
+    }
+    *total = all;
+    return before + s - v;
+}
+
+// Sorted places, the non-empty cells, their chunks of at most kc keys and their tiles of
+// 32 queries (one block per side; four codes per thread).
+__global__ __launch_bounds__(1024) void k_cell_lists(CellPrep P) {
+    __shared__ int sh[16];
+    const CellSide& S = P.side[blockIdx.x];
+    constexpr int per = kCellIds / 1024;
+    int n[per], pts = 0, cells = 0, chunks = 0, tiles = 0;
+    for (int k = 0; k < per; ++k) {
+        const int id = (int)threadIdx.x * per + k;
+        n[k] = id < P.ids ? (int)S.first[id] : 0;
+        pts += n[k];
+        cells += n[k] > 0;
+        chunks += (n[k] + S.kc - 1) / S.kc;
+        tiles += (n[k] + kCellTile - 1) / kCellTile;
+    }
+    int tp, tc, th, tt;
+    int at = block_scan(pts, sh, &tp);
+    int ic = block_scan(cells, sh, &tc);
+    int ih = block_scan(chunks, sh, &th);
+    int it = block_scan(tiles, sh, &tt);
+    bool fits = tc <= S.cmax && th <= S.chmax && tt <= S.tmax && S.box[6] == 0u;
+    float lo[3] = {0.f, 0.f, 0.f};
+    for (int t = 0; t < P.d; ++t) {
+        lo[t] = from_ordered(S.box[t]);
+        // every point in the cell of its code (one part in 10^4 of slack in the side of a cell)
+        fits = fits && (from_ordered(S.box[3 + t]) - lo[t]) <= P.cell * (float)(1 << P.bits);
+    }
+    if (threadIdx.x == 0) {
+        S.cnt[0] = tc;
+        S.cnt[1] = th;
+        S.cnt[2] = tt;
+        S.cnt[3] = fits ? 0 : 1;
+    }
+    for (int k = 0; k < per; ++k) {
+        const int id = (int)threadIdx.x * per + k;
+        if (id >= P.ids) break;
+        S.first[id] = (unsigned)at;
+        const int end = at + n[k];
+        if (fits && n[k] > 0) {
+            float c[3] = {0.f, 0.f, 0.f};
+            for (int t = 0; t < P.d; ++t) {
+                int g = 0;
+                for (int b = 0; b < P.bits; ++b) g |= ((id >> (b * P.d + t)) & 1) << b;
+                c[t] = lo[t] + ((float)g + 0.5f) * P.cell;
+            }
+            const float4 cen = make_float4(c[0], c[1], c[2], 0.f);
+            S.cen[ic] = cen;
+            for (int q = at; q < end; q += S.kc) {
+                S.chunk[ih] = make_int4(q, min(end, q + S.kc), ic, 0);
+                S.chcen[ih] = cen;
+                ++ih;
+            }
+            for (int q = at; q < end; q += kCellTile)
+                S.tile[it++] = make_int4(q, min(end, q + kCellTile), ic, 0);
+            ++ic;
+        }
+        at = end;
+    }
+}
+
+// Stable scatter: one wave per block of points walks them in order, 64 at a time; the
+// lanes of one code rank themselves by ballots over the code's bits.
+__global__ __launch_bounds__(64) void k_cell_scatter(CellPrep P) {
+    __shared__ unsigned cur[kCellIds];
+    const CellSide& S = P.side[blockIdx.y];
+    const int b = (int)blockIdx.x, lane = (int)threadIdx.x;
+    if (b >= S.nb) return;
+    for (int i = lane; i < P.ids; i += 64) cur[i] = S.first[i] + S.bh[(size_t)b * P.ids + i];
+    __syncthreads();
+    const int i1 = min(S.n, (b + 1) * S.per);
+    const int nbit = P.bits * P.d;
+    for (int i0 = b * S.per; i0 < i1; i0 += 64) {
+        const int i = i0 + lane;
+        const bool on = i < i1;
+        const int id = on ? (int)S.id[i] : 0;
+        unsigned long long same = __ballot(on);
+        for (int k = 0; k < nbit; ++k) {
+            const unsigned long long m = __ballot((id >> k) & 1);
+            same &= ((id >> k) & 1) ? m : ~m;
+        }
+        const int rank = __popcll(same & ((1ull << lane) - 1ull));
+        unsigned base = 0u;
+        if (on) base = cur[id];
+        __syncthreads();
+        if (on) {
+            S.perm[base + rank] = i;
+            if (rank == 0) cur[id] = base + (unsigned)__popcll(same);
+        }
+        __syncthreads();
+    }
+}
+
+// Multiply-adds of one sweep in the cell form: moment tiles of 32 query cells by every
+// key, value tiles of 32 queries by every chunk of keys (in tiles of 32).
+__device__ double cell_work(const CellSide& q, const CellSide& k) {
+    const double at = (q.cnt[0] + kCellTile - 1) / kCellTile * kCellTile;
+    const double ct = (k.cnt[1] + kCellTile - 1) / kCellTile * kCellTile;
+    return at * ((double)k.n + 4.0 * k.cnt[1]) + (double)q.cnt[2] * kCellTile * ct;
+}
+
+// Points, weights and starting potentials in cell order; the first thread settles the
+// form of the sweeps (see kCellGain).
+constexpr double kCellGain = 0.7;
+__global__ __launch_bounds__(256) void k_cell_gather(CellPrep P) {
+    const CellSide& X = P.side[0];
+    const CellSide& Y = P.side[1];
+    const int d = P.d;
+    const int i = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (i == 0) {
+        const int N = d == 2 ? CellDim<2>::N : CellDim<3>::N;
+        const size_t cx = X.cnt[0], cy = Y.cnt[0], hx = X.cnt[1], hy = Y.cnt[1];
+        const size_t cross = max(cx * hy, cy * hx) * N;
+        bool ok = X.cnt[3] == 0 && Y.cnt[3] == 0 && cross <= P.mom_cap[0] &&
+                  cx * hx * N <= P.mom_cap[1] && (!P.need_ref || cy * hy * N <= P.mom_cap[2]);
+        double cell = cell_work(X, Y) + cell_work(Y, X) + cell_work(X, X);
+        double pairs = 2.0 * X.n * Y.n + (double)X.n * X.n;
+        if (P.need_ref) {
+            cell += cell_work(Y, Y);
+            pairs += (double)Y.n * Y.n;
+        }
+        // clocks of a compute unit: 128 multiply-adds per clock in the matrix cores against
+        // the pair's instructions in the vector units
+        const double pair = d == 2 ? 2.0 / 128 + 2.0 / 64 + 1.0 / 32 : 2.0 / 128 + 3.0 / 64 + 1.0 / 32;
+        ok = ok && cell * N / 128.0 < kCellGain * pairs * pair;
+        *P.mode = ok ? 1 : 0;
+    }
+    if (i < X.n) {
+        const int s = X.perm[i];
+        for (int t = 0; t < d; ++t) P.xs[(size_t)i * d + t] = X.pts[(size_t)s * d + t];
+        if (P.pot_in) {
+            P.pot_s[i] = P.pot_in[s];
+            P.pot_s[(size_t)X.n + Y.n + i] = P.pot_in[(size_t)X.n + Y.n + s];
+        }
+    }
+    if (i < Y.n) {
+        const int s = Y.perm[i];
+        for (int t = 0; t < d; ++t) P.ys[(size_t)i * d + t] = Y.pts[(size_t)s * d + t];
+        if (P.w) P.ws[i] = P.w[s];
+        if (P.pot_in) {
+            P.pot_s[(size_t)X.n + i] = P.pot_in[(size_t)X.n + s];
+            P.pot_s[2 * (size_t)X.n + Y.n + i] = P.pot_in[2 * (size_t)X.n + Y.n + s];
+        }
+    }
+}
+
+// -------------------------------------------------------------------- moments
+
+template <int D>
+struct MomentSmem {
+    float4 key[kCellChunkMax];                    // (2u, [..], h - |u|^2), .z (2-D) or .w (3-D)
+    float tab[4][D * CellDim<D>::F * 65];         // T_n(u) of 64 keys per wave, rows of 65
+    float mu[4][kCellTile];
+};
+
+// Moments of chunk `c` for 32 query cells.  The four waves take a quarter of the chunk's
+// keys each; an MFMA multiplies the weights of 2 keys for 32 query cells (A: lane = cell,
+// half wave = key) with 32 of the keys' products of Chebyshev polynomials (B: lane =
+// product), and the waves' sums meet in LDS.
+template <int D>
+__device__ __forceinline__ void cell_moments(const CellJob& C, const Job& J, int c, int at, int nch,
+                                             int ncq, float inv_cell, MomentSmem<D>& sm) {
+    constexpr int N = CellDim<D>::N, F = CellDim<D>::F, CT = N / 32;
+    const int tid = (int)threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63, col = lane & 31, half = lane >> 5;
+    const int4 ch = C.chunk[c];
+    const float4 cc = C.chcen[c];
+    const int nk = ch.y - ch.x, nkp = (nk + 7) & ~7;
+    for (int i = tid; i < nkp; i += kBlock) {
+        float4 k = make_float4(0.f, 0.f, D == 2 ? kNegInf : 0.f, kNegInf);
+        if (i < nk) {
+            const float4 r = J.krec[ch.x + i];
+            const float ux = r.x - cc.x, uy = r.y - cc.y;
+            if (D == 2) {
+                k = make_float4(2.f * ux, 2.f * uy, r.z - __builtin_fmaf(ux, ux, uy * uy), 0.f);
+            } else {
+                const float uz = r.z - cc.z;
+                k = make_float4(2.f * ux, 2.f * uy, 2.f * uz,
+                                r.w - __builtin_fmaf(ux, ux, __builtin_fmaf(uy, uy, uz * uz)));
+            }
+        }
+        sm.key[i] = k;
+    }
+    const int a = min(at * kCellTile + col, ncq - 1);
+    const float4 qc = C.qcen[a];
+    const float dx = qc.x - cc.x, dy = qc.y - cc.y, dz = D == 3 ? qc.z - cc.z : 0.f;
+    auto expo = [&](const float4& k) {
+        if (D == 2) return __builtin_fmaf(dx, k.x, __builtin_fmaf(dy, k.y, k.z));
+        return __builtin_fmaf(dx, k.x, __builtin_fmaf(dy, k.y, __builtin_fmaf(dz, k.z, k.w)));
+    };
+    // products of this lane's columns: rows of the table
+    int row[CT][D];
+#pragma unroll
+    for (int t = 0; t < CT; ++t)
+#pragma unroll
+        for (int x = 0; x < D; ++x) row[t][x] = (x * F + term<D>(t * 32 + col, x)) * 65;
+    __syncthreads();
+    const int kw = nkp >> 2, kb = wave * kw;   // even, this wave's keys [kb, kb + kw)
+    float mx = kNegInf;
+#pragma unroll 4
+    for (int k = 0; k < kw; k += 2) mx = fmaxf(mx, expo(sm.key[kb + k + half]));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    if (half == 0) sm.mu[wave][col] = mx;
+    __syncthreads();
+    float mu = fmaxf(fmaxf(sm.mu[0][col], sm.mu[1][col]), fmaxf(sm.mu[2][col], sm.mu[3][col]));
+    const float shift = mu == kNegInf ? 0.f : mu;
+    f32x16 acc[CT];
+#pragma unroll
+    for (int t = 0; t < CT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+    float* tab = sm.tab[wave];
+    for (int k0 = 0; k0 < kw; k0 += 64) {
+        const int nn = min(64, kw - k0);
+        __builtin_amdgcn_wave_barrier();
+        if (lane < nn) {
+            const float4 k = sm.key[kb + k0 + lane];
+#pragma unroll
+            for (int x = 0; x < D; ++x) {
+                const float u = (x == 0 ? k.x : x == 1 ? k.y : k.z) * inv_cell;   // on [-1, 1]
+                float t0 = 1.f, t1 = u;
+#pragma unroll
+                for (int n = 0; n < F; ++n) {
+                    tab[(x * F + n) * 65 + lane] = t0;
+                    const float t2 = __builtin_fmaf(2.f * u, t1, -t0);
+                    t0 = t1;
+                    t1 = t2;
+                }
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        for (int p = 0; p < nn; p += 2) {
+            const int k = p + half;
+            const float W = ex2(expo(sm.key[kb + k0 + k]) - shift);
+#pragma unroll
+            for (int t = 0; t < CT; ++t) {
+                float b = tab[row[t][0] + k] * tab[row[t][1] + k];
+                if (D == 3) b *= tab[row[t][D - 1] + k];
+                acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(W, b, acc[t], 0, 0, 0);
+            }
+        }
+    }
+    // the four waves' sums, 32 products at a time (4 KB per wave in the keys' place)
+    float* red = reinterpret_cast<float*>(sm.key);
+    static_assert(sizeof(sm.key) >= 4 * 1024 * sizeof(float), "room for four waves' tiles");
+#pragma unroll
+    for (int t = 0; t < CT; ++t) {
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            red[wave * 1024 + (8 * (r >> 2) + 4 * half + (r & 3)) * 32 + col] = acc[t][r];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int e = i * 256 + tid, aa = at * kCellTile + (e >> 5);
+            const float v = (red[e] + red[1024 + e]) + (red[2048 + e] + red[3072 + e]);
+            if (aa < ncq) C.mom[((size_t)aa * nch + c) * N + t * 32 + (e & 31)] = v;
+        }
+    }
+    if (wave == 0 && half == 0 && at * kCellTile + col < ncq)
+        C.mu[(size_t)a * nch + c] =
+            mu - __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz));
+    __syncthreads();
+}
+
+// --------------------------------------------------------------------- values
+
+// (n ? 2 : 1) I_n(z) for n < F by the ascending series, |z| <= 1 or so.
+template <int F>
+__device__ __forceinline__ void bessel(float z, float* out, int stride) {
+    const float q = 0.25f * z * z;
+    float lead = 1.f;   // (z/2)^n / n!
+#pragma unroll
+    for (int n = 0; n < F; ++n) {
+        float s = 1.f;
+#pragma unroll
+        for (int m = 5; m >= 1; --m) s = __builtin_fmaf(s * (1.f / (float)(m * (n + m))), q, 1.f);
+        out[n * stride] = (n ? 2.f : 1.f) * lead * s;
+        lead *= 0.5f * z * (1.f / (float)(n + 1));
+    }
+}
+
+template <int D>
+struct ValueSmem {
+    float in[D * CellDim<D>::F * 33];   // phi_n per axis of 32 queries, rows of 33
+    float4 cd[4][kCellTile];            // per wave: (-2d, mu - |d|^2) of 32 chunks
+    float red[4][kCellTile];
+    int flist[kCellTile];
+    int nflag;
+};
+
+// Values of one tile of 32 queries.  The waves take every fourth tile of 32 chunks; an
+// MFMA multiplies the chunks' moments (A: lane = chunk) with the queries' functions (B:
+// lane = query), so that a lane holds 16 chunks' sums of its own query.
+template <int D, bool LAGGED>
+__device__ __forceinline__ void cell_values(const CellJob& C, const Job& J, int u, int nch,
+                                            float inv_cell, float kappa, float inv_kappa,
+                                            float inv_sqrt_kappa, ValueSmem<D>& sm) {
+    constexpr int N = CellDim<D>::N, F = CellDim<D>::F, H = N / 2;
+    const int tid = (int)threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63, col = lane & 31, half = lane >> 5;
+    const int4 tl = C.tile[u];
+    const float4 qc = C.qcen[tl.z];
+    const int q = min(tl.x + col, tl.y - 1);
+    const float4 v = J.qrec[q];
+    const float sx = v.x - qc.x, sy = v.y - qc.y, sz = D == 3 ? v.z - qc.z : 0.f;
+    const float sq = __builtin_fmaf(sx, sx, __builtin_fmaf(sy, sy, sz * sz));
+    if (tid == 0) sm.nflag = 0;
+    if ((tid >> 5) < D) {
+        const int x = tid >> 5;
+        const float s = (x == 0 ? sx : x == 1 ? sy : sz) * 2.f * inv_cell;   // on [-1, 1]
+        bessel<F>((float)CellDim<D>::lambda * s, sm.in + x * F * 33 + col, 33);
+    }
+    __syncthreads();
+    // the functions' places in LDS, kept out of registers that live across tiles
+    int sel = half, colv = col;
+    float b[H];
+#pragma unroll
+    for (int s = 0; s < H; ++s) {
+        if (s % 8 == 0) asm volatile("" : "+v"(sel), "+v"(colv));
+        float p = 1.f;
+#pragma unroll
+        for (int x = 0; x < D; ++x) {
+            const int r0 = (x * F + term<D>(s, x)) * 33, r1 = (x * F + term<D>(s + H, x)) * 33;
+            const float f = sm.in[(sel ? r1 : r0) + colv];
+            p = x == 0 ? f : p * f;
+        }
+        b[s] = p;
+        asm volatile("" : "+v"(b[s]));
+    }
+    float4* cd = sm.cd[wave];
+    auto load_cd = [&](int ct) {
+        // (-2d, mu - |d|^2) of the tile's chunks; past the last one mu = -inf
+        __builtin_amdgcn_wave_barrier();
+        if (half == 0) {
+            const int c = min(ct * kCellTile + col, nch - 1);
+            const float4 kc = C.chcen[c];
+            const float m = ct * kCellTile + col < nch ? C.mu[(size_t)tl.z * nch + c] : kNegInf;
+            cd[col] = make_float4(-2.f * (qc.x - kc.x), -2.f * (qc.y - kc.y),
+                                  D == 3 ? -2.f * (qc.z - kc.z) : 0.f, m);
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+    auto expo = [&](int r, float base) {
+        const float4 k = cd[8 * (r >> 2) + 4 * half + (r & 3)];
+        float e = __builtin_fmaf(sy, k.y, k.w);
+        if (D == 3) e = __builtin_fmaf(sz, k.z, e);
+        return __builtin_fmaf(sx, k.x, e) + base;
+    };
+    const int ntc = (nch + kCellTile - 1) / kCellTile;
+    float m;
+    if (LAGGED) {
+        m = -J.qpot[q] * kappa;
+    } else {
+        m = kNegInf;
+        for (int ct = wave; ct < ntc; ct += 4) {
+            load_cd(ct);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) m = fmaxf(m, expo(r, -sq));
+        }
+        m = fmaxf(m, __shfl_xor(m, 32));
+        if (half == 0) sm.red[wave][col] = m;
+        __syncthreads();
+        m = fmaxf(fmaxf(sm.red[0][col], sm.red[1][col]), fmaxf(sm.red[2][col], sm.red[3][col]));
+        if (m == kNegInf) m = 0.f;
+        __syncthreads();
+    }
+    const float base = -sq - m;
+    float sum = 0.f;
+    // 4 V products of a chunk's moments per step, read one step ahead
+    constexpr int V = D == 2 ? 8 : 4, G = H / (4 * V);
+    auto load = [&](int ct, int g, float4 (&A)[V]) {
+        const int c = min(ct * kCellTile + col, nch - 1);
+        const float4* M = reinterpret_cast<const float4*>(
+            C.mom + ((size_t)tl.z * nch + c) * N + half * H) + g * V;
+#pragma unroll
+        for (int i = 0; i < V; ++i) A[i] = M[i];
+    };
+    float4 A[V];
+    if (wave < ntc) load(wave, 0, A);
+#pragma unroll 1
+    for (int ct = wave; ct < ntc; ct += 4) {
+        load_cd(ct);
+        f32x16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            float4 nx[V];
+            if (g + 1 < G) load(ct, g + 1, nx);
+            else load(min(ct + 4, ntc - 1), 0, nx);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < V; ++i) {
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(A[i].x, b[4 * (g * V + i)], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(A[i].y, b[4 * (g * V + i) + 1], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(A[i].z, b[4 * (g * V + i) + 2], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(A[i].w, b[4 * (g * V + i) + 3], acc, 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < V; ++i) A[i] = nx[i];
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum = __builtin_fmaf(acc[r], ex2(expo(r, base)), sum);
+    }
+    sum += __shfl_xor(sum, 32);
+    if (half == 0) sm.red[wave][col] = sum;
+    __syncthreads();
+    if (tid < kCellTile) {
+        const float s = (sm.red[0][tid] + sm.red[1][tid]) + (sm.red[2][tid] + sm.red[3][tid]);
+        if (tl.x + tid < tl.y)
+            finish_or_flag<D, LAGGED>(J, tl.x + tid, m, s, nullptr, sm.flist, &sm.nflag, kappa,
+                                      inv_kappa, inv_sqrt_kappa);
+    }
+    __syncthreads();
+    if (LAGGED) {
+        const int n = sm.nflag;
+        if (n > 0) rescue_rows<D, false>(J, sm.flist, n, kappa, inv_kappa, inv_sqrt_kappa);
+        __syncthreads();
+    }
+}
+
+// --------------------------------------------------------------- launch kernels
+
+template <int D, int R>
+union StepSmem {
+    MomentSmem<D> m;
+    SweepSmem<D, R> s;
+};
+
+// First launch of a sweep: the moments of every (chunk, 32 query cells) of its jobs, or
+// the direct sweep's work units.  Both walk their units with the grid as the stride: how
+// many there are is known on the device only.
+template <int D, int R, int WS, bool LAGGED>
+__global__ __launch_bounds__(kBlock, 2) void k_cell_moments(Launch L, CellLaunch C) {
+    __shared__ StepSmem<D, R> sm;
+    const int grid = (int)gridDim.x;
+    if (*C.mode) {
+        int u = (int)blockIdx.x;
+        for (int j = 0; j < L.njobs; ++j) {
+            const int nch = *C.job[j].nch, ncq = *C.job[j].ncq;
+            const int nu = nch * ((ncq + kCellTile - 1) / kCellTile);
+            for (; u < nu; u += grid)
+                cell_moments<D>(C.job[j], L.job[j], u % nch, u / nch, nch, ncq, C.inv_cell, sm.m);
+            u -= nu;
+        }
+        return;
+    }
+    for (int b = (int)blockIdx.x; b < C.nblocks; b += grid) {
+        int j = 0;
+        while (j + 1 < L.njobs && b >= L.blk_end[j]) ++j;
+        const Job& J = L.job[j];
+        const int local = b - (j ? L.blk_end[j - 1] : 0);
+        sweep_unit<D, R, WS, LAGGED, false, true, LAGGED>(J, local % J.nqb, local / J.nqb, L.kappa,
+                                                          L.inv_kappa, L.inv_sqrt_kappa, sm.s);
+        __syncthreads();
+    }
+}
+
+// Second launch: the values of every query tile, or the direct sweep's merge.
+template <int D, bool LAGGED>
+__global__ __launch_bounds__(kBlock, 2) void k_cell_values(Launch L, CellLaunch C) {
+    const int grid = (int)gridDim.x;
+    if (*C.mode) {
+        __shared__ ValueSmem<D> sm;
+        int u = (int)blockIdx.x;
+        for (int j = 0; j < L.njobs; ++j) {
+            const int nch = *C.job[j].nch, nt = *C.job[j].ntile;
+            for (; u < nt; u += grid)
+                cell_values<D, LAGGED>(C.job[j], L.job[j], u, nch, C.inv_cell, L.kappa,
+                                       L.inv_kappa, L.inv_sqrt_kappa, sm);
+            u -= nt;
+        }
+        return;
+    }
+    int b = (int)blockIdx.x;
+    for (int j = 0; j < L.njobs; ++j) {
+        const Job& J = L.job[j];
+        const int nb = J.splits > 1 ? (J.nq + kMergeRows - 1) / kMergeRows : 0;
+        for (; b < nb; b += grid) {
+            merge_block<D, LAGGED, false>(J, b * kMergeRows, J.nqb * 64 * C.R * (4 / C.WS), L.kappa,
+                                          L.inv_kappa, L.inv_sqrt_kappa);
+            __syncthreads();
+        }
+        b -= nb;
+    }
+}
+
+template <int D, int R, int WS>
+hipError_t moments_drw(bool lagged, const Launch& L, const CellLaunch& C, int nb, hipStream_t s,
+                       hipEvent_t e0, hipEvent_t e1) {
+    auto go = [&](auto kernel) {
+        if (e0) hipExtLaunchKernelGGL(kernel, dim3(nb), dim3(kBlock), 0, s, e0, e1, 0, L, C);
+        else hipLaunchKernelGGL(kernel, dim3(nb), dim3(kBlock), 0, s, L, C);
+    };
+    if (lagged) go(k_cell_moments<D, R, WS, true>);
+    else go(k_cell_moments<D, R, WS, false>);
+    return hipGetLastError();
+}
+
+template <int D, int R>
+hipError_t moments_dr(bool lagged, const Launch& L, const CellLaunch& C, int nb, hipStream_t s,
+                      hipEvent_t e0, hipEvent_t e1) {
+    switch (C.WS) {
+        case 1: return moments_drw<D, R, 1>(lagged, L, C, nb, s, e0, e1);
+        case 2: return moments_drw<D, R, 2>(lagged, L, C, nb, s, e0, e1);
+        default: return moments_drw<D, R, 4>(lagged, L, C, nb, s, e0, e1);
+    }
+}
+
+template <int D>
+hipError_t moments_d(bool lagged, const Launch& L, const CellLaunch& C, int nb, hipStream_t s,
+                     hipEvent_t e0, hipEvent_t e1) {
+    switch (C.R) {
+        case 1: return moments_dr<D, 1>(lagged, L, C, nb, s, e0, e1);
+        case 2: return moments_dr<D, 2>(lagged, L, C, nb, s, e0, e1);
+        case 4: return moments_dr<D, 4>(lagged, L, C, nb, s, e0, e1);
+        default: return moments_dr<D, 8>(lagged, L, C, nb, s, e0, e1);
+    }
+}
+
+template <int D>
+hipError_t values_d(bool lagged, const Launch& L, const CellLaunch& C, int nb, hipStream_t s,
+                    hipEvent_t e0, hipEvent_t e1) {
+    auto go = [&](auto kernel) {
+        if (e0) hipExtLaunchKernelGGL(kernel, dim3(nb), dim3(kBlock), 0, s, e0, e1, 0, L, C);
+        else hipLaunchKernelGGL(kernel, dim3(nb), dim3(kBlock), 0, s, L, C);
+    };
+    if (lagged) go(k_cell_values<D, true>);
+    else go(k_cell_values<D, false>);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+double cell_side(int d) {
+    const double lambda = d == 2 ? CellDim<2>::lambda : CellDim<3>::lambda;
+    return std::sqrt(2.0 * lambda / 0.6931471805599453);
+}
+
+int cell_chunk(int n) { return n <= 32768 ? 256 : n <= 131072 ? 512 : kCellChunkMax; }
+
+hipError_t launch_cell_prep(const CellPrep& P, hipStream_t s) {
+    const int nbm = std::max(P.side[0].nb, P.side[1].nb);
+    const int n = std::max(P.side[0].n, P.side[1].n);
+    hipLaunchKernelGGL(k_cell_init, dim3(1), dim3(64), 0, s, P);
+    hipLaunchKernelGGL(k_cell_box, dim3(std::min(128, (n + 1023) / 1024), 2), dim3(256), 0, s, P);
+    hipLaunchKernelGGL(k_cell_hist, dim3(nbm, 2), dim3(256), 0, s, P);
+    hipLaunchKernelGGL(k_cell_scan, dim3((P.ids + 255) / 256, 2), dim3(256), 0, s, P);
+    hipLaunchKernelGGL(k_cell_lists, dim3(2), dim3(1024), 0, s, P);
+    hipLaunchKernelGGL(k_cell_scatter, dim3(nbm, 2), dim3(64), 0, s, P);
+    hipLaunchKernelGGL(k_cell_gather, dim3((n + 255) / 256), dim3(256), 0, s, P);
+    return hipGetLastError();
+}
+
+hipError_t launch_cell_sweep(int d, const Schedule& sc, bool lagged, const Launch& L,
+                             const CellLaunch& C, hipStream_t s) {
+    // grids for the units one can expect (both kernels walk whatever there is)
+    int units = 0, tiles = 0, merges = 0;
+    double pairs = 0.0;
+    for (int j = 0; j < L.njobs; ++j) {
+        const Job& J = L.job[j];
+        units += (J.nk / cell_chunk(J.nk) + 128) * 4;
+        tiles += J.nq / kCellTile + 128;
+        if (J.splits > 1) merges += (J.nq + kMergeRows - 1) / kMergeRows;
+        pairs += (double)J.nq * J.nk;
+    }
+    const int nm = std::min(2048, std::max(units, std::min(C.nblocks, 2048)));
+    const int nv = std::min(4096, std::max(tiles, merges));
+    const int code = sc.R * 100 + sc.WS * 10 + sc.sep + (lagged && L.expanded ? 1000 : 0);
+    hipEvent_t e0, e1;
+    void* tok = profile_kernel_begin(&e0, &e1);
+    hipError_t e = d == 2 ? moments_d<2>(lagged, L, C, nm, s, e0, e1)
+                          : moments_d<3>(lagged, L, C, nm, s, e0, e1);
+    // kind 50/51: moments (or a direct sweep) of a safe/lagged sweep; 60/61: its values
+    profile_kernel_end(tok, 50 + lagged, 0, code, nm, pairs);
+    if (e != hipSuccess) return e;
+    tok = profile_kernel_begin(&e0, &e1);
+    e = d == 2 ? values_d<2>(lagged, L, C, nv, s, e0, e1) : values_d<3>(lagged, L, C, nv, s, e0, e1);
+    profile_kernel_end(tok, 60 + lagged, 0, code, nv, 0.0);
+    return e;
+}
+
+}  // namespace ct

@@ -7,6 +7,7 @@
 #include <map>
 #include <mutex>
 
+#include "cells.h"
 #include "ct_internal.h"
 
 namespace ct {
@@ -176,15 +177,36 @@ __global__ __launch_bounds__(256) void k_stage(StageArgs A) {
 }
 
 // grad_x = 2 a (Ds - Dy)  (debiased) or -2 a Dy; NaN after a barrier of the fused
-// solve gave up (*expired).
+// solve gave up (*expired).  perm: the caller's index of each row, or null.
 __global__ __launch_bounds__(256) void k_grad_x(const float* __restrict__ dy,
-                                                const float* __restrict__ ds, int n, float two_a,
+                                                const float* __restrict__ ds, int n, int d,
+                                                float two_a, const int* __restrict__ perm,
                                                 const unsigned* __restrict__ expired,
                                                 float* __restrict__ out) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const float v = ds ? ds[i] - dy[i] : -dy[i];
-    out[i] = *expired ? __builtin_nanf("") : two_a * v;
+    const size_t at = perm ? (size_t)perm[i / d] * d + i % d : (size_t)i;
+    out[at] = *expired ? __builtin_nanf("") : two_a * v;
+}
+
+// out = (a [T], b [M], c [T], e [M]) with every set back in the caller's order.
+__global__ __launch_bounds__(256) void k_pot_out(const float* __restrict__ a,
+                                                 const float* __restrict__ b,
+                                                 const float* __restrict__ c,
+                                                 const float* __restrict__ e, int T, int M,
+                                                 const int* __restrict__ px,
+                                                 const int* __restrict__ py,
+                                                 float* __restrict__ out) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < T) {
+        out[px[i]] = a[i];
+        out[(size_t)T + M + px[i]] = c[i];
+    }
+    if (i < M) {
+        out[(size_t)T + py[i]] = b[i];
+        out[2 * (size_t)T + M + py[i]] = e[i];
+    }
 }
 
 struct ReduceArgs {
@@ -260,12 +282,13 @@ __global__ __launch_bounds__(256) void k_grad_w(const float* __restrict__ gp,
                                                 const float* __restrict__ qp, int M,
                                                 const double* __restrict__ bG,
                                                 const double* __restrict__ wsum,
+                                                const int* __restrict__ perm,
                                                 const unsigned* __restrict__ expired,
                                                 float* __restrict__ out) {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= M) return;
     const double G = qp ? (double)gp[j] - (double)qp[j] : (double)gp[j];
-    out[j] = *expired ? __builtin_nanf("") : (float)((G - *bG) / *wsum);
+    out[perm ? perm[j] : j] = *expired ? __builtin_nanf("") : (float)((G - *bG) / *wsum);
 }
 
 __global__ void k_counters_out(const unsigned* __restrict__ c, float* __restrict__ aux) {
@@ -298,12 +321,78 @@ struct SkLayout {
     size_t ntick;
     unsigned* bar;           // [kFusedBarWords] barrier words of the fused solve
     unsigned long long* xch; // [2 (2T + 2M)] versioned potential words of the exchange solve
+    bool cells;              // the cell form's arrays are there:
+    CellPrep prep;           //   partitions, sorted inputs, mode
+    float* mom[3];           //   moments: cross, x self, y self
+    float* mu[3];
     size_t bytes;
 };
 
 constexpr int kCounters = 8;
 
-static SkLayout sk_layout(void* ws, int T, int M, int d) {
+// Cell form of the sweeps (see cells.h): by default where the library would launch one
+// direct sweep at a time (an iteration has more than kMeshAutoPairs point pairs), from
+// kCellMinIters iterations on (splitting the points into cells costs about one iteration of
+// the smallest such problem) and up to kCellMaxPoints points a side (16-bit cell codes sorted
+// by at most 512 blocks).  Whether it pays and fits for the points at hand, k_cell_gather
+// settles on the device.  CT_UNFUSED, CT_DIFFERENCE, CT_SAFE_LSE and the flags of the other
+// executions rule it out, and so does a workspace without its arrays.
+constexpr int kCellMinIters = 8;
+constexpr int kCellMaxPoints = 1 << 22;
+constexpr size_t kCellMomentsMax = size_t(96) << 20;   // floats of one moments buffer
+constexpr int kCellMinPoints = 24;   // mean points of a cell below which the form cannot pay
+constexpr double kMeshAutoPairs = 1.5e7;
+
+static bool cells_possible(int T, int M) {
+    const double pairs = 2.0 * T * M + (double)T * T + (double)M * M;
+    return pairs > kMeshAutoPairs && T <= kCellMaxPoints && M <= kCellMaxPoints;
+}
+
+static void cell_layout(Arena& a, SkLayout& L, int T, int M, int d) {
+    CellPrep& P = L.prep;
+    std::memset(&P, 0, sizeof(P));
+    P.d = d;
+    P.bits = d == 2 ? CellDim<2>::bits : CellDim<3>::bits;
+    P.ids = 1 << (P.bits * d);
+    P.cell = (float)cell_side(d);
+    const int N = d == 2 ? CellDim<2>::N : CellDim<3>::N;
+    for (int s = 0; s < 2; ++s) {
+        CellSide& S = P.side[s];
+        S.n = s ? M : T;
+        S.per = std::max(1024, ((S.n + 511) / 512 + 63) / 64 * 64);
+        S.nb = (S.n + S.per - 1) / S.per;
+        S.kc = cell_chunk(S.n);
+        S.cmax = std::min(P.ids, S.n / kCellMinPoints + 1);
+        S.chmax = S.cmax + S.n / S.kc;
+        S.tmax = S.cmax + S.n / kCellTile;
+        S.box = a.take<unsigned>(8);
+        S.id = a.take<unsigned short>(S.n);
+        S.bh = a.take<unsigned>((size_t)S.nb * P.ids);
+        S.first = a.take<unsigned>(P.ids);
+        S.perm = a.take<int>(S.n);
+        S.cen = a.take<float4>(S.cmax);
+        S.chunk = a.take<int4>(S.chmax);
+        S.chcen = a.take<float4>(S.chmax);
+        S.tile = a.take<int4>(S.tmax);
+        S.cnt = a.take<int>(4);
+    }
+    P.mode = a.take<int>(1);
+    P.xs = a.take<float>((size_t)T * d);
+    P.ys = a.take<float>((size_t)M * d);
+    P.ws = a.take<float>(M);
+    P.pot_s = a.take<float>(2 * ((size_t)T + M));
+    const CellSide &X = P.side[0], &Y = P.side[1];
+    const size_t rows[3] = {std::max((size_t)X.cmax * Y.chmax, (size_t)Y.cmax * X.chmax),
+                            (size_t)X.cmax * X.chmax, (size_t)Y.cmax * Y.chmax};
+    for (int i = 0; i < 3; ++i) {
+        const size_t r = std::min(rows[i], kCellMomentsMax / N);
+        P.mom_cap[i] = r * N;
+        L.mom[i] = a.take<float>(r * N);
+        L.mu[i] = a.take<float>(r);
+    }
+}
+
+static SkLayout sk_layout(void* ws, int T, int M, int d, bool cells) {
     Arena a(ws);
     SkLayout L;
     const int Tp = pad_keys(T), Mp = pad_keys(M);
@@ -334,6 +423,8 @@ static SkLayout sk_layout(void* ws, int T, int M, int d) {
     for (int i = 0; i < 3; ++i) L.tick[i] = a.take<unsigned>(L.ntick);
     L.bar = a.take<unsigned>(kFusedBarWords);
     L.xch = a.take<unsigned long long>(4 * ((size_t)T + M));
+    L.cells = cells && cells_possible(T, M);
+    if (L.cells) cell_layout(a, L, T, M, d);
     L.bytes = a.off + 256;
     return L;
 }
@@ -386,14 +477,19 @@ static SkConsts sk_consts(int T, int M, const ct_sinkhorn_opts* o) {
 
 struct JobSet {
     Job j[kMaxJobs];
+    CellJob cell[kMaxJobs];
     int n = 0;
-    void add(const Job& x) {
-        if (x.nq > 0) j[n++] = x;
+    void add(const Job& x, const CellJob& y = CellJob()) {
+        if (x.nq > 0) {
+            j[n] = x;
+            cell[n++] = y;
+        }
     }
 };
 
+// Sweep the jobs: in the cell form where `cells` has their arrays (else null).
 static ct_status launch_set(const JobSet& js, const SkConsts& c, const Schedule& sc, bool lagged,
-                            bool bary, hipStream_t st) {
+                            bool bary, const SkLayout* cells, hipStream_t st) {
     if (js.n == 0) return CT_OK;
     Launch Lc;
     std::memset(&Lc, 0, sizeof(Lc));
@@ -408,6 +504,18 @@ static ct_status launch_set(const JobSet& js, const SkConsts& c, const Schedule&
         Lc.blk_end[i] = nb;
     }
     Lc.njobs = js.n;
+    if (cells) {
+        CellLaunch C;
+        std::memset(&C, 0, sizeof(C));
+        for (int i = 0; i < js.n; ++i) C.job[i] = js.cell[i];
+        C.mode = cells->prep.mode;
+        C.nblocks = nb;
+        C.R = sc.R;
+        C.WS = sc.WS;
+        C.inv_cell = (float)(1.0 / cell_side(c.d));
+        CT_CHECK_HIP(launch_cell_sweep(c.d, sc, lagged, Lc, C, st));
+        return CT_OK;
+    }
     CT_CHECK_HIP(launch_sweep(c.d, sc, lagged, bary, Lc, nb, st));
     return CT_OK;
 }
@@ -454,6 +562,23 @@ struct SkJobs {
         j.part = L.part[2]; j.ticket = L.tick[2];
         j.out_pot = out_pot; j.out_rec = out_rec;
         return j;
+    }
+    // queries of side qs against keys of side ks, moments in buffer b
+    CellJob cell(int qs, int ks, int b) const {
+        CellJob C;
+        std::memset(&C, 0, sizeof(C));
+        if (!L.cells) return C;
+        const CellSide &Q = L.prep.side[qs], &K = L.prep.side[ks];
+        C.ncq = Q.cnt;
+        C.qcen = Q.cen;
+        C.tile = Q.tile;
+        C.ntile = Q.cnt + 2;
+        C.nch = K.cnt + 1;
+        C.chunk = K.chunk;
+        C.chcen = K.chcen;
+        C.mom = L.mom[b];
+        C.mu = L.mu[b];
+        return C;
     }
 };
 
@@ -659,7 +784,6 @@ static ct_status run_tiny(const SkLayout& L, const SkConsts& c, const ct_sinkhor
 // launches, so the default stops below.  CT_MESH forces it (CT_E_UNSUPPORTED when it
 // cannot plan); CT_FUSED, CT_UNFUSED and CT_TINY rule it out.
 constexpr double kMeshMinPairs = 40000.0;
-constexpr double kMeshAutoPairs = 1.5e7;
 constexpr unsigned kMeshWaitPolls = 1u << 18;
 
 static ct_status run_mesh(const SkLayout& L, const SkConsts& c, const ct_sinkhorn_opts* o,
@@ -732,8 +856,9 @@ static ct_status run_mesh(const SkLayout& L, const SkConsts& c, const ct_sinkhor
 
 // Iterate-and-extrapolate for one problem whose arrays are staged in L.
 static ct_status run_problem(const SkLayout& L, int T, int M, const ct_sinkhorn_opts* o,
-                             hipStream_t st, const ForkJoin* fj) {
+                             bool cells, hipStream_t st, const ForkJoin* fj) {
     const int d = o->d;
+    const SkLayout* cl = cells ? &L : nullptr;
     const bool debias = o->flags & CT_DEBIAS;
     const bool want_v = o->flags & (CT_VALUE | CT_GRAD_W);
     const bool need_ref = debias && want_v;
@@ -791,9 +916,9 @@ static ct_status run_problem(const SkLayout& L, int T, int M, const ct_sinkhorn_
         for (int k = 0; k < o->iters; ++k) {
             const bool lagged = !safe_only && (warm || k > 0);
             JobSet Sf;
-            if (debias) Sf.add(J.p(cur, true, L.p, L.xrec[2 + (cur ^ 1)], nullptr));
-            if (ref_iter) Sf.add(J.q(cur, true, L.q, L.yrec[1 + (cur ^ 1)]));
-            ct_status rc = launch_set(Sf, c, sS, lagged, false, sst);
+            if (debias) Sf.add(J.p(cur, true, L.p, L.xrec[2 + (cur ^ 1)], nullptr), J.cell(0, 0, 1));
+            if (ref_iter) Sf.add(J.q(cur, true, L.q, L.yrec[1 + (cur ^ 1)]), J.cell(1, 1, 2));
+            ct_status rc = launch_set(Sf, c, sS, lagged, false, cl, sst);
             if (rc) return rc;
             cur ^= 1;
         }
@@ -801,11 +926,11 @@ static ct_status run_problem(const SkLayout& L, int T, int M, const ct_sinkhorn_
     for (int k = 0; k < (fused ? 0 : o->iters); ++k) {
         const bool lagged = !safe_only && (warm || k > 0);
         JobSet A, B;
-        A.add(J.f(L.f, L.xrec[0], nullptr));
-        B.add(J.g(L.xrec[0], L.g, L.yrec[0]));
-        ct_status rc = launch_set(A, c, sA, lagged, false, st);
+        A.add(J.f(L.f, L.xrec[0], nullptr), J.cell(0, 1, 0));
+        B.add(J.g(L.xrec[0], L.g, L.yrec[0]), J.cell(1, 0, 0));
+        ct_status rc = launch_set(A, c, sA, lagged, false, cl, st);
         if (rc) return rc;
-        rc = launch_set(B, c, sB, lagged, false, st);
+        rc = launch_set(B, c, sB, lagged, false, cl, st);
         if (rc) return rc;
     }
     if (two_streams) {
@@ -821,14 +946,14 @@ static ct_status run_problem(const SkLayout& L, int T, int M, const ct_sinkhorn_
         JobSet F;
         F.add(J.f(L.fp, L.xrec[1], L.dy));
         if (debias) F.add(J.p(cur, false, L.pp, nullptr, L.ds));
-        ct_status rc = launch_set(F, c, sA, lagged_final, true, st);
+        ct_status rc = launch_set(F, c, sA, lagged_final, true, nullptr, st);
         if (rc) return rc;
     }
     if (want_v) {
         JobSet F;
-        F.add(J.g(L.xrec[1], L.gp, nullptr));
-        if (need_ref) F.add(J.q(ref_iter ? cur : 0, false, L.qp, nullptr));
-        ct_status rc = launch_set(F, c, sB, lagged_final, false, st);
+        F.add(J.g(L.xrec[1], L.gp, nullptr), J.cell(1, 0, 0));
+        if (need_ref) F.add(J.q(ref_iter ? cur : 0, false, L.qp, nullptr), J.cell(1, 1, 2));
+        ct_status rc = launch_set(F, c, sB, lagged_final, false, cl, st);
         if (rc) return rc;
     }
     return CT_OK;
@@ -842,7 +967,7 @@ extern "C" size_t ct_sinkhorn_workspace_size(int64_t T, int64_t M, const ct_sink
     if (!o || (o->d != 2 && o->d != 3) || T < 1 || M < 1 || T > (int64_t(1) << 30) ||
         M > (int64_t(1) << 30))
         return 0;
-    return sk_layout(nullptr, (int)T, (int)M, o->d).bytes;
+    return sk_layout(nullptr, (int)T, (int)M, o->d, true).bytes;
 }
 
 namespace ct {
@@ -874,7 +999,9 @@ static ct_status sinkhorn_grad_impl(const float* x, int64_t T64, const float* y,
     const int T = (int)T64, M = (int)M64, d = o->d;
     if (!ws) return fail(CT_E_ARG, "workspace is null");
     if (reinterpret_cast<uintptr_t>(ws) % 256) return fail(CT_E_WORKSPACE, "workspace not 256-byte aligned");
-    SkLayout L = sk_layout(ws, T, M, d);
+    // a workspace without room for the cell form's arrays serves the direct sweeps
+    SkLayout L = sk_layout(ws, T, M, d, true);
+    if (L.cells && ws_bytes < L.bytes) L = sk_layout(ws, T, M, d, false);
     if (ws_bytes < L.bytes)
         return fail(CT_E_WORKSPACE, "workspace too small: %zu < %zu bytes", ws_bytes, L.bytes);
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -897,8 +1024,35 @@ static ct_status sinkhorn_grad_impl(const float* x, int64_t T64, const float* y,
     CT_CHECK_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_origin, dim3(1), dim3(1024), 0, st, x, T, y, M, d, L.origin);
     CT_CHECK_HIP(hipGetLastError());
+    const double iter_pairs = 2.0 * T * M + (debias ? (double)T * T : 0.0) +
+                              (need_ref && !(o->flags & CT_REF_CACHED) ? (double)M * M : 0.0);
+    const bool cells = L.cells && o->iters >= kCellMinIters && iter_pairs > kMeshAutoPairs &&
+                       !(o->flags & (CT_UNFUSED | CT_DIFFERENCE | CT_SAFE_LSE | CT_FUSED | CT_TINY |
+                                     CT_MESH));
+    const bool pot_given = o->flags & (CT_WARM_START | CT_REF_CACHED);
+    const int* perm_x = nullptr;
+    const int* perm_y = nullptr;
     StageArgs A;
     A.x = x; A.y = y; A.w = w; A.pot_in = pot;
+    if (cells) {
+        // everything below works on the points in cell order; the outputs go back through
+        // the permutations
+        CellPrep& P = L.prep;
+        P.side[0].pts = x;
+        P.side[1].pts = y;
+        P.w = w;
+        P.origin = L.origin;
+        P.need_ref = need_ref ? 1 : 0;
+        P.sqrt_kappa = (float)std::sqrt(kappa_d);
+        P.pot_in = pot_given ? pot : nullptr;
+        CT_CHECK_HIP(launch_cell_prep(P, st));
+        A.x = P.xs;
+        A.y = P.ys;
+        A.w = w ? P.ws : nullptr;
+        A.pot_in = pot_given ? P.pot_s : nullptr;
+        perm_x = P.side[0].perm;
+        perm_y = P.side[1].perm;
+    }
     A.warm = (o->flags & CT_WARM_START) ? 1 : 0;
     A.ref_cached = (o->flags & CT_REF_CACHED) ? 1 : 0;
     A.T = T; A.M = M; A.d = d; A.Tpad = pad_keys(T); A.Mpad = pad_keys(M);
@@ -915,11 +1069,11 @@ static ct_status sinkhorn_grad_impl(const float* x, int64_t T64, const float* y,
     hipLaunchKernelGGL(k_stage, dim3((n + 255) / 256), dim3(256), 0, st, A);
     CT_CHECK_HIP(hipGetLastError());
 
-    rc = run_problem(L, T, M, o, st, fj);
+    rc = run_problem(L, T, M, o, cells, st, fj);
     if (rc) return rc;
 
     hipLaunchKernelGGL(k_grad_x, dim3((T * d + 255) / 256), dim3(256), 0, st, L.dy,
-                       debias ? L.ds : nullptr, T * d, (float)(2.0 / T), L.counters + 4, grad_x);
+                       debias ? L.ds : nullptr, T * d, d, (float)(2.0 / T), perm_x, L.counters + 4, grad_x);
     CT_CHECK_HIP(hipGetLastError());
     if (want_v) {
         ReduceArgs R;
@@ -932,7 +1086,8 @@ static ct_status sinkhorn_grad_impl(const float* x, int64_t T64, const float* y,
         CT_CHECK_HIP(hipGetLastError());
         if (grad_w) {
             hipLaunchKernelGGL(k_grad_w, dim3((M + 255) / 256), dim3(256), 0, st, L.gp,
-                               need_ref ? L.qp : nullptr, M, L.bG, L.wsum, L.counters + 4, grad_w);
+                               need_ref ? L.qp : nullptr, M, L.bG, L.wsum, perm_y, L.counters + 4,
+                               grad_w);
             CT_CHECK_HIP(hipGetLastError());
         }
     } else if (aux) {
@@ -943,6 +1098,17 @@ static ct_status sinkhorn_grad_impl(const float* x, int64_t T64, const float* y,
     if (aux) {
         hipLaunchKernelGGL(k_counters_out, dim3(1), dim3(64), 0, st, L.counters, aux);
         CT_CHECK_HIP(hipGetLastError());
+    }
+    if (cells) {
+        const dim3 grid((std::max(T, M) + 255) / 256);
+        if (pot)
+            hipLaunchKernelGGL(k_pot_out, grid, dim3(256), 0, st, L.f, L.g, L.p, L.q, T, M, perm_x,
+                               perm_y, pot);
+        if (pot_plus)
+            hipLaunchKernelGGL(k_pot_out, grid, dim3(256), 0, st, L.fp, L.gp, L.pp, L.qp, T, M,
+                               perm_x, perm_y, pot_plus);
+        CT_CHECK_HIP(hipGetLastError());
+        return CT_OK;
     }
     if (pot) {
         CT_CHECK_HIP(hipMemcpyAsync(pot, L.f, sizeof(float) * T, hipMemcpyDeviceToDevice, st));
@@ -1020,7 +1186,7 @@ extern "C" ct_status ct_sinkhorn_grad_static(const float* x, int64_t T64, const 
     clear_error();
     ct_status rc = validate_call(x, T64, y, M64, o, grad_x, grad_w, value, pot);
     if (rc) return rc;
-    const size_t need = sk_layout(nullptr, (int)T64, (int)M64, o->d).bytes;
+    const size_t need = sk_layout(nullptr, (int)T64, (int)M64, o->d, false).bytes;
     if (need > kStaticScratchBytes)
         return fail(CT_E_WORKSPACE,
                     "problem needs %zu bytes of scratch; the static scratch holds %zu "
@@ -1097,7 +1263,7 @@ extern "C" ct_status ct_autotune_sinkhorn(int64_t T64, int64_t M64, const ct_sin
     if (rc) return rc;
     if (!ws) return fail(CT_E_ARG, "workspace is null");
     const int T = (int)T64, M = (int)M64, d = o->d;
-    SkLayout L = sk_layout(ws, T, M, d);
+    SkLayout L = sk_layout(ws, T, M, d, false);
     if (ws_bytes < L.bytes) return fail(CT_E_WORKSPACE, "workspace too small: %zu < %zu", ws_bytes, L.bytes);
     hipStream_t st = static_cast<hipStream_t>(stream);
     rc = refuse_capture(st, "ct_autotune_sinkhorn");
@@ -1134,12 +1300,12 @@ extern "C" ct_status ct_autotune_sinkhorn(int64_t T64, int64_t M64, const ct_sin
         float best = 1e30f;
         Schedule bs = cand[0];
         for (int ci = 0; ci < nc; ++ci) {
-            ct_status rc2 = launch_set(S, c, cand[ci], true, false, st);  // warm-up
+            ct_status rc2 = launch_set(S, c, cand[ci], true, false, nullptr, st);  // warm-up
             if (rc2) return rc2;
             CT_CHECK_HIP(hipEventRecord(e0, st));
             const int reps = 3;
             for (int r = 0; r < reps; ++r) {
-                rc2 = launch_set(S, c, cand[ci], true, false, st);
+                rc2 = launch_set(S, c, cand[ci], true, false, nullptr, st);
                 if (rc2) return rc2;
             }
             CT_CHECK_HIP(hipEventRecord(e1, st));
@@ -1171,7 +1337,7 @@ extern "C" ct_status ct_status_sync(const void* ws, float resid_tol, uint32_t* n
     // the counters come before every size-dependent buffer of the layout; a stand-in
     // base (never dereferenced) gives their offset
     char* const probe = reinterpret_cast<char*>(uintptr_t(1) << 20);
-    const size_t off = static_cast<size_t>(reinterpret_cast<char*>(sk_layout(probe, 1, 1, 2).counters) - probe);
+    const size_t off = static_cast<size_t>(reinterpret_cast<char*>(sk_layout(probe, 1, 1, 2, false).counters) - probe);
     unsigned c[kCounters] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
     CT_CHECK_HIP(hipMemcpyAsync(c, static_cast<const char*>(ws) + off, sizeof(c),
                                 hipMemcpyDeviceToHost, st));
