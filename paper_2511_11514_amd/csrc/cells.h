@@ -64,6 +64,8 @@ struct CellSide {
     int4* chunk;           // [chmax] (first key, end, cell, 0)
     float4* chcen;         // [chmax] centre of the chunk's cell
     int4* tile;            // [tmax] (first query, end, cell, 0)
+    float4* phi;           // [tmax][N / 8][64] a tile's functions: products 4 i.. (lanes < 32: of
+                           // the first half of the products) of query lane % 32
     int* cnt;              // [4] cells, chunks, tiles, 1: does not fit
 };
 
@@ -72,11 +74,11 @@ struct CellPrep {
     const float* w;        // caller's reference weights or null
     const float* origin;   // [3] subtracted before scaling
     int d, ids, bits;
-    int need_ref;          // the y-y problem is swept too
     float sqrt_kappa;
     float cell;            // side of a cell, scaled
     size_t mom_cap[3];     // room for moments: cross, x-x, y-y (floats)
-    int* mode;             // out: 1 the cell form pays and fits, 0 the direct sweeps
+    int* mode;             // out: [4] of the f, g, p, q sweeps: 1 the cell form pays and fits,
+                           // 0 the direct sweep
     float *xs, *ys, *ws;   // out: points and weights in cell order
     const float* pot_in;   // [2T+2M] starting potentials or null
     float* pot_s;          // out: the same in cell order (when pot_in)
@@ -84,10 +86,13 @@ struct CellPrep {
 
 // A soft-min job in the cell form, beside its direct form (Job).
 struct CellJob {
+    const int* mode;       // 1: cell form
     const int* ncq;        // query cells (device)
     const float4* qcen;
     const int4* tile;      // query tiles
     const int* ntile;
+    const float4* phi;
+    int tmax;              // room of the tile array
     const int* nch;        // key chunks
     const int4* chunk;
     const float4* chcen;
@@ -97,9 +102,7 @@ struct CellJob {
 
 struct CellLaunch {
     CellJob job[2];
-    const int* mode;
-    int nblocks;           // work units of the direct sweep
-    int R, WS;             // its schedule
+    int R, WS;             // the direct sweep's schedule
     float inv_cell;        // 1 / w
 };
 

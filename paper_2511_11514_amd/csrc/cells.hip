@@ -287,22 +287,18 @@ __global__ __launch_bounds__(256) void k_cell_gather(CellPrep P) {
     const int d = P.d;
     const int i = (int)(blockIdx.x * 256 + threadIdx.x);
     if (i == 0) {
-        const int N = d == 2 ? CellDim<2>::N : CellDim<3>::N;
-        const size_t cx = X.cnt[0], cy = Y.cnt[0], hx = X.cnt[1], hy = Y.cnt[1];
-        const size_t cross = max(cx * hy, cy * hx) * N;
-        bool ok = X.cnt[3] == 0 && Y.cnt[3] == 0 && cross <= P.mom_cap[0] &&
-                  cx * hx * N <= P.mom_cap[1] && (!P.need_ref || cy * hy * N <= P.mom_cap[2]);
-        double cell = cell_work(X, Y) + cell_work(Y, X) + cell_work(X, X);
-        double pairs = 2.0 * X.n * Y.n + (double)X.n * X.n;
-        if (P.need_ref) {
-            cell += cell_work(Y, Y);
-            pairs += (double)Y.n * Y.n;
-        }
+        const size_t N = d == 2 ? CellDim<2>::N : CellDim<3>::N;
         // clocks of a compute unit: 128 multiply-adds per clock in the matrix cores against
         // the pair's instructions in the vector units
         const double pair = d == 2 ? 2.0 / 128 + 2.0 / 64 + 1.0 / 32 : 2.0 / 128 + 3.0 / 64 + 1.0 / 32;
-        ok = ok && cell * N / 128.0 < kCellGain * pairs * pair;
-        *P.mode = ok ? 1 : 0;
+        auto pays = [&](const CellSide& q, const CellSide& k, size_t cap) {
+            if (q.cnt[3] || k.cnt[3] || (size_t)q.cnt[0] * k.cnt[1] * N > cap) return 0;
+            return cell_work(q, k) * N / 128.0 < kCellGain * ((double)q.n * k.n) * pair ? 1 : 0;
+        };
+        P.mode[0] = pays(X, Y, P.mom_cap[0]);
+        P.mode[1] = pays(Y, X, P.mom_cap[0]);
+        P.mode[2] = pays(X, X, P.mom_cap[1]);
+        P.mode[3] = pays(Y, Y, P.mom_cap[2]);
     }
     if (i < X.n) {
         const int s = X.perm[i];
@@ -320,6 +316,58 @@ __global__ __launch_bounds__(256) void k_cell_gather(CellPrep P) {
             P.pot_s[(size_t)X.n + i] = P.pot_in[(size_t)X.n + s];
             P.pot_s[2 * (size_t)X.n + Y.n + i] = P.pot_in[2 * (size_t)X.n + Y.n + s];
         }
+    }
+}
+
+// (n ? 2 : 1) I_n(z) for n < F by the ascending series, |z| <= 1 or so.
+template <int F>
+__device__ __forceinline__ void bessel(float z, float* out, int stride) {
+    const float q = 0.25f * z * z;
+    float lead = 1.f;   // (z/2)^n / n!
+#pragma unroll
+    for (int n = 0; n < F; ++n) {
+        float s = 1.f;
+#pragma unroll
+        for (int m = 5; m >= 1; --m) s = __builtin_fmaf(s * (1.f / (float)(m * (n + m))), q, 1.f);
+        out[n * stride] = (n ? 2.f : 1.f) * lead * s;
+        lead *= 0.5f * z * (1.f / (float)(n + 1));
+    }
+}
+
+// The functions phi_n(s) of every tile's queries, laid out as the values kernel takes them.
+// They depend on the points alone: made once per call, read by every sweep (making them
+// in each sweep took as long as a whole tile's matrix products).
+template <int D>
+__global__ __launch_bounds__(256) void k_cell_functions(CellPrep P) {
+    constexpr int N = CellDim<D>::N, F = CellDim<D>::F, H = N / 2;
+    __shared__ float in[D * F * 33];
+    const CellSide& S = P.side[blockIdx.y];
+    const float* pts = blockIdx.y ? P.ys : P.xs;
+    if (S.cnt[3]) return;
+    const int nt = S.cnt[2], tid = (int)threadIdx.x, col = tid & 31;
+    const float inv = 2.f / P.cell;
+    for (int t = (int)blockIdx.x; t < nt; t += (int)gridDim.x) {
+        const int4 tl = S.tile[t];
+        if ((tid >> 5) < D) {
+            const int x = tid >> 5;
+            const float4 c = S.cen[tl.z];
+            const int q = min(tl.x + col, tl.y - 1);
+            const float v = (pts[(size_t)q * D + x] - P.origin[x]) * P.sqrt_kappa;
+            const float s = (v - (x == 0 ? c.x : x == 1 ? c.y : c.z)) * inv;   // on [-1, 1]
+            bessel<F>((float)CellDim<D>::lambda * s, in + x * F * 33 + col, 33);
+        }
+        __syncthreads();
+        for (int e = tid; e < H * 16; e += 256) {
+            const int lane = e & 63, i = e >> 6;
+            float p[4];
+            for (int k = 0; k < 4; ++k) {
+                const int n = (lane >> 5) * H + 4 * i + k;
+                p[k] = 1.f;
+                for (int x = 0; x < D; ++x) p[k] *= in[(x * F + term<D>(n, x)) * 33 + (lane & 31)];
+            }
+            S.phi[(size_t)t * (H * 16) + e] = make_float4(p[0], p[1], p[2], p[3]);
+        }
+        __syncthreads();
     }
 }
 
@@ -377,8 +425,14 @@ __device__ __forceinline__ void cell_moments(const CellJob& C, const Job& J, int
     __syncthreads();
     const int kw = nkp >> 2, kb = wave * kw;   // even, this wave's keys [kb, kb + kw)
     float mx = kNegInf;
-#pragma unroll 4
-    for (int k = 0; k < kw; k += 2) mx = fmaxf(mx, expo(sm.key[kb + k + half]));
+    int k1 = 0;
+    for (; k1 + 8 <= kw; k1 += 8) {
+        float e[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) e[i] = expo(sm.key[kb + k1 + 2 * i + half]);
+        mx = fmaxf(mx, fmaxf(fmaxf(e[0], e[1]), fmaxf(e[2], e[3])));
+    }
+    for (; k1 < kw; k1 += 2) mx = fmaxf(mx, expo(sm.key[kb + k1 + half]));
     mx = fmaxf(mx, __shfl_xor(mx, 32));
     if (half == 0) sm.mu[wave][col] = mx;
     __syncthreads();
@@ -409,16 +463,24 @@ __device__ __forceinline__ void cell_moments(const CellJob& C, const Job& J, int
             }
         }
         __builtin_amdgcn_wave_barrier();
-        for (int p = 0; p < nn; p += 2) {
-            const int k = p + half;
-            const float W = ex2(expo(sm.key[kb + k0 + k]) - shift);
+        auto step = [&](int k, float W) {
 #pragma unroll
             for (int t = 0; t < CT; ++t) {
                 float b = tab[row[t][0] + k] * tab[row[t][1] + k];
                 if (D == 3) b *= tab[row[t][D - 1] + k];
                 acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(W, b, acc[t], 0, 0, 0);
             }
+        };
+        // four steps' LDS reads in flight together
+        int p = 0;
+        for (; p + 8 <= nn; p += 8) {
+            float W[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) W[i] = ex2(expo(sm.key[kb + k0 + p + 2 * i + half]) - shift);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) step(p + 2 * i + half, W[i]);
         }
+        for (; p < nn; p += 2) step(p + half, ex2(expo(sm.key[kb + k0 + p + half]) - shift));
     }
     // the four waves' sums, 32 products at a time (4 KB per wave in the keys' place)
     float* red = reinterpret_cast<float*>(sm.key);
@@ -445,70 +507,52 @@ __device__ __forceinline__ void cell_moments(const CellJob& C, const Job& J, int
 
 // --------------------------------------------------------------------- values
 
-// (n ? 2 : 1) I_n(z) for n < F by the ascending series, |z| <= 1 or so.
-template <int F>
-__device__ __forceinline__ void bessel(float z, float* out, int stride) {
-    const float q = 0.25f * z * z;
-    float lead = 1.f;   // (z/2)^n / n!
-#pragma unroll
-    for (int n = 0; n < F; ++n) {
-        float s = 1.f;
-#pragma unroll
-        for (int m = 5; m >= 1; --m) s = __builtin_fmaf(s * (1.f / (float)(m * (n + m))), q, 1.f);
-        out[n * stride] = (n ? 2.f : 1.f) * lead * s;
-        lead *= 0.5f * z * (1.f / (float)(n + 1));
-    }
-}
-
 template <int D>
 struct ValueSmem {
-    float in[D * CellDim<D>::F * 33];   // phi_n per axis of 32 queries, rows of 33
     float4 cd[4][kCellTile];            // per wave: (-2d, mu - |d|^2) of 32 chunks
     float red[4][kCellTile];
-    int flist[kCellTile];
+    int flist[4 * kCellTile];
     int nflag;
 };
 
-// Values of one tile of 32 queries.  The waves take every fourth tile of 32 chunks; an
-// MFMA multiplies the chunks' moments (A: lane = chunk) with the queries' functions (B:
-// lane = query), so that a lane holds 16 chunks' sums of its own query.
-template <int D, bool LAGGED>
-__device__ __forceinline__ void cell_values(const CellJob& C, const Job& J, int u, int nch,
-                                            float inv_cell, float kappa, float inv_kappa,
-                                            float inv_sqrt_kappa, ValueSmem<D>& sm) {
-    constexpr int N = CellDim<D>::N, F = CellDim<D>::F, H = N / 2;
+// Values of tiles of 32 queries: WS waves of a block share a tile (each takes every WS-th
+// tile of 32 chunks), 4 / WS tiles per block.  An MFMA multiplies the chunks' moments (A:
+// lane = chunk) with the queries' functions (B: lane = query), so that a lane holds 16
+// chunks' sums of its own query.
+template <int D, bool LAGGED, int WS>
+__device__ __forceinline__ void cell_values(const CellJob& C, const Job& J, int u, int nt, int nch,
+                                            float kappa, float inv_kappa, float inv_sqrt_kappa,
+                                            ValueSmem<D>& sm) {
+    constexpr int N = CellDim<D>::N, H = N / 2;
     const int tid = (int)threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, col = lane & 31, half = lane >> 5;
-    const int4 tl = C.tile[u];
+    const int part = wave % WS, ti = min(u * (4 / WS) + wave / WS, C.tmax - 1);
+    const int4 t0 = C.tile[ti];   // in its array whatever nt is, so the load need not wait for it
+    const bool on = ti < nt;
+    const int4 tl = on ? t0 : make_int4(0, 1, 0, 0);
+    const int ntc = on ? (nch + kCellTile - 1) / kCellTile : 0;
+    // 4 V products of a chunk's moments per step, read one step ahead
+    constexpr int V = D == 2 ? 8 : 4, G = H / (4 * V);
+    auto load = [&](int ct, int g, float4 (&A)[V]) {
+        const int c = min(ct * kCellTile + col, nch - 1);
+        const float4* M = reinterpret_cast<const float4*>(
+            C.mom + ((size_t)tl.z * nch + c) * N + half * H) + g * V;
+#pragma unroll
+        for (int i = 0; i < V; ++i) A[i] = M[i];
+    };
+    float4 A[V];
+    if (part < ntc) load(part, 0, A);
+    float4 b[H / 4];
+#pragma unroll
+    for (int i = 0; i < H / 4; ++i) b[i] = C.phi[((size_t)ti * (H / 4) + i) * 64 + lane];
     const float4 qc = C.qcen[tl.z];
     const int q = min(tl.x + col, tl.y - 1);
     const float4 v = J.qrec[q];
     const float sx = v.x - qc.x, sy = v.y - qc.y, sz = D == 3 ? v.z - qc.z : 0.f;
     const float sq = __builtin_fmaf(sx, sx, __builtin_fmaf(sy, sy, sz * sz));
+    const float old = J.qpot[q], lw = J.qlog2w ? J.qlog2w[q] : J.qlog2w_s;
     if (tid == 0) sm.nflag = 0;
-    if ((tid >> 5) < D) {
-        const int x = tid >> 5;
-        const float s = (x == 0 ? sx : x == 1 ? sy : sz) * 2.f * inv_cell;   // on [-1, 1]
-        bessel<F>((float)CellDim<D>::lambda * s, sm.in + x * F * 33 + col, 33);
-    }
-    __syncthreads();
-    // the functions' places in LDS, kept out of registers that live across tiles
-    int sel = half, colv = col;
-    float b[H];
-#pragma unroll
-    for (int s = 0; s < H; ++s) {
-        if (s % 8 == 0) asm volatile("" : "+v"(sel), "+v"(colv));
-        float p = 1.f;
-#pragma unroll
-        for (int x = 0; x < D; ++x) {
-            const int r0 = (x * F + term<D>(s, x)) * 33, r1 = (x * F + term<D>(s + H, x)) * 33;
-            const float f = sm.in[(sel ? r1 : r0) + colv];
-            p = x == 0 ? f : p * f;
-        }
-        b[s] = p;
-        asm volatile("" : "+v"(b[s]));
-    }
     float4* cd = sm.cd[wave];
     auto load_cd = [&](int ct) {
         // (-2d, mu - |d|^2) of the tile's chunks; past the last one mu = -inf
@@ -528,39 +572,30 @@ __device__ __forceinline__ void cell_values(const CellJob& C, const Job& J, int 
         if (D == 3) e = __builtin_fmaf(sz, k.z, e);
         return __builtin_fmaf(sx, k.x, e) + base;
     };
-    const int ntc = (nch + kCellTile - 1) / kCellTile;
     float m;
     if (LAGGED) {
-        m = -J.qpot[q] * kappa;
+        m = -old * kappa;
     } else {
         m = kNegInf;
-        for (int ct = wave; ct < ntc; ct += 4) {
+        for (int ct = part; ct < ntc; ct += WS) {
             load_cd(ct);
 #pragma unroll
             for (int r = 0; r < 16; ++r) m = fmaxf(m, expo(r, -sq));
         }
         m = fmaxf(m, __shfl_xor(m, 32));
-        if (half == 0) sm.red[wave][col] = m;
-        __syncthreads();
-        m = fmaxf(fmaxf(sm.red[0][col], sm.red[1][col]), fmaxf(sm.red[2][col], sm.red[3][col]));
+        if (WS > 1) {
+            if (half == 0) sm.red[wave][col] = m;
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < WS; ++w) m = fmaxf(m, sm.red[wave - part + w][col]);
+            __syncthreads();
+        }
         if (m == kNegInf) m = 0.f;
-        __syncthreads();
     }
     const float base = -sq - m;
     float sum = 0.f;
-    // 4 V products of a chunk's moments per step, read one step ahead
-    constexpr int V = D == 2 ? 8 : 4, G = H / (4 * V);
-    auto load = [&](int ct, int g, float4 (&A)[V]) {
-        const int c = min(ct * kCellTile + col, nch - 1);
-        const float4* M = reinterpret_cast<const float4*>(
-            C.mom + ((size_t)tl.z * nch + c) * N + half * H) + g * V;
-#pragma unroll
-        for (int i = 0; i < V; ++i) A[i] = M[i];
-    };
-    float4 A[V];
-    if (wave < ntc) load(wave, 0, A);
 #pragma unroll 1
-    for (int ct = wave; ct < ntc; ct += 4) {
+    for (int ct = part; ct < ntc; ct += WS) {
         load_cd(ct);
         f32x16 acc;
 #pragma unroll
@@ -569,14 +604,15 @@ __device__ __forceinline__ void cell_values(const CellJob& C, const Job& J, int 
         for (int g = 0; g < G; ++g) {
             float4 nx[V];
             if (g + 1 < G) load(ct, g + 1, nx);
-            else load(min(ct + 4, ntc - 1), 0, nx);
+            else load(min(ct + WS, ntc - 1), 0, nx);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < V; ++i) {
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(A[i].x, b[4 * (g * V + i)], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(A[i].y, b[4 * (g * V + i) + 1], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(A[i].z, b[4 * (g * V + i) + 2], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(A[i].w, b[4 * (g * V + i) + 3], acc, 0, 0, 0);
+                const float4 f = b[g * V + i];
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(A[i].x, f.x, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(A[i].y, f.y, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(A[i].z, f.z, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(A[i].w, f.w, acc, 0, 0, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -586,13 +622,22 @@ __device__ __forceinline__ void cell_values(const CellJob& C, const Job& J, int 
         for (int r = 0; r < 16; ++r) sum = __builtin_fmaf(acc[r], ex2(expo(r, base)), sum);
     }
     sum += __shfl_xor(sum, 32);
-    if (half == 0) sm.red[wave][col] = sum;
+    if (WS > 1 && half == 0) sm.red[wave][col] = sum;
     __syncthreads();
-    if (tid < kCellTile) {
-        const float s = (sm.red[0][tid] + sm.red[1][tid]) + (sm.red[2][tid] + sm.red[3][tid]);
-        if (tl.x + tid < tl.y)
-            finish_or_flag<D, LAGGED>(J, tl.x + tid, m, s, nullptr, sm.flist, &sm.nflag, kappa,
-                                      inv_kappa, inv_sqrt_kappa);
+    if (part == 0 && half == 0 && on && tl.x + col < tl.y) {
+        float s = sum;
+#pragma unroll
+        for (int w = 1; w < WS; ++w) s += sm.red[wave + w][col];
+        if (LAGGED && !(s >= kSumLo && s <= kSumHi)) {
+            sm.flist[atomicAdd(&sm.nflag, 1)] = q;
+        } else {
+            // as finish_row, with the loads already there
+            const float t = -(m + __log2f(s)) * inv_kappa;
+            const float nv = J.self_avg ? 0.5f * (old + t) : t;
+            J.out_pot[q] = nv;
+            if (J.out_rec)
+                reinterpret_cast<float*>(J.out_rec + q)[D == 2 ? 2 : 3] = __builtin_fmaf(nv, kappa, lw);
+        }
     }
     __syncthreads();
     if (LAGGED) {
@@ -610,61 +655,72 @@ union StepSmem {
     SweepSmem<D, R> s;
 };
 
-// First launch of a sweep: the moments of every (chunk, 32 query cells) of its jobs, or
-// the direct sweep's work units.  Both walk their units with the grid as the stride: how
-// many there are is known on the device only.
+// First launch of a sweep: of each job the moments of every (chunk, 32 query cells), or the
+// direct sweep's work units.  The units are walked with the grid as the stride: how many
+// there are is known on the device only.
 template <int D, int R, int WS, bool LAGGED>
 __global__ __launch_bounds__(kBlock, 2) void k_cell_moments(Launch L, CellLaunch C) {
     __shared__ StepSmem<D, R> sm;
     const int grid = (int)gridDim.x;
-    if (*C.mode) {
-        int u = (int)blockIdx.x;
-        for (int j = 0; j < L.njobs; ++j) {
-            const int nch = *C.job[j].nch, ncq = *C.job[j].ncq;
-            const int nu = nch * ((ncq + kCellTile - 1) / kCellTile);
-            for (; u < nu; u += grid)
-                cell_moments<D>(C.job[j], L.job[j], u % nch, u / nch, nch, ncq, C.inv_cell, sm.m);
-            u -= nu;
-        }
-        return;
-    }
-    for (int b = (int)blockIdx.x; b < C.nblocks; b += grid) {
-        int j = 0;
-        while (j + 1 < L.njobs && b >= L.blk_end[j]) ++j;
+    int u = (int)blockIdx.x;
+    // both jobs' counts at once (job[1] repeats job[0] where there is one)
+    const int mode[2] = {*C.job[0].mode, *C.job[1].mode};
+    const int nchs[2] = {*C.job[0].nch, *C.job[1].nch}, ncqs[2] = {*C.job[0].ncq, *C.job[1].ncq};
+    for (int j = 0; j < L.njobs; ++j) {
         const Job& J = L.job[j];
-        const int local = b - (j ? L.blk_end[j - 1] : 0);
-        sweep_unit<D, R, WS, LAGGED, false, true, LAGGED>(J, local % J.nqb, local / J.nqb, L.kappa,
-                                                          L.inv_kappa, L.inv_sqrt_kappa, sm.s);
-        __syncthreads();
+        const CellJob& K = C.job[j];
+        int nu;
+        if (j ? mode[1] : mode[0]) {
+            const int nch = j ? nchs[1] : nchs[0], ncq = j ? ncqs[1] : ncqs[0];
+            nu = nch * ((ncq + kCellTile - 1) / kCellTile);
+            for (; u < nu; u += grid)
+                cell_moments<D>(K, J, u % nch, u / nch, nch, ncq, C.inv_cell, sm.m);
+        } else {
+            nu = J.nqb * J.splits;
+            for (; u < nu; u += grid) {
+                sweep_unit<D, R, WS, LAGGED, false, true, LAGGED>(
+                    J, u % J.nqb, u / J.nqb, L.kappa, L.inv_kappa, L.inv_sqrt_kappa, sm.s);
+                __syncthreads();
+            }
+        }
+        u -= nu;
     }
 }
 
 // Second launch: the values of every query tile, or the direct sweep's merge.
-template <int D, bool LAGGED>
+template <int D, bool LAGGED, int VS>
 __global__ __launch_bounds__(kBlock, 2) void k_cell_values(Launch L, CellLaunch C) {
+    __shared__ ValueSmem<D> sm;
     const int grid = (int)gridDim.x;
-    if (*C.mode) {
-        __shared__ ValueSmem<D> sm;
-        int u = (int)blockIdx.x;
-        for (int j = 0; j < L.njobs; ++j) {
-            const int nch = *C.job[j].nch, nt = *C.job[j].ntile;
-            for (; u < nt; u += grid)
-                cell_values<D, LAGGED>(C.job[j], L.job[j], u, nch, C.inv_cell, L.kappa,
-                                       L.inv_kappa, L.inv_sqrt_kappa, sm);
-            u -= nt;
-        }
-        return;
-    }
-    int b = (int)blockIdx.x;
+    int u = (int)blockIdx.x;
+    const int mode[2] = {*C.job[0].mode, *C.job[1].mode};
+    const int nchs[2] = {*C.job[0].nch, *C.job[1].nch}, nts[2] = {*C.job[0].ntile, *C.job[1].ntile};
     for (int j = 0; j < L.njobs; ++j) {
         const Job& J = L.job[j];
-        const int nb = J.splits > 1 ? (J.nq + kMergeRows - 1) / kMergeRows : 0;
-        for (; b < nb; b += grid) {
-            merge_block<D, LAGGED, false>(J, b * kMergeRows, J.nqb * 64 * C.R * (4 / C.WS), L.kappa,
-                                          L.inv_kappa, L.inv_sqrt_kappa);
-            __syncthreads();
+        const CellJob& K = C.job[j];
+        int nu;
+        if (j ? mode[1] : mode[0]) {
+            const int nch = j ? nchs[1] : nchs[0], nt = j ? nts[1] : nts[0];
+            nu = (nt + 4 / VS - 1) / (4 / VS);
+            // workgroup b runs on die b mod 8, each with its own L2: a die takes a run of tiles,
+            // which share their cells' moments
+            const int per = (nu + 7) >> 3;
+            for (; u < 8 * per; u += grid) {
+                const int v = (u & 7) * per + (u >> 3);
+                if (v < nu)
+                    cell_values<D, LAGGED, VS>(K, J, v, nt, nch, L.kappa, L.inv_kappa,
+                                               L.inv_sqrt_kappa, sm);
+            }
+            nu = 8 * per;
+        } else {
+            nu = J.splits > 1 ? (J.nq + kMergeRows - 1) / kMergeRows : 0;
+            for (; u < nu; u += grid) {
+                merge_block<D, LAGGED, false>(J, u * kMergeRows, J.nqb * 64 * C.R * (4 / C.WS),
+                                              L.kappa, L.inv_kappa, L.inv_sqrt_kappa);
+                __syncthreads();
+            }
         }
-        b -= nb;
+        u -= nu;
     }
 }
 
@@ -701,15 +757,15 @@ hipError_t moments_d(bool lagged, const Launch& L, const CellLaunch& C, int nb, 
     }
 }
 
-template <int D>
+template <int D, int VS>
 hipError_t values_d(bool lagged, const Launch& L, const CellLaunch& C, int nb, hipStream_t s,
                     hipEvent_t e0, hipEvent_t e1) {
     auto go = [&](auto kernel) {
         if (e0) hipExtLaunchKernelGGL(kernel, dim3(nb), dim3(kBlock), 0, s, e0, e1, 0, L, C);
         else hipLaunchKernelGGL(kernel, dim3(nb), dim3(kBlock), 0, s, L, C);
     };
-    if (lagged) go(k_cell_values<D, true>);
-    else go(k_cell_values<D, false>);
+    if (lagged) go(k_cell_values<D, true, VS>);
+    else go(k_cell_values<D, false, VS>);
     return hipGetLastError();
 }
 
@@ -720,7 +776,10 @@ double cell_side(int d) {
     return std::sqrt(2.0 * lambda / 0.6931471805599453);
 }
 
-int cell_chunk(int n) { return n <= 32768 ? 256 : n <= 131072 ? 512 : kCellChunkMax; }
+// Smaller chunks make more, evener work of the moments and more chunks for the values (one
+// iteration with 256 / 512 / 1024 keys: 46 / 48 / 55 us at M = 16384, 68 / 65 / 75 at 30001,
+// 537 / 407 / 385 at 262144).
+int cell_chunk(int n) { return n <= 24576 ? 256 : n <= 131072 ? 512 : kCellChunkMax; }
 
 hipError_t launch_cell_prep(const CellPrep& P, hipStream_t s) {
     const int nbm = std::max(P.side[0].nb, P.side[1].nb);
@@ -732,23 +791,33 @@ hipError_t launch_cell_prep(const CellPrep& P, hipStream_t s) {
     hipLaunchKernelGGL(k_cell_lists, dim3(2), dim3(1024), 0, s, P);
     hipLaunchKernelGGL(k_cell_scatter, dim3(nbm, 2), dim3(64), 0, s, P);
     hipLaunchKernelGGL(k_cell_gather, dim3((n + 255) / 256), dim3(256), 0, s, P);
+    const dim3 gf(std::min(2048, n / kCellTile + 128), 2);
+    if (P.d == 2) hipLaunchKernelGGL(k_cell_functions<2>, gf, dim3(256), 0, s, P);
+    else hipLaunchKernelGGL(k_cell_functions<3>, gf, dim3(256), 0, s, P);
     return hipGetLastError();
 }
 
 hipError_t launch_cell_sweep(int d, const Schedule& sc, bool lagged, const Launch& L,
                              const CellLaunch& C, hipStream_t s) {
-    // grids for the units one can expect (both kernels walk whatever there is)
-    int units = 0, tiles = 0, merges = 0;
+    // grids for the units one can expect, up to the blocks that are resident at once (both
+    // kernels walk whatever there is; blocks beyond that only queue)
+    int units = 0, tiles = 0, direct = 0, merges = 0;
     double pairs = 0.0;
     for (int j = 0; j < L.njobs; ++j) {
         const Job& J = L.job[j];
-        units += (J.nk / cell_chunk(J.nk) + 128) * 4;
-        tiles += J.nq / kCellTile + 128;
+        units += (J.nk / cell_chunk(J.nk) + 64) * 4;
+        tiles += J.nq / kCellTile + 64;
+        direct += J.nqb * J.splits;
         if (J.splits > 1) merges += (J.nq + kMergeRows - 1) / kMergeRows;
         pairs += (double)J.nq * J.nk;
     }
-    const int nm = std::min(2048, std::max(units, std::min(C.nblocks, 2048)));
-    const int nv = std::min(4096, std::max(tiles, merges));
+    // Waves per tile of the values: few tiles leave the GPU idle unless several waves share one,
+    // many repeat the tile's loads (one iteration at T = 4096, M = 16384: 46 us with 4 waves, 48
+    // with 2, 52 with 1; T = 9001, M = 30001: 68, 63, 69; T = 65536, M = 262144: 438, 406, 405).
+    const int vs = tiles < 900 ? 4 : tiles < 3000 ? 2 : 1;
+    // In 3-D a launch can mix a direct sweep, which prefers resident blocks only.
+    const int nm = std::min(d == 2 ? 4096 : 768, std::max(units, std::min(direct, 768)));
+    const int nv = std::min(1024, std::max((tiles * vs + 3) / 4, merges));
     const int code = sc.R * 100 + sc.WS * 10 + sc.sep + (lagged && L.expanded ? 1000 : 0);
     hipEvent_t e0, e1;
     void* tok = profile_kernel_begin(&e0, &e1);
@@ -758,7 +827,12 @@ hipError_t launch_cell_sweep(int d, const Schedule& sc, bool lagged, const Launc
     profile_kernel_end(tok, 50 + lagged, 0, code, nm, pairs);
     if (e != hipSuccess) return e;
     tok = profile_kernel_begin(&e0, &e1);
-    e = d == 2 ? values_d<2>(lagged, L, C, nv, s, e0, e1) : values_d<3>(lagged, L, C, nv, s, e0, e1);
+    if (vs == 4)
+        e = d == 2 ? values_d<2, 4>(lagged, L, C, nv, s, e0, e1) : values_d<3, 4>(lagged, L, C, nv, s, e0, e1);
+    else if (vs == 2)
+        e = d == 2 ? values_d<2, 2>(lagged, L, C, nv, s, e0, e1) : values_d<3, 2>(lagged, L, C, nv, s, e0, e1);
+    else
+        e = d == 2 ? values_d<2, 1>(lagged, L, C, nv, s, e0, e1) : values_d<3, 1>(lagged, L, C, nv, s, e0, e1);
     profile_kernel_end(tok, 60 + lagged, 0, code, nv, 0.0);
     return e;
 }

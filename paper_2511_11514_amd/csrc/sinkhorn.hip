@@ -374,9 +374,10 @@ static void cell_layout(Arena& a, SkLayout& L, int T, int M, int d) {
         S.chunk = a.take<int4>(S.chmax);
         S.chcen = a.take<float4>(S.chmax);
         S.tile = a.take<int4>(S.tmax);
+        S.phi = a.take<float4>((size_t)S.tmax * N * 8);
         S.cnt = a.take<int>(4);
     }
-    P.mode = a.take<int>(1);
+    P.mode = a.take<int>(4);
     P.xs = a.take<float>((size_t)T * d);
     P.ys = a.take<float>((size_t)M * d);
     P.ws = a.take<float>(M);
@@ -507,9 +508,7 @@ static ct_status launch_set(const JobSet& js, const SkConsts& c, const Schedule&
     if (cells) {
         CellLaunch C;
         std::memset(&C, 0, sizeof(C));
-        for (int i = 0; i < js.n; ++i) C.job[i] = js.cell[i];
-        C.mode = cells->prep.mode;
-        C.nblocks = nb;
+        for (int i = 0; i < 2; ++i) C.job[i] = js.cell[std::min(i, js.n - 1)];
         C.R = sc.R;
         C.WS = sc.WS;
         C.inv_cell = (float)(1.0 / cell_side(c.d));
@@ -563,16 +562,20 @@ struct SkJobs {
         j.out_pot = out_pot; j.out_rec = out_rec;
         return j;
     }
-    // queries of side qs against keys of side ks, moments in buffer b
-    CellJob cell(int qs, int ks, int b) const {
+    // queries of side qs against keys of side ks (0: x, 1: y)
+    CellJob cell(int qs, int ks) const {
         CellJob C;
         std::memset(&C, 0, sizeof(C));
         if (!L.cells) return C;
         const CellSide &Q = L.prep.side[qs], &K = L.prep.side[ks];
+        const int b = qs != ks ? 0 : 1 + qs;   // the moments' buffer
+        C.mode = L.prep.mode + (qs != ks ? qs : 2 + qs);
         C.ncq = Q.cnt;
         C.qcen = Q.cen;
         C.tile = Q.tile;
         C.ntile = Q.cnt + 2;
+        C.phi = Q.phi;
+        C.tmax = Q.tmax;
         C.nch = K.cnt + 1;
         C.chunk = K.chunk;
         C.chcen = K.chcen;
@@ -916,8 +919,8 @@ static ct_status run_problem(const SkLayout& L, int T, int M, const ct_sinkhorn_
         for (int k = 0; k < o->iters; ++k) {
             const bool lagged = !safe_only && (warm || k > 0);
             JobSet Sf;
-            if (debias) Sf.add(J.p(cur, true, L.p, L.xrec[2 + (cur ^ 1)], nullptr), J.cell(0, 0, 1));
-            if (ref_iter) Sf.add(J.q(cur, true, L.q, L.yrec[1 + (cur ^ 1)]), J.cell(1, 1, 2));
+            if (debias) Sf.add(J.p(cur, true, L.p, L.xrec[2 + (cur ^ 1)], nullptr), J.cell(0, 0));
+            if (ref_iter) Sf.add(J.q(cur, true, L.q, L.yrec[1 + (cur ^ 1)]), J.cell(1, 1));
             ct_status rc = launch_set(Sf, c, sS, lagged, false, cl, sst);
             if (rc) return rc;
             cur ^= 1;
@@ -926,8 +929,8 @@ static ct_status run_problem(const SkLayout& L, int T, int M, const ct_sinkhorn_
     for (int k = 0; k < (fused ? 0 : o->iters); ++k) {
         const bool lagged = !safe_only && (warm || k > 0);
         JobSet A, B;
-        A.add(J.f(L.f, L.xrec[0], nullptr), J.cell(0, 1, 0));
-        B.add(J.g(L.xrec[0], L.g, L.yrec[0]), J.cell(1, 0, 0));
+        A.add(J.f(L.f, L.xrec[0], nullptr), J.cell(0, 1));
+        B.add(J.g(L.xrec[0], L.g, L.yrec[0]), J.cell(1, 0));
         ct_status rc = launch_set(A, c, sA, lagged, false, cl, st);
         if (rc) return rc;
         rc = launch_set(B, c, sB, lagged, false, cl, st);
@@ -951,8 +954,8 @@ static ct_status run_problem(const SkLayout& L, int T, int M, const ct_sinkhorn_
     }
     if (want_v) {
         JobSet F;
-        F.add(J.g(L.xrec[1], L.gp, nullptr), J.cell(1, 0, 0));
-        if (need_ref) F.add(J.q(ref_iter ? cur : 0, false, L.qp, nullptr), J.cell(1, 1, 2));
+        F.add(J.g(L.xrec[1], L.gp, nullptr), J.cell(1, 0));
+        if (need_ref) F.add(J.q(ref_iter ? cur : 0, false, L.qp, nullptr), J.cell(1, 1));
         ct_status rc = launch_set(F, c, sB, lagged_final, false, cl, st);
         if (rc) return rc;
     }
@@ -1042,7 +1045,6 @@ static ct_status sinkhorn_grad_impl(const float* x, int64_t T64, const float* y,
         P.side[1].pts = y;
         P.w = w;
         P.origin = L.origin;
-        P.need_ref = need_ref ? 1 : 0;
         P.sqrt_kappa = (float)std::sqrt(kappa_d);
         P.pot_in = pot_given ? pot : nullptr;
         CT_CHECK_HIP(launch_cell_prep(P, st));
