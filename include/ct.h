@@ -116,9 +116,10 @@ const char* ct_version(void);
                            library picks, by the point pairs of one iteration: the
                            one-workgroup solve up to 4e4, the exchange solve up to 1.5e7 where
                            it plans, else the one-workgroup solve up to 1.5e5, the fused
-                           solve up to 1.05e6, and per-sweep launches beyond.  Above 1.5e7
-                           pairs, from 8 iterations on, those launches take the cell form of
-                           a sweep where it pays (a grid of cells over each point set, sums
+                           solve up to 1.05e6, and per-sweep launches beyond.  Above 1e8
+                           pairs (d = 3: where a sweep has 1.2e9), from 8 iterations and 1e10
+                           pairs in all on, those launches take the cell form of a sweep
+                           where it pays (a grid of cells over each point set, sums
                            over pairs of cells by truncated expansions that leave out less
                            than 1e-7 of any pair's term; decided on the device), unless
                            CT_UNFUSED, CT_DIFFERENCE or CT_SAFE_LSE is given or the
@@ -140,7 +141,7 @@ typedef struct ct_sinkhorn_opts {
     uint32_t flags; /* CT_* flags above */
 } ct_sinkhorn_opts;
 
-/* Workspace bytes needed by ct_sinkhorn_grad for these sizes and options.  From 1.5e7 point
+/* Workspace bytes needed by ct_sinkhorn_grad for these sizes and options.  From 1e8 point
  * pairs per iteration on, most of it holds the cell form's moments (at most 384 MiB for each
  * of three buffers: 253 MB in all at T = 4096, M = 16384, 1.4 GB at T = 65536, M = 262144).
  * A smaller workspace that holds the rest is accepted and gets the direct sweeps. */
@@ -261,7 +262,10 @@ ct_status ct_status_sync(const void* ws, float resid_tol, uint32_t* nonfinite, u
  *   lockstep (CT_UNFUSED, and the default otherwise): two launches per iteration
  *     (every problem's f and self updates, then every problem's g update) over
  *     job tables prepared in the workspace, each job split over keys so that all
- *     blocks sweep about the same number of pairs;
+ *     blocks sweep about the same number of pairs; without CT_UNFUSED, from 8
+ *     iterations and the pairs per iteration of one problem on (at most 341
+ *     problems), a problem's sweeps take the cell form where it pays (as for one
+ *     problem; decided on the device);
  *   persistent (CT_PERSISTENT): one kernel that walks a dependency-ordered work
  *     list.
  * The extrapolation pass and the reductions follow as lockstep launches in every

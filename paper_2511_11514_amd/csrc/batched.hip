@@ -42,6 +42,7 @@
 #include <numeric>
 #include <vector>
 
+#include "cells.h"
 #include "ct_internal.h"
 #include "sweep_device.h"
 
@@ -106,6 +107,10 @@ struct BLayout {
     int* lmrg;              // [kLockKinds][3B] merge-block prefix ends
     MeshArgs* mtab;         // [B] exchange-solve arguments per problem
     int* mblk;              // [B] exchange-solve block prefix ends
+    CellBatch cells;        // the cell form's tables and pool (B = 0: none)
+    int *permx, *permy;     // [sumT], [sumM] sorted place -> index within the problem
+    float *xs, *ys, *ws;    // inputs in cell order
+    char* cell_part;        // the partitions' arrays
     float* lpart;           // partial sums of split lockstep jobs (one launch at a time)
     unsigned* done;         // [B] completed units per problem
     unsigned* head;         // [1] next unit
@@ -123,10 +128,20 @@ struct BLayout {
     size_t table_bytes;     // bytes of the host-built table (header .. mblk)
 };
 
+// Room that a batch's cell form takes: the partitions' arrays and the moments' pool.
+struct CellRoom {
+    bool on = false;
+    size_t part_bytes = 0;   // partitions of all problems
+    long long rows = 0;      // (query cell, chunk) pairs of the pool
+    int max_n = 0, max_nb = 0;
+};
+
 static BLayout b_layout(void* ws, int B, int64_t sumT, int64_t sumM, int64_t sumTpad,
-                        int64_t sumMpad, int d, size_t part_floats) {
+                        int64_t sumMpad, int d, size_t part_floats, const CellRoom& room) {
     Arena a(ws);
     BLayout L;
+    std::memset(&L.cells, 0, sizeof(L.cells));
+    L.permx = L.permy = nullptr;
     L.hdr = a.take<BHeader>(1);
     L.prob = a.take<BProb>(B);
     L.order = a.take<int>(B);
@@ -165,6 +180,26 @@ static BLayout b_layout(void* ws, int B, int64_t sumT, int64_t sumM, int64_t sum
     L.dy = a.take<float>((size_t)sumT * d);
     L.ds = a.take<float>((size_t)sumT * d);
     L.xch = a.take<unsigned long long>(4 * ((size_t)sumT + sumM));
+    if (room.on) {
+        const size_t N = d == 2 ? CellDim<2>::N : CellDim<3>::N;
+        L.cells.B = B;
+        L.cells.kinds = kLockKinds;
+        L.cells.stride = 3 * B;
+        L.cells.rows = room.rows;
+        L.cells.prep = a.take<CellPrep>(B);
+        L.cells.jobs = a.take<CellJob>((size_t)kLockKinds * 3 * B);
+        L.cells.njobs = a.take<int>(kLockKinds);
+        L.cells.uend = a.take<int>((size_t)kLockKinds * 2 * 3 * B);
+        L.cells.info = a.take<int>(kLockKinds);
+        L.xs = a.take<float>((size_t)sumT * d);
+        L.ys = a.take<float>((size_t)sumM * d);
+        L.ws = a.take<float>(sumM);
+        L.permx = a.take<int>(sumT);
+        L.permy = a.take<int>(sumM);
+        L.cells.mom = a.take<float>((size_t)room.rows * N);
+        L.cells.mu = a.take<float>((size_t)room.rows);
+        L.cell_part = a.take<char>(room.part_bytes);
+    }
     L.bytes = a.off + 256;
     return L;
 }
@@ -478,7 +513,8 @@ __global__ __launch_bounds__(256) void k_breduce(BLayout L, float kappa, float* 
     for (int i = threadIdx.x; i < P.T * d; i += 256) {
         const size_t gi = (size_t)P.xo * d + i;
         const float v = H.debias ? L.ds[gi] - L.dy[gi] : -L.dy[gi];
-        grad_x[gi] = expired ? nan : two_a * v;
+        const size_t at = L.permx ? (size_t)(P.xo + L.permx[P.xo + i / d]) * d + i % d : gi;
+        grad_x[at] = expired ? nan : two_a * v;
     }
     if (!value && !grad_w) return;
     double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -522,7 +558,7 @@ __global__ __launch_bounds__(256) void k_breduce(BLayout L, float kappa, float* 
         for (int j = threadIdx.x; j < P.M; j += 256) {
             const int gj = P.yo + j;
             const double G = H.need_ref ? (double)L.gp[gj] - (double)L.qp[gj] : (double)L.gp[gj];
-            grad_w[gj] = expired ? nan : (float)((G - s_bG) / ws);
+            grad_w[L.permy ? P.yo + L.permy[gj] : gj] = expired ? nan : (float)((G - s_bG) / ws);
         }
     }
 }
@@ -542,6 +578,7 @@ struct Prepared {
     unsigned long long signature;
     LockInfo lock;
     MeshInfo mesh;
+    CellRoom cells;
 };
 std::map<const void*, Prepared> g_prepared;   // workspace -> what it was prepared for
 
@@ -826,12 +863,56 @@ __global__ __launch_bounds__(256) void k_bfill_ones64(unsigned long long* a, int
     if (i < n) a[i] = ~0ull;
 }
 
+// Whether the lockstep launches may take the cell form (cells.h), and the room for it.  The
+// flags and the least number of iterations are those of a single problem; the jobs of a
+// launch have to fit kCellBatchJobs, and the pool holds at most kCellPoolFloats of moments
+// (problems beyond it sweep directly).  Problems of 512 keys a chunk: a batch has work
+// enough for the chip without the smaller chunks of a single problem.
+constexpr size_t kCellPoolFloats = size_t(256) << 20;
+constexpr int kCellBatchChunk = 512;
+
+CellRoom cell_room(int B, const int64_t* To, const int64_t* Mo, const ct_sinkhorn_opts* o) {
+    CellRoom r;
+    if (B * 3 > kCellBatchJobs || o->iters < kCellMinIters ||
+        (o->flags & (CT_PERSISTENT | CT_MESH | CT_UNFUSED | CT_SAFE_LSE | CT_DIFFERENCE)))
+        return r;
+    const size_t N = o->d == 2 ? CellDim<2>::N : CellDim<3>::N;
+    double pairs = 0.0;
+    int64_t most = 0;
+    for (int b = 0; b < B; ++b) {
+        const int64_t T = To[b + 1] - To[b], M = Mo[b + 1] - Mo[b];
+        most = std::max(most, std::max(T, M));
+        pairs += 2.0 * T * M + (double)T * T;
+    }
+    // as for one problem: launches or calls too small to gain
+    const CellLimits lim = cell_limits();
+    if (pairs <= lim.pairs || o->iters * pairs <= lim.work || most > kCellMaxPoints ||
+        !cell_candidate(o->d, (int)most, (int)most))
+        return r;
+    Arena a(nullptr);
+    for (int b = 0; b < B; ++b) {
+        const int64_t T = To[b + 1] - To[b], M = Mo[b + 1] - Mo[b];
+        CellPrep P;
+        cell_prep_layout(a, P, o->d, (int)T, (int)M, 0, 0, kCellBatchChunk, kCellBatchChunk);
+        const CellSide &X = P.side[0], &Y = P.side[1];
+        r.rows += std::max((long long)X.cmax * Y.chmax, (long long)Y.cmax * X.chmax) +
+                  (long long)X.cmax * X.chmax + (long long)Y.cmax * Y.chmax;
+        r.max_n = std::max(r.max_n, std::max(X.n, Y.n));
+        r.max_nb = std::max(r.max_nb, std::max(X.nb, Y.nb));
+    }
+    r.on = true;
+    r.part_bytes = a.off + 256;
+    r.rows = std::min(r.rows, (long long)(kCellPoolFloats / N));
+    return r;
+}
+
 // Floats of lockstep partial sums for this batch (the planning does not depend
 // on where the workspace is).
 size_t lock_part_floats(int B, const int64_t* To, const int64_t* Mo, const ct_sinkhorn_opts* o,
                         const BatchSizes& S) {
     const std::vector<BProb> P = base_probs(B, To, Mo);
-    const BLayout L0 = b_layout(nullptr, B, S.sumT, S.sumM, S.sumTpad, S.sumMpad, o->d, 0);
+    const BLayout L0 = b_layout(nullptr, B, S.sumT, S.sumM, S.sumTpad, S.sumMpad, o->d, 0,
+                                CellRoom());
     std::vector<Job> jobs((size_t)kLockKinds * 3 * B);
     std::vector<int> blk(jobs.size()), mrg(jobs.size());
     LockInfo info;
@@ -850,7 +931,8 @@ extern "C" size_t ct_sinkhorn_batched_workspace_size(int32_t B, const int64_t* T
     BatchSizes S;
     if (b_validate(B, To, Mo, o, S)) return 0;
     const size_t pf = lock_part_floats(B, To, Mo, o, S);
-    return b_layout(nullptr, B, S.sumT, S.sumM, S.sumTpad, S.sumMpad, o->d, pf).bytes;
+    return b_layout(nullptr, B, S.sumT, S.sumM, S.sumTpad, S.sumMpad, o->d, pf,
+                    cell_room(B, To, Mo, o)).bytes;
 }
 
 extern "C" ct_status ct_sinkhorn_batched_prepare(int32_t B, const int64_t* To, const int64_t* Mo,
@@ -863,7 +945,13 @@ extern "C" ct_status ct_sinkhorn_batched_prepare(int32_t B, const int64_t* To, c
     if (!ws) return fail(CT_E_ARG, "workspace is null");
     if (reinterpret_cast<uintptr_t>(ws) % 256) return fail(CT_E_WORKSPACE, "workspace not 256-byte aligned");
     const size_t pf = lock_part_floats(B, To, Mo, o, S);
-    BLayout L = b_layout(ws, B, S.sumT, S.sumM, S.sumTpad, S.sumMpad, o->d, pf);
+    // a workspace without room for the cell form serves the direct sweeps
+    CellRoom room = cell_room(B, To, Mo, o);
+    BLayout L = b_layout(ws, B, S.sumT, S.sumM, S.sumTpad, S.sumMpad, o->d, pf, room);
+    if (room.on && ws_bytes < L.bytes) {
+        room = CellRoom();
+        L = b_layout(ws, B, S.sumT, S.sumM, S.sumTpad, S.sumMpad, o->d, pf, room);
+    }
     if (ws_bytes < L.bytes) return fail(CT_E_WORKSPACE, "workspace too small: %zu < %zu", ws_bytes, L.bytes);
     rc = refuse_capture(static_cast<hipStream_t>(stream), "ct_sinkhorn_batched_prepare");
     if (rc) return rc;
@@ -876,7 +964,7 @@ extern "C" ct_status ct_sinkhorn_batched_prepare(int32_t B, const int64_t* To, c
 
     // host image of the table: header, problems, order, prefixes, record offsets
     std::vector<char> img(L.table_bytes, 0);
-    BLayout H0 = b_layout(img.data(), B, S.sumT, S.sumM, S.sumTpad, S.sumMpad, o->d, pf);
+    BLayout H0 = b_layout(img.data(), B, S.sumT, S.sumM, S.sumTpad, S.sumMpad, o->d, pf, CellRoom());
     BHeader& H = *H0.hdr;
     std::vector<double> cost(B);
     int xp = 0, yp = 0;
@@ -960,11 +1048,58 @@ extern "C" ct_status ct_sinkhorn_batched_prepare(int32_t B, const int64_t* To, c
                             kMeshBatchPairs);
         }
     }
+    if (minfo.blocks > 0) room.on = false;   // the exchange solve serves the batch
+    std::vector<CellPrep> cprep(room.on ? B : 0);
+    std::vector<CellJob> cjobs(room.on ? (size_t)kLockKinds * 3 * B : 0);
+    if (room.on) {
+        std::memset(cprep.data(), 0, cprep.size() * sizeof(CellPrep));
+        std::memset(cjobs.data(), 0, cjobs.size() * sizeof(CellJob));
+        Arena a(L.cell_part);
+        for (int b = 0; b < B; ++b) {
+            const BProb& Q = BP[b];
+            CellPrep& P = cprep[b];
+            cell_prep_layout(a, P, o->d, Q.T, Q.M, Q.xo, Q.yo, kCellBatchChunk, kCellBatchChunk);
+            P.origin = L.origin + (size_t)b * 4;
+            P.side[0].perm = L.permx + Q.xo;
+            P.side[1].perm = L.permy + Q.yo;
+            P.xs = L.xs + (size_t)Q.xo * o->d;
+            P.ys = L.ys + (size_t)Q.yo * o->d;
+            P.ws = L.ws + Q.yo;
+        }
+        for (int k = 0; k < kLockKinds; ++k) {
+            const int n = info.njobs[k], per = n / B;
+            for (int i = 0; i < n; ++i) {
+                // per problem: f (p (q)) | f (p (q)) | g | f+ (p+) | g+ (q+)
+                const int t = i % per, m = k < 2 || k == 3 ? (t == 0 ? 0 : 1 + t) : (t == 0 ? 1 : 3);
+                const CellPrep& P = cprep[i / per];
+                const CellSide& Q = P.side[m == 1 || m == 3];
+                const CellSide& K = P.side[m == 0 || m == 3];
+                CellJob& J = cjobs[(size_t)k * 3 * B + i];
+                J.mode = P.mode + m;
+                J.ncq = Q.cnt;
+                J.qcen = Q.cen;
+                J.tile = Q.tile;
+                J.ntile = Q.cnt + 2;
+                J.tmax = Q.tmax;
+                J.nch = K.cnt + 1;
+                J.chunk = K.chunk;
+                J.chcen = K.chcen;
+            }
+        }
+    }
     hipStream_t st = static_cast<hipStream_t>(stream);
     CT_CHECK_HIP(hipMemcpyAsync(ws, img.data(), img.size(), hipMemcpyHostToDevice, st));
+    if (room.on) {
+        CT_CHECK_HIP(hipMemcpyAsync(L.cells.prep, cprep.data(), cprep.size() * sizeof(CellPrep),
+                                    hipMemcpyHostToDevice, st));
+        CT_CHECK_HIP(hipMemcpyAsync(L.cells.jobs, cjobs.data(), cjobs.size() * sizeof(CellJob),
+                                    hipMemcpyHostToDevice, st));
+        CT_CHECK_HIP(hipMemcpyAsync(L.cells.njobs, info.njobs, sizeof(info.njobs),
+                                    hipMemcpyHostToDevice, st));
+    }
     CT_CHECK_HIP(hipStreamSynchronize(st));
     std::lock_guard<std::mutex> lk(g_prep_mu);
-    g_prepared[ws] = Prepared{H.signature, info, minfo};
+    g_prepared[ws] = Prepared{H.signature, info, minfo, room};
     return CT_OK;
 }
 
@@ -984,11 +1119,12 @@ extern "C" ct_status ct_sinkhorn_grad_batched(int32_t B, const int64_t* To, cons
     if (!value && (o->flags & CT_VALUE)) return fail(CT_E_ARG, "CT_VALUE needs value");
     if (!ws) return fail(CT_E_ARG, "workspace is null");
     const size_t pf = lock_part_floats(B, To, Mo, o, S);
-    BLayout L = b_layout(ws, B, S.sumT, S.sumM, S.sumTpad, S.sumMpad, o->d, pf);
+    BLayout L = b_layout(ws, B, S.sumT, S.sumM, S.sumTpad, S.sumMpad, o->d, pf, CellRoom());
     if (ws_bytes < L.bytes) return fail(CT_E_WORKSPACE, "workspace too small: %zu < %zu", ws_bytes, L.bytes);
     const Schedule sc = batched_schedule(o->d);
     LockInfo info;
     MeshInfo minfo;
+    CellRoom room;
     {
         std::lock_guard<std::mutex> lk(g_prep_mu);
         auto it = g_prepared.find(ws);
@@ -997,6 +1133,13 @@ extern "C" ct_status ct_sinkhorn_grad_batched(int32_t B, const int64_t* To, cons
                                   "(call ct_sinkhorn_batched_prepare first)");
         info = it->second.lock;
         minfo = it->second.mesh;
+        room = it->second.cells;
+    }
+    if (room.on) {
+        L = b_layout(ws, B, S.sumT, S.sumM, S.sumTpad, S.sumMpad, o->d, pf, room);
+        if (ws_bytes < L.bytes)
+            return fail(CT_E_WORKSPACE, "workspace smaller than when it was prepared: %zu < %zu",
+                        ws_bytes, L.bytes);
     }
     if (minfo.blocks > 0 && minfo.eps != o->eps)
         return fail(CT_E_ARG, "the batch's exchange-solve tables were prepared for eps=%g (got %g)",
@@ -1005,8 +1148,13 @@ extern "C" ct_status ct_sinkhorn_grad_batched(int32_t B, const int64_t* To, cons
     const double kappa_d = kLog2e / (double)o->eps;
     hipLaunchKernelGGL(k_bwsum, dim3(B), dim3(256), 0, st, L, x, y, w, o->d);
     CT_CHECK_HIP(hipGetLastError());
+    if (room.on)
+        CT_CHECK_HIP(launch_cell_prep_batch(o->d, L.cells,
+                                            CellInputs{x, y, w, nullptr, (float)std::sqrt(kappa_d)},
+                                            room.max_n, room.max_nb, st));
     const int64_t n = std::max(S.sumTpad, S.sumMpad);
-    hipLaunchKernelGGL(k_bstage, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, L, x, y, w,
+    hipLaunchKernelGGL(k_bstage, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, L,
+                       room.on ? L.xs : x, room.on ? L.ys : y, room.on && w ? L.ws : w,
                        (float)std::sqrt(kappa_d), (float)kappa_d);
     CT_CHECK_HIP(hipGetLastError());
     if (!(o->flags & CT_PERSISTENT)) {
@@ -1027,7 +1175,8 @@ extern "C" ct_status ct_sinkhorn_grad_batched(int32_t B, const int64_t* To, cons
             t.njobs = info.njobs[k];
             t.nblocks = info.nblocks[k];
             t.nmerge = info.nmerge[k];
-            CT_CHECK_HIP(launch_tab(o->d, lsc, lagged, bary, t, st));
+            if (room.on && !bary) CT_CHECK_HIP(launch_cell_tab(o->d, lsc, lagged, t, L.cells, k, st));
+            else CT_CHECK_HIP(launch_tab(o->d, lsc, lagged, bary, t, st));
             return CT_OK;
         };
         const bool safe_only = o->flags & CT_SAFE_LSE;

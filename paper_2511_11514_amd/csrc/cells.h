@@ -50,8 +50,7 @@ constexpr int kCellChunkMax = 1024;  // most keys of one chunk
 
 // One point set's partition, in the workspace.
 struct CellSide {
-    const float* pts;      // [n][d] caller's points
-    int n;
+    int off, n;            // the set's first point in the caller's array, points
     int nb, per;           // blocks of `per` points in the counting sort
     int kc;                // most keys of a chunk
     int cmax, chmax, tmax; // room for cells, chunks and tiles
@@ -71,17 +70,22 @@ struct CellSide {
 
 struct CellPrep {
     CellSide side[2];      // x, y
-    const float* w;        // caller's reference weights or null
     const float* origin;   // [3] subtracted before scaling
     int d, ids, bits;
-    float sqrt_kappa;
     float cell;            // side of a cell, scaled
     size_t mom_cap[3];     // room for moments: cross, x-x, y-y (floats)
-    int* mode;             // out: [4] of the f, g, p, q sweeps: 1 the cell form pays and fits,
-                           // 0 the direct sweep
+    int* mode;             // out: [5] of the f, g, p, q sweeps: 1 the cell form pays and fits,
+                           // 0 the direct sweep; then 0
     float *xs, *ys, *ws;   // out: points and weights in cell order
-    const float* pot_in;   // [2T+2M] starting potentials or null
-    float* pot_s;          // out: the same in cell order (when pot_in)
+    float* pot_s;          // out: the starting potentials in cell order (when given)
+};
+
+// What a call passes to the partition beside it.
+struct CellInputs {
+    const float *x, *y;    // caller's points
+    const float* w;        // caller's reference weights or null
+    const float* pot;      // [2T+2M] starting potentials or null (one problem only)
+    float sqrt_kappa;
 };
 
 // A soft-min job in the cell form, beside its direct form (Job).
@@ -102,19 +106,62 @@ struct CellJob {
 
 struct CellLaunch {
     CellJob job[2];
+    const int* never;      // a zero mode
     int R, WS;             // the direct sweep's schedule
     float inv_cell;        // 1 / w
 };
 
 // Side of a cell in scaled coordinates: lambda = ln2 w^2 / 2.
 double cell_side(int d);
+// Sizes of a problem's partition and its arrays from the arena (all but the function tables,
+// the sorted inputs and the moments).
+void cell_prep_layout(Arena& a, CellPrep& P, int d, int T, int M, int xo, int yo, int kcx, int kcy);
+// Mean points of a cell below which the form cannot pay: bounds the room for cells.
+constexpr int kCellMinPoints = 24;
 // Largest number of keys in a chunk for a set of n points.
 int cell_chunk(int n);
 
-hipError_t launch_cell_prep(const CellPrep& P, hipStream_t s);
-// One sweep of one or two jobs: moments then values, or (*mode == 0) the direct sweep
-// then its merge.
+hipError_t launch_cell_prep(const CellPrep& P, const CellInputs& in, hipStream_t s);
+// Calls too small for the cell form; the environment variable CT_CELL_MIN_PAIRS (a test and
+// tuning hook) replaces `pairs` and `pairs3` and drops `work`.
+constexpr int kCellMinIters = 8;
+constexpr int kCellMaxPoints = 1 << 22;
+struct CellLimits {
+    // Pairs of one iteration below which the two forms' launches take the same time (150
+    // iterations: 4.7e7 pairs 5.4 against 5.0 ms, 1.04e8 pairs 5.0 against 5.7).
+    double pairs = 1e8;
+    // Pairs of all iterations below which splitting the points (0.1 ms) costs more than it
+    // saves: 40 iterations at T = 3174, M = 12915 (3.7e9 pairs) 1.69 against 1.54 ms.
+    double work = 1e10;
+    // Pairs of a 3-D sweep below which it stays direct: cells of so few points are too sparse
+    // to pay (40 iterations at T = 16355, M = 22674 lose 2 %, at T = 10246, M = 35898 win 26 %).
+    double pairs3 = 1.2e9;
+};
+CellLimits cell_limits();
+bool cell_candidate(int d, int nq, int nk);
+// One sweep of one or two jobs (nblocks direct work units): moments then values, or the
+// direct sweep then its merge.
 hipError_t launch_cell_sweep(int d, const Schedule& sc, bool lagged, const Launch& L,
-                             const CellLaunch& C, hipStream_t s);
+                             const CellLaunch& C, int nblocks, hipStream_t s);
 
+// The batched path: the same over tables in device memory.  Kind k of the lockstep
+// launches has njobs jobs; every job of the direct table has a cell job beside it.
+constexpr int kCellBatchJobs = 1024;   // most jobs of a launch (their prefix sums sit in LDS)
+struct CellBatch {
+    CellPrep* prep;        // [B]
+    CellJob* jobs;         // [kinds][3B]
+    int* uend;             // [kinds][2][3B] ends of the jobs' units: moments, values
+    int* info;             // [kinds] 1: some job takes the direct sweep
+    int* njobs;            // [kinds]
+    float* mom;            // pool of moments and of their exponents
+    float* mu;
+    long long rows;        // (query cell, chunk) pairs that the pool holds
+    int B, kinds, stride;  // stride = 3B
+};
+// Partitions of every problem, then the jobs' modes, places in the pool and units.
+hipError_t launch_cell_prep_batch(int d, const CellBatch& C, const CellInputs& in, int max_n,
+                                  int max_nb, hipStream_t s);
+// One lockstep launch of kind k: the cell form's jobs and the direct ones of L.
+hipError_t launch_cell_tab(int d, const Schedule& sc, bool lagged, const TabLaunch& L,
+                           const CellBatch& C, int k, hipStream_t s);
 }  // namespace ct

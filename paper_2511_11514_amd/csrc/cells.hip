@@ -4,6 +4,8 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstdlib>
+#include <cstring>
 
 #include "cells.h"
 #include "sweep_device.h"
@@ -56,10 +58,13 @@ __device__ __forceinline__ float from_ordered(unsigned u) {
     return __uint_as_float((u & 0x80000000u) ? u & 0x7fffffffu : ~u);
 }
 
-__global__ __launch_bounds__(64) void k_cell_init(CellPrep P) {
+// The partition kernels take one problem by value, or (TAB) blockIdx.z's of a table.
+template <bool TAB>
+__global__ __launch_bounds__(64) void k_cell_init(CellPrep one, const CellPrep* tab) {
+    const CellPrep& P = TAB ? tab[blockIdx.z] : one;
     const int i = (int)threadIdx.x;
     if (i < 16) {
-        CellSide& S = P.side[i >> 3];
+        const CellSide& S = P.side[i >> 3];
         S.box[i & 7] = (i & 7) < 3 ? 0xffffffffu : 0u;
     }
 }
@@ -67,22 +72,25 @@ __global__ __launch_bounds__(64) void k_cell_init(CellPrep P) {
 // Bounding box of the scaled points (minima and maxima do not depend on the order of the
 // atomics), and the number of points that no cell can take: non-finite coordinates, or
 // weights that are not positive and finite.
-__global__ __launch_bounds__(256) void k_cell_box(CellPrep P) {
+template <bool TAB>
+__global__ __launch_bounds__(256) void k_cell_box(CellPrep one, const CellPrep* tab, CellInputs in) {
+    const CellPrep& P = TAB ? tab[blockIdx.z] : one;
     const CellSide& S = P.side[blockIdx.y];
+    const float* pts = (blockIdx.y ? in.y : in.x) + (size_t)S.off * P.d;
     const int d = P.d;
     unsigned lo[3] = {0xffffffffu, 0xffffffffu, 0xffffffffu}, hi[3] = {0u, 0u, 0u}, bad = 0u;
     for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < S.n; i += (int)gridDim.x * 256) {
         bool ok = true;
         for (int t = 0; t < d; ++t) {
-            const float c = (S.pts[(size_t)i * d + t] - P.origin[t]) * P.sqrt_kappa;
+            const float c = (pts[(size_t)i * d + t] - P.origin[t]) * in.sqrt_kappa;
             ok = ok && isfinite(c);
             if (isfinite(c)) {
                 lo[t] = min(lo[t], ordered(c));
                 hi[t] = max(hi[t], ordered(c));
             }
         }
-        if (blockIdx.y == 1 && P.w) {
-            const float w = P.w[i];
+        if (blockIdx.y == 1 && in.w) {
+            const float w = in.w[S.off + i];
             ok = ok && w > 0.f && isfinite(w);
         }
         bad += ok ? 0u : 1u;
@@ -119,9 +127,12 @@ __device__ __forceinline__ int cell_code(const float* c, const float* lo, float 
 }
 
 // Counts per block of `per` points and code.
-__global__ __launch_bounds__(256) void k_cell_hist(CellPrep P) {
+template <bool TAB>
+__global__ __launch_bounds__(256) void k_cell_hist(CellPrep one, const CellPrep* tab, CellInputs in) {
     __shared__ unsigned h[kCellIds];
+    const CellPrep& P = TAB ? tab[blockIdx.z] : one;
     const CellSide& S = P.side[blockIdx.y];
+    const float* pts = (blockIdx.y ? in.y : in.x) + (size_t)S.off * P.d;
     const int b = (int)blockIdx.x;
     if (b >= S.nb) return;
     for (int i = (int)threadIdx.x; i < P.ids; i += 256) h[i] = 0u;
@@ -132,7 +143,7 @@ __global__ __launch_bounds__(256) void k_cell_hist(CellPrep P) {
     for (int i = b * S.per + (int)threadIdx.x; i < i1; i += 256) {
         float c[3];
         for (int t = 0; t < P.d; ++t)
-            c[t] = (S.pts[(size_t)i * P.d + t] - P.origin[t]) * P.sqrt_kappa;
+            c[t] = (pts[(size_t)i * P.d + t] - P.origin[t]) * in.sqrt_kappa;
         const int id = cell_code(c, lo, 1.f / P.cell, P.d, P.bits);
         S.id[i] = (unsigned short)id;
         atomicAdd(&h[id], 1u);
@@ -141,20 +152,31 @@ __global__ __launch_bounds__(256) void k_cell_hist(CellPrep P) {
     for (int i = (int)threadIdx.x; i < P.ids; i += 256) S.bh[(size_t)b * P.ids + i] = h[i];
 }
 
-// Per code: exclusive sums of its counts over the blocks, and its total.
-__global__ __launch_bounds__(256) void k_cell_scan(CellPrep P) {
+// Per code: exclusive sums of its counts over the blocks, and its total.  The four waves of a
+// block take a quarter of the blocks each for 64 codes: first their sums, then the places.
+template <bool TAB>
+__global__ __launch_bounds__(256) void k_cell_scan(CellPrep one, const CellPrep* tab) {
+    __shared__ unsigned part[4][64];
+    const CellPrep& P = TAB ? tab[blockIdx.z] : one;
     const CellSide& S = P.side[blockIdx.y];
-    const int id = (int)(blockIdx.x * 256 + threadIdx.x);
-    if (id >= P.ids) return;
-    unsigned run = 0u;
+    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+    const int id = (int)blockIdx.x * 64 + lane;
+    const int per = (S.nb + 3) / 4, b0 = min(S.nb, wave * per), b1 = min(S.nb, b0 + per);
+    unsigned sum = 0u;
 #pragma unroll 8
-    for (int b = 0; b < S.nb; ++b) {
+    for (int b = b0; b < b1; ++b) sum += S.bh[(size_t)b * P.ids + id];
+    part[wave][lane] = sum;
+    __syncthreads();
+    unsigned run = 0u;
+    for (int w = 0; w < wave; ++w) run += part[w][lane];
+#pragma unroll 8
+    for (int b = b0; b < b1; ++b) {
         const size_t at = (size_t)b * P.ids + id;
         const unsigned v = S.bh[at];
         S.bh[at] = run;
         run += v;
     }
-    S.first[id] = run;   // the total; k_cell_lists turns it into the first place
+    if (wave == 3) S.first[id] = run;   // the total; k_cell_lists turns it into the first place
 }
 
 // Inclusive block scan of one int per thread (1024 threads); returns the exclusive sum
@@ -179,9 +201,12 @@ __device__ __forceinline__ int block_scan(int v, int* sh, int* total) {
 }
 
 // Sorted places, the non-empty cells, their chunks of at most kc keys and their tiles of
-// 32 queries (one block per side; four codes per thread).
-__global__ __launch_bounds__(1024) void k_cell_lists(CellPrep P) {
+// 32 queries (one block per side; four codes per thread count, all threads write the lists).
+template <bool TAB>
+__global__ __launch_bounds__(1024) void k_cell_lists(CellPrep one, const CellPrep* tab) {
     __shared__ int sh[16];
+    __shared__ int at0[kCellIds + 1], ih0[kCellIds], it0[kCellIds];   // per non-empty cell
+    const CellPrep& P = TAB ? tab[blockIdx.z] : one;
     const CellSide& S = P.side[blockIdx.x];
     constexpr int per = kCellIds / 1024;
     int n[per], pts = 0, cells = 0, chunks = 0, tiles = 0;
@@ -202,7 +227,7 @@ __global__ __launch_bounds__(1024) void k_cell_lists(CellPrep P) {
     float lo[3] = {0.f, 0.f, 0.f};
     for (int t = 0; t < P.d; ++t) {
         lo[t] = from_ordered(S.box[t]);
-        // every point in the cell of its code (one part in 10^4 of slack in the side of a cell)
+        // every point in the cell of its code
         fits = fits && (from_ordered(S.box[3 + t]) - lo[t]) <= P.cell * (float)(1 << P.bits);
     }
     if (threadIdx.x == 0) {
@@ -215,33 +240,55 @@ __global__ __launch_bounds__(1024) void k_cell_lists(CellPrep P) {
         const int id = (int)threadIdx.x * per + k;
         if (id >= P.ids) break;
         S.first[id] = (unsigned)at;
-        const int end = at + n[k];
-        if (fits && n[k] > 0) {
-            float c[3] = {0.f, 0.f, 0.f};
-            for (int t = 0; t < P.d; ++t) {
-                int g = 0;
-                for (int b = 0; b < P.bits; ++b) g |= ((id >> (b * P.d + t)) & 1) << b;
-                c[t] = lo[t] + ((float)g + 0.5f) * P.cell;
+        if (n[k] > 0) {
+            at0[ic] = at;
+            ih0[ic] = ih;
+            it0[ic] = it;
+            if (fits) {
+                float c[3] = {0.f, 0.f, 0.f};
+                for (int t = 0; t < P.d; ++t) {
+                    int g = 0;
+                    for (int b = 0; b < P.bits; ++b) g |= ((id >> (b * P.d + t)) & 1) << b;
+                    c[t] = lo[t] + ((float)g + 0.5f) * P.cell;
+                }
+                S.cen[ic] = make_float4(c[0], c[1], c[2], 0.f);
             }
-            const float4 cen = make_float4(c[0], c[1], c[2], 0.f);
-            S.cen[ic] = cen;
-            for (int q = at; q < end; q += S.kc) {
-                S.chunk[ih] = make_int4(q, min(end, q + S.kc), ic, 0);
-                S.chcen[ih] = cen;
-                ++ih;
-            }
-            for (int q = at; q < end; q += kCellTile)
-                S.tile[it++] = make_int4(q, min(end, q + kCellTile), ic, 0);
             ++ic;
+            ih += (n[k] + S.kc - 1) / S.kc;
+            it += (n[k] + kCellTile - 1) / kCellTile;
         }
-        at = end;
+        at += n[k];
+    }
+    if (threadIdx.x == 0) at0[tc] = tp;
+    if (!fits) return;   // the same in every thread
+    __syncthreads();
+    // the cell of entry e: the last one whose entries start at or before e
+    auto cell_of = [&](const int* first, int e) {
+        int a = 0, b = tc - 1;
+        while (a < b) {
+            const int mid = (a + b + 1) >> 1;
+            if (first[mid] <= e) a = mid;
+            else b = mid - 1;
+        }
+        return a;
+    };
+    for (int e = (int)threadIdx.x; e < th; e += 1024) {
+        const int c = cell_of(ih0, e), q = at0[c] + (e - ih0[c]) * S.kc;
+        S.chunk[e] = make_int4(q, min(at0[c + 1], q + S.kc), c, 0);
+        S.chcen[e] = S.cen[c];
+    }
+    for (int e = (int)threadIdx.x; e < tt; e += 1024) {
+        const int c = cell_of(it0, e), q = at0[c] + (e - it0[c]) * kCellTile;
+        S.tile[e] = make_int4(q, min(at0[c + 1], q + kCellTile), c, 0);
     }
 }
 
 // Stable scatter: one wave per block of points walks them in order, 64 at a time; the
 // lanes of one code rank themselves by ballots over the code's bits.
-__global__ __launch_bounds__(64) void k_cell_scatter(CellPrep P) {
+template <bool TAB>
+__global__ __launch_bounds__(64) void k_cell_scatter(CellPrep one, const CellPrep* tab) {
     __shared__ unsigned cur[kCellIds];
+    const CellPrep& P = TAB ? tab[blockIdx.z] : one;
     const CellSide& S = P.side[blockIdx.y];
     const int b = (int)blockIdx.x, lane = (int)threadIdx.x;
     if (b >= S.nb) return;
@@ -270,52 +317,138 @@ __global__ __launch_bounds__(64) void k_cell_scatter(CellPrep P) {
     }
 }
 
-// Multiply-adds of one sweep in the cell form: moment tiles of 32 query cells by every
-// key, value tiles of 32 queries by every chunk of keys (in tiles of 32).
-__device__ double cell_work(const CellSide& q, const CellSide& k) {
-    const double at = (q.cnt[0] + kCellTile - 1) / kCellTile * kCellTile;
-    const double ct = (k.cnt[1] + kCellTile - 1) / kCellTile * kCellTile;
-    return at * ((double)k.n + 4.0 * k.cnt[1]) + (double)q.cnt[2] * kCellTile * ct;
+// Whether a sweep pays in the cell form, from a model of both forms' times in clocks of one
+// compute unit, fitted to launches of 4096 to 262144 points (d = 2: T = 4096, M = 16384, f: 18 us
+// measured, 16 modelled, direct 20 and 19; T = 65536, M = 262144, g: 166 and 150, direct
+// 2290 and 2900; d = 3, M = 65521: the q sweep 450 and 446, direct 800 and 884).
+//   moments  the keys' products for 32 query cells at a time at 73 % of the matrix cores'
+//            128 multiply-adds per clock, and a fixed part per (chunk, 32 cells)
+//   values   twice the products' clocks, and a fixed part per tile
+//   direct   the pairs' instructions at 75 % of their issue rate
+// and per sweep the launches (`launch`, in microseconds; a batch shares them).
+__device__ bool cell_pays(const CellSide& q, const CellSide& k, int d, double launch) {
+    if (q.cnt[3] || k.cnt[3]) return false;
+    const double N = d == 2 ? CellDim<2>::N : CellDim<3>::N;
+    const double pair = d == 2 ? 2.0 / 128 + 2.0 / 64 + 1.0 / 32 : 2.0 / 128 + 3.0 / 64 + 1.0 / 32;
+    const double at = (q.cnt[0] + kCellTile - 1) / kCellTile, ct = (k.cnt[1] + kCellTile - 1) / kCellTile;
+    const double moments = at * (kCellTile * N / 128.0 / 0.73 * k.n + (d == 2 ? 9e3 : 18e3) * k.cnt[1]);
+    const double values = q.cnt[2] * (ct * 2.0 * kCellTile * kCellTile * N / 128.0 + 1e3);
+    const double direct = (double)q.n * k.n * pair / 0.75;
+    const double per_us = 256.0 * 2400.0;
+    return (moments + values) / per_us + 0.6 * launch < 0.9 * (direct / per_us + launch);
 }
+constexpr double kCellLaunch = 8.0;
 
-// Points, weights and starting potentials in cell order; the first thread settles the
-// form of the sweeps (see kCellGain).
-constexpr double kCellGain = 0.7;
-__global__ __launch_bounds__(256) void k_cell_gather(CellPrep P) {
+// Points, weights and starting potentials in cell order.
+template <bool TAB>
+__global__ __launch_bounds__(256) void k_cell_gather(CellPrep one, const CellPrep* tab,
+                                                     CellInputs in) {
+    const CellPrep& P = TAB ? tab[blockIdx.z] : one;
     const CellSide& X = P.side[0];
     const CellSide& Y = P.side[1];
     const int d = P.d;
     const int i = (int)(blockIdx.x * 256 + threadIdx.x);
-    if (i == 0) {
+    if (!TAB && i == 0) {
         const size_t N = d == 2 ? CellDim<2>::N : CellDim<3>::N;
-        // clocks of a compute unit: 128 multiply-adds per clock in the matrix cores against
-        // the pair's instructions in the vector units
-        const double pair = d == 2 ? 2.0 / 128 + 2.0 / 64 + 1.0 / 32 : 2.0 / 128 + 3.0 / 64 + 1.0 / 32;
-        auto pays = [&](const CellSide& q, const CellSide& k, size_t cap) {
-            if (q.cnt[3] || k.cnt[3] || (size_t)q.cnt[0] * k.cnt[1] * N > cap) return 0;
-            return cell_work(q, k) * N / 128.0 < kCellGain * ((double)q.n * k.n) * pair ? 1 : 0;
-        };
-        P.mode[0] = pays(X, Y, P.mom_cap[0]);
-        P.mode[1] = pays(Y, X, P.mom_cap[0]);
-        P.mode[2] = pays(X, X, P.mom_cap[1]);
-        P.mode[3] = pays(Y, Y, P.mom_cap[2]);
+        const CellSide* q[4] = {&X, &Y, &X, &Y};
+        const CellSide* k[4] = {&Y, &X, &X, &Y};
+        for (int j = 0; j < 4; ++j) {
+            const size_t need = (size_t)q[j]->cnt[0] * k[j]->cnt[1] * N;
+            P.mode[j] = need <= P.mom_cap[j < 2 ? 0 : j - 1] && cell_pays(*q[j], *k[j], d, kCellLaunch) ? 1 : 0;
+        }
+        P.mode[4] = 0;
     }
     if (i < X.n) {
         const int s = X.perm[i];
-        for (int t = 0; t < d; ++t) P.xs[(size_t)i * d + t] = X.pts[(size_t)s * d + t];
-        if (P.pot_in) {
-            P.pot_s[i] = P.pot_in[s];
-            P.pot_s[(size_t)X.n + Y.n + i] = P.pot_in[(size_t)X.n + Y.n + s];
+        const float* pts = in.x + (size_t)X.off * d;
+        for (int t = 0; t < d; ++t) P.xs[(size_t)i * d + t] = pts[(size_t)s * d + t];
+        if (in.pot) {
+            P.pot_s[i] = in.pot[s];
+            P.pot_s[(size_t)X.n + Y.n + i] = in.pot[(size_t)X.n + Y.n + s];
         }
     }
     if (i < Y.n) {
         const int s = Y.perm[i];
-        for (int t = 0; t < d; ++t) P.ys[(size_t)i * d + t] = Y.pts[(size_t)s * d + t];
-        if (P.w) P.ws[i] = P.w[s];
-        if (P.pot_in) {
-            P.pot_s[(size_t)X.n + i] = P.pot_in[(size_t)X.n + s];
-            P.pot_s[2 * (size_t)X.n + Y.n + i] = P.pot_in[2 * (size_t)X.n + Y.n + s];
+        const float* pts = in.y + (size_t)Y.off * d;
+        for (int t = 0; t < d; ++t) P.ys[(size_t)i * d + t] = pts[(size_t)s * d + t];
+        if (in.w) P.ws[i] = in.w[Y.off + s];
+        if (in.pot) {
+            P.pot_s[(size_t)X.n + i] = in.pot[(size_t)X.n + s];
+            P.pot_s[2 * (size_t)X.n + Y.n + i] = in.pot[2 * (size_t)X.n + Y.n + s];
         }
+    }
+}
+
+// A batch's modes, places in the pool and units (one block).  A problem's three buffers
+// (cross, x-x, y-y) are taken in problem order while they fit; the rest of the batch sweeps
+// directly.
+__global__ __launch_bounds__(1024) void k_cell_plan(CellBatch C, int d) {
+    __shared__ int sh[16];
+    const int N = d == 2 ? CellDim<2>::N : CellDim<3>::N;
+    long long used = 0;
+    for (int b0 = 0; b0 < C.B; b0 += 1024) {
+        const int b = b0 + (int)threadIdx.x;
+        int rows[3] = {0, 0, 0};
+        bool pays[4] = {false, false, false, false};
+        if (b < C.B) {
+            const CellSide& X = C.prep[b].side[0];
+            const CellSide& Y = C.prep[b].side[1];
+            pays[0] = cell_pays(X, Y, d, 0.0);
+            pays[1] = cell_pays(Y, X, d, 0.0);
+            pays[2] = cell_pays(X, X, d, 0.0);
+            pays[3] = cell_pays(Y, Y, d, 0.0);
+            const int cx = X.cnt[0], cy = Y.cnt[0], hx = X.cnt[1], hy = Y.cnt[1];
+            rows[0] = max(pays[0] ? cx * hy : 0, pays[1] ? cy * hx : 0);
+            rows[1] = pays[2] ? cx * hx : 0;
+            rows[2] = pays[3] ? cy * hy : 0;
+        }
+        int total;
+        const int mine = rows[0] + rows[1] + rows[2];
+        const long long at = used + block_scan(mine, sh, &total);
+        used += total;
+        if (b < C.B) {
+            const bool fits = at + mine <= C.rows;
+            for (int j = 0; j < 4; ++j) C.prep[b].mode[j] = fits && pays[j] ? 1 : 0;
+            long long r[3] = {at, at + rows[0], at + rows[0] + rows[1]};
+            for (int k = 0; k < C.kinds; ++k) {
+                const int per = C.njobs[k] / C.B;
+                for (int i = 0; i < per; ++i) {
+                    CellJob& J = C.jobs[(size_t)k * C.stride + (size_t)b * per + i];
+                    const int m = (int)(J.mode - C.prep[b].mode);   // 0 f, 1 g, 2 p, 3 q
+                    const long long row = fits ? r[m < 2 ? 0 : m - 1] : 0;
+                    J.mom = C.mom + row * N;
+                    J.mu = C.mu + row;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    __threadfence_block();
+    for (int k = 0; k < C.kinds; ++k) {
+        int before[2] = {0, 0}, direct = 0;
+        for (int j0 = 0; j0 < C.njobs[k]; j0 += 1024) {
+            const int j = j0 + (int)threadIdx.x;
+            int n[2] = {0, 0}, dir = 0;
+            if (j < C.njobs[k]) {
+                const CellJob& J = C.jobs[(size_t)k * C.stride + j];
+                if (*J.mode) {
+                    n[0] = *J.nch * ((*J.ncq + kCellTile - 1) / kCellTile);
+                    n[1] = (*J.ntile + 3) / 4;
+                } else {
+                    dir = 1;
+                }
+            }
+            for (int v = 0; v < 2; ++v) {
+                int total;
+                const int e = before[v] + block_scan(n[v], sh, &total) + n[v];
+                if (j < C.njobs[k]) C.uend[((size_t)k * 2 + v) * C.stride + j] = e;
+                before[v] += total;
+            }
+            int total;
+            block_scan(dir, sh, &total);
+            direct += total;
+        }
+        if (threadIdx.x == 0) C.info[k] = direct;
     }
 }
 
@@ -338,9 +471,9 @@ __device__ __forceinline__ void bessel(float z, float* out, int stride) {
 // They depend on the points alone: made once per call, read by every sweep (making them
 // in each sweep took as long as a whole tile's matrix products).
 template <int D>
-__global__ __launch_bounds__(256) void k_cell_functions(CellPrep P) {
+__global__ __launch_bounds__(256) void k_cell_functions(CellPrep P, CellInputs in) {
     constexpr int N = CellDim<D>::N, F = CellDim<D>::F, H = N / 2;
-    __shared__ float in[D * F * 33];
+    __shared__ float fn[D * F * 33];
     const CellSide& S = P.side[blockIdx.y];
     const float* pts = blockIdx.y ? P.ys : P.xs;
     if (S.cnt[3]) return;
@@ -352,9 +485,9 @@ __global__ __launch_bounds__(256) void k_cell_functions(CellPrep P) {
             const int x = tid >> 5;
             const float4 c = S.cen[tl.z];
             const int q = min(tl.x + col, tl.y - 1);
-            const float v = (pts[(size_t)q * D + x] - P.origin[x]) * P.sqrt_kappa;
+            const float v = (pts[(size_t)q * D + x] - P.origin[x]) * in.sqrt_kappa;
             const float s = (v - (x == 0 ? c.x : x == 1 ? c.y : c.z)) * inv;   // on [-1, 1]
-            bessel<F>((float)CellDim<D>::lambda * s, in + x * F * 33 + col, 33);
+            bessel<F>((float)CellDim<D>::lambda * s, fn + x * F * 33 + col, 33);
         }
         __syncthreads();
         for (int e = tid; e < H * 16; e += 256) {
@@ -363,7 +496,7 @@ __global__ __launch_bounds__(256) void k_cell_functions(CellPrep P) {
             for (int k = 0; k < 4; ++k) {
                 const int n = (lane >> 5) * H + 4 * i + k;
                 p[k] = 1.f;
-                for (int x = 0; x < D; ++x) p[k] *= in[(x * F + term<D>(n, x)) * 33 + (lane & 31)];
+                for (int x = 0; x < D; ++x) p[k] *= fn[(x * F + term<D>(n, x)) * 33 + (lane & 31)];
             }
             S.phi[(size_t)t * (H * 16) + e] = make_float4(p[0], p[1], p[2], p[3]);
         }
@@ -507,8 +640,9 @@ __device__ __forceinline__ void cell_moments(const CellJob& C, const Job& J, int
 
 // --------------------------------------------------------------------- values
 
-template <int D>
+template <int D, bool PHI>
 struct ValueSmem {
+    float fn[PHI ? 1 : 4][PHI ? 1 : D * CellDim<D>::F * 33];   // per wave: phi_n per axis
     float4 cd[4][kCellTile];            // per wave: (-2d, mu - |d|^2) of 32 chunks
     float red[4][kCellTile];
     int flist[4 * kCellTile];
@@ -518,12 +652,14 @@ struct ValueSmem {
 // Values of tiles of 32 queries: WS waves of a block share a tile (each takes every WS-th
 // tile of 32 chunks), 4 / WS tiles per block.  An MFMA multiplies the chunks' moments (A:
 // lane = chunk) with the queries' functions (B: lane = query), so that a lane holds 16
-// chunks' sums of its own query.
-template <int D, bool LAGGED, int WS>
+// chunks' sums of its own query.  The functions come from the table, or (PHI false: many
+// problems, whose tables would take gigabytes) are made here, about a tenth of a tile's work.
+template <int D, bool LAGGED, int WS, bool PHI>
 __device__ __forceinline__ void cell_values(const CellJob& C, const Job& J, int u, int nt, int nch,
-                                            float kappa, float inv_kappa, float inv_sqrt_kappa,
-                                            ValueSmem<D>& sm) {
-    constexpr int N = CellDim<D>::N, H = N / 2;
+                                            float inv_cell, float kappa, float inv_kappa,
+                                            float inv_sqrt_kappa, ValueSmem<D, PHI>& sm) {
+    constexpr int N = CellDim<D>::N, F = CellDim<D>::F, H = N / 2;
+    static_assert(PHI || WS == 1, "the functions are made by the wave that owns the tile");
     const int tid = (int)threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, col = lane & 31, half = lane >> 5;
@@ -544,13 +680,45 @@ __device__ __forceinline__ void cell_values(const CellJob& C, const Job& J, int 
     float4 A[V];
     if (part < ntc) load(part, 0, A);
     float4 b[H / 4];
+    if constexpr (PHI) {
 #pragma unroll
-    for (int i = 0; i < H / 4; ++i) b[i] = C.phi[((size_t)ti * (H / 4) + i) * 64 + lane];
+        for (int i = 0; i < H / 4; ++i) b[i] = C.phi[((size_t)ti * (H / 4) + i) * 64 + lane];
+    }
     const float4 qc = C.qcen[tl.z];
     const int q = min(tl.x + col, tl.y - 1);
     const float4 v = J.qrec[q];
     const float sx = v.x - qc.x, sy = v.y - qc.y, sz = D == 3 ? v.z - qc.z : 0.f;
     const float sq = __builtin_fmaf(sx, sx, __builtin_fmaf(sy, sy, sz * sz));
+    if constexpr (!PHI) {
+        float* fn = sm.fn[wave];
+        __builtin_amdgcn_wave_barrier();
+        // half a wave per axis; the third axis by the first half
+#pragma unroll
+        for (int x0 = 0; x0 < D; x0 += 2) {
+            const int x = x0 + half;
+            const float s = (x == 0 ? sx : x == 1 ? sy : sz) * 2.f * inv_cell;   // on [-1, 1]
+            if (x < D) bessel<F>((float)CellDim<D>::lambda * s, fn + x * F * 33 + col, 33);
+        }
+        __builtin_amdgcn_wave_barrier();
+        // the empty asm keeps the places' addresses from living in registers across tiles
+        int sel = half, at = col;
+#pragma unroll
+        for (int n = 0; n < H; ++n) {
+            if (n % 8 == 0) asm volatile("" : "+v"(sel), "+v"(at));
+            float p = 1.f;
+#pragma unroll
+            for (int x = 0; x < D; ++x) {
+                const int r0 = (x * F + term<D>(n, x)) * 33, r1 = (x * F + term<D>(n + H, x)) * 33;
+                const float f = fn[(sel ? r1 : r0) + at];
+                p = x == 0 ? f : p * f;
+            }
+            asm volatile("" : "+v"(p));
+            if (n % 4 == 0) b[n / 4].x = p;
+            else if (n % 4 == 1) b[n / 4].y = p;
+            else if (n % 4 == 2) b[n / 4].z = p;
+            else b[n / 4].w = p;
+        }
+    }
     const float old = J.qpot[q], lw = J.qlog2w ? J.qlog2w[q] : J.qlog2w_s;
     if (tid == 0) sm.nflag = 0;
     float4* cd = sm.cd[wave];
@@ -649,10 +817,21 @@ __device__ __forceinline__ void cell_values(const CellJob& C, const Job& J, int 
 
 // --------------------------------------------------------------- launch kernels
 
+// In 2-D a launch carries a job's direct sweep too, for the points that the device leaves to
+// it.  In 3-D the moments need twice the registers, which cost such a sweep 6 to 20 %: there
+// the direct sweeps keep their own launch and leave it where the cell form is on
+// (Launch::skip); their merges ride in the values' launch.
+template <int D>
+constexpr bool kBoth = D == 2;
+
 template <int D, int R>
 union StepSmem {
     MomentSmem<D> m;
     SweepSmem<D, R> s;
+};
+template <int R>
+union StepSmem<3, R> {
+    MomentSmem<3> m;
 };
 
 // First launch of a sweep: of each job the moments of every (chunk, 32 query cells), or the
@@ -675,6 +854,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_cell_moments(Launch L, CellLaunch
             nu = nch * ((ncq + kCellTile - 1) / kCellTile);
             for (; u < nu; u += grid)
                 cell_moments<D>(K, J, u % nch, u / nch, nch, ncq, C.inv_cell, sm.m);
+        } else if constexpr (!kBoth<D>) {
+            nu = 0;
         } else {
             nu = J.nqb * J.splits;
             for (; u < nu; u += grid) {
@@ -690,7 +871,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cell_moments(Launch L, CellLaunch
 // Second launch: the values of every query tile, or the direct sweep's merge.
 template <int D, bool LAGGED, int VS>
 __global__ __launch_bounds__(kBlock, 2) void k_cell_values(Launch L, CellLaunch C) {
-    __shared__ ValueSmem<D> sm;
+    __shared__ ValueSmem<D, true> sm;
     const int grid = (int)gridDim.x;
     int u = (int)blockIdx.x;
     const int mode[2] = {*C.job[0].mode, *C.job[1].mode};
@@ -708,8 +889,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_cell_values(Launch L, CellLaunch 
             for (; u < 8 * per; u += grid) {
                 const int v = (u & 7) * per + (u >> 3);
                 if (v < nu)
-                    cell_values<D, LAGGED, VS>(K, J, v, nt, nch, L.kappa, L.inv_kappa,
-                                               L.inv_sqrt_kappa, sm);
+                    cell_values<D, LAGGED, VS, true>(K, J, v, nt, nch, C.inv_cell, L.kappa,
+                                                     L.inv_kappa, L.inv_sqrt_kappa, sm);
             }
             nu = 8 * per;
         } else {
@@ -722,6 +903,126 @@ __global__ __launch_bounds__(kBlock, 2) void k_cell_values(Launch L, CellLaunch 
         }
         u -= nu;
     }
+}
+
+// The same launches over job tables (the batched path).  A block keeps the ends of the jobs'
+// units in LDS and finds each unit's job by bisection; where some job takes the direct
+// sweep, its work units follow.
+__device__ __forceinline__ int unit_owner(const int* end, int n, int u) {
+    int lo = 0, hi = n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (end[mid] > u) hi = mid;
+        else lo = mid + 1;
+    }
+    return __builtin_amdgcn_readfirstlane(lo);
+}
+
+template <int D, int R, int WS, bool LAGGED>
+__global__ __launch_bounds__(kBlock, 2) void k_cell_tab_moments(TabLaunch L, CellBatch C, int k,
+                                                               float inv_cell) {
+    __shared__ StepSmem<D, R> sm;
+    __shared__ int end[kCellBatchJobs];
+    const int grid = (int)gridDim.x;
+    const CellJob* jobs = C.jobs + (size_t)k * C.stride;
+    const int* ends = C.uend + (size_t)k * 2 * C.stride;
+    const int direct = C.info[k];
+    for (int i = (int)threadIdx.x; i < L.njobs; i += kBlock) end[i] = ends[i];
+    __syncthreads();
+    const int total = end[L.njobs - 1];
+    for (int u = (int)blockIdx.x; u < total; u += grid) {
+        const int j = unit_owner(end, L.njobs, u);
+        const CellJob& K = jobs[j];
+        const int v = u - (j ? end[j - 1] : 0), nch = *K.nch;
+        cell_moments<D>(K, L.jobs[j], v % nch, v / nch, nch, *K.ncq, inv_cell, sm.m);
+    }
+    if constexpr (kBoth<D>) {
+        if (direct == 0) return;
+        __syncthreads();
+        for (int i = (int)threadIdx.x; i < L.njobs; i += kBlock) end[i] = L.blk_end[i];
+        __syncthreads();
+        for (int u = (int)blockIdx.x; u < L.nblocks; u += grid) {
+            const int j = unit_owner(end, L.njobs, u);
+            if (*jobs[j].mode) continue;
+            const Job& J = L.jobs[j];
+            const int v = u - (j ? end[j - 1] : 0);
+            sweep_unit<D, R, WS, LAGGED, false, true, LAGGED>(J, v % J.nqb, v / J.nqb, L.kappa,
+                                                              L.inv_kappa, L.inv_sqrt_kappa, sm.s);
+            __syncthreads();
+        }
+    }
+}
+
+template <int D, bool LAGGED>
+__global__ __launch_bounds__(kBlock, 2) void k_cell_tab_values(TabLaunch L, CellBatch C, int k,
+                                                              float inv_cell, int qpb) {
+    __shared__ ValueSmem<D, false> sm;
+    __shared__ int end[kCellBatchJobs];
+    const int grid = (int)gridDim.x;
+    const CellJob* jobs = C.jobs + (size_t)k * C.stride;
+    const int* ends = C.uend + (size_t)(k * 2 + 1) * C.stride;
+    const int direct = C.info[k];
+    for (int i = (int)threadIdx.x; i < L.njobs; i += kBlock) end[i] = ends[i];
+    __syncthreads();
+    const int total = end[L.njobs - 1], per = (total + 7) >> 3;
+    for (int u = (int)blockIdx.x; u < 8 * per; u += grid) {
+        const int w = (u & 7) * per + (u >> 3);   // runs of tiles per die, as in k_cell_values
+        if (w >= total) continue;
+        const int j = unit_owner(end, L.njobs, w);
+        const CellJob& K = jobs[j];
+        cell_values<D, LAGGED, 1, false>(K, L.jobs[j], w - (j ? end[j - 1] : 0), *K.ntile, *K.nch,
+                                         inv_cell, L.kappa, L.inv_kappa, L.inv_sqrt_kappa, sm);
+    }
+    if (!kBoth<D> || direct == 0 || L.nmerge == 0) return;
+    __syncthreads();
+    for (int i = (int)threadIdx.x; i < L.njobs; i += kBlock) end[i] = L.mrg_end[i];
+    __syncthreads();
+    for (int u = (int)blockIdx.x; u < L.nmerge; u += grid) {
+        const int j = unit_owner(end, L.njobs, u);
+        if (*jobs[j].mode) continue;
+        const Job& J = L.jobs[j];
+        merge_block<D, LAGGED, false>(J, (u - (j ? end[j - 1] : 0)) * kMergeRows, J.nqb * qpb,
+                                      L.kappa, L.inv_kappa, L.inv_sqrt_kappa);
+        __syncthreads();
+    }
+}
+
+template <int D, int R, int WS>
+void tab_moments(bool lagged, const TabLaunch& L, const CellBatch& C, int k, float inv_cell, int nb,
+                 hipStream_t s) {
+    if (lagged)
+        hipLaunchKernelGGL((k_cell_tab_moments<D, R, WS, true>), dim3(nb), dim3(kBlock), 0, s, L, C,
+                           k, inv_cell);
+    else
+        hipLaunchKernelGGL((k_cell_tab_moments<D, R, WS, false>), dim3(nb), dim3(kBlock), 0, s, L, C,
+                           k, inv_cell);
+}
+
+template <int D>
+hipError_t tab_launch(const Schedule& sc, bool lagged, const TabLaunch& L, const CellBatch& C, int k,
+                      hipStream_t s) {
+    const float inv_cell = (float)(1.0 / cell_side(D));
+    const int nm = 4096, nv = 2048, qpb = 64 * sc.R * (4 / sc.WS);
+    if constexpr (!kBoth<D>) {
+        tab_moments<D, 4, 4>(lagged, L, C, k, inv_cell, nm, s);
+    } else if (sc.WS == 2) {
+        if (sc.R == 1) tab_moments<D, 1, 2>(lagged, L, C, k, inv_cell, nm, s);
+        else if (sc.R == 2) tab_moments<D, 2, 2>(lagged, L, C, k, inv_cell, nm, s);
+        else tab_moments<D, 4, 2>(lagged, L, C, k, inv_cell, nm, s);
+    } else {
+        if (sc.R == 1) tab_moments<D, 1, 4>(lagged, L, C, k, inv_cell, nm, s);
+        else if (sc.R == 2) tab_moments<D, 2, 4>(lagged, L, C, k, inv_cell, nm, s);
+        else tab_moments<D, 4, 4>(lagged, L, C, k, inv_cell, nm, s);
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (lagged)
+        hipLaunchKernelGGL((k_cell_tab_values<D, true>), dim3(nv), dim3(kBlock), 0, s, L, C, k,
+                           inv_cell, qpb);
+    else
+        hipLaunchKernelGGL((k_cell_tab_values<D, false>), dim3(nv), dim3(kBlock), 0, s, L, C, k,
+                           inv_cell, qpb);
+    return hipGetLastError();
 }
 
 template <int D, int R, int WS>
@@ -749,11 +1050,15 @@ hipError_t moments_dr(bool lagged, const Launch& L, const CellLaunch& C, int nb,
 template <int D>
 hipError_t moments_d(bool lagged, const Launch& L, const CellLaunch& C, int nb, hipStream_t s,
                      hipEvent_t e0, hipEvent_t e1) {
-    switch (C.R) {
-        case 1: return moments_dr<D, 1>(lagged, L, C, nb, s, e0, e1);
-        case 2: return moments_dr<D, 2>(lagged, L, C, nb, s, e0, e1);
-        case 4: return moments_dr<D, 4>(lagged, L, C, nb, s, e0, e1);
-        default: return moments_dr<D, 8>(lagged, L, C, nb, s, e0, e1);
+    if constexpr (!kBoth<D>) {
+        return moments_drw<D, 4, 4>(lagged, L, C, nb, s, e0, e1);
+    } else {
+        switch (C.R) {
+            case 1: return moments_dr<D, 1>(lagged, L, C, nb, s, e0, e1);
+            case 2: return moments_dr<D, 2>(lagged, L, C, nb, s, e0, e1);
+            case 4: return moments_dr<D, 4>(lagged, L, C, nb, s, e0, e1);
+            default: return moments_dr<D, 8>(lagged, L, C, nb, s, e0, e1);
+        }
     }
 }
 
@@ -781,24 +1086,110 @@ double cell_side(int d) {
 // 537 / 407 / 385 at 262144).
 int cell_chunk(int n) { return n <= 24576 ? 256 : n <= 131072 ? 512 : kCellChunkMax; }
 
-hipError_t launch_cell_prep(const CellPrep& P, hipStream_t s) {
-    const int nbm = std::max(P.side[0].nb, P.side[1].nb);
+void cell_prep_layout(Arena& a, CellPrep& P, int d, int T, int M, int xo, int yo, int kcx, int kcy) {
+    P.d = d;
+    P.bits = d == 2 ? CellDim<2>::bits : CellDim<3>::bits;
+    P.ids = 1 << (P.bits * d);
+    P.cell = (float)cell_side(d);
+    for (int s = 0; s < 2; ++s) {
+        CellSide& S = P.side[s];
+        S.off = s ? yo : xo;
+        S.n = s ? M : T;
+        // points per block of the sort: few, since one wave scatters them in order, but at most
+        // 256 blocks up to 2^18 points, since every code's counts are summed over the blocks
+        S.per = std::max(256, ((S.n + 255) / 256 + 63) / 64 * 64);
+        S.nb = (S.n + S.per - 1) / S.per;
+        S.kc = s ? kcy : kcx;
+        S.cmax = std::min(P.ids, S.n / kCellMinPoints + 1);
+        S.chmax = S.cmax + S.n / S.kc;
+        S.tmax = S.cmax + S.n / kCellTile;
+        S.box = a.take<unsigned>(8);
+        S.id = a.take<unsigned short>(S.n);
+        S.bh = a.take<unsigned>((size_t)S.nb * P.ids);
+        S.first = a.take<unsigned>(P.ids);
+        S.perm = a.take<int>(S.n);
+        S.cen = a.take<float4>(S.cmax);
+        S.chunk = a.take<int4>(S.chmax);
+        S.chcen = a.take<float4>(S.chmax);
+        S.tile = a.take<int4>(S.tmax);
+        S.cnt = a.take<int>(4);
+    }
+    P.mode = a.take<int>(5);
+}
+
+// The partition's launches; TAB: of nprob problems of at most n points and nb sort blocks.
+template <bool TAB>
+static void partition(const CellPrep& P, const CellPrep* tab, const CellInputs& in, int ids, int n,
+                      int nb, int nprob, hipStream_t s) {
+    hipLaunchKernelGGL(k_cell_init<TAB>, dim3(1, 1, nprob), dim3(64), 0, s, P, tab);
+    hipLaunchKernelGGL(k_cell_box<TAB>, dim3(std::min(512, (n + 1023) / 1024), 2, nprob), dim3(256),
+                       0, s, P, tab, in);
+    hipLaunchKernelGGL(k_cell_hist<TAB>, dim3(nb, 2, nprob), dim3(256), 0, s, P, tab, in);
+    hipLaunchKernelGGL(k_cell_scan<TAB>, dim3(ids / 64, 2, nprob), dim3(256), 0, s, P, tab);
+    hipLaunchKernelGGL(k_cell_lists<TAB>, dim3(2, 1, nprob), dim3(1024), 0, s, P, tab);
+    hipLaunchKernelGGL(k_cell_scatter<TAB>, dim3(nb, 2, nprob), dim3(64), 0, s, P, tab);
+    hipLaunchKernelGGL(k_cell_gather<TAB>, dim3((n + 255) / 256, 1, nprob), dim3(256), 0, s, P, tab,
+                       in);
+}
+
+hipError_t launch_cell_prep(const CellPrep& P, const CellInputs& in, hipStream_t s) {
     const int n = std::max(P.side[0].n, P.side[1].n);
-    hipLaunchKernelGGL(k_cell_init, dim3(1), dim3(64), 0, s, P);
-    hipLaunchKernelGGL(k_cell_box, dim3(std::min(128, (n + 1023) / 1024), 2), dim3(256), 0, s, P);
-    hipLaunchKernelGGL(k_cell_hist, dim3(nbm, 2), dim3(256), 0, s, P);
-    hipLaunchKernelGGL(k_cell_scan, dim3((P.ids + 255) / 256, 2), dim3(256), 0, s, P);
-    hipLaunchKernelGGL(k_cell_lists, dim3(2), dim3(1024), 0, s, P);
-    hipLaunchKernelGGL(k_cell_scatter, dim3(nbm, 2), dim3(64), 0, s, P);
-    hipLaunchKernelGGL(k_cell_gather, dim3((n + 255) / 256), dim3(256), 0, s, P);
+    partition<false>(P, nullptr, in, P.ids, n, std::max(P.side[0].nb, P.side[1].nb), 1, s);
     const dim3 gf(std::min(2048, n / kCellTile + 128), 2);
-    if (P.d == 2) hipLaunchKernelGGL(k_cell_functions<2>, gf, dim3(256), 0, s, P);
-    else hipLaunchKernelGGL(k_cell_functions<3>, gf, dim3(256), 0, s, P);
+    if (P.d == 2) hipLaunchKernelGGL(k_cell_functions<2>, gf, dim3(256), 0, s, P, in);
+    else hipLaunchKernelGGL(k_cell_functions<3>, gf, dim3(256), 0, s, P, in);
     return hipGetLastError();
 }
 
-hipError_t launch_cell_sweep(int d, const Schedule& sc, bool lagged, const Launch& L,
-                             const CellLaunch& C, hipStream_t s) {
+hipError_t launch_cell_prep_batch(int d, const CellBatch& C, const CellInputs& in, int max_n,
+                                  int max_nb, hipStream_t s) {
+    CellPrep none;
+    std::memset(&none, 0, sizeof(none));
+    const int bits = d == 2 ? CellDim<2>::bits : CellDim<3>::bits;
+    partition<true>(none, C.prep, in, 1 << (bits * d), max_n, max_nb, C.B, s);
+    hipLaunchKernelGGL(k_cell_plan, dim3(1), dim3(1024), 0, s, C, d);
+    return hipGetLastError();
+}
+
+hipError_t launch_cell_tab(int d, const Schedule& sc, bool lagged, const TabLaunch& L,
+                           const CellBatch& C, int k, hipStream_t s) {
+    if (d == 2) return tab_launch<2>(sc, lagged, L, C, k, s);
+    TabLaunch T = L;
+    T.cell = C.jobs + (size_t)k * C.stride;
+    const hipError_t e = launch_tab(d, sc, lagged, false, T, s);
+    return e != hipSuccess ? e : tab_launch<3>(sc, lagged, L, C, k, s);
+}
+
+CellLimits cell_limits() {
+    CellLimits l;
+    if (const char* e = std::getenv("CT_CELL_MIN_PAIRS")) {
+        l.pairs = l.pairs3 = std::atof(e);
+        l.work = 0.0;
+    }
+    return l;
+}
+
+bool cell_candidate(int d, int nq, int nk) {
+    return d == 2 || (double)nq * nk >= cell_limits().pairs3;
+}
+
+hipError_t launch_cell_sweep(int d, const Schedule& sc, bool lagged, const Launch& L0,
+                             const CellLaunch& C0, int nblocks, hipStream_t s) {
+    Launch L = L0;
+    CellLaunch C = C0;
+    if (d == 3) {
+        bool any = false;
+        for (int j = 0; j < L.njobs; ++j) {
+            if (cell_candidate(d, L.job[j].nq, L.job[j].nk)) any = true;
+            else C.job[j].mode = C.never;
+            L.skip[j] = C.job[j].mode;
+        }
+        if (L.njobs == 1) C.job[1] = C.job[0];
+        if (!any) return launch_sweep(d, sc, lagged, false, L0, nblocks, s);
+        const hipError_t e = launch_sweep(d, Schedule{sc.R, sc.WS, sc.blocks_per_cu, 1}, lagged,
+                                          false, L, nblocks, s, false);
+        if (e != hipSuccess) return e;
+    }
     // grids for the units one can expect, up to the blocks that are resident at once (both
     // kernels walk whatever there is; blocks beyond that only queue)
     int units = 0, tiles = 0, direct = 0, merges = 0;

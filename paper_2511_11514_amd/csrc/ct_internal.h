@@ -78,6 +78,7 @@ constexpr int kMaxJobs = 4;
 struct Launch {
     Job job[kMaxJobs];
     int blk_end[kMaxJobs]; // job j owns blocks [blk_end[j-1], blk_end[j])
+    const int* skip[kMaxJobs]; // not null: the job's blocks leave at once where *skip is set
     int njobs;
     int expanded;          // 1: lagged sweeps without offsets use the expanded pair form
     float kappa, inv_kappa, inv_sqrt_kappa;
@@ -104,8 +105,9 @@ constexpr int kMaxCandidates = 128;
 int schedule_candidates(Schedule* out, int max);
 
 // Launch one sweep kernel (one or two jobs).
+// merge false: the caller's next launch merges the split jobs (separate-merge schedules).
 hipError_t launch_sweep(int d, const Schedule& sc, bool lagged, bool bary, const Launch& L,
-                        int nblocks, hipStream_t s);
+                        int nblocks, hipStream_t s, bool merge = true);
 
 // Lockstep launches over a job table in device memory (the batched path): job j
 // owns sweep blocks [blk_end[j-1], blk_end[j]) and merge blocks
@@ -116,6 +118,7 @@ struct TabLaunch {
     const int* mrg_end;
     int njobs;
     int nblocks, nmerge;
+    const struct CellJob* cell; // not null: jobs whose cell form is on (cells.h) leave at once
     int expanded;          // 1: lagged sweeps without offsets use the expanded pair form
     float kappa, inv_kappa, inv_sqrt_kappa;
 };

@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cmath>
 
+#include "cells.h"
 #include "ct_internal.h"
 #include "sweep_device.h"
 
@@ -27,6 +28,7 @@ __global__ __launch_bounds__(kBlock) void k_sweep_tab(TabLaunch L) {
     __shared__ SweepSmem<D, R> sm;
     const int bid = (int)blockIdx.x;
     const int j = __builtin_amdgcn_readfirstlane(owner(L.blk_end, L.njobs, bid));
+    if (L.cell && *L.cell[j].mode) return;
     const Job J = L.jobs[j];
     const int local = bid - (j ? L.blk_end[j - 1] : 0);
     const int qb = local % J.nqb;
@@ -39,6 +41,7 @@ template <int D, bool LAGGED, bool BARY>
 __global__ __launch_bounds__(kBlock) void k_merge_tab(TabLaunch L, int qpb) {
     const int bid = (int)blockIdx.x;
     const int j = __builtin_amdgcn_readfirstlane(owner(L.mrg_end, L.njobs, bid));
+    if (L.cell && *L.cell[j].mode) return;
     const Job J = L.jobs[j];
     const int q0 = (bid - (j ? L.mrg_end[j - 1] : 0)) * kMergeRows;
     merge_block<D, LAGGED, BARY>(J, q0, J.nqb * qpb, L.kappa, L.inv_kappa, L.inv_sqrt_kappa);

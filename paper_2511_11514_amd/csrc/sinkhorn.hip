@@ -331,53 +331,24 @@ struct SkLayout {
 constexpr int kCounters = 8;
 
 // Cell form of the sweeps (see cells.h): by default where the library would launch one
-// direct sweep at a time (an iteration has more than kMeshAutoPairs point pairs), from
-// kCellMinIters iterations on (splitting the points into cells costs about one iteration of
-// the smallest such problem) and up to kCellMaxPoints points a side (16-bit cell codes sorted
-// by at most 512 blocks).  Whether it pays and fits for the points at hand, k_cell_gather
-// settles on the device.  CT_UNFUSED, CT_DIFFERENCE, CT_SAFE_LSE and the flags of the other
+// direct sweep at a time and the call is large enough (cell_limits), up to kCellMaxPoints
+// points a side (16-bit cell codes sorted by at most 512 blocks).  Whether it pays and fits
+// for the points at hand, k_cell_gather settles on the device.  CT_UNFUSED, CT_DIFFERENCE, CT_SAFE_LSE and the flags of the other
 // executions rule it out, and so does a workspace without its arrays.
-constexpr int kCellMinIters = 8;
-constexpr int kCellMaxPoints = 1 << 22;
 constexpr size_t kCellMomentsMax = size_t(96) << 20;   // floats of one moments buffer
-constexpr int kCellMinPoints = 24;   // mean points of a cell below which the form cannot pay
 constexpr double kMeshAutoPairs = 1.5e7;
 
 static bool cells_possible(int T, int M) {
     const double pairs = 2.0 * T * M + (double)T * T + (double)M * M;
-    return pairs > kMeshAutoPairs && T <= kCellMaxPoints && M <= kCellMaxPoints;
+    return pairs > cell_limits().pairs && T <= kCellMaxPoints && M <= kCellMaxPoints;
 }
 
 static void cell_layout(Arena& a, SkLayout& L, int T, int M, int d) {
     CellPrep& P = L.prep;
     std::memset(&P, 0, sizeof(P));
-    P.d = d;
-    P.bits = d == 2 ? CellDim<2>::bits : CellDim<3>::bits;
-    P.ids = 1 << (P.bits * d);
-    P.cell = (float)cell_side(d);
+    cell_prep_layout(a, P, d, T, M, 0, 0, cell_chunk(T), cell_chunk(M));
     const int N = d == 2 ? CellDim<2>::N : CellDim<3>::N;
-    for (int s = 0; s < 2; ++s) {
-        CellSide& S = P.side[s];
-        S.n = s ? M : T;
-        S.per = std::max(1024, ((S.n + 511) / 512 + 63) / 64 * 64);
-        S.nb = (S.n + S.per - 1) / S.per;
-        S.kc = cell_chunk(S.n);
-        S.cmax = std::min(P.ids, S.n / kCellMinPoints + 1);
-        S.chmax = S.cmax + S.n / S.kc;
-        S.tmax = S.cmax + S.n / kCellTile;
-        S.box = a.take<unsigned>(8);
-        S.id = a.take<unsigned short>(S.n);
-        S.bh = a.take<unsigned>((size_t)S.nb * P.ids);
-        S.first = a.take<unsigned>(P.ids);
-        S.perm = a.take<int>(S.n);
-        S.cen = a.take<float4>(S.cmax);
-        S.chunk = a.take<int4>(S.chmax);
-        S.chcen = a.take<float4>(S.chmax);
-        S.tile = a.take<int4>(S.tmax);
-        S.phi = a.take<float4>((size_t)S.tmax * N * 8);
-        S.cnt = a.take<int>(4);
-    }
-    P.mode = a.take<int>(4);
+    for (int s = 0; s < 2; ++s) P.side[s].phi = a.take<float4>((size_t)P.side[s].tmax * N * 8);
     P.xs = a.take<float>((size_t)T * d);
     P.ys = a.take<float>((size_t)M * d);
     P.ws = a.take<float>(M);
@@ -509,10 +480,11 @@ static ct_status launch_set(const JobSet& js, const SkConsts& c, const Schedule&
         CellLaunch C;
         std::memset(&C, 0, sizeof(C));
         for (int i = 0; i < 2; ++i) C.job[i] = js.cell[std::min(i, js.n - 1)];
+        C.never = cells->prep.mode + 4;
         C.R = sc.R;
         C.WS = sc.WS;
         C.inv_cell = (float)(1.0 / cell_side(c.d));
-        CT_CHECK_HIP(launch_cell_sweep(c.d, sc, lagged, Lc, C, st));
+        CT_CHECK_HIP(launch_cell_sweep(c.d, sc, lagged, Lc, C, nb, st));
         return CT_OK;
     }
     CT_CHECK_HIP(launch_sweep(c.d, sc, lagged, bary, Lc, nb, st));
@@ -1029,7 +1001,12 @@ static ct_status sinkhorn_grad_impl(const float* x, int64_t T64, const float* y,
     CT_CHECK_HIP(hipGetLastError());
     const double iter_pairs = 2.0 * T * M + (debias ? (double)T * T : 0.0) +
                               (need_ref && !(o->flags & CT_REF_CACHED) ? (double)M * M : 0.0);
-    const bool cells = L.cells && o->iters >= kCellMinIters && iter_pairs > kMeshAutoPairs &&
+    const bool candidate = cell_candidate(d, T, M) || cell_candidate(d, T, T) ||
+                     (need_ref && cell_candidate(d, M, M));
+    const CellLimits lim = cell_limits();
+    const bool cells = L.cells && candidate && o->iters >= kCellMinIters &&
+                       iter_pairs > std::max(lim.pairs, kMeshAutoPairs) &&
+                       o->iters * iter_pairs > lim.work &&
                        !(o->flags & (CT_UNFUSED | CT_DIFFERENCE | CT_SAFE_LSE | CT_FUSED | CT_TINY |
                                      CT_MESH));
     const bool pot_given = o->flags & (CT_WARM_START | CT_REF_CACHED);
@@ -1041,13 +1018,9 @@ static ct_status sinkhorn_grad_impl(const float* x, int64_t T64, const float* y,
         // everything below works on the points in cell order; the outputs go back through
         // the permutations
         CellPrep& P = L.prep;
-        P.side[0].pts = x;
-        P.side[1].pts = y;
-        P.w = w;
         P.origin = L.origin;
-        P.sqrt_kappa = (float)std::sqrt(kappa_d);
-        P.pot_in = pot_given ? pot : nullptr;
-        CT_CHECK_HIP(launch_cell_prep(P, st));
+        CT_CHECK_HIP(launch_cell_prep(P, CellInputs{x, y, w, pot_given ? pot : nullptr,
+                                                    (float)std::sqrt(kappa_d)}, st));
         A.x = P.xs;
         A.y = P.ys;
         A.w = w ? P.ws : nullptr;

@@ -15,6 +15,7 @@ __global__ __launch_bounds__(kBlock) void k_sweep(Launch L) {
     const int bid = (int)blockIdx.x;
     int j = 0;
     while (j + 1 < L.njobs && bid >= L.blk_end[j]) ++j;
+    if (L.skip[j] && *L.skip[j]) return;
     const Job& J = L.job[j];
     const int local = bid - (j ? L.blk_end[j - 1] : 0);
     const int qb = local % J.nqb;
@@ -36,6 +37,7 @@ __global__ __launch_bounds__(kBlock) void k_merge(Launch L, int R, int WS) {
         start += nb;
         ++j;
     }
+    if (L.skip[j] && *L.skip[j]) return;
     const Job& J = L.job[j];
     const int nqpad = J.nqb * 64 * R * (4 / WS);
     merge_block<D, LAGGED, BARY>(J, (bid - start) * kMergeRows, nqpad, L.kappa, L.inv_kappa,
@@ -171,7 +173,7 @@ static hipError_t launch_d(const Schedule& sc, bool lagged, bool bary, const Lau
 // kernel's start and end: kind4[0] is 0/1 for a safe/lagged sweep and 10/11 for
 // its merge.
 hipError_t launch_sweep(int d, const Schedule& sc, bool lagged, bool bary, const Launch& L,
-                        int nblocks, hipStream_t s) {
+                        int nblocks, hipStream_t s, bool merge) {
     if (nblocks <= 0) return hipSuccess;
     double pairs = 0.0;
     for (int j = 0; j < L.njobs; ++j) pairs += (double)L.job[j].nq * L.job[j].nk;
@@ -182,7 +184,7 @@ hipError_t launch_sweep(int d, const Schedule& sc, bool lagged, bool bary, const
     hipError_t e = d == 2 ? launch_d<2>(sc, lagged, bary, L, nblocks, s, e0, e1)
                           : launch_d<3>(sc, lagged, bary, L, nblocks, s, e0, e1);
     profile_kernel_end(tok, lagged, bary, code, nblocks, pairs);
-    if (e != hipSuccess || !sc.sep) return e;
+    if (e != hipSuccess || !sc.sep || !merge) return e;
     const int nm = merge_blocks(L);
     if (nm == 0) return hipSuccess;
     tok = profile_kernel_begin(&e0, &e1);

@@ -1,5 +1,5 @@
-"""The cell form of the sweeps (default above 1.5e7 point pairs per iteration) against the
-direct sweeps on the same inputs (fused=False) and the FP64 oracle: both dimensions, chunk
+"""The cell form of the sweeps (the default of large calls; CT_CELL_MIN_PAIRS lets these
+sizes take it) against the direct sweeps on the same inputs (fused=False) and the FP64 oracle: both dimensions, chunk
 and tile remainders, warm start, cached reference, no debiasing, weights, one dense cell,
 points that do not fit the coded box, non-finite inputs, small workspaces and graphs.
 
@@ -18,6 +18,11 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 TOL = 2e-5
+
+
+@pytest.fixture(autouse=True)
+def _small_calls_take_the_cell_form(monkeypatch):
+    monkeypatch.setenv("CT_CELL_MIN_PAIRS", "1.5e7")
 
 
 def _inputs(d, T, M, seed=0):
@@ -167,4 +172,40 @@ def test_graph_replays(ct):
         assert torch.equal(out.grad_x, want.grad_x) and torch.equal(out.grad_w, want.grad_w)
         assert torch.equal(out.value, want.value)
         ct.sinkhorn_grad(y, x, None, eps=0.01, iters=9)   # eager work between the replays
+        torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("d,sizes", [
+    (2, [(900, 9000), (3000, 700), (2049, 5121), (1, 3), (400, 12000)]),   # mixed: some problems sweep directly
+    (3, [(600, 20000), (2500, 2600)]),
+])
+def test_batch_matches_direct_sweeps(ct, d, sizes):
+    """The lockstep launches' cell form against mode="lockstep" (direct sweeps), eagerly and as a
+    replayed graph with other calls between the replays."""
+    rng = np.random.default_rng(d)
+    t = lambda a: torch.as_tensor(a, device="cuda")
+    xs, ys, ws = [], [], []
+    for T, M in sizes:
+        g = W.gmm_params(rng, 4, d, 0.03, 0.12)
+        xs.append(t(W.random_walk(rng, T, d)))
+        ys.append(t(W.gmm_sample(rng, g, M)))
+        ws.append(t(W.positive_weights(rng, M)))
+    kw = dict(eps=0.01, iters=10, value=True, grad_w=True)
+    a = ct.sinkhorn_grad_batched(xs, ys, ws, **kw)
+    b = ct.sinkhorn_grad_batched(xs, ys, ws, mode="lockstep", **kw)
+    assert any(not torch.equal(u, v) for u, v in zip(a.grad_x, b.grad_x))
+    for u, v in list(zip(a.grad_x, b.grad_x)) + list(zip(a.grad_w, b.grad_w)):
+        if v.numel() > 8:
+            assert rel(u.cpu().numpy(), v.cpu().numpy()) < TOL
+    assert rel(a.value.cpu().numpy(), b.value.cpu().numpy()) < TOL
+    bs = ct.BatchedSinkhorn(xs, ys, ws, **kw)
+    bs.run()
+    torch.cuda.synchronize()
+    g = bs.capture()
+    for _ in range(3):
+        bs.grad_x.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(bs.grad_x, torch.cat(a.grad_x)) and torch.equal(bs.value, a.value)
+        ct.sinkhorn_grad(ys[0], xs[0], None, eps=0.01, iters=9)
         torch.cuda.synchronize()
