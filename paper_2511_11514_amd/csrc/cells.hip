@@ -326,7 +326,7 @@ __global__ __launch_bounds__(64) void k_cell_scatter(CellPrep one, const CellPre
 //   values   twice the products' clocks, and a fixed part per tile
 //   direct   the pairs' instructions at 75 % of their issue rate
 // and per sweep the launches (`launch`, in microseconds; a batch shares them).
-__device__ bool cell_pays(const CellSide& q, const CellSide& k, int d, double launch) {
+__device__ bool cell_pays(const CellSide& q, const CellSide& k, int d, double launch, double gain) {
     if (q.cnt[3] || k.cnt[3]) return false;
     const double N = d == 2 ? CellDim<2>::N : CellDim<3>::N;
     const double pair = d == 2 ? 2.0 / 128 + 2.0 / 64 + 1.0 / 32 : 2.0 / 128 + 3.0 / 64 + 1.0 / 32;
@@ -335,9 +335,14 @@ __device__ bool cell_pays(const CellSide& q, const CellSide& k, int d, double la
     const double values = q.cnt[2] * (ct * 2.0 * kCellTile * kCellTile * N / 128.0 + 1e3);
     const double direct = (double)q.n * k.n * pair / 0.75;
     const double per_us = 256.0 * 2400.0;
-    return (moments + values) / per_us + 0.6 * launch < 0.9 * (direct / per_us + launch);
+    return (moments + values) / per_us + 0.6 * launch < gain * (direct / per_us + launch);
 }
 constexpr double kCellLaunch = 8.0;
+// Modelled gain below which a sweep goes direct in a single problem; a batch's launch is slower
+// the more of its jobs are direct (their units wait behind the moments, three blocks to a
+// compute unit), so there the form is taken unless the model puts it at twice the direct time
+// (24 ragged problems, 150 iterations: 0.9 53.2 ms, 1.2 50.8, 1.6 46.0, 2.5 45.9, 4 45.1).
+constexpr double kGain = 0.9, kBatchGain = 2.0;
 
 // Points, weights and starting potentials in cell order.
 template <bool TAB>
@@ -354,7 +359,7 @@ __global__ __launch_bounds__(256) void k_cell_gather(CellPrep one, const CellPre
         const CellSide* k[4] = {&Y, &X, &X, &Y};
         for (int j = 0; j < 4; ++j) {
             const size_t need = (size_t)q[j]->cnt[0] * k[j]->cnt[1] * N;
-            P.mode[j] = need <= P.mom_cap[j < 2 ? 0 : j - 1] && cell_pays(*q[j], *k[j], d, kCellLaunch) ? 1 : 0;
+            P.mode[j] = need <= P.mom_cap[j < 2 ? 0 : j - 1] && cell_pays(*q[j], *k[j], d, kCellLaunch, kGain) ? 1 : 0;
         }
         P.mode[4] = 0;
     }
@@ -393,10 +398,10 @@ __global__ __launch_bounds__(1024) void k_cell_plan(CellBatch C, int d) {
         if (b < C.B) {
             const CellSide& X = C.prep[b].side[0];
             const CellSide& Y = C.prep[b].side[1];
-            pays[0] = cell_pays(X, Y, d, 0.0);
-            pays[1] = cell_pays(Y, X, d, 0.0);
-            pays[2] = cell_pays(X, X, d, 0.0);
-            pays[3] = cell_pays(Y, Y, d, 0.0);
+            pays[0] = cell_pays(X, Y, d, 0.0, kBatchGain);
+            pays[1] = cell_pays(Y, X, d, 0.0, kBatchGain);
+            pays[2] = cell_pays(X, X, d, 0.0, kBatchGain);
+            pays[3] = cell_pays(Y, Y, d, 0.0, kBatchGain);
             const int cx = X.cnt[0], cy = Y.cnt[0], hx = X.cnt[1], hy = Y.cnt[1];
             rows[0] = max(pays[0] ? cx * hy : 0, pays[1] ? cy * hx : 0);
             rows[1] = pays[2] ? cx * hx : 0;
