@@ -105,8 +105,9 @@ const char* ct_version(void);
                            in LDS (no synchronisation beyond the workgroup); CT_E_UNSUPPORTED
                            when the problem does not fit in the LDS of one workgroup (about
                            48 to 80 bytes per point of x and y, depending on the self terms). */
-#define CT_MESH 4096u   /* run all K iterations in one launch of 2 to 64 workgroups, each with
-                           every point in LDS and at most 64 rows of x and of y of its own;
+#define CT_MESH 4096u   /* run all K iterations in one launch of 1 to 128 workgroups, each with
+                           every point in LDS and at most 64 rows of x and of y of its own
+                           (one workgroup has up to 128);
                            the workgroups exchange their rows' new potentials through
                            versioned words in device memory (relaxed device-scope atomics),
                            with no grid barrier; CT_E_UNSUPPORTED when it cannot plan (T and
@@ -114,8 +115,9 @@ const char* ct_version(void);
                            fit in one workgroup's LDS).  Without any of CT_FUSED,
                            CT_UNFUSED, CT_TINY and CT_MESH (at most one may be given) the
                            library picks, by the point pairs of one iteration: the
-                           one-workgroup solve up to 4e4, the exchange solve up to 1.5e7 where
-                           it plans, else the one-workgroup solve up to 1.5e5, the fused
+                           exchange solve where T and M are at most 128 and one is above 16,
+                           the one-workgroup solve up to 4e4, the exchange solve up to 1.5e7
+                           where it plans, else the one-workgroup solve up to 1.5e5, the fused
                            solve up to 1.05e6, and per-sweep launches beyond.  Above 1e8
                            pairs (d = 3: where a sweep has 1.2e9), from 8 iterations and 1e10
                            pairs in all on, those launches take the cell form of a sweep
@@ -254,7 +256,8 @@ ct_status ct_status_sync(const void* ws, float resid_tol, uint32_t* nonfinite, u
  *   exchange (CT_MESH; the default when it applies): one launch for the whole
  *     batch, each problem given the blocks of its exchange solve (see CT_MESH:
  *     every point of the problem in each block's LDS, at most 64 own rows of x and
- *     of y per block, potentials passed between the problem's blocks as versioned
+ *     of y per block, fewer where the blocks fit, potentials passed between the problem's
+ *     blocks as versioned
  *     words); it applies when every problem has at most 1.5e7 point pairs per
  *     iteration and fits one workgroup's LDS and all the blocks fit on the device
  *     at once (decided by ct_sinkhorn_batched_prepare; CT_E_UNSUPPORTED there for

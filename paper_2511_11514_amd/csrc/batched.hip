@@ -783,7 +783,7 @@ size_t device_lds_per_block() {
 }
 
 bool plan_mesh_batch(const BLayout& L, const std::vector<BProb>& P, const ct_sinkhorn_opts* o,
-                     MeshArgs* tab, int* blk, MeshInfo& info) {
+                     int rows, int share, MeshArgs* tab, int* blk, MeshInfo& info) {
     info = MeshInfo{0, 0, 0.0, o->eps};
     const int B = (int)P.size(), d = o->d;
     const bool debias = o->flags & CT_DEBIAS;
@@ -809,7 +809,8 @@ bool plan_mesh_batch(const BLayout& L, const std::vector<BProb>& P, const ct_sin
         MeshArgs& A = tab[b];
         size_t lds = 0;
         int G = 0;
-        if (!mesh_plan(Q.T, Q.M, d, debias, need_ref, cap, true, A, lds, &G)) return false;
+        if (!mesh_plan(Q.T, Q.M, d, debias, need_ref, cap, true, rows, kMeshBatchThreads, A, lds, &G))
+            return false;
         A.cx = L.cx + Q.xo;
         A.cy = L.cy + Q.yo;
         A.log2b = L.log2b + Q.yo;
@@ -826,15 +827,6 @@ bool plan_mesh_batch(const BLayout& L, const std::vector<BProb>& P, const ct_sin
         A.xch_p = x0 + 2 * (size_t)Q.T;
         A.xch_g = x0 + 4 * (size_t)Q.T;
         A.xch_q = x0 + 4 * (size_t)Q.T + 2 * (size_t)Q.M;
-        for (int h = 0; h < 2; ++h)
-            for (int j = 0; j < A.njobs[h]; ++j) {
-                MeshJob& J = A.job[h][j];
-                J.xch = J.yside ? (J.avg ? A.xch_q : A.xch_g) : (J.avg ? A.xch_p : A.xch_f);
-            }
-        A.gat[0][0].xch = A.xch_g;
-        if (A.ngat[0] > 1) A.gat[0][1].xch = A.xch_p;
-        A.gat[1][0].xch = A.xch_f;
-        if (A.ngat[1] > 1) A.gat[1][1].xch = A.xch_q;
         A.rescued = L.counters + 1;
         A.expired = L.counters + 2;   // the batched outputs' invalid flag
         A.polls = polls;
@@ -851,7 +843,7 @@ bool plan_mesh_batch(const BLayout& L, const std::vector<BProb>& P, const ct_sin
         lds_max = std::max(lds_max, lds);
         pairs += o->iters * pp;
     }
-    if (blocks > mesh_resident_blocks(d, lds_max, true)) return false;
+    if (blocks > mesh_resident_blocks(d, lds_max, nullptr) / share) return false;
     info.blocks = blocks;
     info.lds = lds_max;
     info.pairs = pairs;
@@ -1038,7 +1030,16 @@ extern "C" ct_status ct_sinkhorn_batched_prepare(int32_t B, const int64_t* To, c
                info);
     MeshInfo minfo{0, 0, 0.0, o->eps};
     if (!(o->flags & (CT_PERSISTENT | CT_UNFUSED)) && o->iters > 0) {
-        const bool ok = plan_mesh_batch(L, BP, o, H0.mtab, H0.mblk, minfo);
+        // The fewest rows per block whose blocks take at most a quarter of what is resident at
+        // once (as for one problem), else the largest plan that fits.  Measured, d = 3, K = 100,
+        // whole call with 8 / 16 / 32 / 64 rows: 4 problems of 500 points 619 / 642 / 740 / 956
+        // us (64 rows of the previous kernel: 1025), 16 of 1000 - / - / 1500 / 1597 (1609), 64
+        // of 200 - / - / 718 / 720 (824).
+        int least = 8;   // test and tuning hook: at least so many own rows per block
+        if (const char* e = std::getenv("CT_MESH_ROWS")) least = std::max(8, std::min(64, std::atoi(e)));
+        bool ok = false;
+        for (int rows = least; rows <= kMeshRows && !ok; rows *= 2)
+            ok = plan_mesh_batch(L, BP, o, rows, rows < 32 ? 4 : 1, H0.mtab, H0.mblk, minfo);
         if (!ok) {
             minfo = MeshInfo{0, 0, 0.0, o->eps};
             if (o->flags & CT_MESH)

@@ -220,37 +220,14 @@ hipError_t launch_tiny(int d, const TinyArgs& A, size_t lds_bytes, hipStream_t s
 // problems stay valid.
 hipError_t ensure_dynamic_lds(const void* fn, size_t bytes);
 
-// Several workgroups, each holding every point in LDS and owning at most 64 rows
-// of each point set, exchanging their rows' potentials through versioned words
-// in global memory instead of grid barriers (mesh.hip).
-constexpr int kMeshThreads = 1024;                 // 16 waves
-constexpr int kMeshWaves = kMeshThreads / 64;
+// Workgroups that each hold every point in LDS and own a few rows of each point set,
+// exchanging their rows' potentials through versioned words in global memory instead of
+// grid barriers, or (one workgroup) through LDS (mesh.hip).
+constexpr int kMeshBatchThreads = 512;             // of the batch kernel (two blocks to a CU)
 constexpr int kMeshRows = 64;                      // rows of one point set per block, at most
-constexpr int kMeshMaxBlocks = 64;
-constexpr int kMeshGatherPerThread = 8;            // words one thread gathers per half-iteration
-// One soft-min job of a half-iteration over the block's own rows.  Offsets are
-// in float4 units for record arrays and in float units for everything else;
-// record arrays are indexed by the global row, potential arrays by the row's
-// place among the block's own rows.
-struct MeshJob {
-    int yside;             // rows of y (g, q) rather than of x (f, p)
-    int keys;              // key points
-    int qrec, krec;        // record arrays of the rows / keys
-    int qpot;              // potential of the block's own rows (from its first own row)
-    int avg;               // 1: new = (old + T)/2 (self problems)
-    int splits, kps;       // key ranges, keys per range
-    int task0;             // first task index of the job within its half-iteration
-    unsigned long long* xch;   // [2][rows] versioned words of the rows' new potentials
-};
-// One potential gathered into the .w of a record array at the start of a
-// half-iteration: version = iteration + lag.
-struct MeshGather {
-    const unsigned long long* xch;   // [2][n]
-    int n;                 // points
-    int rec;               // record array that takes H = h - |v'|^2 (|v'|^2 from its (2v'))
-    int lw;                // log2 mass, or -1: the constant log2a
-    int lag;               // 0: the version the iteration starts from, 1: the next one
-};
+constexpr int kMeshLocalRows = 128;                // the same for a problem of one block
+constexpr int kMeshMaxBlocks = 64;                 // blocks of kMeshRows rows a problem may need
+constexpr int kMeshGatherPerThread = 4;            // words one thread gathers at a time
 struct MeshArgs {
     const float4* cx;      // [T] staged coordinates of x (global)
     const float4* cy;      // [M] staged coordinates of y
@@ -266,27 +243,38 @@ struct MeshArgs {
     unsigned polls;        // poll bound of one gathered word
     unsigned version_extra;   // added to the awaited versions (0; a test hook makes waits unsatisfiable)
     int T, M, d, iters, lagged0, safe_only, debias, ref_iter;
+    int threads;           // of a block: 512 or 1024
+    int local;             // 1: one block, potentials pass through LDS
     int xr, yr;            // own rows per block of x and of y
+    int lx, ly;            // log2 of the row slots of x and y: 2^lx rows, two per thread
     float kappa, inv_kappa, log2a;
-    MeshJob job[2][2];     // [half-iteration][job]
-    int njobs[2], ntasks[2];
-    MeshGather gat[2][2];
-    int ngat[2];
     // LDS offsets: record arrays (float4 units), then floats
     int o_rf, o_rg, o_rp, o_rq;
-    int o_f, o_g, o_p, o_q, o_lb, o_ps, o_pm;
-    int ntask_max;
-    double est_cycles;     // the plan's modelled cycles per iteration (compute only)
+    int o_f, o_g, o_p, o_q, o_lb;
+    int o_cross, o_self;   // partial (sum, maximum) of the waves: [2][waves][rows]
+    int rows;              // of a partial array: 2^max(lx, ly)
 };
-// Plans blocks, tasks and the LDS layout (fills everything but the pointers and
-// the iteration options); false if the problem needs a single block (unless
-// allow_single), more than kMeshMaxBlocks blocks, or more than lds_cap bytes of
-// LDS per block.  Returns the grid size in *blocks.
+// Plans the blocks and the LDS layout for at most `rows` own rows of a point set per block
+// (8, 16, 32, 64; kMeshLocalRows: one block; fills everything but the pointers and the
+// iteration options); false if the problem needs a single block of kMeshRows (unless
+// allow_single), more than kMeshMaxBlocks of them, or more than lds_cap bytes of LDS per
+// block.  Returns the grid size in *blocks.
 bool mesh_plan(int T, int M, int d, bool debias, bool ref_iter, size_t lds_cap, bool allow_single,
-               MeshArgs& A, size_t& lds_bytes, int* blocks);
-// Blocks of the exchange kernel (single problem, or the batch kernel) that fit
-// on the device at once with this much dynamic LDS each.
-int mesh_resident_blocks(int d, size_t lds_bytes, bool batch);
+               int rows, int threads, MeshArgs& A, size_t& lds_bytes, int* blocks);
+// The plan of one problem: one block for at most kMeshLocalRows points a side; else the fewest
+// rows per block whose blocks take at most a quarter of what fits the device at once (so that
+// the solves of four hardware queues stay resident side by side), two 512-thread blocks to a
+// compute unit where LDS allows; from 32 rows on 1024 threads; kMeshRows rows otherwise.
+// Measured on an MI355X, us per iteration with 8 / 16 / 32 / 64 rows (and one block), cached
+// reference: d = 3, T = M = 100: 4.9 / 5.1 / 4.8 / 5.1 (3.8); 300: 5.3 / 5.4 / 6.0 / 7.1; 500:
+// 5.6 / 5.9 / 6.8 / 8.9; 2000 (1024 threads): 8.8 / 10.7 / 14.9 / 23.4; before rows were swept
+// two per thread over key subsets and self sweeps ran during the exchanges, with 64 rows:
+// 4.9 (one-workgroup solve), 7.9, 10.0 and 24.9.
+bool mesh_choose(int T, int M, int d, bool debias, bool ref_iter, size_t lds_cap, bool allow_single,
+                 MeshArgs& A, size_t& lds_bytes, int* blocks);
+// Blocks of the exchange kernel of plan `one` (null: the batch kernel) that fit on the
+// device at once with this much dynamic LDS each.
+int mesh_resident_blocks(int d, size_t lds_bytes, const MeshArgs* one);
 hipError_t launch_mesh(int d, const MeshArgs& A, size_t lds_bytes, int blocks, hipStream_t s);
 // All problems of a batch in one launch: tab[p] (device) holds problem p's
 // arguments, blk_end[p] (device) the end of its blocks; lds_bytes is the largest

@@ -3,24 +3,42 @@
 // Sinkhorn's algorithm; eq. 6's self terms) in one launch of G workgroups
 // without grid barriers.
 //
-// Every block holds all points (their records) in LDS and owns at most 64 rows
-// of each point set: rows [b*xr, (b+1)*xr) of x (the f and p updates) and
-// [b*yr, (b+1)*yr) of y (the g and q updates).  A half-iteration of a block:
-//   gather  the potentials its keys need from every block (f: the new one; g, p,
-//           q: the ones the iteration starts from) into the .w of its records;
-//   sweep   its own rows over all keys (tasks of 64 rows times one key range,
-//           partials in LDS, as in the one-workgroup solve);
-//   combine its rows, keep their new potentials and publish them.
+// Every block holds all points (their records) in LDS and owns some rows (8 to 64) of
+// each point set: rows [b*xr, (b+1)*xr) of x (the f and p updates) and [b*yr,
+// (b+1)*yr) of y (the g and q updates).  An iteration k of a block:
+//   gather g and p of version k; finish and publish q(k); sweep f;
+//   finish and publish f(k+1); sweep p; gather f(k+1) and q(k);
+//   finish and publish p(k+1); sweep g; finish and publish g(k+1); sweep q.
+// A sweep gives each thread two own rows and a subset of the keys: the lanes of a wave
+// split over row pairs first and keys for the rest (all of them where a block owns two
+// rows), the waves split over the remaining row pairs and key ranges.  Two rows per
+// thread read each key record once for two terms: one row per thread is bound by LDS
+// reads.  Lane sums go through DPP and permlane swaps, waves' partials through LDS.
+// What bounds an iteration of a small problem is the chain of two exchanges (a
+// published word takes about a microsecond to be seen), which is why the self sweeps
+// (p, q) run while the cross potentials travel and are finished half an iteration
+// late by other waves than the cross rows.  At 1000 points the sweeps' own issue time
+// is the larger part, hence as few rows per block as the device has room for.
+// LOCAL (one block, at most 128 points a side): the finished rows write their records
+// directly and nothing is exchanged; its registers are not bound to two blocks per
+// compute unit.  Measured, us per iteration (d = 3, cached reference; before: 64 rows
+// per block, one row per lane, f and p published together): T = M = 100 3.8 (4.9 in
+// the one-workgroup solve), 300 5.3 (7.9), 500 5.6 (10.0), 1000 8.0 (14.5), 2000 12.1
+// (24.9).  Launching a block per compute unit at 1024 threads (no two resident) was
+// 0.3 us faster at 8 rows, but leaves room for one solve less on each hardware queue.
+//
 // Potentials travel as 64-bit words (version << 32 | float bits), stored and
 // polled with relaxed device-scope atomics: a reader waits until a word carries
 // the version it needs, so each value brings its own synchronisation and no
 // block writes back or invalidates a cache (a grid barrier's release and
 // acquire fences do, and cost several microseconds at every half-iteration).
-// Words of version v live in buffer v mod 2: a block can publish version v + 2
-// only after it has read version v + 1 of every other block's rows, which each
-// of them publishes only after it has read its own inputs of version v, so no
-// word is overwritten before every reader has taken it.  The buffers are filled
-// with a never-matching version before each launch.
+// Words of version v live in buffer v mod 2.  No word is overwritten before every
+// reader has taken it: version v + 2 of f (p) is published after the gather of g at
+// version v + 1 (of f at v + 2), which waits on every block with y (x) rows, and each
+// of them publishes those only after its own reads of version v; the same holds for g
+// and q with x and y exchanged, and a block without rows of one set is waited on
+// through its rows of the other, which every block has.  The buffers are filled with a
+// never-matching version before each launch.
 //
 // All G blocks must be resident together (the plan keeps G at or below what
 // fits).  Every wait is bounded; a wait that gives up sets a flag that makes
@@ -30,6 +48,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstdlib>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -53,48 +72,55 @@ __device__ __forceinline__ float rec_norm(float x2, float y2, float z2) {
     return 0.25f * __builtin_fmaf(x2, x2, __builtin_fmaf(y2, y2, z2 * z2));
 }
 
-// Gather the half-iteration's potentials into the key records.  A thread takes
-// up to kMeshGatherPerThread words: their first loads are issued together, then
-// each word not yet at the awaited version is polled on its own.
-__device__ __forceinline__ void gather(const MeshArgs& A, int h, int k, float* lds) {
+// Gather one or two potentials (the second: null xch for none) into the key records.  A thread
+// takes up to kMeshGatherPerThread words: their first loads are issued together, then each
+// word not yet at the awaited version is polled on its own.
+struct Gather {
+    const unsigned long long* xch;   // [2][n]
+    int n;                           // points
+    int rec;                         // record array that takes H = h - |v'|^2
+    int lw;                          // log2 mass, or -1: the constant log2a
+    unsigned version;                // awaited
+};
+template <int NT>
+__device__ __forceinline__ void gather(const MeshArgs& A, const Gather& G0, const Gather& G1,
+                                       float* lds) {
     const int tid = (int)threadIdx.x;
-    const int ng = A.ngat[h];
-    const MeshGather& G0 = A.gat[h][0];
-    const MeshGather& G1 = A.gat[h][ng > 1 ? 1 : 0];
-    const int n0 = G0.n, ntot = n0 + (ng > 1 ? G1.n : 0);
-    const unsigned v0 = (unsigned)(k + G0.lag), v1 = (unsigned)(k + G1.lag);
-    const unsigned long long* X0 = G0.xch + (size_t)(v0 & 1u) * G0.n;
-    const unsigned long long* X1 = G1.xch + (size_t)(v1 & 1u) * G1.n;
-    unsigned long long w[kMeshGatherPerThread];
+    const int n0 = G0.n, ntot = n0 + G1.n;
+    const unsigned long long* X0 = G0.xch + (size_t)(G0.version & 1u) * G0.n;
+    const unsigned long long* X1 = G1.xch + (size_t)(G1.version & 1u) * G1.n;
+    for (int e0 = tid; e0 < ntot; e0 += NT * kMeshGatherPerThread) {
+        unsigned long long w[kMeshGatherPerThread];
 #pragma unroll
-    for (int s = 0; s < kMeshGatherPerThread; ++s) {
-        const int e = tid + s * kMeshThreads;
-        if (e < ntot) w[s] = e < n0 ? ldx(X0 + e) : ldx(X1 + (e - n0));
-    }
-#pragma unroll
-    for (int s = 0; s < kMeshGatherPerThread; ++s) {
-        const int e = tid + s * kMeshThreads;
-        if (e >= ntot) break;
-        const bool sec = e >= n0;
-        const int i = sec ? e - n0 : e;
-        const unsigned long long* a = sec ? X1 + i : X0 + i;
-        const unsigned want = (sec ? v1 : v0) + A.version_extra;
-        unsigned spins = 0;
-        while ((unsigned)(w[s] >> 32) != want) {
-            if (spins >= A.polls ||
-                __hip_atomic_load(A.expired, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) {
-                atomicOr(A.expired, 1u);
-                break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-            ++spins;
-            w[s] = ldx(a);
+        for (int s = 0; s < kMeshGatherPerThread; ++s) {
+            const int e = e0 + s * NT;
+            if (e < ntot) w[s] = e < n0 ? ldx(X0 + e) : ldx(X1 + (e - n0));
         }
-        const float v = __uint_as_float((unsigned)w[s]);
-        const int lw = sec ? G1.lw : G0.lw;
-        const float l = lw >= 0 ? lds[lw + i] : A.log2a;
-        float* rec = lds + 4 * ((sec ? G1.rec : G0.rec) + i);
-        rec[3] = __builtin_fmaf(v, A.kappa, l) - rec_norm(rec[0], rec[1], rec[2]);
+#pragma unroll
+        for (int s = 0; s < kMeshGatherPerThread; ++s) {
+            const int e = e0 + s * NT;
+            if (e >= ntot) break;
+            const bool sec = e >= n0;
+            const int i = sec ? e - n0 : e;
+            const unsigned long long* a = sec ? X1 + i : X0 + i;
+            const unsigned want = (sec ? G1.version : G0.version) + A.version_extra;
+            unsigned spins = 0;
+            while ((unsigned)(w[s] >> 32) != want) {
+                if (spins >= A.polls ||
+                    __hip_atomic_load(A.expired, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) {
+                    atomicOr(A.expired, 1u);
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+                ++spins;
+                w[s] = ldx(a);
+            }
+            const float v = __uint_as_float((unsigned)w[s]);
+            const int lw = sec ? G1.lw : G0.lw;
+            const float l = lw >= 0 ? lds[lw + i] : A.log2a;
+            float* rec = lds + 4 * ((sec ? G1.rec : G0.rec) + i);
+            rec[3] = __builtin_fmaf(v, A.kappa, l) - rec_norm(rec[0], rec[1], rec[2]);
+        }
     }
 }
 
@@ -105,139 +131,328 @@ __device__ __forceinline__ void publish(unsigned long long* xch, int n, int row,
                        __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// One point set's own rows as a thread sees them: two rows (slots r and r + 2^(lg-1) of
+// 2^lg), swept over every 2^(11-lg)-th key.  Lanes of a wave that share rows sit 2^(lg-1)
+// apart, so a wave reads 2^(7-lg) adjacent records at a time.
+struct Rows {
+    int first, n, lg, sub, nsub, slot;
+    float q[2][3], nrm[2];
+};
+template <int D, int NT>
+__device__ __forceinline__ Rows rows_of(const MeshArgs& A, bool yside, int b, const float4* lds4) {
+    Rows R;
+    const int tid = (int)threadIdx.x, N = yside ? A.M : A.T, per = yside ? A.yr : A.xr;
+    R.first = min(N, b * per);
+    R.n = min(N, R.first + per) - R.first;
+    R.lg = yside ? A.ly : A.lx;
+    const int half = 1 << (R.lg - 1);
+    R.slot = tid & (half - 1);
+    R.sub = tid >> (R.lg - 1);
+    R.nsub = NT >> (R.lg - 1);
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        // slots past the last row repeat it; nothing reads their sums
+        const int i = R.first + max(0, min(R.n - 1, R.slot + r * half));
+        const float4 v = lds4[(yside ? A.o_rg : A.o_rf) + min(i, N - 1)];
+        R.q[r][0] = 0.5f * v.x;
+        R.q[r][1] = 0.5f * v.y;
+        R.q[r][2] = 0.5f * v.z;
+        R.nrm[r] = rec_norm(v.x, v.y, v.z);
+    }
+    return R;
+}
+
+// Sum over the lanes whose numbers agree modulo `step` (a power of two), the same in each of
+// them.  Rotations inside rows of 16 lanes, then swaps of rows and halves: register moves, a
+// tenth of the latency of shuffles through LDS.
+template <int CTRL>
+__device__ __forceinline__ float rot(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float swap16(float v) {
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+__device__ __forceinline__ float swap32(float v) {
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+__device__ __forceinline__ float lane_sum(float v, int step) {
+    if (step >= 64) return v;
+    if (step == 32) return swap32(v);
+    if (step == 16) return swap32(swap16(v));
+    v += rot<0x128>(v);   // row_ror:8
+    if (step < 8) {
+        v += rot<0x124>(v);
+        if (step < 4) {
+            v += rot<0x122>(v);
+            if (step < 2) v += rot<0x121>(v);
+        }
+    }
+    return swap32(swap16(v));
+}
+
+// (m, s) and (m2, s2): a sum of 2^(e - m) each.
+__device__ __forceinline__ void join(float& m, float& s, float m2, float s2) {
+    const float t = fmaxf(m, m2);
+    const float u = t == -__builtin_huge_valf() ? 0.f : t;
+    s = s * tex2(m - u) + s2 * tex2(m2 - u);
+    m = t;
+}
+
+// Sums of the own rows over all keys with a tracked maximum, left as the waves' partials
+// part[0][wave][row] (sums) and part[1][wave][row] (maxima).  Out of line: only a cold first
+// iteration and CT_SAFE_LSE run it, and the loop's code should stay in the instruction cache.
+template <int D, int NT>
+__device__ __attribute__((noinline)) void sweep_tracked(const Rows R, const float4* kr, int keys,
+                                                        int prows, float* part) {
+    const int half = 1 << (R.lg - 1), tid = (int)threadIdx.x, st = R.nsub;
+    float C[2], m[2], s[2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        m[r] = -__builtin_huge_valf();
+        C[r] = -R.nrm[r];
+        s[r] = 0.f;
+    }
+    for (int j = R.sub; j < keys; j += st) {
+        const float4 k = kr[j];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) m[r] = fmaxf(m[r], kdot<D>(k, R.q[r]) + C[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r) C[r] -= m[r] == -__builtin_huge_valf() ? 0.f : m[r];
+    for (int j = R.sub; j < keys; j += st) {
+        const float4 k = kr[j];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) s[r] += tex2(kdot<D>(k, R.q[r]) + C[r]);
+    }
+    for (int x = half; x < 64; x <<= 1) {
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const float s2 = __shfl_xor(s[r], x), m2 = __shfl_xor(m[r], x);
+            // the same order of the pair in both lanes
+            float ma = (tid & x) ? m2 : m[r], sa = (tid & x) ? s2 : s[r];
+            join(ma, sa, (tid & x) ? m[r] : m2, (tid & x) ? s[r] : s2);
+            m[r] = ma;
+            s[r] = sa;
+        }
+    }
+    if ((tid & 63) < half) {
+        float* P = part + (tid >> 6) * prows + R.slot;
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            P[r * half] = s[r];
+            P[(NT / 64) * prows + r * half] = m[r];
+        }
+    }
+}
+
+// The same with the rows' own potentials as shifts: sums only.
+template <int D, int NT>
+__device__ __forceinline__ void sweep_rows(const MeshArgs& A, const Rows& R, const float4* kr,
+                                           int keys, const float* pot, bool lagged, float* part) {
+    if (R.n <= 0) return;
+    if (!lagged) {
+        sweep_tracked<D, NT>(R, kr, keys, A.rows, part);
+        return;
+    }
+    const int half = 1 << (R.lg - 1), tid = (int)threadIdx.x, st = R.nsub;
+    float C[2], acc[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+        C[r] = __builtin_fmaf(pot[min(R.n - 1, R.slot + r * half)], A.kappa, -R.nrm[r]);
+    int j = R.sub;
+    // four keys' records in flight together
+    for (; j + 3 * st < keys; j += 4 * st) {
+        float4 k[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) k[u] = kr[j + u * st];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int r = 0; r < 2; ++r) acc[r][u & 1] += tex2(kdot<D>(k[u], R.q[r]) + C[r]);
+    }
+    for (; j < keys; j += st) {
+        const float4 k = kr[j];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) acc[r][0] += tex2(kdot<D>(k, R.q[r]) + C[r]);
+    }
+    const float s0 = lane_sum(acc[0][0] + acc[0][1], half), s1 = lane_sum(acc[1][0] + acc[1][1], half);
+    if ((tid & 63) < half) {
+        float* P = part + (tid >> 6) * A.rows + R.slot;
+        P[0] = s0;
+        P[half] = s1;
+    }
+}
+
+// A row whose lagged sum left [2^-64, 2^64], with a tracked maximum over every key.
+template <int D>
+__device__ __attribute__((noinline)) float tracked_row(const float4 c, const float4* kr, int keys) {
+    const float q[1][3] = {{c.x, c.y, D == 3 ? c.z : 0.f}};
+    const float C[1] = {-norm2<D>(c)};
+    float m[1], s[1];
+    sum_safe<D, 1>(kr, 0, keys, q, C, m, s);
+    return m[0] + __log2f(s[0]);
+}
+
+// Finish the own rows from the waves' partials: their new potentials, kept and published
+// (or, one block, written into the key records).  By the threads from wave `w0` on, one wave
+// or (more than 64 rows) two.
+template <int D, int NT, bool LOCAL>
+__device__ __forceinline__ void finish_rows(const MeshArgs& A, const Rows& R, int w0, bool yside,
+                                            bool avg, const float4* kr, int keys, float* pot,
+                                            bool lagged, const float* part, unsigned long long* xch,
+                                            float* rec, const float* lw, unsigned version) {
+    const int rows = 1 << R.lg, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (R.n <= 0 || wave < w0 || wave >= w0 + max(1, rows >> 6)) return;
+    // opaque, so that what follows from it is formed here and not kept across iterations (70
+    // registers, the difference between one and two blocks per compute unit)
+    int t = (int)threadIdx.x - w0 * 64;
+    if (!LOCAL) asm volatile("" : "+v"(t));
+    const int row = t & (rows - 1);
+    const int groups = rows >= 64 ? 1 : 64 >> R.lg;   // lanes that share a row
+    const int row_c = min(row, R.n - 1);
+    const float old = pot[row_c];
+    const float* P = part + row;
+    const int g = (t >> R.lg) & (groups - 1);
+    float m, s = 0.f;
+    if (lagged) {
+        m = -old * A.kappa;
+        // a uniform count of reads per lane, four in flight (lanes beyond the waves add nothing)
+        const int n = max(1, NT / 64 / groups), st = groups * A.rows;
+        const float* Q = P + min(g, NT / 64 - 1) * A.rows;
+        if (n >= 4) {
+            for (int i = 0; i < n; i += 4) s += (Q[i * st] + Q[(i + 1) * st]) + (Q[(i + 2) * st] + Q[(i + 3) * st]);
+        } else {
+            for (int i = 0; i < n; ++i) s += Q[i * st];
+        }
+        s = lane_sum(g < NT / 64 ? s : 0.f, rows);
+    } else {
+        m = -__builtin_huge_valf();
+        for (int w = g; w < NT / 64; w += groups) join(m, s, P[(NT / 64 + w) * A.rows], P[w * A.rows]);
+        for (int x = rows; x < 64; x <<= 1) join(m, s, __shfl_xor(m, x), __shfl_xor(s, x));
+    }
+    if (t >= rows || row >= R.n) return;
+    float lse = m + __log2f(s);
+    if (lagged && !(s >= kLo && s <= kHi)) {
+        lse = tracked_row<D>((yside ? A.cy : A.cx)[R.first + row], kr, keys);
+        atomicAdd(A.rescued, 1u);
+    }
+    const float tn = -lse * A.inv_kappa;
+    const float nv = avg ? 0.5f * (old + tn) : tn;
+    pot[row] = nv;
+    if (LOCAL) {
+        float* r = rec + 4 * row;
+        r[3] = __builtin_fmaf(nv, A.kappa, lw ? lw[row] : A.log2a) - rec_norm(r[0], r[1], r[2]);
+    } else {
+        publish(xch, yside ? A.M : A.T, R.first + row, version, nv);
+    }
+}
+
 extern __shared__ float4 mesh_lds4[];
 
 // Block b of one problem's exchange solve.
-template <int D>
+template <int D, int NT, bool LOCAL>
 __device__ __forceinline__ void mesh_solve(const MeshArgs& A, const int b) {
     float4* lds4 = mesh_lds4;
     float* lds = reinterpret_cast<float*>(lds4);
     const int tid = (int)threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int lane = tid & 63;
-    const float ninf = -__builtin_huge_valf();
     const float kap = A.kappa;
     const int x0 = min(A.T, b * A.xr), x1 = min(A.T, x0 + A.xr);
     const int y0 = min(A.M, b * A.yr), y1 = min(A.M, y0 + A.yr);
 
-    // load: every point's record (2v', .w filled by the gathers) and log2 b; the
-    // own rows' potentials (indexed from the block's first own row), published as
-    // version 0
-    for (int i = tid; i < A.T; i += kMeshThreads) {
+    // load: every point's record (2v', .w filled by the gathers) and log2 b; the own rows'
+    // potentials (indexed from the block's first own row), published as version 0
+    for (int i = tid; i < A.T; i += NT) {
         const float4 c = A.cx[i];
         const float4 r = make_float4(2.f * c.x, 2.f * c.y, D == 3 ? 2.f * c.z : 0.f, 0.f);
         lds4[A.o_rf + i] = r;
-        if (A.debias) lds4[A.o_rp + i] = r;
+        if (A.debias) {
+            const float p = LOCAL ? A.p[i] : 0.f;
+            lds4[A.o_rp + i] = make_float4(r.x, r.y, r.z, __builtin_fmaf(p, kap, A.log2a) -
+                                                              rec_norm(r.x, r.y, r.z));
+        }
     }
-    for (int j = tid; j < A.M; j += kMeshThreads) {
+    for (int j = tid; j < A.M; j += NT) {
         const float4 c = A.cy[j];
         const float4 r = make_float4(2.f * c.x, 2.f * c.y, D == 3 ? 2.f * c.z : 0.f, 0.f);
-        lds4[A.o_rg + j] = r;
-        if (A.ref_iter) lds4[A.o_rq + j] = r;
-        lds[A.o_lb + j] = A.log2b[j];
+        const float lb = A.log2b[j], n = rec_norm(r.x, r.y, r.z);
+        const float g = LOCAL ? A.g[j] : 0.f, q = LOCAL ? A.q[j] : 0.f;
+        lds4[A.o_rg + j] = make_float4(r.x, r.y, r.z, __builtin_fmaf(g, kap, lb) - n);
+        if (A.ref_iter) lds4[A.o_rq + j] = make_float4(r.x, r.y, r.z, __builtin_fmaf(q, kap, lb) - n);
+        lds[A.o_lb + j] = lb;
     }
-    for (int i = x0 + tid; i < x1; i += kMeshThreads) {
+    for (int i = x0 + tid; i < x1; i += NT) {
         lds[A.o_f + i - x0] = A.f[i];   // f's version 0 is never awaited: iteration 0 reads version 1
         if (A.debias) {
             const float p = A.p[i];
             lds[A.o_p + i - x0] = p;
-            publish(A.xch_p, A.T, i, 0u, p);
+            if (!LOCAL) publish(A.xch_p, A.T, i, 0u, p);
         }
     }
-    for (int j = y0 + tid; j < y1; j += kMeshThreads) {
+    for (int j = y0 + tid; j < y1; j += NT) {
         const float g = A.g[j];
         lds[A.o_g + j - y0] = g;
-        publish(A.xch_g, A.M, j, 0u, g);
+        if (!LOCAL) publish(A.xch_g, A.M, j, 0u, g);
         if (A.ref_iter) {
             const float q = A.q[j];
             lds[A.o_q + j - y0] = q;
-            publish(A.xch_q, A.M, j, 0u, q);
+            if (!LOCAL) publish(A.xch_q, A.M, j, 0u, q);
         }
     }
     __syncthreads();
+    const Rows X = rows_of<D, NT>(A, false, b, lds4), Y = rows_of<D, NT>(A, true, b, lds4);
+    const float4 *rf = lds4 + A.o_rf, *rg = lds4 + A.o_rg, *rp = lds4 + A.o_rp, *rq = lds4 + A.o_rq;
+    float *pf = lds + A.o_f, *pg = lds + A.o_g, *pp = lds + A.o_p, *pq = lds + A.o_q;
+    float *cross = lds + A.o_cross, *self = lds + A.o_self;
+    const Gather none{A.xch_f, 0, 0, -1, 0u};
 
+    // An iteration: f over the keys of g, p while the new f travels, g over the keys of f, q
+    // while the new g travels (and before the next f).  p is finished and published after the
+    // wait for f, q after the next wait for g: each arrives half an iteration before it is
+    // read.  Waves 0 (1) finish the cross rows, waves 2 (3) the self rows, beside the sweep
+    // that the others have begun.
+    bool lag_q = false;   // mode of the sweep of q that waits to be finished
     for (int k = 0; k < A.iters; ++k) {
         const bool lagged = !A.safe_only && (A.lagged0 || k > 0);
-        for (int h = 0; h < 2; ++h) {
-            gather(A, h, k, lds);
-            __syncthreads();
-            const int nj = A.njobs[h];
-            // sweep: the block's rows (one per lane) over one key range per task
-            for (int t = wave; t < A.ntasks[h]; t += kMeshWaves) {
-                const int jj = (nj > 1 && t >= A.job[h][1].task0) ? 1 : 0;
-                const MeshJob& J = A.job[h][jj];
-                const int r0 = J.yside ? y0 : x0;
-                const int nr = (J.yside ? y1 : x1) - r0;
-                if (nr <= 0) continue;
-                const int split = t - J.task0;
-                const int k0 = min(J.keys, split * J.kps), k1 = min(J.keys, k0 + J.kps);
-                // lanes past the last row repeat it; the combine never reads them
-                const int lr = min(lane, nr - 1);
-                const float4 v = lds4[J.qrec + r0 + lr];
-                const float q[1][3] = {{0.5f * v.x, 0.5f * v.y, 0.5f * v.z}};
-                float m[1] = {lagged ? -lds[J.qpot + lr] * kap : 0.f};
-                const float C[1] = {-rec_norm(v.x, v.y, v.z) - m[0]};
-                float s[1];
-                if (lagged) sum_lagged<D, 1>(lds4 + J.krec, k0, k1, q, C, s);
-                else sum_safe<D, 1>(lds4 + J.krec, k0, k1, q, C, m, s);
-                lds[A.o_ps + t * 64 + lane] = s[0];
-                if (!lagged) lds[A.o_pm + t * 64 + lane] = m[0];
-            }
-            __syncthreads();
-            // combine and publish: one thread per own row of the half-iteration's jobs
-            const MeshJob& J0 = A.job[h][0];
-            const MeshJob& J1 = A.job[h][nj > 1 ? 1 : 0];
-            const int a0 = J0.yside ? y0 : x0;
-            const int a1 = J1.yside ? y0 : x0;
-            const int n0 = max(0, (J0.yside ? y1 : x1) - a0);
-            const int nrows = n0 + (nj > 1 ? max(0, (J1.yside ? y1 : x1) - a1) : 0);
-            for (int idx = tid; idx < nrows; idx += kMeshThreads) {
-                const bool sec = idx >= n0;
-                const int row = sec ? a1 + (idx - n0) : a0 + idx;
-                const int lrow = sec ? idx - n0 : idx;
-                const int task0 = sec ? J1.task0 : J0.task0;
-                const int splits = sec ? J1.splits : J0.splits;
-                const int qpot = sec ? J1.qpot : J0.qpot;
-                const int avg = sec ? J1.avg : J0.avg;
-                const float* ps = lds + A.o_ps + task0 * 64 + lrow;
-                const float* pm = lds + A.o_pm + task0 * 64 + lrow;
-                const float old = lds[qpot + lrow];
-                float mm, ss = 0.f;
-                if (lagged) {
-                    mm = -old * kap;
-                    for (int sp = 0; sp < splits; ++sp) ss += ps[sp * 64];
-                } else {
-                    mm = ninf;
-                    for (int sp = 0; sp < splits; ++sp) mm = fmaxf(mm, pm[sp * 64]);
-                    for (int sp = 0; sp < splits; ++sp) {
-                        const float mk = pm[sp * 64];
-                        if (mk != ninf) ss += ps[sp * 64] * tex2(mk - mm);
-                    }
-                }
-                if (lagged && !(ss >= kLo && ss <= kHi)) {
-                    // the row's shift was unusable: recompute with a tracked maximum
-                    const float4 v = lds4[(sec ? J1.qrec : J0.qrec) + row];
-                    const float qv[1][3] = {{0.5f * v.x, 0.5f * v.y, 0.5f * v.z}};
-                    const float C1[1] = {-rec_norm(v.x, v.y, v.z)};
-                    float m1[1], s1[1];
-                    sum_safe<D, 1>(lds4 + (sec ? J1.krec : J0.krec), 0, sec ? J1.keys : J0.keys,
-                                   qv, C1, m1, s1);
-                    mm = m1[0];
-                    ss = s1[0];
-                    atomicAdd(A.rescued, 1u);
-                }
-                const float tn = -(mm + __log2f(ss)) * A.inv_kappa;
-                const float nv = avg ? 0.5f * (old + tn) : tn;
-                lds[qpot + lrow] = nv;
-                publish(sec ? J1.xch : J0.xch, (sec ? J1.yside : J0.yside) ? A.M : A.T, row,
-                        (unsigned)(k + 1), nv);
-            }
+        const unsigned v = (unsigned)k;
+        if (!LOCAL)
+            gather<NT>(A, Gather{A.xch_g, A.M, A.o_rg, A.o_lb, v},
+                   A.debias ? Gather{A.xch_p, A.T, A.o_rp, -1, v} : none, lds);
+        __syncthreads();
+        if (A.ref_iter && k > 0)
+            finish_rows<D, NT, LOCAL>(A, Y, 2, true, true, rq, A.M, pq, lag_q, self, A.xch_q,
+                           lds + 4 * A.o_rq, lds + A.o_lb, v);
+        sweep_rows<D, NT>(A, X, rg, A.M, pf, lagged, cross);
+        __syncthreads();
+        finish_rows<D, NT, LOCAL>(A, X, 0, false, false, rg, A.M, pf, lagged, cross, A.xch_f,
+                       lds + 4 * A.o_rf, nullptr, v + 1u);
+        if (A.debias) sweep_rows<D, NT>(A, X, rp, A.T, pp, lagged, self);
+        if (!LOCAL)
+            gather<NT>(A, Gather{A.xch_f, A.T, A.o_rf, -1, v + 1u},
+                   A.ref_iter ? Gather{A.xch_q, A.M, A.o_rq, A.o_lb, v} : none, lds);
+        __syncthreads();
+        if (A.debias)
+            finish_rows<D, NT, LOCAL>(A, X, 2, false, true, rp, A.T, pp, lagged, self, A.xch_p,
+                           lds + 4 * A.o_rp, nullptr, v + 1u);
+        sweep_rows<D, NT>(A, Y, rf, A.T, pg, lagged, cross);
+        __syncthreads();
+        finish_rows<D, NT, LOCAL>(A, Y, 0, true, false, rf, A.T, pg, lagged, cross, A.xch_g,
+                       lds + 4 * A.o_rg, lds + A.o_lb, v + 1u);
+        if (A.ref_iter) {
+            sweep_rows<D, NT>(A, Y, rq, A.M, pq, lagged, self);
+            lag_q = lagged;
         }
     }
+    __syncthreads();
+    if (A.ref_iter && A.iters > 0)
+        finish_rows<D, NT, LOCAL>(A, Y, 2, true, true, rq, A.M, pq, lag_q, self, A.xch_q, lds + 4 * A.o_rq,
+                       lds + A.o_lb, (unsigned)A.iters);
+    __syncthreads();
 
     // store the own rows: potentials and the key terms the final pass reads
     const int hofs = D == 2 ? 2 : 3;
-    for (int i = x0 + tid; i < x1; i += kMeshThreads) {
+    for (int i = x0 + tid; i < x1; i += NT) {
         const float f = lds[A.o_f + i - x0];
         A.f[i] = f;
         reinterpret_cast<float*>(A.xrec_f + i)[hofs] = __builtin_fmaf(f, kap, A.log2a);
@@ -247,7 +462,7 @@ __device__ __forceinline__ void mesh_solve(const MeshArgs& A, const int b) {
             reinterpret_cast<float*>(A.xrec_p + i)[hofs] = __builtin_fmaf(p, kap, A.log2a);
         }
     }
-    for (int j = y0 + tid; j < y1; j += kMeshThreads) {
+    for (int j = y0 + tid; j < y1; j += NT) {
         const float g = lds[A.o_g + j - y0], lb = lds[A.o_lb + j];
         A.g[j] = g;
         reinterpret_cast<float*>(A.yrec_g + j)[hofs] = __builtin_fmaf(g, kap, lb);
@@ -259,9 +474,10 @@ __device__ __forceinline__ void mesh_solve(const MeshArgs& A, const int b) {
     }
 }
 
-template <int D>
-__global__ __launch_bounds__(kMeshThreads) void k_mesh(MeshArgs A) {
-    mesh_solve<D>(A, (int)blockIdx.x);
+// NT threads per block: 512 (two blocks to a compute unit) or 1024; one block (LOCAL) 512.
+template <int D, int NT, bool LOCAL>
+__global__ __launch_bounds__(NT, LOCAL ? 2 : 4) void k_mesh(MeshArgs A) {
+    mesh_solve<D, NT, LOCAL>(A, (int)blockIdx.x);
 }
 
 // Many problems in one launch: blk_end[p] is the end of problem p's blocks.  A
@@ -269,7 +485,7 @@ __global__ __launch_bounds__(kMeshThreads) void k_mesh(MeshArgs A) {
 // problem's exchange solve as its block (blockIdx.x - start).  Every problem
 // exchanges only among its own blocks.
 template <int D>
-__global__ __launch_bounds__(kMeshThreads) void k_mesh_batch(const MeshArgs* __restrict__ tab,
+__global__ __launch_bounds__(kMeshBatchThreads, 4) void k_mesh_batch(const MeshArgs* __restrict__ tab,
                                                              const int* __restrict__ blk_end,
                                                              int nprob) {
     __shared__ MeshArgs sA;
@@ -283,29 +499,40 @@ __global__ __launch_bounds__(kMeshThreads) void k_mesh_batch(const MeshArgs* __r
     const int start = lo ? blk_end[lo - 1] : 0;
     const unsigned* src = reinterpret_cast<const unsigned*>(tab + lo);
     unsigned* dst = reinterpret_cast<unsigned*>(&sA);
-    for (int i = (int)threadIdx.x; i < (int)(sizeof(MeshArgs) / 4); i += kMeshThreads) dst[i] = src[i];
+    for (int i = (int)threadIdx.x; i < (int)(sizeof(MeshArgs) / 4); i += kMeshBatchThreads) dst[i] = src[i];
     __syncthreads();
-    mesh_solve<D>(sA, bid - start);
+    mesh_solve<D, kMeshBatchThreads, false>(sA, bid - start);
 }
 
 }  // namespace
 
 bool mesh_plan(int T, int M, int d, bool debias, bool ref_iter, size_t lds_cap, bool allow_single,
-               MeshArgs& A, size_t& lds_bytes, int* blocks) {
+               int rows, int threads, MeshArgs& A, size_t& lds_bytes, int* blocks) {
     std::memset(&A, 0, sizeof(A));
     lds_bytes = 0;
     *blocks = 0;
-    const int G = std::max((T + kMeshRows - 1) / kMeshRows, (M + kMeshRows - 1) / kMeshRows);
-    if (G < (allow_single ? 1 : 2) || G > kMeshMaxBlocks) return false;
-    // the words one thread gathers in a half-iteration
-    const int gmax = std::max(M + (debias ? T : 0), T + (ref_iter ? M : 0));
-    if (gmax > kMeshGatherPerThread * kMeshThreads) return false;
+    const int most = std::max(T, M);
+    const int need = (most + kMeshRows - 1) / kMeshRows;
+    if (need < (allow_single ? 1 : 2) || need > kMeshMaxBlocks) return false;
+    if (rows > kMeshRows && most > rows) return false;
+    const int G = (most + rows - 1) / rows;
     A.T = T;
     A.M = M;
     A.debias = debias;
     A.ref_iter = ref_iter;
+    A.threads = threads;
+    A.local = G == 1 && rows > kMeshRows;
     A.xr = (T + G - 1) / G;
     A.yr = (M + G - 1) / G;
+    // row slots: at least two (a thread has two rows), so that a wave's lanes split keys too
+    auto lg = [](int n) {
+        int l = 1;
+        while ((1 << l) < n) ++l;
+        return l;
+    };
+    A.lx = lg(A.xr);
+    A.ly = lg(A.yr);
+    A.rows = 1 << std::max(A.lx, A.ly);
     int r4 = 0;
     A.o_rf = r4; r4 += T;
     A.o_rg = r4; r4 += M;
@@ -323,81 +550,8 @@ bool mesh_plan(int T, int M, int d, bool debias, bool ref_iter, size_t lds_cap, 
     A.o_p = take(debias ? A.xr : 0);
     A.o_q = take(ref_iter ? A.yr : 0);
     A.o_lb = take(M);
-    auto mk = [&](int yside, int keys, int qrec, int krec, int qpot, int avg) {
-        MeshJob j;
-        std::memset(&j, 0, sizeof(j));
-        j.yside = yside; j.keys = keys; j.qrec = qrec; j.krec = krec; j.qpot = qpot; j.avg = avg;
-        return j;
-    };
-    A.njobs[0] = A.njobs[1] = 0;
-    A.job[0][A.njobs[0]++] = mk(0, M, A.o_rf, A.o_rg, A.o_f, 0);
-    if (debias) A.job[0][A.njobs[0]++] = mk(0, T, A.o_rf, A.o_rp, A.o_p, 1);
-    A.job[1][A.njobs[1]++] = mk(1, T, A.o_rg, A.o_rf, A.o_g, 0);
-    if (ref_iter) A.job[1][A.njobs[1]++] = mk(1, M, A.o_rg, A.o_rq, A.o_q, 1);
-    // gathers: half 0 needs g and p as the iteration starts; half 1 the new f and q
-    auto gt = [&](int n, int rec, int lw, int lag) {
-        MeshGather g;
-        std::memset(&g, 0, sizeof(g));
-        g.n = n; g.rec = rec; g.lw = lw; g.lag = lag;
-        return g;
-    };
-    A.ngat[0] = A.ngat[1] = 0;
-    A.gat[0][A.ngat[0]++] = gt(M, A.o_rg, A.o_lb, 0);
-    if (debias) A.gat[0][A.ngat[0]++] = gt(T, A.o_rp, -1, 0);
-    A.gat[1][A.ngat[1]++] = gt(T, A.o_rf, -1, 1);
-    if (ref_iter) A.gat[1][A.ngat[1]++] = gt(M, A.o_rq, A.o_lb, 0);
-
-    // Key ranges: each job gets a share of the 16 waves' tasks in proportion to
-    // its keys (at least 16 keys per range); a few multiples of 16 tasks are
-    // tried and the one with the least modelled time per SIMD kept (a wave's
-    // pass over one key: d + 2 VALU instructions and one exp; a task's set-up).
-    const double c_key = 2.0 * (d + 2) + 8.0, c_task = 160.0;
-    double est = 0.0;
-    int ntask_max = 0;
-    for (int h = 0; h < 2; ++h) {
-        double ktot = 0.0;
-        for (int j = 0; j < A.njobs[h]; ++j) ktot += A.job[h][j].keys;
-        double best = 0.0;
-        int best_sp[2] = {1, 1};
-        for (int mult = 1; mult <= 4; mult *= 2) {
-            int sp[2] = {1, 1}, kps[2] = {1, 1}, t = 0;
-            double simd[4] = {0.0, 0.0, 0.0, 0.0};
-            for (int j = 0; j < A.njobs[h]; ++j) {
-                const int keys = A.job[h][j].keys;
-                const int cap = std::max(1, (keys + 15) / 16);
-                sp[j] = std::min(cap, std::max(1, (int)std::lround(kMeshWaves * mult * keys / ktot)));
-                kps[j] = (keys + sp[j] - 1) / sp[j];
-                sp[j] = (keys + kps[j] - 1) / kps[j];
-                for (int u = 0; u < sp[j]; ++u) {
-                    const int k0 = std::min(keys, u * kps[j]);
-                    const int nk = std::min(keys, k0 + kps[j]) - k0;
-                    simd[(t + u) % 4] += c_task + nk * c_key;
-                }
-                t += sp[j];
-            }
-            const double cyc = std::max(std::max(simd[0], simd[1]), std::max(simd[2], simd[3]));
-            if (mult == 1 || cyc < best) {
-                best = cyc;
-                best_sp[0] = sp[0];
-                best_sp[1] = sp[1];
-            }
-        }
-        int t = 0;
-        for (int j = 0; j < A.njobs[h]; ++j) {
-            MeshJob& J = A.job[h][j];
-            J.kps = (J.keys + best_sp[j] - 1) / best_sp[j];
-            J.splits = (J.keys + J.kps - 1) / J.kps;
-            J.task0 = t;
-            t += J.splits;
-        }
-        A.ntasks[h] = t;
-        ntask_max = std::max(ntask_max, t);
-        est += best;
-    }
-    A.ntask_max = ntask_max;
-    A.o_ps = take(64 * ntask_max);
-    A.o_pm = take(64 * ntask_max);
-    A.est_cycles = est;
+    A.o_cross = take(2 * (threads / 64) * A.rows);
+    A.o_self = take(debias || ref_iter ? 2 * (threads / 64) * A.rows : 0);
     lds_bytes = (size_t)off * sizeof(float);
     if (lds_bytes > lds_cap) return false;
     *blocks = G;
@@ -419,34 +573,68 @@ hipError_t ensure_dynamic_lds(const void* fn, size_t bytes) {
     return e;
 }
 
-static const void* mesh_kernel(int d, bool batch) {
-    if (batch)
-        return d == 2 ? reinterpret_cast<const void*>(&k_mesh_batch<2>)
-                      : reinterpret_cast<const void*>(&k_mesh_batch<3>);
-    return d == 2 ? reinterpret_cast<const void*>(&k_mesh<2>)
-                  : reinterpret_cast<const void*>(&k_mesh<3>);
+enum MeshKernel { kOne512, kOne1024, kOneLocal, kBatch };
+static const void* mesh_kernel(int d, int which) {
+    switch (which) {
+        case kOne512:
+            return d == 2 ? reinterpret_cast<const void*>(&k_mesh<2, 512, false>)
+                          : reinterpret_cast<const void*>(&k_mesh<3, 512, false>);
+        case kOne1024:
+            return d == 2 ? reinterpret_cast<const void*>(&k_mesh<2, 1024, false>)
+                          : reinterpret_cast<const void*>(&k_mesh<3, 1024, false>);
+        case kOneLocal:
+            return d == 2 ? reinterpret_cast<const void*>(&k_mesh<2, 512, true>)
+                          : reinterpret_cast<const void*>(&k_mesh<3, 512, true>);
+        default:
+            return d == 2 ? reinterpret_cast<const void*>(&k_mesh_batch<2>)
+                          : reinterpret_cast<const void*>(&k_mesh_batch<3>);
+    }
+}
+static int mesh_which(const MeshArgs& A) {
+    return A.local ? kOneLocal : A.threads == 1024 ? kOne1024 : kOne512;
 }
 
-int mesh_resident_blocks(int d, size_t lds_bytes, bool batch) {
+static int resident_blocks(int d, size_t lds_bytes, int which, int threads) {
     static std::mutex mu;
     static std::map<std::pair<int, std::pair<int, size_t>>, int> cache;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
-    const auto key = std::make_pair(dev * 2 + (batch ? 1 : 0), std::make_pair(d, lds_bytes));
+    const auto key = std::make_pair(dev * 4 + which, std::make_pair(d, lds_bytes));
     std::lock_guard<std::mutex> lk(mu);
     auto it = cache.find(key);
     if (it != cache.end()) return it->second;
     int per_cu = 0, cus = 0;
-    const void* fn = mesh_kernel(d, batch);
+    const void* fn = mesh_kernel(d, which);
     if (ensure_dynamic_lds(fn, lds_bytes) != hipSuccess)
         per_cu = 0;
-    else if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kMeshThreads, lds_bytes) !=
-             hipSuccess)
+    else if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds_bytes) != hipSuccess)
         per_cu = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
     const int n = std::max(0, per_cu) * std::max(0, cus);
     cache.emplace(key, n);
     return n;
+}
+
+int mesh_resident_blocks(int d, size_t lds_bytes, const MeshArgs* one) {
+    return one ? resident_blocks(d, lds_bytes, mesh_which(*one), one->threads)
+               : resident_blocks(d, lds_bytes, kBatch, kMeshBatchThreads);
+}
+
+bool mesh_choose(int T, int M, int d, bool debias, bool ref_iter, size_t lds_cap, bool allow_single,
+                 MeshArgs& A, size_t& lds_bytes, int* blocks) {
+    // test and tuning hook: at most so many own rows per block
+    int force = 0;
+    if (const char* e = std::getenv("CT_MESH_ROWS")) force = std::atoi(e);
+    auto plan = [&](int rows, int threads, int share) {
+        return mesh_plan(T, M, d, debias, ref_iter, lds_cap, allow_single, rows, threads, A,
+                         lds_bytes, blocks) &&
+               *blocks * share <= mesh_resident_blocks(d, lds_bytes, &A);
+    };
+    if ((force == 0 || force == kMeshLocalRows) && plan(kMeshLocalRows, 512, 1)) return true;
+    for (int rows = 8; rows <= 16; rows *= 2)
+        if ((force == 0 || force == rows) && plan(rows, 512, 4)) return true;
+    if ((force == 0 || force == 32) && plan(32, 1024, 4)) return true;
+    return plan(kMeshRows, 1024, 1) || plan(kMeshRows, 512, 1);   // (512 threads: less LDS)
 }
 
 hipError_t launch_mesh(int d, const MeshArgs& A, size_t lds_bytes, int blocks, hipStream_t s) {
@@ -455,16 +643,17 @@ hipError_t launch_mesh(int d, const MeshArgs& A, size_t lds_bytes, int blocks, h
     const double pairs = (double)A.iters * ((double)A.T * A.M * 2 + (A.debias ? (double)A.T * A.T : 0.0) +
                                             (A.ref_iter ? (double)A.M * A.M : 0.0));
     {
-        const hipError_t e = ensure_dynamic_lds(mesh_kernel(d, false), lds_bytes);
+        const hipError_t e = ensure_dynamic_lds(mesh_kernel(d, mesh_which(A)), lds_bytes);
         if (e != hipSuccess) return e;
     }
-    if (d == 2) {
-        if (e0) hipExtLaunchKernelGGL((k_mesh<2>), dim3(blocks), dim3(kMeshThreads), lds_bytes, s, e0, e1, 0, A);
-        else hipLaunchKernelGGL((k_mesh<2>), dim3(blocks), dim3(kMeshThreads), lds_bytes, s, A);
-    } else {
-        if (e0) hipExtLaunchKernelGGL((k_mesh<3>), dim3(blocks), dim3(kMeshThreads), lds_bytes, s, e0, e1, 0, A);
-        else hipLaunchKernelGGL((k_mesh<3>), dim3(blocks), dim3(kMeshThreads), lds_bytes, s, A);
-    }
+    auto go = [&](auto kernel) {
+        if (e0) hipExtLaunchKernelGGL(kernel, dim3(blocks), dim3(A.threads), lds_bytes, s, e0, e1, 0, A);
+        else hipLaunchKernelGGL(kernel, dim3(blocks), dim3(A.threads), lds_bytes, s, A);
+    };
+    const int which = mesh_which(A);
+    if (which == kOneLocal) d == 2 ? go(k_mesh<2, 512, true>) : go(k_mesh<3, 512, true>);
+    else if (which == kOne512) d == 2 ? go(k_mesh<2, 512, false>) : go(k_mesh<3, 512, false>);
+    else d == 2 ? go(k_mesh<2, 1024, false>) : go(k_mesh<3, 1024, false>);
     const hipError_t e = hipGetLastError();
     // kind 40/41: a multi-workgroup exchange solve (safe / lagged from its first iteration)
     profile_kernel_end(tok, 40 + A.lagged0, 0, 0, blocks, pairs);
@@ -477,15 +666,15 @@ hipError_t launch_mesh_batch(int d, const MeshArgs* tab, const int* blk_end, int
     void* tok = profile_kernel_begin(&e0, &e1);
     {
         // set when the batch was planned (so not during a graph capture of the run)
-        const hipError_t e = ensure_dynamic_lds(mesh_kernel(d, true), lds_bytes);
+        const hipError_t e = ensure_dynamic_lds(mesh_kernel(d, kBatch), lds_bytes);
         if (e != hipSuccess) return e;
     }
     if (d == 2) {
-        if (e0) hipExtLaunchKernelGGL((k_mesh_batch<2>), dim3(blocks), dim3(kMeshThreads), lds_bytes, s, e0, e1, 0, tab, blk_end, nprob);
-        else hipLaunchKernelGGL((k_mesh_batch<2>), dim3(blocks), dim3(kMeshThreads), lds_bytes, s, tab, blk_end, nprob);
+        if (e0) hipExtLaunchKernelGGL((k_mesh_batch<2>), dim3(blocks), dim3(kMeshBatchThreads), lds_bytes, s, e0, e1, 0, tab, blk_end, nprob);
+        else hipLaunchKernelGGL((k_mesh_batch<2>), dim3(blocks), dim3(kMeshBatchThreads), lds_bytes, s, tab, blk_end, nprob);
     } else {
-        if (e0) hipExtLaunchKernelGGL((k_mesh_batch<3>), dim3(blocks), dim3(kMeshThreads), lds_bytes, s, e0, e1, 0, tab, blk_end, nprob);
-        else hipLaunchKernelGGL((k_mesh_batch<3>), dim3(blocks), dim3(kMeshThreads), lds_bytes, s, tab, blk_end, nprob);
+        if (e0) hipExtLaunchKernelGGL((k_mesh_batch<3>), dim3(blocks), dim3(kMeshBatchThreads), lds_bytes, s, e0, e1, 0, tab, blk_end, nprob);
+        else hipLaunchKernelGGL((k_mesh_batch<3>), dim3(blocks), dim3(kMeshBatchThreads), lds_bytes, s, tab, blk_end, nprob);
     }
     const hipError_t e = hipGetLastError();
     // kind 42: the exchange solve of a whole batch in one launch

@@ -746,19 +746,20 @@ static ct_status run_tiny(const SkLayout& L, const SkConsts& c, const ct_sinkhor
     return CT_OK;
 }
 
-// Multi-workgroup exchange solve (all K iterations in one launch of blocks that
-// each hold every point in LDS and own at most 64 rows of each point set; see
-// mesh.hip).  By default it is taken when it plans (two or more blocks, every
-// point in one block's LDS, all blocks resident at once), one iteration has more
-// than kMeshMinPairs point pairs (below that the one-workgroup solve is as fast)
-// and at most kMeshAutoPairs.  Measured on an MI355X, K = 100, d = 3, T = M,
-// cached reference potential, whole call (exchange / one-workgroup / fused /
-// per-sweep launches): T = 100: 0.63 / 0.59 / 1.34 / 1.41 ms; 300: 0.87 / 1.94 /
-// 1.87 / 2.26; 500: 1.08 / 3.65 / 2.63 / 2.66; 1000: 1.54 / - / 7.0 / 2.70;
-// 2000: 2.57 / - / 23.5 / 3.13; 2500 (1.9e7 pairs): 3.20 against 3.16 for per-sweep
-// launches, so the default stops below.  CT_MESH forces it (CT_E_UNSUPPORTED when it
-// cannot plan); CT_FUSED, CT_UNFUSED and CT_TINY rule it out.
+// Exchange solve (all K iterations in one launch of blocks that each hold every point
+// in LDS; see mesh.hip and mesh_choose).  By default it is taken when it plans (every
+// point in one block's LDS, all blocks resident at once) and one iteration has at most
+// kMeshAutoPairs point pairs and more than kMeshMinPairs, or both sides fit its
+// one-block form and one has more than kMeshMinPoints points: elsewhere the one-workgroup
+// solve is as fast or faster (130 x 20 points: 490 us against 531; 20 x 400: 516 / 591;
+// 130 x 60: 518 / 515).  Measured on an MI355X, K = 100, d = 3, T = M, whole call (exchange /
+// one-workgroup): T = 10: 272 / 265 us; 30: 272 / 311; 64: 300 / 324; 100: 372 / 522;
+// 128: 408 / 536; 180: 534 / 739; cached reference (exchange / fused / per-sweep
+// launches): T = 300: 0.60 / 1.87 / 2.26 ms; 500: 0.64 / 2.63 / 2.66; 1000: 0.9 / 7.0 /
+// 2.70; 2000: 1.3 / 23.5 / 3.13.  CT_MESH forces it (CT_E_UNSUPPORTED when it cannot
+// plan); CT_FUSED, CT_UNFUSED and CT_TINY rule it out.
 constexpr double kMeshMinPairs = 40000.0;
+constexpr int kMeshMinPoints = 16;
 constexpr unsigned kMeshWaitPolls = 1u << 18;
 
 static ct_status run_mesh(const SkLayout& L, const SkConsts& c, const ct_sinkhorn_opts* o,
@@ -769,16 +770,18 @@ static ct_status run_mesh(const SkLayout& L, const SkConsts& c, const ct_sinkhor
     const bool forced = o->flags & CT_MESH;
     const double pairs = 2.0 * T * M + (debias ? (double)T * T : 0.0) +
                          (ref_iter ? (double)M * M : 0.0);
-    if (!forced && (pairs > kMeshAutoPairs || pairs <= kMeshMinPairs)) return CT_OK;
+    if (!forced && (pairs > kMeshAutoPairs ||
+                    (pairs <= kMeshMinPairs && (std::max(T, M) > kMeshLocalRows ||
+                                                std::max(T, M) <= kMeshMinPoints))))
+        return CT_OK;
     MeshArgs A;
     size_t lds = 0;
     int blocks = 0;
     const size_t cap = std::min(kTinyMaxLds, device_max_lds());
-    const bool planned = mesh_plan(T, M, d, debias, ref_iter, cap, false, A, lds, &blocks);
-    if (!planned || blocks > mesh_resident_blocks(d, lds, false)) {
+    if (!mesh_choose(T, M, d, debias, ref_iter, cap, !forced, A, lds, &blocks)) {
         if (forced)
             return fail(CT_E_UNSUPPORTED, "the exchange solve has no plan for T=%d, M=%d (it needs "
-                                          "2 to %d blocks of at most %d rows and every point in "
+                                          "a side of more than 64 points, at most %d blocks of at most %d rows and every point in "
                                           "%zu bytes of LDS)", T, M, kMeshMaxBlocks, kMeshRows, cap);
         return CT_OK;
     }
@@ -798,16 +801,6 @@ static ct_status run_mesh(const SkLayout& L, const SkConsts& c, const ct_sinkhor
     A.xch_p = L.xch + 2 * (size_t)T;
     A.xch_g = L.xch + 4 * (size_t)T;
     A.xch_q = L.xch + 4 * (size_t)T + 2 * (size_t)M;
-    for (int h = 0; h < 2; ++h) {
-        for (int j = 0; j < A.njobs[h]; ++j) {
-            MeshJob& J = A.job[h][j];
-            J.xch = J.yside ? (J.avg ? A.xch_q : A.xch_g) : (J.avg ? A.xch_p : A.xch_f);
-        }
-    }
-    A.gat[0][0].xch = A.xch_g;
-    if (A.ngat[0] > 1) A.gat[0][1].xch = A.xch_p;
-    A.gat[1][0].xch = A.xch_f;
-    if (A.ngat[1] > 1) A.gat[1][1].xch = A.xch_q;
     A.rescued = L.counters + 1;
     A.expired = L.counters + 4;
     A.polls = kMeshWaitPolls;
