@@ -1,0 +1,51 @@
+// Cell form of the Stein sum in 2-D (stein.hip): shared declarations.
+#pragma once
+
+#include "ct_internal.h"
+
+namespace ct {
+
+// Points from which the form is tried: below it the direct sum's rounding error is smaller (2048
+// samples' flow against float64, four point sets: 24576 points 1.1 to 1.7e-7 against 1.1 to
+// 2.3e-7, 32768 points 1.0 to 2.0e-7 against 1.4 to 4.0e-7), and the time is close (a call with a
+// given bandwidth: 16384 points 115 us against 94, 24576 126 / 183, 32768 133 / 294, 65536
+// 163 / 1076).
+constexpr int kSteinCellMinT = 32768;
+constexpr int kSteinCellMaxT = 1 << 22;
+constexpr int kSteinBits = 5;                    // cells per axis: at most 2^bits
+constexpr int kSteinIds = 1 << (2 * kSteinBits);
+constexpr int kSteinCells = 256;                 // most non-empty cells
+constexpr int kSteinTerms = 64;                  // products of 8 x 8 functions
+constexpr int kSteinMom = 3 * kSteinTerms;       // floats of a (query cell, key cell) pair
+constexpr float kSteinSide = 1.3125f;            // of a cell, scaled: few mantissa bits (see stein.hip)
+constexpr int kSteinBoxes = 64;                  // blocks of the bounding box
+constexpr int kSteinTile = 64;                   // queries of a tile (one wave)
+
+struct SteinCells {
+    int n, nb, per;        // points, blocks of `per` points in the counting sort
+    int kc;                // most keys of a chunk
+    int chmax, tmax;       // room for chunks and tiles
+    unsigned* box;         // [5][kSteinBoxes] blocks' ordered-integer minima, maxima, unusable points
+    unsigned short* id;    // [n]
+    unsigned* bh;          // [nb][ids] counts, then places
+    unsigned* first;       // [ids]
+    int* perm;             // [n] sorted place -> point
+    float4* rec;           // [n] (x', score) in cell order
+    float4* cen;           // [cells] centres (x, y)
+    int4* chunk;           // [chmax] (first key, end, cell, 0)
+    int4* tile;            // [tmax]
+    int2* own;             // [cells] the cell's chunks (first, end)
+    int* cnt;              // cells, chunks, tiles, mode (1: cell form, 0: direct sum)
+    float* part;           // [chmax][cells][192] a chunk's moments for every query cell
+    float* mom;            // [query cell][key cell][192]
+};
+
+// Lays out the arrays after a flow's own (a no-op for sizes that the form does not take).
+bool stein_cells_for(int T, int d);
+void stein_cells_layout(Arena& a, SteinCells& S, int T);
+// Partition, moments and values; with mode 1 the flow phi[T][2] is written, else nothing.
+// qc, krec, h: of the staged points (krec = (x', score)).
+hipError_t launch_stein_cells(const SteinCells& S, const float4* krec, const float* h, float* phi,
+                              float* h_used, hipStream_t s);
+
+}  // namespace ct

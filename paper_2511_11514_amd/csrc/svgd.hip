@@ -23,7 +23,9 @@
 //   k_svgd_stage  bandwidth h = med^2 / ln T (or the caller's h), coordinates
 //                 pre-scaled by sqrt(log2(e)/h) so k_ij = 2^-|x'_i - x'_j|^2;
 //   k_svgd_sum / k_svgd_merge   the T x T sum, split over keys like the Sinkhorn
-//                 sweep (keys read as wave-uniform records), fixed-order merge.
+//                 sweep (keys read as wave-uniform records), fixed-order merge; in
+//                 2-D from kSteinCellMinT points on they end at once where the cell
+//                 form (stein.hip) has written the flow.
 #include <hip/hip_ext.h>
 
 #include <cmath>
@@ -31,6 +33,7 @@
 #include <cstring>
 
 #include "ct_internal.h"
+#include "stein.h"
 
 namespace ct {
 
@@ -1047,6 +1050,7 @@ struct SvgdJob {
     const MedState* st;
     float* phi;
     float* h_used;
+    const int* cells;       // 1: the cell form has written phi (null: direct)
 };
 
 template <int D>
@@ -1144,6 +1148,7 @@ __global__ __launch_bounds__(256) void k_svgd_stage(const float* __restrict__ x,
 // Partial sums A_i = sum_j k_ij score_j and B_i = sum_j k_ij (x'_i - x'_j) over one key range.
 template <int D, int R>
 __global__ __launch_bounds__(256) void k_svgd_sum(SvgdJob J) {
+    if (J.cells && *J.cells) return;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int lane = (int)threadIdx.x & 63;
     const int qb = (int)blockIdx.x % J.nqb;
@@ -1234,6 +1239,7 @@ constexpr int kSvMergeRows = 64;
 template <int D>
 __global__ __launch_bounds__(256) void k_svgd_merge(SvgdJob J, int R) {
     __shared__ float red[3][2 * D][kSvMergeRows];
+    if (J.cells && *J.cells) return;
     const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
     const int i = (int)blockIdx.x * kSvMergeRows + lane;
     const float h = J.st->h;
@@ -1293,6 +1299,9 @@ struct SvLayout {
     float4* qc;
     float4* krec;
     float* part;
+    size_t base;       // bytes without the cell form's part
+    bool cells;
+    SteinCells sc;
     size_t bytes;
 };
 
@@ -1340,7 +1349,12 @@ static SvLayout sv_layout(void* ws, int T, int d) {
     L.qc = a.take<float4>(T);
     L.krec = a.take<float4>((size_t)Tpad * (d == 2 ? 1 : 2));
     L.part = a.take<float>((size_t)2 * d * splits * nqb * 256 * kSvR);
-    L.bytes = a.off + 256;
+    L.base = L.bytes = a.off + 256;
+    L.cells = stein_cells_for(T, d);
+    if (L.cells) {
+        stein_cells_layout(a, L.sc, T);
+        L.bytes = a.off + 256;
+    }
     return L;
 }
 
@@ -1375,7 +1389,8 @@ ct_status svgd_check(const float* x, int64_t T64, int32_t d, float h, float* phi
     if (!ws) return fail(CT_E_ARG, "workspace is null");
     if (reinterpret_cast<uintptr_t>(ws) % 256) return fail(CT_E_WORKSPACE, "workspace not 256-byte aligned");
     L = sv_layout(ws, (int)T64, d);
-    if (ws_bytes < L.bytes) return fail(CT_E_WORKSPACE, "workspace too small: %zu < %zu", ws_bytes, L.bytes);
+    if (ws_bytes < L.base) return fail(CT_E_WORKSPACE, "workspace too small: %zu < %zu", ws_bytes, L.base);
+    L.cells = L.cells && ws_bytes >= L.bytes;   // a smaller workspace: the direct sum
     return CT_OK;
 }
 
@@ -1469,7 +1484,9 @@ ct_status svgd_flow(const float* x, int T, int d, const float* score, float h, f
     hipLaunchKernelGGL(k_svgd_stage, dim3((Tpad + 255) / 256), dim3(256), 0, st, x, score, T, Tpad,
                        d, h > 0.f ? h : 0.f, L.st, L.origin, L.qc, L.krec);
     CT_CHECK_HIP(hipGetLastError());
+    if (L.cells) CT_CHECK_HIP(launch_stein_cells(L.sc, L.krec, &L.st->h, phi, h_used, st));
     SvgdJob J;
+    J.cells = L.cells ? L.sc.cnt + 3 : nullptr;
     J.qc = L.qc;
     J.krec = L.krec;
     J.T = T;
