@@ -9,9 +9,9 @@
 // Kernels:
 //   k_gmm_score   score of every sample, in float64 (responsibilities of far-away
 //                 points are differences of large log-densities);
-//   k_med_hist / k_med_select   exact median of the T(T-1)/2 squared distances
+//   k_med_hist    exact median of the T(T-1)/2 squared distances
 //                 (i < j) by a three-pass radix selection on their float32 bit
-//                 patterns (12 + 11 + 8 bits), both middle ranks tracked so an
+//                 patterns (11 + 10 + 10 bits), both middle ranks tracked so an
 //                 even count takes the mean of the two middle distances; for
 //                 large T the same selection runs over the pairs inside a
 //                 bracket found on a sample (k_med_sample, then one pass over
@@ -38,7 +38,8 @@
 namespace ct {
 
 constexpr int kMaxK = 64;
-constexpr int kMedBins = 4096;     // first pass: bits 30..19
+constexpr int kMedBins = 2048;     // first pass: bits 30..20
+constexpr int kMedThreads = 1024;  // of a histogram's block: one histogram per 16 waves
 constexpr double kLog2eD = 1.4426950408889634;
 
 // ------------------------------------------------------------------ score
@@ -120,6 +121,7 @@ struct MedState {
     unsigned long long novf;     // of them appended to the shared overflow list
     unsigned nitems;             // pairs of groups listed for the pair-by-pair pass
     int skip0;                   // the candidates share the first pass's bits: it is skipped
+    unsigned done;               // blocks of the running histogram that have flushed theirs
 };
 
 // Large T: an exact selection over a bracket.  kMedSample pseudo-random pairs
@@ -177,27 +179,9 @@ struct MedPass {
 };
 
 __device__ __forceinline__ MedPass med_pass(int p) {
-    if (p == 0) return MedPass{19, 12, 0u};
-    if (p == 1) return MedPass{8, 11, 0x7FF80000u};
-    return MedPass{0, 8, 0x7FFFFF00u};
-}
-
-__global__ __launch_bounds__(256) void k_med_init(MedState* st, unsigned long long* hist, int T) {
-    const unsigned long long n = (unsigned long long)T * (T - 1) / 2;
-    for (int i = threadIdx.x; i < 2 * kMedBins; i += blockDim.x) hist[i] = 0ull;
-    if (threadIdx.x == 0) {
-        st->rank[0] = n ? (n - 1) / 2 : 0;
-        st->rank[1] = n / 2;
-        st->prefix[0] = st->prefix[1] = 0u;
-        st->h = 1.f;
-        st->med = 0.f;
-        st->mode = 0;
-        st->below = 0ull;
-        st->ncand = 0ull;
-        st->novf = 0ull;
-        st->nitems = 0u;
-        st->skip0 = 0;
-    }
+    if (p == 0) return MedPass{20, 11, 0u};
+    if (p == 1) return MedPass{10, 10, 0x7FF00000u};
+    return MedPass{0, 10, 0x7FFFFC00u};
 }
 
 // SplitMix64 finaliser (Steele, Lea, Flood 2014) as the sample's index hash.
@@ -206,15 +190,6 @@ __device__ __forceinline__ unsigned long long mix64(unsigned long long z) {
     z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
     z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
     return z ^ (z >> 31);
-}
-
-__global__ __launch_bounds__(64) void k_sample_init(MedState* sst) {
-    if (threadIdx.x == 0) {
-        sst->rank[0] = kSampleLo;
-        sst->rank[1] = kSampleHi;
-        sst->prefix[0] = sst->prefix[1] = 0u;
-        sst->mode = 0;
-    }
 }
 
 // Squared distances of kMedSample pseudo-random pairs i != j (T >= 2).
@@ -230,102 +205,206 @@ __global__ __launch_bounds__(256) void k_med_sample(const float4* __restrict__ c
     out[k] = sqdist<D>(c[i], c[j]);
 }
 
-// Histogram of the squared-distance bit patterns of pairs i < j matching each
-// target's prefix.  A block takes 256 rows i against 256 / sub columns j (staged
-// in LDS); tiles below the diagonal are skipped.  Narrow column tiles (sub = 4)
-// give small problems enough blocks; wide ones amortise the per-block clearing
-// and flushing of the histogram when there are many tiles.
-__host__ __device__ constexpr int med_sub(int nt) { return nt * (nt + 1) / 2 < 1024 ? 4 : 1; }
-
-// Tile t of the (row tile, column tile) index space: rows bi*256.., columns
-// bj*256 + sub*jw..; false for tiles below the diagonal or past the end.
-struct MedTile {
-    int i0, j0, j1;
+// What a pair histogram keeps in LDS: one histogram per target; in the first pass, where both
+// targets share one and a wave's values crowd into a few bins, four copies of it, interleaved,
+// a lane adding to copy lane % 4.  A block's additions to the pass's global bins are the
+// other cost of a pass: 256 blocks of 16 waves and passes of 11 + 10 + 10 bits keep them few.
+// Measured, the three passes over the pairs of 10007 points in 2-D: 38, 42 and 32 us, with the
+// selection in each; before (blocks of four waves, one copy, 12 + 11 + 8 bits, columns in LDS,
+// a launch for each selection) 93, 53 and 44 us and three launches of 5 us; 1000 points: 13,
+// 11 and 11 against 13, 11, 11 and three of 5 to 9 us.
+struct MedHist {
+    unsigned h[4 * kMedBins];
+    unsigned long long wsum[4];
+    int last;
 };
-__device__ __forceinline__ bool med_tile(int t, int T, int nt, MedTile& mt) {
-    const int nsub = med_sub(nt), jw = 256 / nsub;
-    const int bi = t % nt, rest = t / nt;
-    const int bj = rest / nsub, sub = rest % nsub;
-    mt.i0 = bi * 256;
-    mt.j0 = bj * 256 + sub * jw;
-    mt.j1 = min(T, mt.j0 + jw);
-    return bj >= bi && mt.j0 < T;
+
+// Clears the histograms (barrier included).
+__device__ __forceinline__ void med_clear(MedHist& H, int pass, bool two) {
+    const int n = pass == 0 ? 4 << med_pass(0).bits : two ? kMedBins + (1 << med_pass(pass).bits)
+                                                          : 1 << med_pass(pass).bits;
+    for (int k = threadIdx.x; k < n; k += kMedThreads) H.h[k] = 0u;
+    __syncthreads();
 }
 
-// Blocks of the pair kernels below: a grid-stride loop over the tiles, so that
-// a launch whose mode does not match exits at once and each block clears and
-// flushes its histogram once.
+// Locate each target's bin, extend its prefix, clear the histograms.  Each of the first 256
+// threads holds a run of bins; a prefix sum of the run totals (wave scans, then the wave
+// totals) tells which thread holds the target rank, and that thread walks its own bins.
+// `finish` turns the final pass's values into the median and the bandwidth.
+__device__ __noinline__ void med_select(MedState* st, unsigned long long* hist, int pass, int T,
+                                        int finish, unsigned long long* wsum) {
+    const MedPass P = med_pass(pass);
+    const int nb = 1 << P.bits;
+    const int per = nb / 256;          // bins per thread (8 or 4)
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool on = tid < 256;
+    const bool two = st->prefix[0] != st->prefix[1];
+    for (int t = 0; t < 2; ++t) {
+        const unsigned long long* H = hist + ((two && t == 1) ? kMedBins : 0);
+        unsigned long long v[8];
+        unsigned long long loc = 0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            v[k] = on && k < per ? __hip_atomic_load(H + tid * per + k, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT)
+                                 : 0ull;
+            loc += v[k];
+        }
+        unsigned long long inc = loc;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned long long u = __shfl_up(inc, o, 64);
+            if (lane >= o) inc += u;
+        }
+        if (on && lane == 63) wsum[wave] = inc;
+        __syncthreads();
+        unsigned long long before = 0;
+        for (int w = 0; w < min(wave, 4); ++w) before += wsum[w];
+        const unsigned long long excl = before + inc - loc;
+        const unsigned long long r = st->rank[t];
+        __syncthreads();               // every thread has read the rank before it changes
+        // the owner of the rank (the last thread if the rank exceeds the count)
+        if (on && ((r >= excl && r < excl + loc) || (tid == 255 && r >= excl + loc))) {
+            unsigned long long cum = excl;
+            int b = 0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                if (k == b && k < per - 1 && r >= cum + v[k]) {
+                    cum += v[k];
+                    b = k + 1;
+                }
+            }
+            st->prefix[t] |= (unsigned)(tid * per + b) << P.shift;
+            st->rank[t] = r - cum;
+        }
+        __syncthreads();
+    }
+    if (tid == 0 && pass == 2 && finish) {
+        const double v1 = (double)__uint_as_float(st->prefix[0]);
+        const double v2 = (double)__uint_as_float(st->prefix[1]);
+        const double med = 0.5 * (sqrt(v1) + sqrt(v2));
+        st->med = (float)med;
+        // a vanishing median (all samples coincide) falls back to h = 1, as for one sample
+        st->h = (T > 1 && med > 0.0) ? (float)(med * med / log((double)T)) : 1.f;
+    }
+    for (int k = tid; k < 2 * kMedBins; k += kMedThreads) hist[k] = 0ull;
+}
+
+// Adds the block's histograms to the pass's; the last block of the launch to do so then
+// selects (a launch of its own for that cost 5 us a pass).  Every block of the launch has to
+// come here.  The counts are added and read by device-scope atomics, and a block counts itself
+// done only after its additions have returned their old values, that is, are performed: no
+// fence is needed, whose write-back of the L2 by every block took 25 us a pass.
+__device__ __forceinline__ void med_flush(MedHist& H, MedState* st, unsigned long long* hist,
+                                          int pass, bool two, int T, int finish) {
+    const int nb = 1 << med_pass(pass).bits;
+    __syncthreads();
+    for (int k = threadIdx.x; k < nb; k += kMedThreads) {
+        const unsigned v = pass == 0 ? H.h[4 * k] + H.h[4 * k + 1] + H.h[4 * k + 2] + H.h[4 * k + 3] : H.h[k];
+        unsigned long long old0 = 0ull, old1 = 0ull;
+        if (v) old0 = atomicAdd(&hist[k], (unsigned long long)v);
+        if (two && H.h[kMedBins + k]) old1 = atomicAdd(&hist[kMedBins + k], (unsigned long long)H.h[kMedBins + k]);
+        asm volatile("" ::"v"(old0), "v"(old1));
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) H.last = atomicAdd(&st->done, 1u) == gridDim.x - 1;
+    __syncthreads();
+    if (!H.last) return;
+    if (threadIdx.x == 0) st->done = 0u;
+    med_select(st, hist, pass, T, finish, H.wsum);
+}
+
+// Histogram of the squared-distance bit patterns of pairs i < j matching each target's
+// prefix.  A wave's unit is 64 rows i (one per lane) against 64 / sub columns j, read as
+// scalars (the column is the same for the wave): no barriers, no LDS reads beside the
+// histogram.  Units below the diagonal are not enumerated.  Narrow units (sub = 4) give small
+// problems enough waves; at most a block to a compute unit, since every block adds its bins
+// to the same words (four blocks of four waves to a unit: 32 us of a pass that finds nothing).
+__host__ __device__ constexpr int med_rows(int T) { return (T + 63) / 64; }
+__host__ __device__ constexpr int med_sub(int nt) { return nt * (nt + 1) / 2 < 2048 ? 4 : 1; }
 inline int med_grid(int T) {
-    const int nt = (T + 255) / 256;
-    return std::min(nt * nt * med_sub(nt), kNumCU * 8);
+    const int nt = med_rows(T);
+    const long long units = (long long)nt * (nt + 1) / 2 * med_sub(nt);
+    return (int)std::min<long long>((units + kMedThreads / 64 - 1) / (kMedThreads / 64), kNumCU);
 }
 
 template <int D>
-__global__ __launch_bounds__(256) void k_med_hist(const float4* __restrict__ c, int T, int pass,
-                                                  const MedState* __restrict__ st,
-                                                  unsigned long long* __restrict__ hist) {
-    __shared__ unsigned h[2][kMedBins];
-    __shared__ float4 cj[256];
-    if (st->mode != 0) return;
-    const int nt = (T + 255) / 256;
-    const int ntiles = nt * nt * med_sub(nt);
+__global__ __launch_bounds__(kMedThreads) void k_med_hist(const float4* __restrict__ c, int T, int pass,
+                                                  MedState* st, unsigned long long* hist, int gate) {
+    __shared__ MedHist H;
+    if (gate && st->mode != 0) return;
     const MedPass P = med_pass(pass);
     const unsigned pa = st->prefix[0], pb = st->prefix[1];
     const bool two = pa != pb;
-    const int nb = 1 << P.bits;
-    for (int k = threadIdx.x; k < nb; k += 256) {
-        h[0][k] = 0u;
-        h[1][k] = 0u;
-    }
-    for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        MedTile mt;
-        if (!med_tile(t, T, nt, mt)) continue;
-        __syncthreads();              // the previous tile's columns are no longer read
-        if ((int)threadIdx.x < mt.j1 - mt.j0) cj[threadIdx.x] = c[mt.j0 + threadIdx.x];
-        __syncthreads();
-        const int i = mt.i0 + (int)threadIdx.x;
-        if (i < T && i < mt.j1 - 1) {
-            const float4 xi = c[i];
-            for (int j = max(mt.j0, i + 1); j < mt.j1; ++j) {
-                const unsigned v = __float_as_uint(sqdist<D>(xi, cj[j - mt.j0]));
-                const unsigned bin = (v >> P.shift) & (unsigned)(nb - 1);
-                if ((v & P.fixed_mask) == pa) atomicAdd(&h[0][bin], 1u);
-                if (two && (v & P.fixed_mask) == pb) atomicAdd(&h[1][bin], 1u);
+    const unsigned binmask = (1u << P.bits) - 1u;
+    const int lane = (int)threadIdx.x & 63;
+    med_clear(H, pass, two);
+    const int nt = med_rows(T), sub = med_sub(nt), jw = 64 / sub;
+    const int units = nt * (nt + 1) / 2 * sub;
+    auto add = [&](unsigned v, bool ok) {
+        if (pass == 0) {
+            if (ok) atomicAdd(&H.h[((v >> P.shift) & binmask) * 4 + (lane & 3)], 1u);
+        } else {
+            const unsigned bin = (v >> P.shift) & binmask;
+            if (ok && (v & P.fixed_mask) == pa) atomicAdd(&H.h[bin], 1u);
+            if (two && ok && (v & P.fixed_mask) == pb) atomicAdd(&H.h[kMedBins + bin], 1u);
+        }
+    };
+    const int w0 = __builtin_amdgcn_readfirstlane((int)blockIdx.x * (kMedThreads / 64) + ((int)threadIdx.x >> 6));
+    for (int u = w0; u < units; u += (int)gridDim.x * (kMedThreads / 64)) {
+        // unit -> (row tile bi <= column tile bj, part of the columns)
+        const int p = u / sub;
+        int bj = (int)((sqrtf(8.f * (float)p + 1.f) - 1.f) * 0.5f);
+        while (bj * (bj + 1) / 2 > p) --bj;
+        while ((bj + 1) * (bj + 2) / 2 <= p) ++bj;
+        bj = __builtin_amdgcn_readfirstlane(bj);
+        const int bi = p - bj * (bj + 1) / 2;
+        const int j0 = bj * 64 + (u - p * sub) * jw, j1 = min(T, j0 + jw);
+        const int i = bi * 64 + lane;
+        const float4 xi = c[min(i, T - 1)];
+        if (bi < bj && j0 + jw <= T) {
+            // all rows and columns are points, every column above every row
+#pragma unroll 2
+            for (int j = j0; j < j1; j += 8) {
+                unsigned v[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = __float_as_uint(sqdist<D>(xi, c[j + k]));
+                bool any = pass == 0 || two;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) any = any || (v[k] & P.fixed_mask) == pa;
+                if (any) {
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) add(v[k], true);
+                }
             }
+        } else {
+            for (int j = j0; j < j1; ++j) add(__float_as_uint(sqdist<D>(xi, c[j])), i < j);
         }
     }
-    __syncthreads();
-    for (int k = threadIdx.x; k < nb; k += 256) {
-        if (h[0][k]) atomicAdd(&hist[k], (unsigned long long)h[0][k]);
-        if (two && h[1][k]) atomicAdd(&hist[kMedBins + k], (unsigned long long)h[1][k]);
-    }
+    med_flush(H, st, hist, pass, two, T, 1);
 }
 
 // The same histogram over a flat array of n squared distances (the bracket's sample).
-__global__ __launch_bounds__(256) void k_flat_hist(const float* __restrict__ v, int n, int pass,
-                                                   const MedState* st,
-                                                   unsigned long long* __restrict__ hist) {
-    __shared__ unsigned h[2][kMedBins];
+__global__ __launch_bounds__(kMedThreads) void k_flat_hist(const float* __restrict__ v, int n, int pass,
+                                                   MedState* st, unsigned long long* hist) {
+    __shared__ MedHist H;
     const MedPass P = med_pass(pass);
     const unsigned pa = st->prefix[0], pb = st->prefix[1];
     const bool two = pa != pb;
-    const int nb = 1 << P.bits;
-    for (int k = threadIdx.x; k < nb; k += 256) {
-        h[0][k] = 0u;
-        h[1][k] = 0u;
-    }
-    __syncthreads();
-    for (long long k = (long long)blockIdx.x * 256 + threadIdx.x; k < n; k += (long long)gridDim.x * 256) {
+    const unsigned binmask = (1u << P.bits) - 1u;
+    const int copy = (int)threadIdx.x & 3;
+    med_clear(H, pass, two);
+    for (long long k = (long long)blockIdx.x * kMedThreads + threadIdx.x; k < n; k += (long long)gridDim.x * kMedThreads) {
         const unsigned u = __float_as_uint(v[k]);
-        const unsigned bin = (u >> P.shift) & (unsigned)(nb - 1);
-        if ((u & P.fixed_mask) == pa) atomicAdd(&h[0][bin], 1u);
-        if (two && (u & P.fixed_mask) == pb) atomicAdd(&h[1][bin], 1u);
+        const unsigned bin = (u >> P.shift) & binmask;
+        if (pass == 0) {
+            atomicAdd(&H.h[bin * 4 + copy], 1u);
+        } else {
+            if ((u & P.fixed_mask) == pa) atomicAdd(&H.h[bin], 1u);
+            if (two && (u & P.fixed_mask) == pb) atomicAdd(&H.h[kMedBins + bin], 1u);
+        }
     }
-    __syncthreads();
-    for (int k = threadIdx.x; k < nb; k += 256) {
-        if (h[0][k]) atomicAdd(&hist[k], (unsigned long long)h[0][k]);
-        if (two && h[1][k]) atomicAdd(&hist[kMedBins + k], (unsigned long long)h[1][k]);
-    }
+    med_flush(H, st, hist, pass, two, 0, 0);
 }
 
 constexpr int kCandSlots = 16;
@@ -884,7 +963,7 @@ __global__ __launch_bounds__(256) void k_med_bracket(const float4* __restrict__ 
 
 // Count the candidates (the segments' counts and the overflow appends); use
 // them if both targets fall inside the bracket and none was lost.  When the
-// bracket's ends agree on the first pass's bits (30..19), so does every
+// bracket's ends agree on the first pass's bits (30..20), so does every
 // candidate: the first pass over them would only find that bin, so its prefix
 // is set here and the pass skipped.
 __global__ __launch_bounds__(1024) void k_med_decide(MedState* st, const MedState* __restrict__ sst,
@@ -905,7 +984,7 @@ __global__ __launch_bounds__(1024) void k_med_decide(MedState* st, const MedStat
     const unsigned long long n = med_pairs(T);
     const unsigned long long ra = n ? (n - 1) / 2 : 0, rb = n / 2;
     const unsigned long long below = st->below;
-    const unsigned first = med_pass(1).fixed_mask;           // bits 30..19
+    const unsigned first = med_pass(1).fixed_mask;           // bits 30..20
     const unsigned lo = sst->prefix[0], hi = sst->prefix[1];
     st->prefix[0] = st->prefix[1] = 0u;
     st->skip0 = 0;
@@ -924,120 +1003,48 @@ __global__ __launch_bounds__(1024) void k_med_decide(MedState* st, const MedStat
     }
 }
 
-// The histogram of k_flat_hist over the candidates: each segment's entries, then
-// the overflow list's.  Runs only when st->mode == 1.
-__global__ __launch_bounds__(256) void k_cand_hist(CandStore C, int pass, const MedState* st,
-                                                   unsigned long long* __restrict__ hist) {
-    __shared__ unsigned h[2][kMedBins];
+// The histogram of k_flat_hist over the candidates: each segment's entries (a wave per segment
+// in turn, four loads in flight), then the overflow list's.  Runs only when st->mode == 1.
+__global__ __launch_bounds__(kMedThreads) void k_cand_hist(CandStore C, int pass, MedState* st,
+                                                   unsigned long long* hist, int T) {
+    __shared__ MedHist H;
     if (st->mode != 1 || (pass == 0 && st->skip0)) return;
     const MedPass P = med_pass(pass);
     const unsigned pa = st->prefix[0], pb = st->prefix[1];
     const bool two = pa != pb;
-    const int nb = 1 << P.bits;
-    for (int k = threadIdx.x; k < nb; k += 256) {
-        h[0][k] = 0u;
-        h[1][k] = 0u;
-    }
-    __syncthreads();
-    // Candidates lie inside the bracket, so most of a wave's values share a bin
-    // (all of them in the first pass, whose 12 bits are coarser than the
-    // bracket): the lanes in the bin of the wave's first active lane add one
-    // count together, the others one each.
+    const unsigned binmask = (1u << P.bits) - 1u;
     const int lane = (int)threadIdx.x & 63;
-    auto add = [&](float v) {
+    med_clear(H, pass, two);
+    auto add = [&](float v, bool ok) {
         const unsigned u = __float_as_uint(v);
-        const unsigned bin = (u >> P.shift) & (unsigned)(nb - 1);
-        const unsigned b0 = __builtin_amdgcn_readfirstlane(bin);
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            if (t == 1 && !two) break;
-            const bool mine = (u & P.fixed_mask) == (t ? pb : pa);
-            const unsigned long long m = __builtin_amdgcn_ballot_w64(mine && bin == b0);
-            if (m && lane == __builtin_ctzll(m)) atomicAdd(&h[t][b0], (unsigned)__popcll(m));
-            if (mine && bin != b0) atomicAdd(&h[t][bin], 1u);
+        const unsigned bin = (u >> P.shift) & binmask;
+        if (pass == 0) {
+            if (ok) atomicAdd(&H.h[bin * 4 + (lane & 3)], 1u);
+        } else {
+            if (ok && (u & P.fixed_mask) == pa) atomicAdd(&H.h[bin], 1u);
+            if (two && ok && (u & P.fixed_mask) == pb) atomicAdd(&H.h[kMedBins + bin], 1u);
         }
     };
-    for (int w = blockIdx.x; w < kBracketWaves; w += gridDim.x) {
-        const float* v = C.cand + (size_t)w * C.seg;
-        const unsigned n = C.segcnt[w];
-        for (unsigned k = threadIdx.x; k < n; k += 256) add(v[k]);
+    if (C.seg) {
+        for (int w = (int)blockIdx.x * (kMedThreads / 64) + ((int)threadIdx.x >> 6); w < kBracketWaves;
+             w += (int)gridDim.x * (kMedThreads / 64)) {
+            const float* v = C.cand + (size_t)w * C.seg;
+            const int n = (int)C.segcnt[w];
+            for (int k = lane; k < n; k += 256) {
+                float x[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) x[r] = v[min(k + 64 * r, n - 1)];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) add(x[r], k + 64 * r < n);
+            }
+        }
     }
     const float* ovf = C.cand + (size_t)kBracketWaves * C.seg;
     const unsigned long long no = min(st->novf, C.ovf_cap);
-    for (unsigned long long k = (unsigned long long)blockIdx.x * 256 + threadIdx.x; k < no;
-         k += (unsigned long long)gridDim.x * 256)
-        add(ovf[k]);
-    __syncthreads();
-    for (int k = threadIdx.x; k < nb; k += 256) {
-        if (h[0][k]) atomicAdd(&hist[k], (unsigned long long)h[0][k]);
-        if (two && h[1][k]) atomicAdd(&hist[kMedBins + k], (unsigned long long)h[1][k]);
-    }
-}
-
-// Locate each target's bin, extend its prefix, clear the histograms.  Each
-// thread holds a run of bins; a block-wide prefix sum of the run totals (wave
-// scans, then the wave totals) tells which thread holds the target rank, and
-// that thread walks its own bins.
-// Runs only when gate < 0 or st->mode == gate; `finish` turns the final pass's
-// values into the median and the bandwidth.
-__global__ __launch_bounds__(256) void k_med_select(MedState* st, unsigned long long* hist,
-                                                    int pass, int T, int gate, int finish) {
-    __shared__ unsigned long long wsum[4];
-    if (gate >= 0 && st->mode != gate) return;
-    if (gate == 1 && pass == 0 && st->skip0) return;       // prefix set by k_med_decide
-    const MedPass P = med_pass(pass);
-    const int nb = 1 << P.bits;
-    const int per = nb / 256;          // bins per thread (16, 8 or 1)
-    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
-    const bool two = st->prefix[0] != st->prefix[1];
-    for (int t = 0; t < 2; ++t) {
-        const unsigned long long* H = hist + ((two && t == 1) ? kMedBins : 0);
-        unsigned long long v[16];
-        unsigned long long loc = 0;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            v[k] = k < per ? H[threadIdx.x * per + k] : 0ull;
-            loc += v[k];
-        }
-        unsigned long long inc = loc;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const unsigned long long u = __shfl_up(inc, o, 64);
-            if (lane >= o) inc += u;
-        }
-        if (lane == 63) wsum[wave] = inc;
-        __syncthreads();
-        unsigned long long before = 0;
-        for (int w = 0; w < wave; ++w) before += wsum[w];
-        const unsigned long long excl = before + inc - loc;
-        const unsigned long long r = st->rank[t];
-        __syncthreads();               // every thread has read the rank before it changes
-        // the owner of the rank (the last thread if the rank exceeds the count)
-        if ((r >= excl && r < excl + loc) || (threadIdx.x == 255 && r >= excl + loc)) {
-            unsigned long long cum = excl;
-            int b = 0;
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                if (k == b && k < per - 1 && r >= cum + v[k]) {
-                    cum += v[k];
-                    b = k + 1;
-                }
-            }
-            st->prefix[t] |= (unsigned)(threadIdx.x * per + b) << P.shift;
-            st->rank[t] = r - cum;
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0 && pass == 2 && finish) {
-        const double v1 = (double)__uint_as_float(st->prefix[0]);
-        const double v2 = (double)__uint_as_float(st->prefix[1]);
-        const double med = 0.5 * (sqrt(v1) + sqrt(v2));
-        st->med = (float)med;
-        // a vanishing median (all samples coincide) falls back to h = 1, as for one sample
-        st->h = (T > 1 && med > 0.0) ? (float)(med * med / log((double)T)) : 1.f;
-    }
-    __syncthreads();
-    for (int k = threadIdx.x; k < 2 * kMedBins; k += blockDim.x) hist[k] = 0ull;
+    for (unsigned long long k = (unsigned long long)blockIdx.x * kMedThreads + threadIdx.x; k < no;
+         k += (unsigned long long)gridDim.x * kMedThreads)
+        add(ovf[k], true);
+    med_flush(H, st, hist, pass, two, T, 1);
 }
 
 // ------------------------------------------------------------------ Stein sum
@@ -1065,12 +1072,36 @@ struct KeyRec {
 // (exact for nearby float32 values) keeps them.
 constexpr int kSvOriginBlocks = 64;
 
-// Partial sums of the mean: block b sums the samples of its contiguous share in
-// a fixed order into part[b] = (sum x, sum y, sum z, count); k_svgd_stage adds
-// the kSvOriginBlocks partials in block order.
-__global__ __launch_bounds__(256) void k_sv_origin(const float* __restrict__ x, int T, int d,
-                                                   double* __restrict__ part) {
+// What the flow's other kernels start from, in one launch (four launches of 5 us each at
+// small T): the selection states, cleared histograms, the samples as records for the median
+// (cmed, may be null) and the partial sums of the mean: block b sums the samples of its
+// contiguous share in a fixed order into part[b] = (sum x, sum y, sum z, count); k_svgd_stage
+// adds the kSvOriginBlocks partials in block order.
+__global__ __launch_bounds__(256) void k_sv_prep(const float* __restrict__ x, int T, int d,
+                                                 double* __restrict__ part, float4* __restrict__ cmed,
+                                                 MedState* st, MedState* sst,
+                                                 unsigned long long* __restrict__ hist) {
     __shared__ double red[4][256];
+    for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < 2 * kMedBins; i += kSvOriginBlocks * 256)
+        hist[i] = 0ull;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        const unsigned long long n = med_pairs(T);
+        MedState s;
+        s.rank[0] = n ? (n - 1) / 2 : 0;
+        s.rank[1] = n / 2;
+        s.prefix[0] = s.prefix[1] = 0u;
+        s.h = 1.f;
+        s.med = 0.f;
+        s.mode = 0;
+        s.below = s.ncand = s.novf = 0ull;
+        s.nitems = 0u;
+        s.skip0 = 0;
+        s.done = 0u;
+        *st = s;
+        s.rank[0] = kSampleLo;
+        s.rank[1] = kSampleHi;
+        *sst = s;
+    }
     const int chunk = (T + kSvOriginBlocks - 1) / kSvOriginBlocks;
     const int i0 = (int)blockIdx.x * chunk, i1 = min(T, i0 + chunk);
     double s[3] = {0.0, 0.0, 0.0}, n = 0.0;
@@ -1086,6 +1117,7 @@ __global__ __launch_bounds__(256) void k_sv_origin(const float* __restrict__ x, 
         }
         for (int t = 0; t < d; ++t) s[t] += ok ? (double)v[t] : 0.0;
         n += ok ? 1.0 : 0.0;
+        if (cmed) cmed[i] = make_float4(v[0], v[1], v[2], 0.f);
     }
     for (int t = 0; t < 3; ++t) red[t][threadIdx.x] = s[t];
     red[3][threadIdx.x] = n;
@@ -1104,7 +1136,7 @@ __global__ __launch_bounds__(256) void k_svgd_stage(const float* __restrict__ x,
                                                     const double* __restrict__ opart,
                                                     float4* __restrict__ qc,
                                                     float4* __restrict__ krec) {
-    // the origin: the mean of k_sv_origin's partials, added in block order
+    // the origin: the mean of k_sv_prep's partials, added in block order
     __shared__ float origin[3];
     if (threadIdx.x < 3) {
         double a = 0.0, n = 0.0;
@@ -1358,15 +1390,6 @@ static SvLayout sv_layout(void* ws, int T, int d) {
     return L;
 }
 
-__global__ __launch_bounds__(256) void k_med_coords(const float* __restrict__ x, int T, int d,
-                                                    float4* __restrict__ c) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= T) return;
-    float v[3] = {0, 0, 0};
-    for (int t = 0; t < d; ++t) v[t] = x[(size_t)i * d + t];
-    c[i] = make_float4(v[0], v[1], v[2], 0.f);
-}
-
 }  // namespace ct
 
 using namespace ct;
@@ -1397,23 +1420,21 @@ ct_status svgd_check(const float* x, int64_t T64, int32_t d, float h, float* phi
 // Bandwidth, staging and the T x T sum for a score already in device memory.
 ct_status svgd_flow(const float* x, int T, int d, const float* score, float h, float* phi,
                     float* h_used, const SvLayout& L, hipStream_t st) {
-    hipLaunchKernelGGL(k_med_init, dim3(1), dim3(256), 0, st, L.st, L.hist, T);
+    const bool median = h <= 0.f && T > 1;
+    hipLaunchKernelGGL(k_sv_prep, dim3(kSvOriginBlocks), dim3(256), 0, st, x, T, d, L.origin,
+                       median ? L.cmed : nullptr, L.st, L.sst, L.hist);
     CT_CHECK_HIP(hipGetLastError());
-    if (h <= 0.f && T > 1) {
-        hipLaunchKernelGGL(k_med_coords, dim3((T + 255) / 256), dim3(256), 0, st, x, T, d, L.cmed);
-        CT_CHECK_HIP(hipGetLastError());
+    if (median) {
         const dim3 tiles(med_grid(T));
         if (T >= kBracketMinT) {
             const unsigned long long cap = cand_cap(T);
-            hipLaunchKernelGGL(k_sample_init, dim3(1), dim3(64), 0, st, L.sst);
             if (d == 2)
                 hipLaunchKernelGGL(k_med_sample<2>, dim3(kMedSample / 256), dim3(256), 0, st, L.cmed, T, L.samp);
             else
                 hipLaunchKernelGGL(k_med_sample<3>, dim3(kMedSample / 256), dim3(256), 0, st, L.cmed, T, L.samp);
             CT_CHECK_HIP(hipGetLastError());
             for (int pass = 0; pass < 3; ++pass) {
-                hipLaunchKernelGGL(k_flat_hist, dim3(1024), dim3(256), 0, st, L.samp, kMedSample, pass, L.sst, L.hist);
-                hipLaunchKernelGGL(k_med_select, dim3(1), dim3(256), 0, st, L.sst, L.hist, pass, T, -1, 0);
+                hipLaunchKernelGGL(k_flat_hist, dim3(kNumCU / 2), dim3(kMedThreads), 0, st, L.samp, kMedSample, pass, L.sst, L.hist);
                 CT_CHECK_HIP(hipGetLastError());
             }
             CandStore C;
@@ -1462,25 +1483,20 @@ ct_status svgd_flow(const float* x, int T, int d, const float* score, float h, f
             hipLaunchKernelGGL(k_med_decide, dim3(1), dim3(1024), 0, st, L.st, L.sst, T, L.segcnt, cap);
             CT_CHECK_HIP(hipGetLastError());
             for (int pass = 0; pass < 3; ++pass) {
-                hipLaunchKernelGGL(k_cand_hist, dim3(1024), dim3(256), 0, st, C, pass, L.st, L.hist);
-                hipLaunchKernelGGL(k_med_select, dim3(1), dim3(256), 0, st, L.st, L.hist, pass, T, 1, 1);
+                hipLaunchKernelGGL(k_cand_hist, dim3(kNumCU), dim3(kMedThreads), 0, st, C, pass, L.st, L.hist, T);
                 CT_CHECK_HIP(hipGetLastError());
             }
         }
         // all pairs (small T, or a bracket that missed): each kernel returns at once otherwise
         for (int pass = 0; pass < 3; ++pass) {
             if (d == 2)
-                hipLaunchKernelGGL(k_med_hist<2>, tiles, dim3(256), 0, st, L.cmed, T, pass, L.st, L.hist);
+                hipLaunchKernelGGL(k_med_hist<2>, tiles, dim3(kMedThreads), 0, st, L.cmed, T, pass, L.st, L.hist, T >= kBracketMinT);
             else
-                hipLaunchKernelGGL(k_med_hist<3>, tiles, dim3(256), 0, st, L.cmed, T, pass, L.st, L.hist);
-            CT_CHECK_HIP(hipGetLastError());
-            hipLaunchKernelGGL(k_med_select, dim3(1), dim3(256), 0, st, L.st, L.hist, pass, T, 0, 1);
+                hipLaunchKernelGGL(k_med_hist<3>, tiles, dim3(kMedThreads), 0, st, L.cmed, T, pass, L.st, L.hist, T >= kBracketMinT);
             CT_CHECK_HIP(hipGetLastError());
         }
     }
     const int Tpad = pad_keys(T);
-    hipLaunchKernelGGL(k_sv_origin, dim3(kSvOriginBlocks), dim3(256), 0, st, x, T, d, L.origin);
-    CT_CHECK_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_svgd_stage, dim3((Tpad + 255) / 256), dim3(256), 0, st, x, score, T, Tpad,
                        d, h > 0.f ? h : 0.f, L.st, L.origin, L.qc, L.krec);
     CT_CHECK_HIP(hipGetLastError());
