@@ -13,6 +13,7 @@
 namespace ct {
 
 constexpr double kLog2e = 1.4426950408889634;
+constexpr int kCounters = 8;   // words of a call's device-side conditions (see OutArgs)
 
 // ------------------------------------------------------------------ kernels
 
@@ -24,69 +25,104 @@ __global__ __launch_bounds__(256) void k_zero3(unsigned* a, int na, unsigned* b,
     if (c && i < nc) c[i] = 0u;
 }
 
-// Fill 64-bit words with all ones (a version no exchange ever awaits).
-__global__ __launch_bounds__(256) void k_fill_ones64(unsigned long long* a, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) a[i] = ~0ull;
-}
-
-// Sum of the reference weights in double, fixed order (one block).
-__global__ __launch_bounds__(1024) void k_wsum(const float* __restrict__ w, int M,
-                                               double* __restrict__ out) {
-    __shared__ double red[1024];
-    double s = 0.0;
-    if (w) {
-        for (int j = threadIdx.x; j < M; j += 1024) s += (double)w[j];
-    } else {
-        s = threadIdx.x == 0 ? (double)M : 0.0;
+// A fixed-order sum over blocks' partial sums part[b][NV], b < nb <= 64, by the first wave; every
+// lane of it gets the totals.
+constexpr int kSumBlocks = 64;
+template <int NV>
+__device__ __forceinline__ void total(const double* __restrict__ part, int nb, double* v) {
+    const int lane = (int)threadIdx.x & 63;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        double s = lane < nb ? part[(size_t)lane * NV + k] : 0.0;
+#pragma unroll
+        for (int m = 1; m < 64; m <<= 1) s += __shfl_xor(s, m);
+        v[k] = s;
     }
-    red[threadIdx.x] = s;
+}
+// The block's sums of each thread's v[NV] (256 threads) into out[NV].
+template <int NV>
+__device__ __forceinline__ void block_total(const double* v, double* __restrict__ out) {
+    __shared__ double red[4][NV];
+    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        double s = v[k];
+#pragma unroll
+        for (int m = 1; m < 64; m <<= 1) s += __shfl_xor(s, m);
+        if (lane == 0) red[wave][k] = s;
+    }
     __syncthreads();
-    for (int h = 512; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = red[0];
+    if ((int)threadIdx.x < NV)
+        out[threadIdx.x] = (red[0][threadIdx.x] + red[1][threadIdx.x]) +
+                           (red[2][threadIdx.x] + red[3][threadIdx.x]);
 }
 
-// Common origin of both point sets (mean of every coordinate, double, fixed
-// order, non-finite values skipped).  The soft-min is translation invariant, but
-// the float32 prescale x * sqrt(kappa) is not: far from the coordinate origin it
-// would round away the low bits of every difference x_i - y_j.  Subtracting the
-// origin first (exact for nearby float32 values) keeps them.
-__global__ __launch_bounds__(1024) void k_origin(const float* __restrict__ x, int T,
-                                                 const float* __restrict__ y, int M, int d,
-                                                 float* __restrict__ out) {
-    __shared__ double red[3][1024];
-    __shared__ double cnt[1024];
-    double s[3] = {0.0, 0.0, 0.0}, n = 0.0;
+// What every call begins with, in one launch (six before: with k_out and k_value a flow call at
+// T = M = 100 takes 383 us instead of 393; at 65536 + 262144 points the two sums took 255 and
+// 72 us in one block each): partial sums of the points'
+// coordinates and of the reference weights, cleared arrival tickets and counters, and the
+// exchange solve's words filled with ones (a version that no exchange awaits).
+//
+// The common origin of both point sets is the mean of every coordinate (double, fixed order,
+// non-finite values skipped).  The soft-min is translation invariant, but the float32 prescale
+// x * sqrt(kappa) is not: far from the coordinate origin it would round away the low bits of
+// every difference x_i - y_j.  Subtracting the origin first (exact for nearby float32 values)
+// keeps them.
+constexpr int kBeginSums = 5;    // sums of x, y, z, the points counted, the weights
+struct BeginArgs {
+    const float *x, *y, *w;
+    int T, M, d, nt, nx;
+    double* part;            // [blocks][kBeginSums]
+    unsigned* tick[3];       // [nt] each
+    unsigned* counters;
+    unsigned long long* xch; // [nx]
+};
+__global__ __launch_bounds__(256) void k_begin(BeginArgs A) {
+    const int tid = (int)(blockIdx.x * 256 + threadIdx.x), nthr = (int)gridDim.x * 256;
+    for (int i = tid; i < A.nt; i += nthr)
+        for (int k = 0; k < 3; ++k) A.tick[k][i] = 0u;
+    if (tid < kCounters) A.counters[tid] = 0u;
+    for (int i = tid; i < A.nx; i += nthr) A.xch[i] = ~0ull;
+    double s[kBeginSums] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    const long long n = (long long)A.T + A.M, chunk = (n + gridDim.x - 1) / gridDim.x;
+    const long long i0 = min(n, (long long)blockIdx.x * chunk), i1 = min(n, i0 + chunk);
     // a skipped point adds zeros (no branch), so eight loads can be in flight
 #pragma unroll 8
-    for (int i = threadIdx.x; i < T + M; i += 1024) {
-        const float* p = i < T ? x + (size_t)i * d : y + (size_t)(i - T) * d;
+    for (long long i = i0 + (int)threadIdx.x; i < i1; i += 256) {
+        const float* p = i < A.T ? A.x + (size_t)i * A.d : A.y + (size_t)(i - A.T) * A.d;
         float v[3] = {0.f, 0.f, 0.f};
         bool ok = true;
-        for (int t = 0; t < d; ++t) {
+        for (int t = 0; t < A.d; ++t) {
             v[t] = p[t];
             ok = ok && isfinite(v[t]);
         }
-        for (int t = 0; t < d; ++t) s[t] += ok ? (double)v[t] : 0.0;
-        n += ok ? 1.0 : 0.0;
+        for (int t = 0; t < A.d; ++t) s[t] += ok ? (double)v[t] : 0.0;
+        s[3] += ok ? 1.0 : 0.0;
     }
-    for (int t = 0; t < 3; ++t) red[t][threadIdx.x] = s[t];
-    cnt[threadIdx.x] = n;
-    __syncthreads();
-    for (int h = 512; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) {
-            for (int t = 0; t < 3; ++t) red[t][threadIdx.x] += red[t][threadIdx.x + h];
-            cnt[threadIdx.x] += cnt[threadIdx.x + h];
-        }
-        __syncthreads();
+    if (A.w) {
+#pragma unroll 8
+        for (int j = tid; j < A.M; j += nthr) s[4] += (double)A.w[j];
+    } else if (tid == 0) {
+        s[4] = (double)A.M;
     }
-    if (threadIdx.x < 3) {
-        const double c = cnt[0] > 0.0 ? cnt[0] : 1.0;
-        out[threadIdx.x] = (int)threadIdx.x < d ? (float)(red[threadIdx.x][0] / c) : 0.f;
+    block_total<kBeginSums>(s, A.part + (size_t)blockIdx.x * kBeginSums);
+}
+
+// The origin and the weights' sum from k_begin's partials, by the first wave.
+__device__ __forceinline__ void begin_totals(const double* __restrict__ part, int nb, int d,
+                                             float* origin, double* wsum) {
+    double v[kBeginSums];
+    total<kBeginSums>(part, nb, v);
+    if (threadIdx.x == 0) {
+        const double c = v[3] > 0.0 ? v[3] : 1.0;
+        for (int t = 0; t < 3; ++t) origin[t] = t < d ? (float)(v[t] / c) : 0.f;
+        *wsum = v[4];
     }
+}
+// The same into the workspace, for the partition into cells, which precedes k_stage.
+__global__ __launch_bounds__(64) void k_totals(const double* __restrict__ part, int nb, int d,
+                                               float* __restrict__ origin, double* __restrict__ wsum) {
+    begin_totals(part, nb, d, origin, wsum);
 }
 
 struct StageArgs {
@@ -97,8 +133,9 @@ struct StageArgs {
     int warm, ref_cached;
     int T, M, d, Tpad, Mpad;
     float sqrt_kappa, kappa, log2a;
-    const double* wsum;
-    const float* origin;     // [3] subtracted before scaling
+    const double* part;      // k_begin's partial sums
+    int nb;                  // of so many blocks
+    double* wsum;            // out
     float4* cx;              // query coordinates of x
     float4* cy;              // query coordinates of y
     float4* xrec[4];         // key records of x: f (g-sweeps), f+ (g+ sweep), p ping-pong
@@ -117,6 +154,13 @@ __device__ __forceinline__ float4 make_rec(const float* c, int d, float h) {
 // Pre-scale coordinates, form the reference masses and the initial key records
 // (h = log2 mass + kappa * potential; padding records get h = -inf).
 __global__ __launch_bounds__(256) void k_stage(StageArgs A) {
+    __shared__ float origin[3];      // subtracted before scaling
+    __shared__ double wsum;
+    if (threadIdx.x < 64) {
+        begin_totals(A.part, A.nb, A.d, origin, &wsum);
+        if (blockIdx.x == 0 && threadIdx.x == 0) *A.wsum = wsum;
+    }
+    __syncthreads();
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const float ninf = -__builtin_huge_valf();
     if (i < A.Tpad) {
@@ -126,7 +170,7 @@ __global__ __launch_bounds__(256) void k_stage(StageArgs A) {
             for (int t = 0; t < A.d; ++t) {
                 const float v = A.x[(size_t)i * A.d + t];
                 bad |= !isfinite(v);
-                c[t] = (v - A.origin[t]) * A.sqrt_kappa;
+                c[t] = (v - origin[t]) * A.sqrt_kappa;
             }
             A.cx[i] = make_float4(c[0], c[1], c[2], 0.f);
             const float f0 = A.warm ? A.pot_in[i] : 0.f;
@@ -151,12 +195,12 @@ __global__ __launch_bounds__(256) void k_stage(StageArgs A) {
             for (int t = 0; t < A.d; ++t) {
                 const float v = A.y[(size_t)i * A.d + t];
                 bad |= !isfinite(v);
-                c[t] = (v - A.origin[t]) * A.sqrt_kappa;
+                c[t] = (v - origin[t]) * A.sqrt_kappa;
             }
             A.cy[i] = make_float4(c[0], c[1], c[2], 0.f);
             const float wj = A.w ? A.w[i] : 1.f;
             bad |= !(wj > 0.f) || !isfinite(wj);
-            const float bj = (float)((double)wj / *A.wsum);
+            const float bj = (float)((double)wj / wsum);
             const float lb = __log2f(bj);
             A.b[i] = bj;
             A.log2b[i] = lb;
@@ -176,73 +220,85 @@ __global__ __launch_bounds__(256) void k_stage(StageArgs A) {
     }
 }
 
-// grad_x = 2 a (Ds - Dy)  (debiased) or -2 a Dy; NaN after a barrier of the fused
-// solve gave up (*expired).  perm: the caller's index of each row, or null.
-__global__ __launch_bounds__(256) void k_grad_x(const float* __restrict__ dy,
-                                                const float* __restrict__ ds, int n, int d,
-                                                float two_a, const int* __restrict__ perm,
-                                                const unsigned* __restrict__ expired,
-                                                float* __restrict__ out) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float v = ds ? ds[i] - dy[i] : -dy[i];
-    const size_t at = perm ? (size_t)perm[i / d] * d + i % d : (size_t)i;
-    out[at] = *expired ? __builtin_nanf("") : two_a * v;
-}
-
-// out = (a [T], b [M], c [T], e [M]) with every set back in the caller's order.
-__global__ __launch_bounds__(256) void k_pot_out(const float* __restrict__ a,
-                                                 const float* __restrict__ b,
-                                                 const float* __restrict__ c,
-                                                 const float* __restrict__ e, int T, int M,
-                                                 const int* __restrict__ px,
-                                                 const int* __restrict__ py,
-                                                 float* __restrict__ out) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < T) {
-        out[px[i]] = a[i];
-        out[(size_t)T + M + px[i]] = c[i];
-    }
-    if (i < M) {
-        out[(size_t)T + py[i]] = b[i];
-        out[2 * (size_t)T + M + py[i]] = e[i];
-    }
-}
-
-struct ReduceArgs {
-    int T, M;
-    int debias, need_ref;
-    float kappa;
-    const float* fp;
-    const float* g;
-    const float* gp;
-    const float* p;
-    const float* pp;
-    const float* q;
-    const float* qp;
-    const float* b;
+// What every call ends with, in two launches (k_out and, with a value or grad_w, k_value; up to
+// eleven before, and at 65536 + 262144 points 233 us in one block for the sums).
+struct OutArgs {
+    int T, M, d, debias, need_ref, want_v;
+    int nb;                     // blocks that sum (k_out's first)
+    float kappa, two_a;
+    const float *dy, *ds;       // ds: null unless debiased
+    const float *f, *g, *p, *q, *fp, *gp, *pp, *qp, *b;
     const double* wsum;
     unsigned* counters;         // [0] non-finite inputs, [1] rescued rows, [2] residual (float
-                                // bits), [3] 1 once the residual is written, [4] a barrier of
-                                // the fused solve gave up
-    double* bG;                 // out: <b, G>
-    float* value;
-    float* aux;
+                                // bits), [3] 1 once the residual is written, [4] a wait of a
+                                // one-launch solve gave up
+    const int *perm_x, *perm_y; // the caller's index of each row, or null
+    double* part;               // [nb][kOutSums]
+    float *grad_x, *grad_w, *value, *pot, *pot_plus, *aux;
 };
+constexpr int kOutSums = 8;
 
-// Dual objectives, value, <b,G> and the column residual, in double, fixed order.
-__global__ __launch_bounds__(1024) void k_reduce(ReduceArgs A) {
-    __shared__ double red[8][1024];
-    double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    const double invT = 1.0 / A.T;
-    for (int i = threadIdx.x; i < A.T; i += 1024) {
-        acc[0] += A.fp[i] * invT;
-        if (A.debias) {
-            acc[1] += A.pp[i] * invT;
-            acc[2] += A.p[i] * invT;
+__device__ __forceinline__ void aux_counters(const OutArgs& A) {
+    A.aux[4] = (float)A.counters[1];
+    A.aux[5] = (float)A.counters[0];
+    A.aux[6] = A.counters[4] ? 1.f : 0.f;
+    A.aux[7] = 0.f;
+}
+
+// grad_x = 2 a (Ds - Dy)  (debiased) or -2 a Dy, NaN after a one-launch solve gave up; the
+// potentials pot = (f [T], g [M], p [T], q [M]) and pot_plus; partial sums of the dual
+// objectives, <b,G> and the column residual (double, fixed order).
+__global__ __launch_bounds__(256) void k_out(OutArgs A) {
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    const int T = A.T, M = A.M;
+    if (i < (long long)T * A.d) {
+        const float v = A.ds ? A.ds[i] - A.dy[i] : -A.dy[i];
+        const size_t at = A.perm_x ? (size_t)A.perm_x[i / A.d] * A.d + i % A.d : (size_t)i;
+        A.grad_x[at] = A.counters[4] ? __builtin_nanf("") : A.two_a * v;
+    }
+    if (A.pot || A.pot_plus) {
+        if (i < T) {
+            const size_t x = A.perm_x ? (size_t)A.perm_x[i] : (size_t)i, p = (size_t)T + M + x;
+            if (A.pot) {
+                A.pot[x] = A.f[i];
+                A.pot[p] = A.p[i];
+            }
+            if (A.pot_plus) {
+                A.pot_plus[x] = A.fp[i];
+                A.pot_plus[p] = A.pp[i];
+            }
+        }
+        if (i < M) {
+            const size_t y = (size_t)T + (A.perm_y ? (size_t)A.perm_y[i] : (size_t)i), q = (size_t)T + M + y;
+            if (A.pot) {
+                A.pot[y] = A.g[i];
+                A.pot[q] = A.q[i];
+            }
+            if (A.pot_plus) {
+                A.pot_plus[y] = A.gp[i];
+                A.pot_plus[q] = A.qp[i];
+            }
         }
     }
-    for (int j = threadIdx.x; j < A.M; j += 1024) {
+    if (!A.want_v) {
+        if (A.aux && blockIdx.x == 0 && threadIdx.x == 0) {
+            for (int k = 0; k < 4; ++k) A.aux[k] = 0.f;
+            aux_counters(A);
+        }
+        return;
+    }
+    if ((int)blockIdx.x >= A.nb) return;
+    double acc[kOutSums] = {0, 0, 0, 0, 0, 0, 0, 0};
+    const double invT = 1.0 / T;
+    const int stride = A.nb * 256;
+    for (long long k = i; k < T; k += stride) {
+        acc[0] += A.fp[k] * invT;
+        if (A.debias) {
+            acc[1] += A.pp[k] * invT;
+            acc[2] += A.p[k] * invT;
+        }
+    }
+    for (long long j = i; j < M; j += stride) {
         const double bj = A.b[j];
         acc[3] += bj * A.g[j];
         if (A.need_ref) {
@@ -253,59 +309,45 @@ __global__ __launch_bounds__(1024) void k_reduce(ReduceArgs A) {
         acc[6] += bj * G;
         acc[7] += bj * fabs(exp2(((double)A.g[j] - (double)A.gp[j]) * (double)A.kappa) - 1.0);
     }
-    for (int k = 0; k < 8; ++k) red[k][threadIdx.x] = acc[k];
-    __syncthreads();
-    for (int h = 512; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h)
-            for (int k = 0; k < 8; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + h];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        const double ot_ab = red[0][0] + red[3][0];
-        const double ot_aa = red[1][0] + red[2][0];
-        const double ot_bb = red[4][0] + red[5][0];
-        const double S = A.debias ? ot_ab - 0.5 * ot_aa - 0.5 * ot_bb : ot_ab;
-        *A.bG = red[6][0];
-        if (A.value) *A.value = A.counters[4] ? __builtin_nanf("") : (float)S;
-        if (A.aux) {
-            A.aux[0] = (float)ot_ab;
-            A.aux[1] = A.debias ? (float)ot_aa : 0.f;
-            A.aux[2] = A.need_ref ? (float)ot_bb : 0.f;
-            A.aux[3] = (float)red[7][0];
+    block_total<kOutSums>(acc, A.part + (size_t)blockIdx.x * kOutSums);
+}
+
+// Dual objectives, value and residual (block 0), and grad_w = (G - <b,G>) / sum w.
+__global__ __launch_bounds__(256) void k_value(OutArgs A) {
+    __shared__ double bG;
+    if (threadIdx.x < 64) {
+        double r[kOutSums];
+        total<kOutSums>(A.part, A.nb, r);
+        if (threadIdx.x == 0) {
+            bG = r[6];
+            if (blockIdx.x == 0) {
+                const double ot_ab = r[0] + r[3], ot_aa = r[1] + r[2], ot_bb = r[4] + r[5];
+                const double S = A.debias ? ot_ab - 0.5 * ot_aa - 0.5 * ot_bb : ot_ab;
+                if (A.value) *A.value = A.counters[4] ? __builtin_nanf("") : (float)S;
+                if (A.aux) {
+                    A.aux[0] = (float)ot_ab;
+                    A.aux[1] = A.debias ? (float)ot_aa : 0.f;
+                    A.aux[2] = A.need_ref ? (float)ot_bb : 0.f;
+                    A.aux[3] = (float)r[7];
+                    aux_counters(A);
+                }
+                A.counters[2] = __float_as_uint((float)r[7]);
+                A.counters[3] = 1u;
+            }
         }
-        A.counters[2] = __float_as_uint((float)red[7][0]);
-        A.counters[3] = 1u;
     }
-}
-
-__global__ __launch_bounds__(256) void k_grad_w(const float* __restrict__ gp,
-                                                const float* __restrict__ qp, int M,
-                                                const double* __restrict__ bG,
-                                                const double* __restrict__ wsum,
-                                                const int* __restrict__ perm,
-                                                const unsigned* __restrict__ expired,
-                                                float* __restrict__ out) {
+    __syncthreads();
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= M) return;
-    const double G = qp ? (double)gp[j] - (double)qp[j] : (double)gp[j];
-    out[perm ? perm[j] : j] = *expired ? __builtin_nanf("") : (float)((G - *bG) / *wsum);
-}
-
-__global__ void k_counters_out(const unsigned* __restrict__ c, float* __restrict__ aux) {
-    if (threadIdx.x == 0) {
-        aux[4] = (float)c[1];
-        aux[5] = (float)c[0];
-        aux[6] = c[4] ? 1.f : 0.f;
-        aux[7] = 0.f;
-    }
+    if (!A.grad_w || j >= A.M) return;
+    const double G = A.need_ref ? (double)A.gp[j] - (double)A.qp[j] : (double)A.gp[j];
+    A.grad_w[A.perm_y ? A.perm_y[j] : j] = A.counters[4] ? __builtin_nanf("") : (float)((G - bG) / *A.wsum);
 }
 
 // --------------------------------------------------------------- layout
 
 struct SkLayout {
     double* wsum;
-    double* bG;
-    unsigned* counters;      // [8]: see ReduceArgs
+    unsigned* counters;      // [8]: see OutArgs
     float4* cx;
     float4* cy;
     float4* xrec[4];         // 0: h from f (keys of g-sweeps), 1: from f+, 2/3: from p (ping-pong)
@@ -328,7 +370,6 @@ struct SkLayout {
     size_t bytes;
 };
 
-constexpr int kCounters = 8;
 
 // Cell form of the sweeps (see cells.h): by default where the library would launch one
 // direct sweep at a time and the call is large enough (cell_limits), up to kCellMaxPoints
@@ -369,7 +410,6 @@ static SkLayout sk_layout(void* ws, int T, int M, int d, bool cells) {
     SkLayout L;
     const int Tp = pad_keys(T), Mp = pad_keys(M);
     L.wsum = a.take<double>(1);
-    L.bG = a.take<double>(1);
     L.counters = a.take<unsigned>(kCounters);
     L.cx = a.take<float4>(T);
     L.cy = a.take<float4>(M);
@@ -814,9 +854,6 @@ static ct_status run_mesh(const SkLayout& L, const SkConsts& c, const ct_sinkhor
     A.kappa = c.kappa;
     A.inv_kappa = c.inv_kappa;
     A.log2a = c.log2a;
-    const int nw = 4 * (T + M);
-    hipLaunchKernelGGL(k_fill_ones64, dim3((nw + 255) / 256), dim3(256), 0, st, L.xch, nw);
-    CT_CHECK_HIP(hipGetLastError());
     CT_CHECK_HIP(launch_mesh(d, A, lds, blocks, st));
     *ran = true;
     return CT_OK;
@@ -978,19 +1015,22 @@ static ct_status sinkhorn_grad_impl(const float* x, int64_t T64, const float* y,
     const bool need_ref = debias && want_v;
     const double kappa_d = kLog2e / (double)o->eps;
 
-    // zero the counters and arrival tickets with a fill kernel (no memset nodes,
-    // so the sequence can be captured into a graph)
-    {
-        const int nt = (int)L.ntick;
-        hipLaunchKernelGGL(k_zero3, dim3((nt + 255) / 256), dim3(256), 0, st, L.tick[0], nt,
-                           L.tick[1], nt, L.tick[2], nt);
-        hipLaunchKernelGGL(k_zero3, dim3(1), dim3(256), 0, st, L.counters, kCounters, nullptr, 0,
-                           nullptr, 0);
-        CT_CHECK_HIP(hipGetLastError());
-    }
-    hipLaunchKernelGGL(k_wsum, dim3(1), dim3(1024), 0, st, w, M, L.wsum);
-    CT_CHECK_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_origin, dim3(1), dim3(1024), 0, st, x, T, y, M, d, L.origin);
+    // (fills by a kernel, no memset nodes, so the sequence can be captured into a graph; the
+    // sums' partials use the words that the fused solve clears for its barrier)
+    static_assert(kFusedBarWords * sizeof(unsigned) >= kSumBlocks * kOutSums * sizeof(double), "partials");
+    BeginArgs B;
+    B.x = x; B.y = y; B.w = w;
+    B.T = T; B.M = M; B.d = d;
+    B.nt = (int)L.ntick;
+    for (int k = 0; k < 3; ++k) B.tick[k] = L.tick[k];
+    B.counters = L.counters;
+    B.xch = L.xch;
+    const bool may_exchange = std::max(T, M) <= kMeshRows * kMeshMaxBlocks &&
+                              !(o->flags & (CT_FUSED | CT_UNFUSED | CT_TINY));
+    B.nx = may_exchange ? 4 * (T + M) : 0;
+    B.part = reinterpret_cast<double*>(L.bar);
+    const int nsum = (int)std::min<int64_t>(kSumBlocks, (T64 + M64 + 1023) / 1024);
+    hipLaunchKernelGGL(k_begin, dim3(nsum), dim3(256), 0, st, B);
     CT_CHECK_HIP(hipGetLastError());
     const double iter_pairs = 2.0 * T * M + (debias ? (double)T * T : 0.0) +
                               (need_ref && !(o->flags & CT_REF_CACHED) ? (double)M * M : 0.0);
@@ -1012,6 +1052,8 @@ static ct_status sinkhorn_grad_impl(const float* x, int64_t T64, const float* y,
         // the permutations
         CellPrep& P = L.prep;
         P.origin = L.origin;
+        hipLaunchKernelGGL(k_totals, dim3(1), dim3(64), 0, st, B.part, nsum, d, L.origin, L.wsum);
+        CT_CHECK_HIP(hipGetLastError());
         CT_CHECK_HIP(launch_cell_prep(P, CellInputs{x, y, w, pot_given ? pot : nullptr,
                                                     (float)std::sqrt(kappa_d)}, st));
         A.x = P.xs;
@@ -1027,7 +1069,7 @@ static ct_status sinkhorn_grad_impl(const float* x, int64_t T64, const float* y,
     A.sqrt_kappa = (float)std::sqrt(kappa_d);
     A.kappa = (float)kappa_d;
     A.log2a = (float)(-std::log2((double)T));
-    A.wsum = L.wsum; A.origin = L.origin; A.cx = L.cx; A.cy = L.cy; A.b = L.b; A.log2b = L.log2b;
+    A.part = B.part; A.nb = nsum; A.wsum = L.wsum; A.cx = L.cx; A.cy = L.cy; A.b = L.b; A.log2b = L.log2b;
     A.f = L.f; A.g = L.g; A.p = L.p; A.q = L.q;
     for (int r = 0; r < 4; ++r) A.xrec[r] = L.xrec[r];
     for (int r = 0; r < 3; ++r) A.yrec[r] = L.yrec[r];
@@ -1040,58 +1082,26 @@ static ct_status sinkhorn_grad_impl(const float* x, int64_t T64, const float* y,
     rc = run_problem(L, T, M, o, cells, st, fj);
     if (rc) return rc;
 
-    hipLaunchKernelGGL(k_grad_x, dim3((T * d + 255) / 256), dim3(256), 0, st, L.dy,
-                       debias ? L.ds : nullptr, T * d, d, (float)(2.0 / T), perm_x, L.counters + 4, grad_x);
+    OutArgs R;
+    R.T = T; R.M = M; R.d = d; R.debias = debias; R.need_ref = need_ref; R.want_v = want_v;
+    R.kappa = (float)kappa_d;
+    R.two_a = (float)(2.0 / T);
+    R.dy = L.dy; R.ds = debias ? L.ds : nullptr;
+    R.f = L.f; R.g = L.g; R.p = L.p; R.q = L.q;
+    R.fp = L.fp; R.gp = L.gp; R.pp = L.pp; R.qp = L.qp;
+    R.b = L.b; R.wsum = L.wsum; R.counters = L.counters;
+    R.perm_x = perm_x; R.perm_y = perm_y;
+    R.part = B.part;
+    R.grad_x = grad_x; R.grad_w = grad_w; R.value = value;
+    R.pot = pot; R.pot_plus = pot_plus; R.aux = aux;
+    const int64_t rows = std::max<int64_t>((int64_t)T * d, M);
+    const int nout = (int)((rows + 255) / 256);
+    R.nb = std::min(nsum, nout);
+    hipLaunchKernelGGL(k_out, dim3(nout), dim3(256), 0, st, R);
     CT_CHECK_HIP(hipGetLastError());
     if (want_v) {
-        ReduceArgs R;
-        R.T = T; R.M = M; R.debias = debias; R.need_ref = need_ref;
-        R.kappa = (float)kappa_d;
-        R.fp = L.fp; R.g = L.g; R.gp = L.gp; R.p = L.p; R.pp = L.pp; R.q = L.q; R.qp = L.qp;
-        R.b = L.b; R.wsum = L.wsum; R.counters = L.counters; R.bG = L.bG;
-        R.value = value; R.aux = aux;
-        hipLaunchKernelGGL(k_reduce, dim3(1), dim3(1024), 0, st, R);
+        hipLaunchKernelGGL(k_value, dim3(grad_w ? (M + 255) / 256 : 1), dim3(256), 0, st, R);
         CT_CHECK_HIP(hipGetLastError());
-        if (grad_w) {
-            hipLaunchKernelGGL(k_grad_w, dim3((M + 255) / 256), dim3(256), 0, st, L.gp,
-                               need_ref ? L.qp : nullptr, M, L.bG, L.wsum, perm_y, L.counters + 4,
-                               grad_w);
-            CT_CHECK_HIP(hipGetLastError());
-        }
-    } else if (aux) {
-        hipLaunchKernelGGL(k_zero3, dim3(1), dim3(256), 0, st, reinterpret_cast<unsigned*>(aux), 4,
-                           nullptr, 0, nullptr, 0);
-        CT_CHECK_HIP(hipGetLastError());
-    }
-    if (aux) {
-        hipLaunchKernelGGL(k_counters_out, dim3(1), dim3(64), 0, st, L.counters, aux);
-        CT_CHECK_HIP(hipGetLastError());
-    }
-    if (cells) {
-        const dim3 grid((std::max(T, M) + 255) / 256);
-        if (pot)
-            hipLaunchKernelGGL(k_pot_out, grid, dim3(256), 0, st, L.f, L.g, L.p, L.q, T, M, perm_x,
-                               perm_y, pot);
-        if (pot_plus)
-            hipLaunchKernelGGL(k_pot_out, grid, dim3(256), 0, st, L.fp, L.gp, L.pp, L.qp, T, M,
-                               perm_x, perm_y, pot_plus);
-        CT_CHECK_HIP(hipGetLastError());
-        return CT_OK;
-    }
-    if (pot) {
-        CT_CHECK_HIP(hipMemcpyAsync(pot, L.f, sizeof(float) * T, hipMemcpyDeviceToDevice, st));
-        CT_CHECK_HIP(hipMemcpyAsync(pot + T, L.g, sizeof(float) * M, hipMemcpyDeviceToDevice, st));
-        CT_CHECK_HIP(hipMemcpyAsync(pot + T + M, L.p, sizeof(float) * T, hipMemcpyDeviceToDevice, st));
-        CT_CHECK_HIP(hipMemcpyAsync(pot + 2 * (size_t)T + M, L.q, sizeof(float) * M,
-                                    hipMemcpyDeviceToDevice, st));
-    }
-    if (pot_plus) {
-        float* pp = pot_plus;
-        CT_CHECK_HIP(hipMemcpyAsync(pp, L.fp, sizeof(float) * T, hipMemcpyDeviceToDevice, st));
-        CT_CHECK_HIP(hipMemcpyAsync(pp + T, L.gp, sizeof(float) * M, hipMemcpyDeviceToDevice, st));
-        CT_CHECK_HIP(hipMemcpyAsync(pp + T + M, L.pp, sizeof(float) * T, hipMemcpyDeviceToDevice, st));
-        CT_CHECK_HIP(hipMemcpyAsync(pp + 2 * (size_t)T + M, L.qp, sizeof(float) * M,
-                                    hipMemcpyDeviceToDevice, st));
     }
     return CT_OK;
 }
