@@ -825,7 +825,7 @@ __device__ __forceinline__ void cell_values(const CellJob& C, const Job& J, int 
 // In 2-D a launch carries a job's direct sweep too, for the points that the device leaves to
 // it.  In 3-D the moments need twice the registers, which cost such a sweep 6 to 20 %: there
 // the direct sweeps keep their own launch and leave it where the cell form is on
-// (Launch::skip); their merges ride in the values' launch.
+// (launch_sweep's skip); their merges ride in the values' launch.
 template <int D>
 constexpr bool kBoth = D == 2;
 
@@ -1184,15 +1184,16 @@ hipError_t launch_cell_sweep(int d, const Schedule& sc, bool lagged, const Launc
     CellLaunch C = C0;
     if (d == 3) {
         bool any = false;
+        const int* skip[kMaxJobs] = {};
         for (int j = 0; j < L.njobs; ++j) {
             if (cell_candidate(d, L.job[j].nq, L.job[j].nk)) any = true;
             else C.job[j].mode = C.never;
-            L.skip[j] = C.job[j].mode;
+            skip[j] = C.job[j].mode;
         }
         if (L.njobs == 1) C.job[1] = C.job[0];
         if (!any) return launch_sweep(d, sc, lagged, false, L0, nblocks, s);
         const hipError_t e = launch_sweep(d, Schedule{sc.R, sc.WS, sc.blocks_per_cu, 1}, lagged,
-                                          false, L, nblocks, s, false);
+                                          false, L, nblocks, s, skip);
         if (e != hipSuccess) return e;
     }
     // grids for the units one can expect, up to the blocks that are resident at once (both

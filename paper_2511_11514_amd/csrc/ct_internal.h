@@ -78,7 +78,6 @@ constexpr int kMaxJobs = 4;
 struct Launch {
     Job job[kMaxJobs];
     int blk_end[kMaxJobs]; // job j owns blocks [blk_end[j-1], blk_end[j])
-    const int* skip[kMaxJobs]; // not null: the job's blocks leave at once where *skip is set
     int njobs;
     int expanded;          // 1: lagged sweeps without offsets use the expanded pair form
     float kappa, inv_kappa, inv_sqrt_kappa;
@@ -105,9 +104,10 @@ constexpr int kMaxCandidates = 128;
 int schedule_candidates(Schedule* out, int max);
 
 // Launch one sweep kernel (one or two jobs).
-// merge false: the caller's next launch merges the split jobs (separate-merge schedules).
+// skip (d = 3, separate-merge schedules): job j is left out where *skip[j] is set on the device,
+// and the caller's next launch merges the split jobs.
 hipError_t launch_sweep(int d, const Schedule& sc, bool lagged, bool bary, const Launch& L,
-                        int nblocks, hipStream_t s, bool merge = true);
+                        int nblocks, hipStream_t s, const int* const* skip = nullptr);
 
 // Lockstep launches over a job table in device memory (the batched path): job j
 // owns sweep blocks [blk_end[j-1], blk_end[j]) and merge blocks

@@ -9,19 +9,38 @@
 
 namespace ct {
 
-template <int D, int R, int WS, bool LAGGED, bool BARY, bool SEP, bool EXP = false>
-__global__ __launch_bounds__(kBlock) void k_sweep(Launch L) {
-    __shared__ SweepSmem<D, R> sm;
-    const int bid = (int)blockIdx.x;
-    int j = 0;
-    while (j + 1 < L.njobs && bid >= L.blk_end[j]) ++j;
-    if (L.skip[j] && *L.skip[j]) return;
+template <int D, int R, int WS, bool LAGGED, bool BARY, bool SEP, bool EXP>
+__device__ __forceinline__ void sweep_block(const Launch& L, int j, SweepSmem<D, R>& sm) {
     const Job& J = L.job[j];
-    const int local = bid - (j ? L.blk_end[j - 1] : 0);
+    const int local = (int)blockIdx.x - (j ? L.blk_end[j - 1] : 0);
     const int qb = local % J.nqb;
     const int split = local / J.nqb;
     sweep_unit<D, R, WS, LAGGED, BARY, SEP, EXP>(J, qb, split, L.kappa, L.inv_kappa,
                                                  L.inv_sqrt_kappa, sm);
+}
+
+template <int D, int R, int WS, bool LAGGED, bool BARY, bool SEP, bool EXP = false>
+__global__ __launch_bounds__(kBlock) void k_sweep(Launch L) {
+    __shared__ SweepSmem<D, R> sm;
+    int j = 0;
+    while (j + 1 < L.njobs && (int)blockIdx.x >= L.blk_end[j]) ++j;
+    sweep_block<D, R, WS, LAGGED, BARY, SEP, EXP>(L, j, sm);
+}
+
+// The same, a job being left out where its *skip is set (the 3-D cell form decides on the
+// device).  A kernel of its own: the pointers in every launch's arguments cost each sweep and
+// merge 0.1 to 0.3 us.
+struct SkipLaunch {
+    Launch L;
+    const int* skip[kMaxJobs];
+};
+template <int D, int R, int WS, bool LAGGED, bool SEP>
+__global__ __launch_bounds__(kBlock) void k_sweep_skip(SkipLaunch S) {
+    __shared__ SweepSmem<D, R> sm;
+    int j = 0;
+    while (j + 1 < S.L.njobs && (int)blockIdx.x >= S.L.blk_end[j]) ++j;
+    if (*S.skip[j]) return;
+    sweep_block<D, R, WS, LAGGED, false, SEP, LAGGED>(S.L, j, sm);
 }
 
 // Merge kernel of the separate-merge mode: blocks of kMergeRows query rows per job
@@ -37,7 +56,6 @@ __global__ __launch_bounds__(kBlock) void k_merge(Launch L, int R, int WS) {
         start += nb;
         ++j;
     }
-    if (L.skip[j] && *L.skip[j]) return;
     const Job& J = L.job[j];
     const int nqpad = J.nqb * 64 * R * (4 / WS);
     merge_block<D, LAGGED, BARY>(J, (bid - start) * kMergeRows, nqpad, L.kappa, L.inv_kappa,
@@ -107,7 +125,17 @@ static void launch_k(K kernel, int nb, hipStream_t s, hipEvent_t e0, hipEvent_t 
 
 template <int D, int R, int WS, bool SEP>
 static hipError_t launch_drws(bool lagged, bool bary, const Launch& L, int nb, hipStream_t s,
-                              hipEvent_t e0, hipEvent_t e1) {
+                              hipEvent_t e0, hipEvent_t e1, const int* const* skip) {
+    if constexpr (D == 3 && SEP) {
+        if (skip) {
+            SkipLaunch S;
+            S.L = L;
+            for (int j = 0; j < kMaxJobs; ++j) S.skip[j] = j < L.njobs ? skip[j] : nullptr;
+            if (lagged) launch_k(k_sweep_skip<D, R, WS, true, SEP>, nb, s, e0, e1, S);
+            else launch_k(k_sweep_skip<D, R, WS, false, SEP>, nb, s, e0, e1, S);
+            return hipGetLastError();
+        }
+    }
     if (lagged) {
         if (bary) launch_k(k_sweep<D, R, WS, true, true, SEP>, nb, s, e0, e1, L);
         else if (L.expanded) launch_k(k_sweep<D, R, WS, true, false, SEP, true>, nb, s, e0, e1, L);
@@ -121,9 +149,9 @@ static hipError_t launch_drws(bool lagged, bool bary, const Launch& L, int nb, h
 
 template <int D, int R, int WS>
 static hipError_t launch_drw(bool sep, bool lagged, bool bary, const Launch& L, int nb,
-                             hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-    return sep ? launch_drws<D, R, WS, true>(lagged, bary, L, nb, s, e0, e1)
-               : launch_drws<D, R, WS, false>(lagged, bary, L, nb, s, e0, e1);
+                             hipStream_t s, hipEvent_t e0, hipEvent_t e1, const int* const* skip) {
+    return sep ? launch_drws<D, R, WS, true>(lagged, bary, L, nb, s, e0, e1, skip)
+               : launch_drws<D, R, WS, false>(lagged, bary, L, nb, s, e0, e1, skip);
 }
 
 static int merge_blocks(const Launch& L) {
@@ -148,23 +176,23 @@ static hipError_t launch_merge(int R, int WS, bool lagged, bool bary, const Laun
 
 template <int D, int R>
 static hipError_t launch_dr(int WS, bool sep, bool lagged, bool bary, const Launch& L, int nb,
-                            hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+                            hipStream_t s, hipEvent_t e0, hipEvent_t e1, const int* const* skip) {
     switch (WS) {
-        case 1: return launch_drw<D, R, 1>(sep, lagged, bary, L, nb, s, e0, e1);
-        case 2: return launch_drw<D, R, 2>(sep, lagged, bary, L, nb, s, e0, e1);
-        default: return launch_drw<D, R, 4>(sep, lagged, bary, L, nb, s, e0, e1);
+        case 1: return launch_drw<D, R, 1>(sep, lagged, bary, L, nb, s, e0, e1, skip);
+        case 2: return launch_drw<D, R, 2>(sep, lagged, bary, L, nb, s, e0, e1, skip);
+        default: return launch_drw<D, R, 4>(sep, lagged, bary, L, nb, s, e0, e1, skip);
     }
 }
 
 template <int D>
 static hipError_t launch_d(const Schedule& sc, bool lagged, bool bary, const Launch& L, int nb,
-                           hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+                           hipStream_t s, hipEvent_t e0, hipEvent_t e1, const int* const* skip) {
     const bool sep = sc.sep != 0;
     switch (sc.R) {
-        case 1: return launch_dr<D, 1>(sc.WS, sep, lagged, bary, L, nb, s, e0, e1);
-        case 2: return launch_dr<D, 2>(sc.WS, sep, lagged, bary, L, nb, s, e0, e1);
-        case 4: return launch_dr<D, 4>(sc.WS, sep, lagged, bary, L, nb, s, e0, e1);
-        default: return launch_dr<D, 8>(sc.WS, sep, lagged, bary, L, nb, s, e0, e1);
+        case 1: return launch_dr<D, 1>(sc.WS, sep, lagged, bary, L, nb, s, e0, e1, skip);
+        case 2: return launch_dr<D, 2>(sc.WS, sep, lagged, bary, L, nb, s, e0, e1, skip);
+        case 4: return launch_dr<D, 4>(sc.WS, sep, lagged, bary, L, nb, s, e0, e1, skip);
+        default: return launch_dr<D, 8>(sc.WS, sep, lagged, bary, L, nb, s, e0, e1, skip);
     }
 }
 
@@ -173,7 +201,7 @@ static hipError_t launch_d(const Schedule& sc, bool lagged, bool bary, const Lau
 // kernel's start and end: kind4[0] is 0/1 for a safe/lagged sweep and 10/11 for
 // its merge.
 hipError_t launch_sweep(int d, const Schedule& sc, bool lagged, bool bary, const Launch& L,
-                        int nblocks, hipStream_t s, bool merge) {
+                        int nblocks, hipStream_t s, const int* const* skip) {
     if (nblocks <= 0) return hipSuccess;
     double pairs = 0.0;
     for (int j = 0; j < L.njobs; ++j) pairs += (double)L.job[j].nq * L.job[j].nk;
@@ -181,10 +209,10 @@ hipError_t launch_sweep(int d, const Schedule& sc, bool lagged, bool bary, const
     const int code = sc.R * 100 + sc.WS * 10 + sc.sep + (lagged && !bary && L.expanded ? 1000 : 0);
     hipEvent_t e0, e1;
     void* tok = profile_kernel_begin(&e0, &e1);
-    hipError_t e = d == 2 ? launch_d<2>(sc, lagged, bary, L, nblocks, s, e0, e1)
-                          : launch_d<3>(sc, lagged, bary, L, nblocks, s, e0, e1);
+    hipError_t e = d == 2 ? launch_d<2>(sc, lagged, bary, L, nblocks, s, e0, e1, skip)
+                          : launch_d<3>(sc, lagged, bary, L, nblocks, s, e0, e1, skip);
     profile_kernel_end(tok, lagged, bary, code, nblocks, pairs);
-    if (e != hipSuccess || !sc.sep || !merge) return e;
+    if (e != hipSuccess || !sc.sep || skip) return e;
     const int nm = merge_blocks(L);
     if (nm == 0) return hipSuccess;
     tok = profile_kernel_begin(&e0, &e1);
