@@ -22,6 +22,7 @@ import argparse
 import ctypes
 import hashlib
 import json
+import math
 import os
 import sys
 import time
@@ -37,10 +38,11 @@ METRIC = "T·M pair-evals/s per gradient pass; batched vs plain speedup at ≤1e
 # v_add_f32 128 lanes, v_fma_f32 64 lanes, v_exp_f32 32 lanes (the live probe,
 # ct_probe_alu_rates, measures them on the box and is reported beside the peak;
 # the published 157.3 TFLOP/s FP32 counts packed FMAs, which these kernels do not
-# use).  The FP32 matrix cores do not help: they issue exclusively of the VALU
-# (measured overlap ratio 1.0) and sum products relative to the largest term.
+# use).  These bound a direct sweep over every pair; the cell form of a sweep runs
+# on the FP32 matrix cores instead (MATRIX_F32_FMA multiply-adds per second).
 NOMINAL_RATES = {"add": 128.0, "fma": 64.0, "exp": 32.0}
 N_CU, CLOCK_HZ = 256, 2.4e9
+MATRIX_F32_FMA = N_CU * 128 * CLOCK_HZ
 
 
 def pair_mix(d: int, expanded: bool = False) -> dict:
@@ -263,6 +265,27 @@ def dominant_sweeps(recs) -> tuple:
     return sum(r[2] for r in sel), sum(r[3] for r in sel), len(sel)
 
 
+def cell_fma(x, y, eps: float) -> dict:
+    """Multiply-adds of one cell-form sweep on the matrix cores (2-D), from the counts of the
+    grid's cells and of their chunks of keys: N products per key and query cell (moments) and
+    per query and key chunk (values).  The grid of cells.h: side sqrt(2 / ln 2) in units of
+    sqrt(eps / log2 e), N = 64."""
+    import numpy as np
+    N, side = 64, math.sqrt(2.0 / math.log(2.0))
+    s = math.sqrt(math.log2(math.e) / eps) / side
+
+    def counts(p):
+        k = np.floor((p - p.min(0)) * s).astype(np.int64)
+        n = np.unique(k[:, 0] * 4096 + k[:, 1], return_counts=True)[1]
+        kc = 256 if len(p) <= 24576 else 512 if len(p) <= 131072 else 1024
+        return len(n), int(np.ceil(n / kc).sum())
+
+    (cx, hx), (cy, hy) = counts(np.asarray(x)), counts(np.asarray(y))
+    nx, ny = len(x), len(y)
+    return {"f": N * (ny * cx + nx * hy), "g": N * (nx * cy + ny * hx), "p": N * (nx * cx + nx * hx),
+            "cells": [cx, cy], "chunks": [hx, hy]}
+
+
 def sinkhorn_step(ct, x, y, w, eps, K, gmm=None, ref_q=None, one_stream=False, expanded=True):
     """One gradient pass: S, dS/dx and dS/dw through the autograd form, then the
     Stein flow on the same samples when a mixture is given."""
@@ -441,6 +464,7 @@ def main() -> int:
     svgd_pairs = T * T
     total_pairs = sk_pairs + svgd_pairs
     ach = dom_pairs / (dom_ms * 1e-3) / 1e12
+    in_cells = any(r[0] == 51 for r in recs)
     mix = pair_mix(d, not args.difference)
     peak = pair_roof(d, NOMINAL_RATES, mix=mix) / 1e12
     probe = ct.probe_alu_rates(str(dev))
@@ -500,6 +524,21 @@ def main() -> int:
             "frac_of_probe_peak": ach / probe_peak,
         },
     }
+    if in_cells:
+        # the sweeps' products run on the matrix cores: their multiply-adds (lagged sweeps: K - 1
+        # of f and g, K - 1 of p) against the float32 matrix rate; the pair rate, beside the
+        # direct sweeps' issue roof, is no longer bounded by it
+        fma = cell_fma(x_np, y_np, eps)
+        passes = args.steps if live_events else 1
+        total = passes * (K - 1) * (fma["f"] + fma["g"] + fma["p"])
+        rate, mpeak = total / (dom_ms * 1e-3) / 1e12, MATRIX_F32_FMA / 1e12
+        res["roofline"].update({
+            "bound": "f32 matrix cores", "unit": "Tfma/s", "achieved": rate, "peak": mpeak,
+            "frac": rate / mpeak, "kernel": "k_cell_moments + k_cell_values (lagged shift, d=2)",
+            "fma_per_sweep": fma, "pair_rate": ach, "direct_issue_roof": peak,
+            "direct_probe_roof": probe_peak, "pair_unit": "Tpair/s"})
+        for k in ("probe_peak", "frac_of_probe_peak", "traffic"):
+            res["roofline"].pop(k)
     res["parity"] = parity_roofline_2d(out, x_np)
     res["system"] = system_info(torch, dev)
     del out, step, ref_q
@@ -583,7 +622,9 @@ def grad_2d_leg(ct, torch, dev, L, _lib, tuned, steps: int = 20, warmup: int = 3
     one()
     torch.cuda.synchronize()
     L.ct_profile_enable(0)
-    dp, dms, nd = dominant_sweeps(read_profile(L, _lib))
+    recs = read_profile(L, _lib)
+    dp, dms, nd = dominant_sweeps(recs)
+    in_cells = any(r[0] == 51 for r in recs)
     pairs = pairs_per_pass(T, M, K) + T * T
     ach = dp / (dms * 1e-3) / 1e12
     peak = pair_roof(d, NOMINAL_RATES, mix=pair_mix(d, True)) / 1e12
@@ -598,8 +639,9 @@ def grad_2d_leg(ct, torch, dev, L, _lib, tuned, steps: int = 20, warmup: int = 3
                         f"dS/dx + dS/dw via autograd (two streams), plus Stein flow",
             "ms_per_step": ms, "pairs_per_step": pairs, "pair_evals_per_s": pairs / (ms * 1e-3),
             "graph_ms_per_step": graph_ms, "schedules": tuned,
-            "sweep_launches": {"achieved": ach, "peak": peak, "unit": "Tpair/s",
-                               "frac": ach / peak, "launches": nd,
+            "sweep_launches": {"form": "cells" if in_cells else "direct", "achieved": ach,
+                               "direct_issue_roof": peak, "unit": "Tpair/s",
+                               "frac": None if in_cells else ach / peak, "launches": nd,
                                "avg_launch_us": dms / max(nd, 1) * 1e3, "traffic": traffic,
                                "events": "one extra step, launches serialised on one stream"},
             "parity": parity_vs_stored_oracle(out, ct, torch, dev)}
@@ -882,8 +924,9 @@ def autograd_3d_leg(ct, torch, dev, reps: int = 2) -> dict:
 def stein_leg(ct, torch, dev, L, _lib) -> dict:
     """The Stein flow at the large workload's size (T = 65536, 16-component mixture
     with a 10 % floor, median bandwidth): whole-flow time, the time with the
-    bandwidth given (no median), and the T x T sum kernel against its issue roof
-    (events stamped with the kernel's start and end)."""
+    bandwidth given (no median; the sum in its cell form), and the direct T x T sum
+    kernel against its issue roof at the first 16384 samples (events stamped with the
+    kernel's start and end)."""
     import workloads as W
     cfg = W.CONFIGS["roofline_2d"]
     x, _y, _w, g = W.config_inputs(cfg, M=16)
@@ -905,9 +948,11 @@ def stein_leg(ct, torch, dev, L, _lib) -> dict:
     flow_ms, (_phi, hu) = timed(None)
     h = float(hu.item())
     fixed_ms, _ = timed(h)
+    xd = xt[:16384].contiguous()
+    ct.svgd_grad(xd, gm, h)
     L.ct_profile_clear()
     L.ct_profile_enable(1)
-    ct.svgd_grad(xt, gm, h)
+    ct.svgd_grad(xd, gm, h)
     torch.cuda.synchronize()
     L.ct_profile_enable(0)
     kind = (ctypes.c_int32 * 4)()
@@ -919,10 +964,10 @@ def stein_leg(ct, torch, dev, L, _lib) -> dict:
             sum_ms = t.value
     L.ct_profile_clear()
     peak = pair_roof(2, NOMINAL_RATES, mix=STEIN_MIX) / 1e12
-    ach = T * T / (sum_ms * 1e-3) / 1e12 if sum_ms else None
+    ach = len(xd) ** 2 / (sum_ms * 1e-3) / 1e12 if sum_ms else None
     return {"workload": f"roofline_2d Stein flow: T={T}, 16-component mixture + 10% floor",
             "flow_ms": flow_ms, "flow_fixed_h_ms": fixed_ms, "median_ms": flow_ms - fixed_ms,
-            "sum_kernel": {"us": None if sum_ms is None else sum_ms * 1e3, "achieved": ach,
+            "sum_kernel": {"samples": len(xd), "us": None if sum_ms is None else sum_ms * 1e3, "achieved": ach,
                            "peak": peak, "unit": "Tpair/s",
                            "frac": None if ach is None else ach / peak, "pair_mix": STEIN_MIX}}
 
