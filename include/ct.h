@@ -332,10 +332,10 @@ typedef struct ct_gmm {
  * bracket's candidates; from T = 24576 on also 4 bytes per pair of 64-point groups and another
  * 8 bytes per 125 pairs (each wave of the pass owns a segment of twice its share of the
  * candidates): 245 MB in all at T = 65536 (d = 3), 458 MB at T = 92681.  For d = 2 and 32768 <=
- * T <= 2^22 also 126 MB and 30 bytes per point for the cell form of the sum (sums over pairs of
- * grid cells by truncated expansions that leave out less than 1e-8 of any pair's term; taken
- * where it pays, decided on the device); a smaller workspace that holds the rest is accepted
- * and sums directly. */
+ * T <= 92681 also some 45 bytes per point for the cell form of the sum, whose moments take the
+ * candidates' place (sums over pairs of grid cells by truncated expansions that leave out less
+ * than 1e-8 of any pair's term; taken where it pays, decided on the device); a smaller
+ * workspace that holds the rest is accepted and sums directly. */
 size_t ct_svgd_workspace_size(int64_t T, int32_t d);
 
 /*

@@ -11,7 +11,7 @@ namespace ct {
 // given bandwidth: 16384 points 115 us against 94, 24576 126 / 183, 32768 133 / 294, 65536
 // 163 / 1076).
 constexpr int kSteinCellMinT = 32768;
-constexpr int kSteinCellMaxT = 1 << 22;
+constexpr int kSteinCellMaxT = 92681;           // up to here the median's buffers hold the moments
 constexpr int kSteinBits = 5;                    // cells per axis: at most 2^bits
 constexpr int kSteinIds = 1 << (2 * kSteinBits);
 constexpr int kSteinCells = 256;                 // most non-empty cells
@@ -36,13 +36,15 @@ struct SteinCells {
     int4* tile;            // [tmax]
     int2* own;             // [cells] the cell's chunks (first, end)
     int* cnt;              // cells, chunks, tiles, mode (1: cell form, 0: direct sum)
-    float* part;           // [chmax][cells][192] a chunk's moments for every query cell
-    float* mom;            // [query cell][key cell][192]
+    float* mom;            // [cells][cells][192] moments of (query cell, key cell), then
+                           // [chunks][cells][192] those of a chunk for every query cell
+    long long room;        // floats of mom: more cells or chunks than fit sum directly
 };
 
 // Lays out the arrays after a flow's own (a no-op for sizes that the form does not take).
 bool stein_cells_for(int T, int d);
-void stein_cells_layout(Arena& a, SteinCells& S, int T);
+// spare: a buffer of the median, no longer used when the sum runs: it holds the moments.
+void stein_cells_layout(Arena& a, SteinCells& S, int T, float* spare, size_t spare_floats);
 // Partition, moments and values; with mode 1 the flow phi[T][2] is written, else nothing.
 // qc, krec, h: of the staged points (krec = (x', score)).
 hipError_t launch_stein_cells(const SteinCells& S, const float4* krec, const float* h, float* phi,

@@ -191,6 +191,7 @@ __global__ __launch_bounds__(kSteinIds) void k_st_lists(SteinCells S) {
     const float cells = 4.6e-4f * (float)tt * (float)tc + 2.5e-4f * (float)(S.n + 128 * th) * (float)((tc + 31) / 32) + 50.f;
     // every point in the cell of its code: nothing outside the coded box
     const bool ok = box[4] == 0u && tc <= kSteinCells && th <= S.chmax && tt <= S.tmax && cells < direct &&
+                    (long long)(th + tc) * tc * kSteinMom <= S.room &&
                     from_ordered(box[2]) - lx < ext && from_ordered(box[3]) - ly < ext;
     if (id == 0) {
         S.cnt[0] = tc;
@@ -335,7 +336,7 @@ __global__ __launch_bounds__(kStWaves * 64, 2) void k_st_moments(SteinCells S, c
     for (int r = 0; r < 16; ++r) {
         const int a = a0 + 8 * (r >> 2) + 4 * hi + (r & 3);
         if (a >= ncell) continue;
-        float* out = S.part + ((size_t)blockIdx.x * kSteinCells + a) * kSteinMom;
+        float* out = S.mom + ((size_t)(ncell + (int)blockIdx.x) * ncell + a) * kSteinMom;
 #pragma unroll
         for (int t = 0; t < 6; ++t) out[(t >> 1) * kSteinTerms + (t & 1) * 32 + col] = acc[t][r];
     }
@@ -352,13 +353,13 @@ __global__ __launch_bounds__(256) void k_st_reduce(SteinCells S) {
         float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 4
         for (int e = own.x; e < own.y; ++e) {
-            const float4 v = reinterpret_cast<const float4*>(S.part + ((size_t)e * kSteinCells + a) * kSteinMom)[lane];
+            const float4 v = reinterpret_cast<const float4*>(S.mom + ((size_t)(ncell + e) * ncell + a) * kSteinMom)[lane];
             s.x += v.x;
             s.y += v.y;
             s.z += v.z;
             s.w += v.w;
         }
-        reinterpret_cast<float4*>(S.mom + ((size_t)a * kSteinCells + c) * kSteinMom)[lane] = s;
+        reinterpret_cast<float4*>(S.mom + ((size_t)a * ncell + c) * kSteinMom)[lane] = s;
     }
 }
 
@@ -417,7 +418,7 @@ __global__ __launch_bounds__(256) void k_st_values(SteinCells S, const float* __
         const double e = (double)exponent_bound(A.x - C.x, A.y - C.y) - __builtin_fma(dx, dx, dy * dy);
         const double n = rint(e);
         const float w = (float)ldexp(exp2_half(e - n), (int)fmax(n, -1000.0));
-        const float* M = mom + ((size_t)a * kSteinCells + c) * kSteinMom;
+        const float* M = mom + ((size_t)a * ncell + c) * kSteinMom;
         float F[3];
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
@@ -454,7 +455,7 @@ __global__ __launch_bounds__(256) void k_st_values(SteinCells S, const float* __
 
 bool stein_cells_for(int T, int d) { return d == 2 && T >= kSteinCellMinT && T <= kSteinCellMaxT; }
 
-void stein_cells_layout(Arena& a, SteinCells& S, int T) {
+void stein_cells_layout(Arena& a, SteinCells& S, int T, float* spare, size_t spare_floats) {
     S.n = T;
     S.per = std::max(256, (T + 1023) / 1024);
     S.per = (S.per + 63) / 64 * 64;
@@ -473,8 +474,8 @@ void stein_cells_layout(Arena& a, SteinCells& S, int T) {
     S.tile = a.take<int4>(S.tmax);
     S.own = a.take<int2>(kSteinCells);
     S.cnt = a.take<int>(4);
-    S.part = a.take<float>((size_t)S.chmax * kSteinCells * kSteinMom);
-    S.mom = a.take<float>((size_t)kSteinCells * kSteinCells * kSteinMom);
+    S.room = (long long)spare_floats;
+    S.mom = spare;
 }
 
 hipError_t launch_stein_cells(const SteinCells& S, const float4* krec, const float* h, float* phi,

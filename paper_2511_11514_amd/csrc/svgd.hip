@@ -1382,9 +1382,10 @@ static SvLayout sv_layout(void* ws, int T, int d) {
     L.krec = a.take<float4>((size_t)Tpad * (d == 2 ? 1 : 2));
     L.part = a.take<float>((size_t)2 * d * splits * nqb * 256 * kSvR);
     L.base = L.bytes = a.off + 256;
+    static_assert(kSteinCellMinT >= kBracketMinT && kSteinCellMaxT <= kMaxMedianT, "the moments lie in L.cand");
     L.cells = stein_cells_for(T, d);
     if (L.cells) {
-        stein_cells_layout(a, L.sc, T);
+        stein_cells_layout(a, L.sc, T, L.cand, (size_t)(kBracketWaves * cand_seg(T) + cand_cap(T)));
         L.bytes = a.off + 256;
     }
     return L;
