@@ -20,8 +20,8 @@
 // the potentials vary.  Per point and cell it costs 64 (192) multiply-adds; per point
 // pair the direct sweep costs 5 (6) instructions, one of them an exponential.  Measured on
 // an MI355X, d = 2, T = 65536, M = 262144, eps = 0.002, 200 iterations: 1142 ms with direct
-// sweeps (94 % of their issue roof), 96.5 ms in this form; T = 4096, M = 16384, eps = 0.005,
-// 200 iterations: 15.9 against 10.0 ms.
+// sweeps (94 % of their issue roof), 84.3 ms in this form; T = 4096, M = 16384, eps = 0.005,
+// 200 iterations: 16.0 against 8.9 ms.
 #pragma once
 
 #include "ct_internal.h"
