@@ -21,7 +21,9 @@
 // is the larger part, hence as few rows per block as the device has room for.
 // LOCAL (one block, at most 128 points a side): the finished rows write their records
 // directly and nothing is exchanged; its registers are not bound to two blocks per
-// compute unit.  Measured, us per iteration (d = 3, cached reference; before: 64 rows
+// compute unit.  The self records have two copies by the iteration's parity, one that is
+// swept (and walked again by a rescued row) and one that takes the new potentials: the two
+// waves that finish more than 64 rows do not wait for each other.  Measured, us per iteration (d = 3, cached reference; before: 64 rows
 // per block, one row per lane, f and p published together): T = M = 100 3.8 (4.9 in
 // the one-workgroup solve), 300 5.3 (7.9), 500 5.6 (10.0), 1000 8.0 (14.5), 2000 12.1
 // (24.9).  Launching a block per compute unit at 1024 threads (no two resident) was
@@ -369,8 +371,9 @@ __device__ __forceinline__ void mesh_solve(const MeshArgs& A, const int b) {
         lds4[A.o_rf + i] = r;
         if (A.debias) {
             const float p = LOCAL ? A.p[i] : 0.f;
-            lds4[A.o_rp + i] = make_float4(r.x, r.y, r.z, __builtin_fmaf(p, kap, A.log2a) -
-                                                              rec_norm(r.x, r.y, r.z));
+            const float h = __builtin_fmaf(p, kap, A.log2a) - rec_norm(r.x, r.y, r.z);
+            for (int c = 0; c < (LOCAL ? 2 : 1); ++c)
+                lds4[A.o_rp + c * A.T + i] = make_float4(r.x, r.y, r.z, h);
         }
     }
     for (int j = tid; j < A.M; j += NT) {
@@ -379,7 +382,9 @@ __device__ __forceinline__ void mesh_solve(const MeshArgs& A, const int b) {
         const float lb = A.log2b[j], n = rec_norm(r.x, r.y, r.z);
         const float g = LOCAL ? A.g[j] : 0.f, q = LOCAL ? A.q[j] : 0.f;
         lds4[A.o_rg + j] = make_float4(r.x, r.y, r.z, __builtin_fmaf(g, kap, lb) - n);
-        if (A.ref_iter) lds4[A.o_rq + j] = make_float4(r.x, r.y, r.z, __builtin_fmaf(q, kap, lb) - n);
+        if (A.ref_iter)
+            for (int c = 0; c < (LOCAL ? 2 : 1); ++c)
+                lds4[A.o_rq + c * A.M + j] = make_float4(r.x, r.y, r.z, __builtin_fmaf(q, kap, lb) - n);
         lds[A.o_lb + j] = lb;
     }
     for (int i = x0 + tid; i < x1; i += NT) {
@@ -402,7 +407,7 @@ __device__ __forceinline__ void mesh_solve(const MeshArgs& A, const int b) {
     }
     __syncthreads();
     const Rows X = rows_of<D, NT>(A, false, b, lds4), Y = rows_of<D, NT>(A, true, b, lds4);
-    const float4 *rf = lds4 + A.o_rf, *rg = lds4 + A.o_rg, *rp = lds4 + A.o_rp, *rq = lds4 + A.o_rq;
+    const float4 *rf = lds4 + A.o_rf, *rg = lds4 + A.o_rg;
     float *pf = lds + A.o_f, *pg = lds + A.o_g, *pp = lds + A.o_p, *pq = lds + A.o_q;
     float *cross = lds + A.o_cross, *self = lds + A.o_self;
     const Gather none{A.xch_f, 0, 0, -1, 0u};
@@ -416,38 +421,44 @@ __device__ __forceinline__ void mesh_solve(const MeshArgs& A, const int b) {
     for (int k = 0; k < A.iters; ++k) {
         const bool lagged = !A.safe_only && (A.lagged0 || k > 0);
         const unsigned v = (unsigned)k;
+        // the self records of this iteration's sweeps, and those of the next one's
+        const int cur = LOCAL ? k & 1 : 0, nxt = LOCAL ? cur ^ 1 : 0;
+        const int rp = A.o_rp + cur * A.T, rpn = A.o_rp + nxt * A.T;
+        const int rq = A.o_rq + cur * A.M, rqp = A.o_rq + nxt * A.M;   // rqp: of the last sweep
         if (!LOCAL)
             gather<NT>(A, Gather{A.xch_g, A.M, A.o_rg, A.o_lb, v},
                    A.debias ? Gather{A.xch_p, A.T, A.o_rp, -1, v} : none, lds);
         __syncthreads();
         if (A.ref_iter && k > 0)
-            finish_rows<D, NT, LOCAL>(A, Y, 2, true, true, rq, A.M, pq, lag_q, self, A.xch_q,
-                           lds + 4 * A.o_rq, lds + A.o_lb, v);
+            finish_rows<D, NT, LOCAL>(A, Y, 2, true, true, lds4 + rqp, A.M, pq, lag_q, self, A.xch_q,
+                           lds + 4 * rq, lds + A.o_lb, v);
         sweep_rows<D, NT>(A, X, rg, A.M, pf, lagged, cross);
         __syncthreads();
         finish_rows<D, NT, LOCAL>(A, X, 0, false, false, rg, A.M, pf, lagged, cross, A.xch_f,
                        lds + 4 * A.o_rf, nullptr, v + 1u);
-        if (A.debias) sweep_rows<D, NT>(A, X, rp, A.T, pp, lagged, self);
+        if (A.debias) sweep_rows<D, NT>(A, X, lds4 + rp, A.T, pp, lagged, self);
         if (!LOCAL)
             gather<NT>(A, Gather{A.xch_f, A.T, A.o_rf, -1, v + 1u},
                    A.ref_iter ? Gather{A.xch_q, A.M, A.o_rq, A.o_lb, v} : none, lds);
         __syncthreads();
         if (A.debias)
-            finish_rows<D, NT, LOCAL>(A, X, 2, false, true, rp, A.T, pp, lagged, self, A.xch_p,
-                           lds + 4 * A.o_rp, nullptr, v + 1u);
+            finish_rows<D, NT, LOCAL>(A, X, 2, false, true, lds4 + rp, A.T, pp, lagged, self, A.xch_p,
+                           lds + 4 * rpn, nullptr, v + 1u);
         sweep_rows<D, NT>(A, Y, rf, A.T, pg, lagged, cross);
         __syncthreads();
         finish_rows<D, NT, LOCAL>(A, Y, 0, true, false, rf, A.T, pg, lagged, cross, A.xch_g,
                        lds + 4 * A.o_rg, lds + A.o_lb, v + 1u);
         if (A.ref_iter) {
-            sweep_rows<D, NT>(A, Y, rq, A.M, pq, lagged, self);
+            sweep_rows<D, NT>(A, Y, lds4 + rq, A.M, pq, lagged, self);
             lag_q = lagged;
         }
     }
     __syncthreads();
-    if (A.ref_iter && A.iters > 0)
-        finish_rows<D, NT, LOCAL>(A, Y, 2, true, true, rq, A.M, pq, lag_q, self, A.xch_q, lds + 4 * A.o_rq,
-                       lds + A.o_lb, (unsigned)A.iters);
+    if (A.ref_iter && A.iters > 0) {
+        const int cur = LOCAL ? A.iters & 1 : 0, last = LOCAL ? cur ^ 1 : 0;
+        finish_rows<D, NT, LOCAL>(A, Y, 2, true, true, lds4 + A.o_rq + last * A.M, A.M, pq, lag_q, self,
+                       A.xch_q, lds + 4 * (A.o_rq + cur * A.M), lds + A.o_lb, (unsigned)A.iters);
+    }
     __syncthreads();
 
     // store the own rows: potentials and the key terms the final pass reads
@@ -536,8 +547,9 @@ bool mesh_plan(int T, int M, int d, bool debias, bool ref_iter, size_t lds_cap, 
     int r4 = 0;
     A.o_rf = r4; r4 += T;
     A.o_rg = r4; r4 += M;
-    A.o_rp = r4; r4 += debias ? T : 0;
-    A.o_rq = r4; r4 += ref_iter ? M : 0;
+    const int copies = A.local ? 2 : 1;   // of the self records
+    A.o_rp = r4; r4 += debias ? copies * T : 0;
+    A.o_rq = r4; r4 += ref_iter ? copies * M : 0;
     int off = 4 * r4;
     auto take = [&](int n) {
         const int o = off;
