@@ -21,9 +21,11 @@
 // is the larger part, hence as few rows per block as the device has room for.
 // LOCAL (one block, at most 128 points a side): the finished rows write their records
 // directly and nothing is exchanged; its registers are not bound to two blocks per
-// compute unit.  The self records have two copies by the iteration's parity, one that is
-// swept (and walked again by a rescued row) and one that takes the new potentials: the two
-// waves that finish more than 64 rows do not wait for each other.  Measured, us per iteration (d = 3, cached reference; before: 64 rows
+// compute unit.  A self sweep's rows write theirs only after the next barrier (put_rows):
+// its records are those that a rescued row walks again, and more than 64 rows are finished
+// by two waves that do not wait for each other.  That costs 0.06 us an iteration of 3.39 at
+// T = M = 100; two copies of the self records by the iteration's parity cost 0.65 (their
+// addresses are no longer the same in every iteration), one wave for all self rows 0.27.  Measured, us per iteration (d = 3, cached reference; before: 64 rows
 // per block, one row per lane, f and p published together): T = M = 100 3.8 (4.9 in
 // the one-workgroup solve), 300 5.3 (7.9), 500 5.6 (10.0), 1000 8.0 (14.5), 2000 12.1
 // (24.9).  Launching a block per compute unit at 1024 threads (no two resident) was
@@ -298,7 +300,7 @@ __device__ __attribute__((noinline)) float tracked_row(const float4 c, const flo
 }
 
 // Finish the own rows from the waves' partials: their new potentials, kept and published
-// (or, one block, written into the key records).  By the threads from wave `w0` on, one wave
+// (or, one block, written into the key records; of a self sweep by put_rows).  By the threads from wave `w0` on, one wave
 // or (more than 64 rows) two.
 template <int D, int NT, bool LOCAL>
 __device__ __forceinline__ void finish_rows(const MeshArgs& A, const Rows& R, int w0, bool yside,
@@ -345,9 +347,22 @@ __device__ __forceinline__ void finish_rows(const MeshArgs& A, const Rows& R, in
     pot[row] = nv;
     if (LOCAL) {
         float* r = rec + 4 * row;
-        r[3] = __builtin_fmaf(nv, A.kappa, lw ? lw[row] : A.log2a) - rec_norm(r[0], r[1], r[2]);
+        if (!avg) r[3] = __builtin_fmaf(nv, A.kappa, lw ? lw[row] : A.log2a) - rec_norm(r[0], r[1], r[2]);
     } else {
         publish(xch, yside ? A.M : A.T, R.first + row, version, nv);
+    }
+}
+
+// One block: the records of self rows that finish_rows has finished before the last barrier, by
+// the same threads.
+__device__ __forceinline__ void put_rows(const MeshArgs& A, const Rows& R, int w0, float* rec,
+                                         const float* pot, const float* lw) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (wave < w0 || wave >= w0 + max(1, (1 << R.lg) >> 6)) return;
+    const int row = (int)threadIdx.x - w0 * 64;
+    if (row < R.n) {
+        float* r = rec + 4 * row;
+        r[3] = __builtin_fmaf(pot[row], A.kappa, lw ? lw[row] : A.log2a) - rec_norm(r[0], r[1], r[2]);
     }
 }
 
@@ -371,9 +386,8 @@ __device__ __forceinline__ void mesh_solve(const MeshArgs& A, const int b) {
         lds4[A.o_rf + i] = r;
         if (A.debias) {
             const float p = LOCAL ? A.p[i] : 0.f;
-            const float h = __builtin_fmaf(p, kap, A.log2a) - rec_norm(r.x, r.y, r.z);
-            for (int c = 0; c < (LOCAL ? 2 : 1); ++c)
-                lds4[A.o_rp + c * A.T + i] = make_float4(r.x, r.y, r.z, h);
+            lds4[A.o_rp + i] = make_float4(r.x, r.y, r.z, __builtin_fmaf(p, kap, A.log2a) -
+                                                              rec_norm(r.x, r.y, r.z));
         }
     }
     for (int j = tid; j < A.M; j += NT) {
@@ -382,9 +396,7 @@ __device__ __forceinline__ void mesh_solve(const MeshArgs& A, const int b) {
         const float lb = A.log2b[j], n = rec_norm(r.x, r.y, r.z);
         const float g = LOCAL ? A.g[j] : 0.f, q = LOCAL ? A.q[j] : 0.f;
         lds4[A.o_rg + j] = make_float4(r.x, r.y, r.z, __builtin_fmaf(g, kap, lb) - n);
-        if (A.ref_iter)
-            for (int c = 0; c < (LOCAL ? 2 : 1); ++c)
-                lds4[A.o_rq + c * A.M + j] = make_float4(r.x, r.y, r.z, __builtin_fmaf(q, kap, lb) - n);
+        if (A.ref_iter) lds4[A.o_rq + j] = make_float4(r.x, r.y, r.z, __builtin_fmaf(q, kap, lb) - n);
         lds[A.o_lb + j] = lb;
     }
     for (int i = x0 + tid; i < x1; i += NT) {
@@ -407,7 +419,7 @@ __device__ __forceinline__ void mesh_solve(const MeshArgs& A, const int b) {
     }
     __syncthreads();
     const Rows X = rows_of<D, NT>(A, false, b, lds4), Y = rows_of<D, NT>(A, true, b, lds4);
-    const float4 *rf = lds4 + A.o_rf, *rg = lds4 + A.o_rg;
+    const float4 *rf = lds4 + A.o_rf, *rg = lds4 + A.o_rg, *rp = lds4 + A.o_rp, *rq = lds4 + A.o_rq;
     float *pf = lds + A.o_f, *pg = lds + A.o_g, *pp = lds + A.o_p, *pq = lds + A.o_q;
     float *cross = lds + A.o_cross, *self = lds + A.o_self;
     const Gather none{A.xch_f, 0, 0, -1, 0u};
@@ -421,44 +433,40 @@ __device__ __forceinline__ void mesh_solve(const MeshArgs& A, const int b) {
     for (int k = 0; k < A.iters; ++k) {
         const bool lagged = !A.safe_only && (A.lagged0 || k > 0);
         const unsigned v = (unsigned)k;
-        // the self records of this iteration's sweeps, and those of the next one's
-        const int cur = LOCAL ? k & 1 : 0, nxt = LOCAL ? cur ^ 1 : 0;
-        const int rp = A.o_rp + cur * A.T, rpn = A.o_rp + nxt * A.T;
-        const int rq = A.o_rq + cur * A.M, rqp = A.o_rq + nxt * A.M;   // rqp: of the last sweep
         if (!LOCAL)
             gather<NT>(A, Gather{A.xch_g, A.M, A.o_rg, A.o_lb, v},
                    A.debias ? Gather{A.xch_p, A.T, A.o_rp, -1, v} : none, lds);
         __syncthreads();
         if (A.ref_iter && k > 0)
-            finish_rows<D, NT, LOCAL>(A, Y, 2, true, true, lds4 + rqp, A.M, pq, lag_q, self, A.xch_q,
-                           lds + 4 * rq, lds + A.o_lb, v);
+            finish_rows<D, NT, LOCAL>(A, Y, 2, true, true, rq, A.M, pq, lag_q, self, A.xch_q,
+                           lds + 4 * A.o_rq, lds + A.o_lb, v);
         sweep_rows<D, NT>(A, X, rg, A.M, pf, lagged, cross);
         __syncthreads();
+        if (LOCAL && A.ref_iter && k > 0) put_rows(A, Y, 2, lds + 4 * A.o_rq, pq, lds + A.o_lb);
         finish_rows<D, NT, LOCAL>(A, X, 0, false, false, rg, A.M, pf, lagged, cross, A.xch_f,
                        lds + 4 * A.o_rf, nullptr, v + 1u);
-        if (A.debias) sweep_rows<D, NT>(A, X, lds4 + rp, A.T, pp, lagged, self);
+        if (A.debias) sweep_rows<D, NT>(A, X, rp, A.T, pp, lagged, self);
         if (!LOCAL)
             gather<NT>(A, Gather{A.xch_f, A.T, A.o_rf, -1, v + 1u},
                    A.ref_iter ? Gather{A.xch_q, A.M, A.o_rq, A.o_lb, v} : none, lds);
         __syncthreads();
         if (A.debias)
-            finish_rows<D, NT, LOCAL>(A, X, 2, false, true, lds4 + rp, A.T, pp, lagged, self, A.xch_p,
-                           lds + 4 * rpn, nullptr, v + 1u);
+            finish_rows<D, NT, LOCAL>(A, X, 2, false, true, rp, A.T, pp, lagged, self, A.xch_p,
+                           lds + 4 * A.o_rp, nullptr, v + 1u);
         sweep_rows<D, NT>(A, Y, rf, A.T, pg, lagged, cross);
         __syncthreads();
+        if (LOCAL && A.debias) put_rows(A, X, 2, lds + 4 * A.o_rp, pp, nullptr);
         finish_rows<D, NT, LOCAL>(A, Y, 0, true, false, rf, A.T, pg, lagged, cross, A.xch_g,
                        lds + 4 * A.o_rg, lds + A.o_lb, v + 1u);
         if (A.ref_iter) {
-            sweep_rows<D, NT>(A, Y, lds4 + rq, A.M, pq, lagged, self);
+            sweep_rows<D, NT>(A, Y, rq, A.M, pq, lagged, self);
             lag_q = lagged;
         }
     }
     __syncthreads();
-    if (A.ref_iter && A.iters > 0) {
-        const int cur = LOCAL ? A.iters & 1 : 0, last = LOCAL ? cur ^ 1 : 0;
-        finish_rows<D, NT, LOCAL>(A, Y, 2, true, true, lds4 + A.o_rq + last * A.M, A.M, pq, lag_q, self,
-                       A.xch_q, lds + 4 * (A.o_rq + cur * A.M), lds + A.o_lb, (unsigned)A.iters);
-    }
+    if (A.ref_iter && A.iters > 0)
+        finish_rows<D, NT, LOCAL>(A, Y, 2, true, true, rq, A.M, pq, lag_q, self, A.xch_q, lds + 4 * A.o_rq,
+                       lds + A.o_lb, (unsigned)A.iters);
     __syncthreads();
 
     // store the own rows: potentials and the key terms the final pass reads
@@ -547,9 +555,8 @@ bool mesh_plan(int T, int M, int d, bool debias, bool ref_iter, size_t lds_cap, 
     int r4 = 0;
     A.o_rf = r4; r4 += T;
     A.o_rg = r4; r4 += M;
-    const int copies = A.local ? 2 : 1;   // of the self records
-    A.o_rp = r4; r4 += debias ? copies * T : 0;
-    A.o_rq = r4; r4 += ref_iter ? copies * M : 0;
+    A.o_rp = r4; r4 += debias ? T : 0;
+    A.o_rq = r4; r4 += ref_iter ? M : 0;
     int off = 4 * r4;
     auto take = [&](int n) {
         const int o = off;
