@@ -7,6 +7,7 @@
 #include <cstdlib>
 #include <cstring>
 
+#include "cell_pool.h"
 #include "cells.h"
 #include "sweep_device.h"
 
@@ -390,40 +391,35 @@ __global__ __launch_bounds__(256) void k_cell_gather(CellPrep one, const CellPre
 __global__ __launch_bounds__(1024) void k_cell_plan(CellBatch C, int d) {
     __shared__ int sh[16];
     const int N = d == 2 ? CellDim<2>::N : CellDim<3>::N;
-    long long used = 0;
-    for (int b0 = 0; b0 < C.B; b0 += 1024) {
-        const int b = b0 + (int)threadIdx.x;
-        int rows[3] = {0, 0, 0};
-        bool pays[4] = {false, false, false, false};
-        if (b < C.B) {
-            const CellSide& X = C.prep[b].side[0];
-            const CellSide& Y = C.prep[b].side[1];
-            pays[0] = cell_pays(X, Y, d, 0.0, kBatchGain);
-            pays[1] = cell_pays(Y, X, d, 0.0, kBatchGain);
-            pays[2] = cell_pays(X, X, d, 0.0, kBatchGain);
-            pays[3] = cell_pays(Y, Y, d, 0.0, kBatchGain);
-            const int cx = X.cnt[0], cy = Y.cnt[0], hx = X.cnt[1], hy = Y.cnt[1];
-            rows[0] = max(pays[0] ? cx * hy : 0, pays[1] ? cy * hx : 0);
-            rows[1] = pays[2] ? cx * hx : 0;
-            rows[2] = pays[3] ? cy * hy : 0;
-        }
-        int total;
-        const int mine = rows[0] + rows[1] + rows[2];
-        const long long at = used + block_scan(mine, sh, &total);
-        used += total;
-        if (b < C.B) {
-            const bool fits = at + mine <= C.rows;
-            for (int j = 0; j < 4; ++j) C.prep[b].mode[j] = fits && pays[j] ? 1 : 0;
-            long long r[3] = {at, at + rows[0], at + rows[0] + rows[1]};
-            for (int k = 0; k < C.kinds; ++k) {
-                const int per = C.njobs[k] / C.B;
-                for (int i = 0; i < per; ++i) {
-                    CellJob& J = C.jobs[(size_t)k * C.stride + (size_t)b * per + i];
-                    const int m = (int)(J.mode - C.prep[b].mode);   // 0 f, 1 g, 2 p, 3 q
-                    const long long row = fits ? r[m < 2 ? 0 : m - 1] : 0;
-                    J.mom = C.mom + row * N;
-                    J.mu = C.mu + row;
-                }
+    __shared__ long long rows[kCellBatchJobs / 3], at[kCellBatchJobs / 3];
+    const int b = (int)threadIdx.x;   // the batch's problems are fewer than the threads
+    PoolRows mine{{0, 0, 0}};
+    bool pays[4] = {false, false, false, false};
+    if (b < C.B) {
+        const CellSide& X = C.prep[b].side[0];
+        const CellSide& Y = C.prep[b].side[1];
+        pays[0] = cell_pays(X, Y, d, 0.0, kBatchGain);
+        pays[1] = cell_pays(Y, X, d, 0.0, kBatchGain);
+        pays[2] = cell_pays(X, X, d, 0.0, kBatchGain);
+        pays[3] = cell_pays(Y, Y, d, 0.0, kBatchGain);
+        mine = pool_rows(X.cnt[0], X.cnt[1], Y.cnt[0], Y.cnt[1], pays);
+        rows[b] = mine.all();
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) pool_places(rows, C.B, C.rows, at);
+    __syncthreads();
+    if (b < C.B) {
+        const bool fits = at[b] >= 0;
+        for (int j = 0; j < 4; ++j) C.prep[b].mode[j] = fits && pays[j] ? 1 : 0;
+        const long long r[3] = {at[b], at[b] + mine.r[0], at[b] + mine.r[0] + mine.r[1]};
+        for (int k = 0; k < C.kinds; ++k) {
+            const int per = C.njobs[k] / C.B;
+            for (int i = 0; i < per; ++i) {
+                CellJob& J = C.jobs[(size_t)k * C.stride + (size_t)b * per + i];
+                const int m = (int)(J.mode - C.prep[b].mode);   // 0 f, 1 g, 2 p, 3 q
+                const long long row = fits ? r[m < 2 ? 0 : m - 1] : 0;
+                J.mom = C.mom + row * N;
+                J.mu = C.mu + row;
             }
         }
     }
