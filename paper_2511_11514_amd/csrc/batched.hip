@@ -133,6 +133,7 @@ struct CellRoom {
     bool on = false;
     size_t part_bytes = 0;   // partitions of all problems
     long long rows = 0;      // (query cell, chunk) pairs of the pool
+    int self_x = 0, self_y = 0;   // sweeps of x (y) against itself
     int max_n = 0, max_nb = 0;
 };
 
@@ -186,6 +187,8 @@ static BLayout b_layout(void* ws, int B, int64_t sumT, int64_t sumM, int64_t sum
         L.cells.kinds = kLockKinds;
         L.cells.stride = 3 * B;
         L.cells.rows = room.rows;
+        L.cells.self_x = room.self_x;
+        L.cells.self_y = room.self_y;
         L.cells.prep = a.take<CellPrep>(B);
         L.cells.jobs = a.take<CellJob>((size_t)kLockKinds * 3 * B);
         L.cells.njobs = a.take<int>(kLockKinds);
@@ -882,13 +885,16 @@ CellRoom cell_room(int B, const int64_t* To, const int64_t* Mo, const ct_sinkhor
         !cell_candidate(o->d, (int)most, (int)most))
         return r;
     Arena a(nullptr);
+    r.self_x = (o->flags & CT_DEBIAS) ? 1 : 0;
+    r.self_y = r.self_x && (o->flags & (CT_VALUE | CT_GRAD_W)) ? 1 : 0;
     for (int b = 0; b < B; ++b) {
         const int64_t T = To[b + 1] - To[b], M = Mo[b + 1] - Mo[b];
         CellPrep P;
         cell_prep_layout(a, P, o->d, (int)T, (int)M, 0, 0, kCellBatchChunk, kCellBatchChunk);
         const CellSide &X = P.side[0], &Y = P.side[1];
         r.rows += std::max((long long)X.cmax * Y.chmax, (long long)Y.cmax * X.chmax) +
-                  (long long)X.cmax * X.chmax + (long long)Y.cmax * Y.chmax;
+                  (r.self_x ? (long long)X.cmax * X.chmax : 0) +
+                  (r.self_y ? (long long)Y.cmax * Y.chmax : 0);
         r.max_n = std::max(r.max_n, std::max(X.n, Y.n));
         r.max_nb = std::max(r.max_nb, std::max(X.nb, Y.nb));
     }

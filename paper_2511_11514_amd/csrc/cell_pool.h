@@ -18,14 +18,15 @@ __host__ __device__ inline PoolRows pool_rows(int cx, int hx, int cy, int hy, co
     return PoolRows{{f > g ? f : g, on[2] ? (long long)cx * hx : 0, on[3] ? (long long)cy * hy : 0}};
 }
 
-// First rows of n problems that need `rows` each, in problem order while they fit `room`; -1: no
-// place, the problem sweeps directly.
+// First rows of n problems that need `rows` each, in problem order, each that still fits `room`;
+// -1: no place, the problem sweeps directly (and takes none from those after it).
 __host__ __device__ inline void pool_places(const long long* rows, int n, long long room,
                                             long long* at) {
     long long used = 0;
     for (int b = 0; b < n; ++b) {
-        at[b] = used + rows[b] <= room ? used : -1;
-        used += rows[b];
+        const bool fits = rows[b] <= room - used;
+        at[b] = fits ? used : -1;
+        used += fits ? rows[b] : 0;
     }
 }
 

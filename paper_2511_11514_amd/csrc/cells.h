@@ -157,6 +157,7 @@ struct CellBatch {
     float* mu;
     long long rows;        // (query cell, chunk) pairs that the pool holds
     int B, kinds, stride;  // stride = 3B
+    int self_x, self_y;    // 1: the batch has sweeps of x (y) against itself
 };
 // Partitions of every problem, then the jobs' modes, places in the pool and units.
 hipError_t launch_cell_prep_batch(int d, const CellBatch& C, const CellInputs& in, int max_n,

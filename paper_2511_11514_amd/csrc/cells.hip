@@ -400,8 +400,8 @@ __global__ __launch_bounds__(1024) void k_cell_plan(CellBatch C, int d) {
         const CellSide& Y = C.prep[b].side[1];
         pays[0] = cell_pays(X, Y, d, 0.0, kBatchGain);
         pays[1] = cell_pays(Y, X, d, 0.0, kBatchGain);
-        pays[2] = cell_pays(X, X, d, 0.0, kBatchGain);
-        pays[3] = cell_pays(Y, Y, d, 0.0, kBatchGain);
+        pays[2] = C.self_x && cell_pays(X, X, d, 0.0, kBatchGain);
+        pays[3] = C.self_y && cell_pays(Y, Y, d, 0.0, kBatchGain);
         mine = pool_rows(X.cnt[0], X.cnt[1], Y.cnt[0], Y.cnt[1], pays);
         rows[b] = mine.all();
     }

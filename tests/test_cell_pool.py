@@ -77,3 +77,28 @@ def test_places_are_disjoint_and_in_the_pool(places):
     assert [r for r, _ in got] == [_rows(*p) for p in probs]
     assert any(a >= 0 for _, a in got) and any(a < 0 for _, a in got)
     _apart(got, room)
+
+
+def test_a_problem_without_a_place_takes_none(places):
+    """One that does not fit leaves the pool to those after it."""
+    small, big = (10, 20, 30, 40, 1, 1, 0, 0), (4096, 9000, 4096, 9000, 1, 1, 1, 1)
+    got = places(1300, [big, small, big, small, small])
+    assert [a for _, a in got] == [-1, 0, -1, 600, -1] and got[1][0] == 600
+    got = places(1800, [big, small, big, small, small])
+    assert [a for _, a in got] == [-1, 0, -1, 600, 1200]
+
+
+def test_batch_without_a_reference_solve_reserves_less():
+    """The pool has no rows for sweeps that the batch does not make."""
+    import ctypes
+    from paper_2511_11514_amd import _lib
+    off = lambda n: (ctypes.c_int64 * 13)(*[n * i for i in range(13)])
+    size = lambda flags: _lib.lib().ct_sinkhorn_batched_workspace_size(
+        12, off(3000), off(9000), ctypes.byref(_lib.SinkhornOpts(2, 100, 0.01, flags)))
+    direct = lambda flags: size(flags | _lib.CT_UNFUSED)
+    room = [size(f) - direct(f) for f in (0, _lib.CT_DEBIAS, _lib.CT_DEBIAS | _lib.CT_VALUE)]
+    # moments of 64 floats a row and their exponents: x-x and y-y rows of 12 problems
+    row = 4 * 65
+    x, y = (3000 // 24 + 1), (9000 // 24 + 1)
+    assert room[1] - room[0] == pytest.approx(12 * row * x * (x + 3000 // 512), rel=0.02)
+    assert room[2] - room[1] == pytest.approx(12 * row * y * (y + 9000 // 512), rel=0.02)
