@@ -143,10 +143,12 @@ typedef struct ct_sinkhorn_opts {
     uint32_t flags; /* CT_* flags above */
 } ct_sinkhorn_opts;
 
-/* Workspace bytes needed by ct_sinkhorn_grad for these sizes and options.  From 1e8 point
- * pairs per iteration on, most of it holds the cell form's moments (at most 384 MiB for each
- * of three buffers: 253 MB in all at T = 4096, M = 16384, 1.4 GB at T = 65536, M = 262144).
- * A smaller workspace that holds the rest is accepted and gets the direct sweeps. */
+/* Workspace bytes needed by ct_sinkhorn_grad for these sizes and options.  For calls that may
+ * take the cell form (see CT_MESH) most of it holds the form's tables and moments (at most 384
+ * MiB of moments for the cross sweeps and for each self problem that the options ask for: 253
+ * MB in all at T = 4096, M = 16384 with a value, 1.4 GB at T = 65536, M = 262144).  A smaller
+ * workspace that holds the rest, such as one sized for other options, is accepted and gets the
+ * direct sweeps. */
 size_t ct_sinkhorn_workspace_size(int64_t T, int64_t M, const ct_sinkhorn_opts* o);
 
 /*

@@ -477,7 +477,7 @@ __global__ __launch_bounds__(256) void k_cell_functions(CellPrep P, CellInputs i
     __shared__ float fn[D * F * 33];
     const CellSide& S = P.side[blockIdx.y];
     const float* pts = blockIdx.y ? P.ys : P.xs;
-    if (S.cnt[3]) return;
+    if (S.cnt[3] || !S.phi) return;   // (null: no sweep of the set takes the form)
     const int nt = S.cnt[2], tid = (int)threadIdx.x, col = tid & 31;
     const float inv = 2.f / P.cell;
     for (int t = (int)blockIdx.x; t < nt; t += (int)gridDim.x) {

@@ -270,6 +270,7 @@ PlanLayout plan_layout(void* ws, const ct_plan_problem* p, const ct_plan_opts* o
     if (o->flow == CT_FLOW_SINKHORN) {
         ct_sinkhorn_opts so = o->sk;
         so.d = p->d;
+        so.flags |= CT_VALUE;   // as ct_plan calls it
         L.inner_bytes = ct_sinkhorn_workspace_size(T, M, &so);
     } else {
         L.inner_bytes = ct_svgd_workspace_size(T, p->d);

@@ -373,23 +373,44 @@ struct SkLayout {
 
 // Cell form of the sweeps (see cells.h): by default where the library would launch one
 // direct sweep at a time and the call is large enough (cell_limits), up to kCellMaxPoints
-// points a side (16-bit cell codes sorted by at most 512 blocks).  Whether it pays and fits
-// for the points at hand, k_cell_gather settles on the device.  CT_UNFUSED, CT_DIFFERENCE, CT_SAFE_LSE and the flags of the other
-// executions rule it out, and so does a workspace without its arrays.
+// points a side (cell codes sorted by at most 256 blocks).  Whether it pays and fits
+// for the points at hand, k_cell_gather settles on the device.  CT_UNFUSED, CT_DIFFERENCE,
+// CT_SAFE_LSE and the flags of the other executions rule it out, and so does a workspace
+// without its arrays.  The workspace's size, its layout and the dispatch ask the same question.
 constexpr size_t kCellMomentsMax = size_t(96) << 20;   // floats of one moments buffer
 constexpr double kMeshAutoPairs = 1.5e7;
 
-static bool cells_possible(int T, int M) {
-    const double pairs = 2.0 * T * M + (double)T * T + (double)M * M;
-    return pairs > cell_limits().pairs && T <= kCellMaxPoints && M <= kCellMaxPoints;
+struct CellSweeps {
+    bool cross = false, x = false, y = false;   // f and g, x against itself, y against itself
+    bool any() const { return cross || x || y; }
+};
+
+// The sweeps of a call that are offered the cell form.
+static CellSweeps cell_sweeps(int T, int M, const ct_sinkhorn_opts* o) {
+    CellSweeps s;
+    const bool debias = o->flags & CT_DEBIAS;
+    const bool need_ref = debias && (o->flags & (CT_VALUE | CT_GRAD_W));
+    const double pairs = 2.0 * T * M + (debias ? (double)T * T : 0.0) +
+                         (need_ref && !(o->flags & CT_REF_CACHED) ? (double)M * M : 0.0);
+    const CellLimits lim = cell_limits();
+    if ((o->flags & (CT_UNFUSED | CT_DIFFERENCE | CT_SAFE_LSE | CT_FUSED | CT_TINY | CT_MESH)) ||
+        o->iters < kCellMinIters || T > kCellMaxPoints || M > kCellMaxPoints ||
+        pairs <= std::max(lim.pairs, kMeshAutoPairs) || o->iters * pairs <= lim.work)
+        return s;
+    s.cross = cell_candidate(o->d, T, M);
+    s.x = debias && cell_candidate(o->d, T, T);
+    s.y = need_ref && cell_candidate(o->d, M, M);
+    return s;
 }
 
-static void cell_layout(Arena& a, SkLayout& L, int T, int M, int d) {
+static void cell_layout(Arena& a, SkLayout& L, int T, int M, int d, const CellSweeps& sweeps) {
     CellPrep& P = L.prep;
     std::memset(&P, 0, sizeof(P));
     cell_prep_layout(a, P, d, T, M, 0, 0, cell_chunk(T), cell_chunk(M));
     const int N = d == 2 ? CellDim<2>::N : CellDim<3>::N;
-    for (int s = 0; s < 2; ++s) P.side[s].phi = a.take<float4>((size_t)P.side[s].tmax * N * 8);
+    for (int s = 0; s < 2; ++s)
+        if (sweeps.cross || (s ? sweeps.y : sweeps.x))
+            P.side[s].phi = a.take<float4>((size_t)P.side[s].tmax * N * 8);
     P.xs = a.take<float>((size_t)T * d);
     P.ys = a.take<float>((size_t)M * d);
     P.ws = a.take<float>(M);
@@ -397,7 +418,10 @@ static void cell_layout(Arena& a, SkLayout& L, int T, int M, int d) {
     const CellSide &X = P.side[0], &Y = P.side[1];
     const size_t rows[3] = {std::max((size_t)X.cmax * Y.chmax, (size_t)Y.cmax * X.chmax),
                             (size_t)X.cmax * X.chmax, (size_t)Y.cmax * Y.chmax};
+    const bool on[3] = {sweeps.cross, sweeps.x, sweeps.y};
     for (int i = 0; i < 3; ++i) {
+        L.mom[i] = L.mu[i] = nullptr;   // mom_cap 0: k_cell_gather leaves the sweep direct
+        if (!on[i]) continue;
         const size_t r = std::min(rows[i], kCellMomentsMax / N);
         P.mom_cap[i] = r * N;
         L.mom[i] = a.take<float>(r * N);
@@ -405,7 +429,8 @@ static void cell_layout(Arena& a, SkLayout& L, int T, int M, int d) {
     }
 }
 
-static SkLayout sk_layout(void* ws, int T, int M, int d, bool cells) {
+// o: the call's options, or null for the layout without the cell form.
+static SkLayout sk_layout(void* ws, int T, int M, int d, const ct_sinkhorn_opts* o) {
     Arena a(ws);
     SkLayout L;
     const int Tp = pad_keys(T), Mp = pad_keys(M);
@@ -435,8 +460,9 @@ static SkLayout sk_layout(void* ws, int T, int M, int d, bool cells) {
     for (int i = 0; i < 3; ++i) L.tick[i] = a.take<unsigned>(L.ntick);
     L.bar = a.take<unsigned>(kFusedBarWords);
     L.xch = a.take<unsigned long long>(4 * ((size_t)T + M));
-    L.cells = cells && cells_possible(T, M);
-    if (L.cells) cell_layout(a, L, T, M, d);
+    const CellSweeps sweeps = o ? cell_sweeps(T, M, o) : CellSweeps();
+    L.cells = sweeps.any();
+    if (L.cells) cell_layout(a, L, T, M, d, sweeps);
     L.bytes = a.off + 256;
     return L;
 }
@@ -861,9 +887,9 @@ static ct_status run_mesh(const SkLayout& L, const SkConsts& c, const ct_sinkhor
 
 // Iterate-and-extrapolate for one problem whose arrays are staged in L.
 static ct_status run_problem(const SkLayout& L, int T, int M, const ct_sinkhorn_opts* o,
-                             bool cells, hipStream_t st, const ForkJoin* fj) {
+                             hipStream_t st, const ForkJoin* fj) {
     const int d = o->d;
-    const SkLayout* cl = cells ? &L : nullptr;
+    const SkLayout* cl = L.cells ? &L : nullptr;
     const bool debias = o->flags & CT_DEBIAS;
     const bool want_v = o->flags & (CT_VALUE | CT_GRAD_W);
     const bool need_ref = debias && want_v;
@@ -972,7 +998,7 @@ extern "C" size_t ct_sinkhorn_workspace_size(int64_t T, int64_t M, const ct_sink
     if (!o || (o->d != 2 && o->d != 3) || T < 1 || M < 1 || T > (int64_t(1) << 30) ||
         M > (int64_t(1) << 30))
         return 0;
-    return sk_layout(nullptr, (int)T, (int)M, o->d, true).bytes;
+    return sk_layout(nullptr, (int)T, (int)M, o->d, o).bytes;
 }
 
 namespace ct {
@@ -1005,8 +1031,8 @@ static ct_status sinkhorn_grad_impl(const float* x, int64_t T64, const float* y,
     if (!ws) return fail(CT_E_ARG, "workspace is null");
     if (reinterpret_cast<uintptr_t>(ws) % 256) return fail(CT_E_WORKSPACE, "workspace not 256-byte aligned");
     // a workspace without room for the cell form's arrays serves the direct sweeps
-    SkLayout L = sk_layout(ws, T, M, d, true);
-    if (L.cells && ws_bytes < L.bytes) L = sk_layout(ws, T, M, d, false);
+    SkLayout L = sk_layout(ws, T, M, d, o);
+    if (L.cells && ws_bytes < L.bytes) L = sk_layout(ws, T, M, d, nullptr);
     if (ws_bytes < L.bytes)
         return fail(CT_E_WORKSPACE, "workspace too small: %zu < %zu bytes", ws_bytes, L.bytes);
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -1032,22 +1058,12 @@ static ct_status sinkhorn_grad_impl(const float* x, int64_t T64, const float* y,
     const int nsum = (int)std::min<int64_t>(kSumBlocks, (T64 + M64 + 1023) / 1024);
     hipLaunchKernelGGL(k_begin, dim3(nsum), dim3(256), 0, st, B);
     CT_CHECK_HIP(hipGetLastError());
-    const double iter_pairs = 2.0 * T * M + (debias ? (double)T * T : 0.0) +
-                              (need_ref && !(o->flags & CT_REF_CACHED) ? (double)M * M : 0.0);
-    const bool candidate = cell_candidate(d, T, M) || cell_candidate(d, T, T) ||
-                     (need_ref && cell_candidate(d, M, M));
-    const CellLimits lim = cell_limits();
-    const bool cells = L.cells && candidate && o->iters >= kCellMinIters &&
-                       iter_pairs > std::max(lim.pairs, kMeshAutoPairs) &&
-                       o->iters * iter_pairs > lim.work &&
-                       !(o->flags & (CT_UNFUSED | CT_DIFFERENCE | CT_SAFE_LSE | CT_FUSED | CT_TINY |
-                                     CT_MESH));
     const bool pot_given = o->flags & (CT_WARM_START | CT_REF_CACHED);
     const int* perm_x = nullptr;
     const int* perm_y = nullptr;
     StageArgs A;
     A.x = x; A.y = y; A.w = w; A.pot_in = pot;
-    if (cells) {
+    if (L.cells) {
         // everything below works on the points in cell order; the outputs go back through
         // the permutations
         CellPrep& P = L.prep;
@@ -1079,7 +1095,7 @@ static ct_status sinkhorn_grad_impl(const float* x, int64_t T64, const float* y,
     hipLaunchKernelGGL(k_stage, dim3((n + 255) / 256), dim3(256), 0, st, A);
     CT_CHECK_HIP(hipGetLastError());
 
-    rc = run_problem(L, T, M, o, cells, st, fj);
+    rc = run_problem(L, T, M, o, st, fj);
     if (rc) return rc;
 
     OutArgs R;
@@ -1164,7 +1180,7 @@ extern "C" ct_status ct_sinkhorn_grad_static(const float* x, int64_t T64, const 
     clear_error();
     ct_status rc = validate_call(x, T64, y, M64, o, grad_x, grad_w, value, pot);
     if (rc) return rc;
-    const size_t need = sk_layout(nullptr, (int)T64, (int)M64, o->d, false).bytes;
+    const size_t need = sk_layout(nullptr, (int)T64, (int)M64, o->d, nullptr).bytes;
     if (need > kStaticScratchBytes)
         return fail(CT_E_WORKSPACE,
                     "problem needs %zu bytes of scratch; the static scratch holds %zu "
@@ -1241,7 +1257,7 @@ extern "C" ct_status ct_autotune_sinkhorn(int64_t T64, int64_t M64, const ct_sin
     if (rc) return rc;
     if (!ws) return fail(CT_E_ARG, "workspace is null");
     const int T = (int)T64, M = (int)M64, d = o->d;
-    SkLayout L = sk_layout(ws, T, M, d, false);
+    SkLayout L = sk_layout(ws, T, M, d, nullptr);
     if (ws_bytes < L.bytes) return fail(CT_E_WORKSPACE, "workspace too small: %zu < %zu", ws_bytes, L.bytes);
     hipStream_t st = static_cast<hipStream_t>(stream);
     rc = refuse_capture(st, "ct_autotune_sinkhorn");
@@ -1315,7 +1331,7 @@ extern "C" ct_status ct_status_sync(const void* ws, float resid_tol, uint32_t* n
     // the counters come before every size-dependent buffer of the layout; a stand-in
     // base (never dereferenced) gives their offset
     char* const probe = reinterpret_cast<char*>(uintptr_t(1) << 20);
-    const size_t off = static_cast<size_t>(reinterpret_cast<char*>(sk_layout(probe, 1, 1, 2, false).counters) - probe);
+    const size_t off = static_cast<size_t>(reinterpret_cast<char*>(sk_layout(probe, 1, 1, 2, nullptr).counters) - probe);
     unsigned c[kCounters] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
     CT_CHECK_HIP(hipMemcpyAsync(c, static_cast<const char*>(ws) + off, sizeof(c),
                                 hipMemcpyDeviceToHost, st));
