@@ -123,7 +123,8 @@ const char* ct_version(void);
                            pairs in all on, those launches take the cell form of a sweep
                            where it pays (a grid of cells over each point set, sums
                            over pairs of cells by truncated expansions that leave out less
-                           than 1e-7 of any pair's term; decided on the device), unless
+                           than 1e-7 of any pair's term; offered where eps gives a unit box
+                           few enough cells for the points, then decided on the device), unless
                            CT_UNFUSED, CT_DIFFERENCE or CT_SAFE_LSE is given or the
                            workspace lacks its arrays. */
 #define CT_DIFFERENCE 1024u /* per-sweep launches: evaluate the lagged sweeps' exponent in the
@@ -270,7 +271,8 @@ ct_status ct_status_sync(const void* ws, float resid_tol, uint32_t* nonfinite, u
  *     blocks sweep about the same number of pairs; without CT_UNFUSED, from 8
  *     iterations and the pairs per iteration of one problem on (at most 341
  *     problems), a problem's sweeps take the cell form where it pays (as for one
- *     problem; decided on the device);
+ *     problem: offered by the sizes and eps that the batch is prepared for, then
+ *     decided on the device);
  *   persistent (CT_PERSISTENT): one kernel that walks a dependency-ordered work
  *     list.
  * The extrapolation pass and the reductions follow as lockstep launches in every

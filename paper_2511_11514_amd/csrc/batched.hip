@@ -884,6 +884,18 @@ CellRoom cell_room(int B, const int64_t* To, const int64_t* Mo, const ct_sinkhor
     if (pairs <= lim.pairs || o->iters * pairs <= lim.work || most > kCellMaxPoints ||
         !cell_candidate(o->d, (int)most, (int)most))
         return r;
+    if (lim.expect) {
+        CellOffer offer(o->d, o->eps, 0.0, kBatchGain, o->d == 2 ? 1.2 : 1.05);
+        for (int b = 0; b < B; ++b) {
+            const int T = (int)(To[b + 1] - To[b]), M = (int)(Mo[b + 1] - Mo[b]);
+            offer.sweep(T, M, kCellBatchChunk, kCellBatchChunk);
+            offer.sweep(M, T, kCellBatchChunk, kCellBatchChunk);
+            if (o->flags & CT_DEBIAS) offer.sweep(T, T, kCellBatchChunk, kCellBatchChunk);
+            if ((o->flags & CT_DEBIAS) && (o->flags & (CT_VALUE | CT_GRAD_W)))
+                offer.sweep(M, M, kCellBatchChunk, kCellBatchChunk);
+        }
+        if (!offer.pays(o->iters, 100.0 + 3.0 * B)) return r;
+    }
     Arena a(nullptr);
     r.self_x = (o->flags & CT_DEBIAS) ? 1 : 0;
     r.self_y = r.self_x && (o->flags & (CT_VALUE | CT_GRAD_W)) ? 1 : 0;

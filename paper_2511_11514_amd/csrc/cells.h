@@ -113,6 +113,42 @@ struct CellLaunch {
 
 // Side of a cell in scaled coordinates: lambda = ln2 w^2 / 2.
 double cell_side(int d);
+
+// What a sweep's time in the cell form depends on, of one point set.
+struct CellCounts {
+    double n, cells, chunks, tiles;
+};
+// Times of one sweep in us from a model of both forms in clocks of one compute unit, fitted to
+// launches of 4096 to 262144 points (d = 2: T = 4096, M = 16384, f: 18 us measured, 16 modelled,
+// direct 20 and 19; T = 65536, M = 262144, g: 166 and 150, direct 2290 and 2900; d = 3, M =
+// 65521: the q sweep 450 and 446, direct 800 and 884).
+//   moments  the keys' products for 32 query cells at a time at 73 % of the matrix cores'
+//            128 multiply-adds per clock, and a fixed part per (chunk, 32 cells)
+//   values   twice the products' clocks, and a fixed part per tile
+//   direct   the pairs' instructions at 75 % of their issue rate
+struct CellTimes {
+    double cell, direct;
+};
+__host__ __device__ inline CellTimes cell_times(const CellCounts& q, const CellCounts& k, int d) {
+    const double N = d == 2 ? CellDim<2>::N : CellDim<3>::N;
+    const double pair = d == 2 ? 2.0 / 128 + 2.0 / 64 + 1.0 / 32 : 2.0 / 128 + 3.0 / 64 + 1.0 / 32;
+    const double at = ceil(q.cells / kCellTile), ct = ceil(k.chunks / kCellTile);
+    const double moments = at * (kCellTile * N / 128.0 / 0.73 * k.n + (d == 2 ? 9e3 : 18e3) * k.chunks);
+    const double values = q.tiles * (ct * 2.0 * kCellTile * kCellTile * N / 128.0 + 1e3);
+    const double direct = q.n * k.n * pair / 0.75;
+    const double per_us = 256.0 * 2400.0;
+    return CellTimes{(moments + values) / per_us, direct / per_us};
+}
+// A sweep's launches in us (a batch shares them), and the modelled gain below which the device
+// leaves a sweep direct in a single problem; a batch's launch is slower the more of its jobs are
+// direct (their units wait behind the moments, three blocks to a compute unit), so there the
+// form is taken unless the model puts it at twice the direct time (24 ragged problems of other
+// seeds than the timed case's, 150 iterations: 0.9 53.2 ms, 1.2 50.8, 1.6 46.0, 2.5 45.9, 4 45.1).
+constexpr double kCellLaunch = 8.0;
+constexpr double kGain = 0.9, kBatchGain = 2.0;
+__host__ __device__ inline bool cell_gains(const CellTimes& t, double launch, double gain) {
+    return t.cell + 0.6 * launch < gain * (t.direct + launch);
+}
 // Sizes of a problem's partition and its arrays from the arena (all but the function tables,
 // the sorted inputs and the moments).
 void cell_prep_layout(Arena& a, CellPrep& P, int d, int T, int M, int xo, int yo, int kcx, int kcy);
@@ -123,7 +159,7 @@ int cell_chunk(int n);
 
 hipError_t launch_cell_prep(const CellPrep& P, const CellInputs& in, hipStream_t s);
 // Calls too small for the cell form; the environment variable CT_CELL_MIN_PAIRS (a test and
-// tuning hook) replaces `pairs` and `pairs3` and drops `work`.
+// tuning hook) replaces `pairs` and `pairs3` and drops `work` and CellOffer's question.
 constexpr int kCellMinIters = 8;
 constexpr int kCellMaxPoints = 1 << 22;
 struct CellLimits {
@@ -136,9 +172,40 @@ struct CellLimits {
     // Pairs of a 3-D sweep below which it stays direct: cells of so few points are too sparse
     // to pay (40 iterations at T = 16355, M = 22674 lose 2 %, at T = 10246, M = 35898 win 26 %).
     double pairs3 = 1.2e9;
+    bool expect = true;   // ask CellOffer
 };
 CellLimits cell_limits();
 bool cell_candidate(int d, int nq, int nk);
+
+// Whether a call is offered the form at all, before the device sees its points.  A call that is
+// offered it and does not take it pays for the partition, for a launch or two more per sweep and,
+// in 2-D, for direct sweeps at the registers and LDS of the moments (three blocks to a compute
+// unit instead of five or six): 5 to 10 % of a single problem (T = 4096, M = 16384, eps = 0.001,
+// 120 iterations: 10.3 ms against 9.7), 18 to 31 % of a batch (16 problems below 4000 x 9000,
+// eps = 0.001: 8.3 against 6.8 ms; 300 below 1000 x 1500: 5.7 against 3.9).  The host knows eps
+// and the sizes, not the extent, so it takes the library's domain, the unit box: a side of it has
+// c = sqrt(log2(e) / eps) / w cells, and points that spread over it lie in about (c + 1/2)^d of
+// them (counted on random walks and mixtures: 0.55 to 1.2 of that in 2-D, where 0.8 is taken, 0.2
+// to 1.1 in 3-D, where 0.3 is taken, since the form's launches there leave direct sweeps at
+// their own speed: 0 to 2 %).  The same model as on the device then says whether the form is
+// likely to pay.  Of 105 calls around the crossover (single problems of 2500 x 10000 to 20000 x
+// 20000 points and batches of 4 to 300, eps 0.0001 to 0.1) none that it offers the form is slower than
+// its direct sweeps, and those that it refuses could have gained 7 % at most.
+class CellOffer {
+public:
+    // d, eps of a call; launch, gain: as for the device's choice; slow: time of a direct sweep
+    // within the form's launches over that of a launch of its own.
+    CellOffer(int d, double eps, double launch, double gain, double slow);
+    CellCounts expect(int n, int chunk_keys, bool* fits) const;
+    void sweep(int nq, int nk, int chunk_q, int chunk_k);   // one more sweep of every iteration
+    // prep_us: the partition.
+    bool pays(int iters, double prep_us) const;
+
+private:
+    int d_;
+    double side_cells_, launch_, gain_, slow_, form_ = 0.0, direct_ = 0.0;
+    bool any_ = false;
+};
 // One sweep of one or two jobs (nblocks direct work units): moments then values, or the
 // direct sweep then its merge.
 hipError_t launch_cell_sweep(int d, const Schedule& sc, bool lagged, const Launch& L,

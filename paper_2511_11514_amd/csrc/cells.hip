@@ -318,32 +318,13 @@ __global__ __launch_bounds__(64) void k_cell_scatter(CellPrep one, const CellPre
     }
 }
 
-// Whether a sweep pays in the cell form, from a model of both forms' times in clocks of one
-// compute unit, fitted to launches of 4096 to 262144 points (d = 2: T = 4096, M = 16384, f: 18 us
-// measured, 16 modelled, direct 20 and 19; T = 65536, M = 262144, g: 166 and 150, direct
-// 2290 and 2900; d = 3, M = 65521: the q sweep 450 and 446, direct 800 and 884).
-//   moments  the keys' products for 32 query cells at a time at 73 % of the matrix cores'
-//            128 multiply-adds per clock, and a fixed part per (chunk, 32 cells)
-//   values   twice the products' clocks, and a fixed part per tile
-//   direct   the pairs' instructions at 75 % of their issue rate
-// and per sweep the launches (`launch`, in microseconds; a batch shares them).
+// Whether a sweep pays in the cell form (and fits).
 __device__ bool cell_pays(const CellSide& q, const CellSide& k, int d, double launch, double gain) {
     if (q.cnt[3] || k.cnt[3]) return false;
-    const double N = d == 2 ? CellDim<2>::N : CellDim<3>::N;
-    const double pair = d == 2 ? 2.0 / 128 + 2.0 / 64 + 1.0 / 32 : 2.0 / 128 + 3.0 / 64 + 1.0 / 32;
-    const double at = (q.cnt[0] + kCellTile - 1) / kCellTile, ct = (k.cnt[1] + kCellTile - 1) / kCellTile;
-    const double moments = at * (kCellTile * N / 128.0 / 0.73 * k.n + (d == 2 ? 9e3 : 18e3) * k.cnt[1]);
-    const double values = q.cnt[2] * (ct * 2.0 * kCellTile * kCellTile * N / 128.0 + 1e3);
-    const double direct = (double)q.n * k.n * pair / 0.75;
-    const double per_us = 256.0 * 2400.0;
-    return (moments + values) / per_us + 0.6 * launch < gain * (direct / per_us + launch);
+    const CellCounts Q{(double)q.n, (double)q.cnt[0], (double)q.cnt[1], (double)q.cnt[2]};
+    const CellCounts K{(double)k.n, (double)k.cnt[0], (double)k.cnt[1], (double)k.cnt[2]};
+    return cell_gains(cell_times(Q, K, d), launch, gain);
 }
-constexpr double kCellLaunch = 8.0;
-// Modelled gain below which a sweep goes direct in a single problem; a batch's launch is slower
-// the more of its jobs are direct (their units wait behind the moments, three blocks to a
-// compute unit), so there the form is taken unless the model puts it at twice the direct time
-// (24 ragged problems, 150 iterations: 0.9 53.2 ms, 1.2 50.8, 1.6 46.0, 2.5 45.9, 4 45.1).
-constexpr double kGain = 0.9, kBatchGain = 2.0;
 
 // Points, weights and starting potentials in cell order.
 template <bool TAB>
@@ -1166,12 +1147,43 @@ CellLimits cell_limits() {
     if (const char* e = std::getenv("CT_CELL_MIN_PAIRS")) {
         l.pairs = l.pairs3 = std::atof(e);
         l.work = 0.0;
+        l.expect = false;
     }
     return l;
 }
 
 bool cell_candidate(int d, int nq, int nk) {
     return d == 2 || (double)nq * nk >= cell_limits().pairs3;
+}
+
+CellOffer::CellOffer(int d, double eps, double launch, double gain, double slow)
+    : d_(d), side_cells_(std::sqrt(1.4426950408889634 / eps) / cell_side(d)), launch_(launch),
+      gain_(gain), slow_(slow) {}
+
+CellCounts CellOffer::expect(int n, int chunk_keys, bool* fits) const {
+    const int bits = d_ == 2 ? CellDim<2>::bits : CellDim<3>::bits;
+    const double box = std::pow(side_cells_ + 0.5, d_) * (d_ == 2 ? 0.8 : 0.3);
+    const double cells = std::max(1.0, box * -std::expm1(-n / box));   // n points at random
+    *fits = side_cells_ <= (1 << bits) && cells <= n / kCellMinPoints + 1;
+    // parts of `most` points of a cell, the cells' sizes spread exponentially
+    auto parts = [&](int most) { return cells / -std::expm1(-most * cells / n); };
+    return CellCounts{(double)n, cells, parts(chunk_keys), parts(kCellTile)};
+}
+
+void CellOffer::sweep(int nq, int nk, int chunk_q, int chunk_k) {
+    bool fq, fk;
+    const CellTimes t = cell_times(expect(nq, chunk_q, &fq), expect(nk, chunk_k, &fk), d_);
+    direct_ += t.direct + launch_;
+    if (fq && fk && cell_gains(t, launch_, gain_)) {
+        any_ = true;
+        form_ += t.cell + 0.6 * launch_;
+    } else {
+        form_ += slow_ * t.direct + launch_;
+    }
+}
+
+bool CellOffer::pays(int iters, double prep_us) const {
+    return any_ && iters * form_ + prep_us < iters * direct_;
 }
 
 hipError_t launch_cell_sweep(int d, const Schedule& sc, bool lagged, const Launch& L0,

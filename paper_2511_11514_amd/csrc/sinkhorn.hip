@@ -400,7 +400,16 @@ static CellSweeps cell_sweeps(int T, int M, const ct_sinkhorn_opts* o) {
     s.cross = cell_candidate(o->d, T, M);
     s.x = debias && cell_candidate(o->d, T, T);
     s.y = need_ref && cell_candidate(o->d, M, M);
-    return s;
+    if (!lim.expect) return s;
+    const int kx = cell_chunk(T), ky = cell_chunk(M);
+    CellOffer offer(o->d, o->eps, kCellLaunch, kGain, o->d == 2 ? 1.06 : 1.0);
+    if (s.cross) {
+        offer.sweep(T, M, kx, ky);
+        offer.sweep(M, T, ky, kx);
+    }
+    if (s.x) offer.sweep(T, T, kx, kx);
+    if (s.y && !(o->flags & CT_REF_CACHED)) offer.sweep(M, M, ky, ky);
+    return offer.pays(o->iters, 150.0) ? s : CellSweeps();
 }
 
 static void cell_layout(Arena& a, SkLayout& L, int T, int M, int d, const CellSweeps& sweeps) {

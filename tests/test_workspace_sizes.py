@@ -41,3 +41,24 @@ def test_buffers_of_the_sweeps_that_run():
     y = size(DB | VAL) - size(DB | VAL | _lib.CT_UNFUSED)
     assert 384 << 20 < y < 800 << 20
     assert size(DB) == size(DB | _lib.CT_UNFUSED)
+
+
+def _batch(d, sizes, flags, eps, iters=100):
+    off = lambda k: (ctypes.c_int64 * (len(sizes) + 1))(*[sum(s[k] for s in sizes[:i])
+                                                          for i in range(len(sizes) + 1)])
+    return _lib.lib().ct_sinkhorn_batched_workspace_size(
+        len(sizes), off(0), off(1), ctypes.byref(_lib.SinkhornOpts(d, iters, eps, flags)))
+
+
+@pytest.mark.parametrize("eps,offered", [(1e-4, False), (1e-3, False), (0.005, True), (0.02, True), (0.2, True)])
+def test_offered_where_a_unit_box_has_few_cells(eps, offered):
+    base = _size(2, 4096, 16384, DB | VAL | _lib.CT_UNFUSED, eps=eps)
+    assert (_size(2, 4096, 16384, DB | VAL, eps=eps) > base) == offered
+
+
+@pytest.mark.parametrize("sizes,eps,offered", [
+    ([(4000, 20000)] * 12, 0.01, True), ([(4000, 20000)] * 12, 0.0005, False),
+    ([(2500, 6000)] * 8, 0.005, False), ([(600, 900)] * 300, 0.1, False),
+])
+def test_batches_offered_where_it_pays(sizes, eps, offered):
+    assert (_batch(2, sizes, DB, eps) > _batch(2, sizes, DB | _lib.CT_UNFUSED, eps)) == offered
