@@ -576,6 +576,7 @@ struct MeshInfo {
     size_t lds;             // dynamic LDS of the launch (the largest problem's)
     double pairs;           // point pairs of its iterations
     float eps;              // the eps its tables were built for
+    bool local = false;     // every problem in one block (kMeshLocalRows)
 };
 struct Prepared {
     unsigned long long signature;
@@ -776,6 +777,7 @@ size_t build_lock(const BLayout& L, const std::vector<BProb>& P, uint32_t flags,
 // once.  Fills tab/blk (device pointers of L) and returns false if it does not
 // apply.
 constexpr double kMeshBatchPairs = 1.5e7;
+constexpr double kMeshLocalPairs = 4e4;
 constexpr unsigned kMeshBatchWaitPolls = 1u << 18;
 
 size_t device_lds_per_block() {
@@ -850,6 +852,7 @@ bool plan_mesh_batch(const BLayout& L, const std::vector<BProb>& P, const ct_sin
     info.blocks = blocks;
     info.lds = lds_max;
     info.pairs = pairs;
+    info.local = rows == kMeshLocalRows;
     return true;
 }
 
@@ -1056,8 +1059,24 @@ extern "C" ct_status ct_sinkhorn_batched_prepare(int32_t B, const int64_t* To, c
         int least = 8;   // test and tuning hook: at least so many own rows per block
         if (const char* e = std::getenv("CT_MESH_ROWS")) least = std::max(8, std::min(64, std::atoi(e)));
         bool ok = false;
-        for (int rows = least; rows <= kMeshRows && !ok; rows *= 2)
+        int planned = 0;
+        for (int rows = least; rows <= kMeshRows && !ok; rows *= 2) {
             ok = plan_mesh_batch(L, BP, o, rows, rows < 32 ? 4 : 1, H0.mtab, H0.mblk, minfo);
+            planned = rows;
+        }
+        // Problems that all fit one block exchange nothing (k_mesh_batch_local), unless they are
+        // few enough for 8 rows a block and large enough to gain from it: d = 3, 40 iterations,
+        // one block / 8 rows: 3 problems of 100 x 128 with values 261 us / 247, 2 of 100 x 100
+        // 251 / 246, without values 201 / 224; 20 of 20 x 20 199 / 246.
+        double most = 0.0;
+        for (const BProb& Q : BP)
+            most = std::max(most, 2.0 * Q.T * Q.M + (debias ? (double)Q.T * Q.T : 0.0) +
+                                      (need_ref ? (double)Q.M * Q.M : 0.0));
+        const bool small = std::all_of(BP.begin(), BP.end(), [](const BProb& Q) {
+            return std::max(Q.T, Q.M) <= kMeshLocalRows;
+        });
+        if (ok && small && !std::getenv("CT_MESH_ROWS") && !(planned == 8 && most > kMeshLocalPairs))
+            ok = plan_mesh_batch(L, BP, o, kMeshLocalRows, 1, H0.mtab, H0.mblk, minfo);
         if (!ok) {
             minfo = MeshInfo{0, 0, 0.0, o->eps};
             if (o->flags & CT_MESH)
@@ -1201,12 +1220,14 @@ extern "C" ct_status ct_sinkhorn_grad_batched(int32_t B, const int64_t* To, cons
         const bool safe_only = o->flags & CT_SAFE_LSE;
         if (minfo.blocks > 0) {
             // the K iterations of every problem in one launch of the exchange solve
-            const int64_t nw = 4 * (S.sumT + S.sumM);
-            hipLaunchKernelGGL(k_bfill_ones64, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, st,
-                               L.xch, nw);
-            CT_CHECK_HIP(hipGetLastError());
-            CT_CHECK_HIP(launch_mesh_batch(o->d, L.mtab, L.mblk, B, minfo.lds, minfo.blocks,
-                                           minfo.pairs, st));
+            if (!minfo.local) {
+                const int64_t nw = 4 * (S.sumT + S.sumM);
+                hipLaunchKernelGGL(k_bfill_ones64, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0,
+                                   st, L.xch, nw);
+                CT_CHECK_HIP(hipGetLastError());
+            }
+            CT_CHECK_HIP(launch_mesh_batch(o->d, L.mtab, L.mblk, B, minfo.local, minfo.lds,
+                                           minfo.blocks, minfo.pairs, st));
         }
         void* tok = profile_begin(st);
         for (int k = 0; k < (minfo.blocks > 0 ? 0 : o->iters); ++k) {

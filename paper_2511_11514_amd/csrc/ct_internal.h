@@ -278,8 +278,9 @@ int mesh_resident_blocks(int d, size_t lds_bytes, const MeshArgs* one);
 hipError_t launch_mesh(int d, const MeshArgs& A, size_t lds_bytes, int blocks, hipStream_t s);
 // All problems of a batch in one launch: tab[p] (device) holds problem p's
 // arguments, blk_end[p] (device) the end of its blocks; lds_bytes is the largest
-// problem's dynamic LDS.
-hipError_t launch_mesh_batch(int d, const MeshArgs* tab, const int* blk_end, int nprob,
+// problem's dynamic LDS.  local: every problem is planned as one block (kMeshLocalRows), which
+// takes less than the 64 KB of LDS that need no attribute.
+hipError_t launch_mesh_batch(int d, const MeshArgs* tab, const int* blk_end, int nprob, bool local,
                              size_t lds_bytes, int blocks, double pairs, hipStream_t s);
 
 // Per-launch event timing (ct_profile_enable); no-ops when disabled.

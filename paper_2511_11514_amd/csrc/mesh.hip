@@ -523,6 +523,15 @@ __global__ __launch_bounds__(kMeshBatchThreads, 4) void k_mesh_batch(const MeshA
     mesh_solve<D, kMeshBatchThreads, false>(sA, bid - start);
 }
 
+// A batch of problems of one block each: the one-block form, problem blockIdx.x.  (Exchanging
+// with itself through device memory such a batch took longer than in blocks of 1024 threads: 250
+// problems of 64 x 64 with values, 40 iterations, 314 us against 276; in this form 258.)
+template <int D>
+__global__ __launch_bounds__(kMeshBatchThreads, 2) void k_mesh_batch_local(const MeshArgs* __restrict__ tab) {
+    const MeshArgs A = tab[blockIdx.x];
+    mesh_solve<D, kMeshBatchThreads, true>(A, 0);
+}
+
 }  // namespace
 
 bool mesh_plan(int T, int M, int d, bool debias, bool ref_iter, size_t lds_cap, bool allow_single,
@@ -679,22 +688,21 @@ hipError_t launch_mesh(int d, const MeshArgs& A, size_t lds_bytes, int blocks, h
     return e;
 }
 
-hipError_t launch_mesh_batch(int d, const MeshArgs* tab, const int* blk_end, int nprob,
+hipError_t launch_mesh_batch(int d, const MeshArgs* tab, const int* blk_end, int nprob, bool local,
                              size_t lds_bytes, int blocks, double pairs, hipStream_t s) {
     hipEvent_t e0, e1;
     void* tok = profile_kernel_begin(&e0, &e1);
     {
         // set when the batch was planned (so not during a graph capture of the run)
-        const hipError_t e = ensure_dynamic_lds(mesh_kernel(d, kBatch), lds_bytes);
+        const hipError_t e = local ? hipSuccess : ensure_dynamic_lds(mesh_kernel(d, kBatch), lds_bytes);
         if (e != hipSuccess) return e;
     }
-    if (d == 2) {
-        if (e0) hipExtLaunchKernelGGL((k_mesh_batch<2>), dim3(blocks), dim3(kMeshBatchThreads), lds_bytes, s, e0, e1, 0, tab, blk_end, nprob);
-        else hipLaunchKernelGGL((k_mesh_batch<2>), dim3(blocks), dim3(kMeshBatchThreads), lds_bytes, s, tab, blk_end, nprob);
-    } else {
-        if (e0) hipExtLaunchKernelGGL((k_mesh_batch<3>), dim3(blocks), dim3(kMeshBatchThreads), lds_bytes, s, e0, e1, 0, tab, blk_end, nprob);
-        else hipLaunchKernelGGL((k_mesh_batch<3>), dim3(blocks), dim3(kMeshBatchThreads), lds_bytes, s, tab, blk_end, nprob);
-    }
+    auto go = [&](auto kernel, auto... args) {
+        if (e0) hipExtLaunchKernelGGL(kernel, dim3(blocks), dim3(kMeshBatchThreads), lds_bytes, s, e0, e1, 0, args...);
+        else hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kMeshBatchThreads), lds_bytes, s, args...);
+    };
+    if (local) d == 2 ? go(k_mesh_batch_local<2>, tab) : go(k_mesh_batch_local<3>, tab);
+    else d == 2 ? go(k_mesh_batch<2>, tab, blk_end, nprob) : go(k_mesh_batch<3>, tab, blk_end, nprob);
     const hipError_t e = hipGetLastError();
     // kind 42: the exchange solve of a whole batch in one launch
     profile_kernel_end(tok, 42, 0, 0, blocks, pairs);
