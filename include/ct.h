@@ -115,7 +115,8 @@ const char* ct_version(void);
                            fit in one workgroup's LDS).  Without any of CT_FUSED,
                            CT_UNFUSED, CT_TINY and CT_MESH (at most one may be given) the
                            library picks, by the point pairs of one iteration: the
-                           exchange solve where T and M are at most 128 and one is above 16,
+                           exchange solve where T and M are at most 128 and one is above 20
+                           (above 64 where the reference's self problem is solved too),
                            the one-workgroup solve up to 4e4, the exchange solve up to 1.5e7
                            where it plans, else the one-workgroup solve up to 1.5e5, the fused
                            solve up to 1.05e6, and per-sweep launches beyond.  Above 1e8

@@ -825,16 +825,18 @@ static ct_status run_tiny(const SkLayout& L, const SkConsts& c, const ct_sinkhor
 // in LDS; see mesh.hip and mesh_choose).  By default it is taken when it plans (every
 // point in one block's LDS, all blocks resident at once) and one iteration has at most
 // kMeshAutoPairs point pairs and more than kMeshMinPairs, or both sides fit its
-// one-block form and one has more than kMeshMinPoints points: elsewhere the one-workgroup
+// one-block form and one has more than kMeshMinPoints points (kMeshMinPointsRef where the
+// reference is solved too): elsewhere the one-workgroup
 // solve is as fast or faster (130 x 20 points: 490 us against 531; 20 x 400: 516 / 591;
 // 130 x 60: 518 / 515).  Measured on an MI355X, K = 100, d = 3, T = M, whole call (exchange /
-// one-workgroup): T = 10: 272 / 265 us; 30: 272 / 311; 64: 300 / 324; 100: 372 / 522;
-// 128: 408 / 536; 180: 534 / 739; cached reference (exchange / fused / per-sweep
+// one-workgroup), without a reference solve: T = 17: 295 / 289 us; 24: 295 / 302; 40: 329 /
+// 341; 64: 327 / 346; 72: 354 / 479; with it: 17: 379 / 304; 40: 424 / 371; 64: 418 / 381; 66:
+// 435 / 515; 20 x 65: 398 / 410; cached reference (exchange / fused / per-sweep
 // launches): T = 300: 0.60 / 1.87 / 2.26 ms; 500: 0.64 / 2.63 / 2.66; 1000: 0.9 / 7.0 /
 // 2.70; 2000: 1.3 / 23.5 / 3.13.  CT_MESH forces it (CT_E_UNSUPPORTED when it cannot
 // plan); CT_FUSED, CT_UNFUSED and CT_TINY rule it out.
 constexpr double kMeshMinPairs = 40000.0;
-constexpr int kMeshMinPoints = 16;
+constexpr int kMeshMinPoints = 20, kMeshMinPointsRef = 64;
 constexpr unsigned kMeshWaitPolls = 1u << 18;
 
 static ct_status run_mesh(const SkLayout& L, const SkConsts& c, const ct_sinkhorn_opts* o,
@@ -847,7 +849,8 @@ static ct_status run_mesh(const SkLayout& L, const SkConsts& c, const ct_sinkhor
                          (ref_iter ? (double)M * M : 0.0);
     if (!forced && (pairs > kMeshAutoPairs ||
                     (pairs <= kMeshMinPairs && (std::max(T, M) > kMeshLocalRows ||
-                                                std::max(T, M) <= kMeshMinPoints))))
+                                                std::max(T, M) <= (ref_iter ? kMeshMinPointsRef
+                                                                            : kMeshMinPoints)))))
         return CT_OK;
     MeshArgs A;
     size_t lds = 0;
