@@ -41,6 +41,22 @@ struct SteinCells {
     long long room;        // floats of mom: more cells or chunks than fit sum directly
 };
 
+// Times of both forms in us, fitted at 65536 points (direct 1085, values 27.4 and moments 33.4
+// with 60 cells): a spread of points over very many cells stays direct.
+struct SteinTimes {
+    float cell, direct;
+};
+__host__ __device__ inline SteinTimes stein_times(int n, int cells, int chunks, int tiles) {
+    return SteinTimes{4.6e-4f * (float)tiles * (float)cells +
+                          2.5e-4f * (float)(n + 128 * chunks) * (float)((cells + 31) / 32) + 50.f,
+                      2.5e-7f * (float)n * (float)n};
+}
+// Whether a flow is offered the form; the points then decide on the device.  The median
+// bandwidth gives them some ten cells per axis; for a given bandwidth h the host takes points that
+// spread over a unit box, the domain of the library: where those have too many cells, the
+// partition would be made in vain (h = 1e-4: 32768 points 319 us against 284 direct, 65536 points
+// 1013 against 976).
+bool stein_cells_offered(int T, float h);
 // Lays out the arrays after a flow's own (a no-op for sizes that the form does not take).
 bool stein_cells_for(int T, int d);
 // spare: a buffer of the median, no longer used when the sum runs: it holds the moments.

@@ -185,12 +185,9 @@ __global__ __launch_bounds__(kSteinIds) void k_st_lists(SteinCells S) {
     const int it = block_scan(nt, sh, &tt);
     const float lx = corner(box[0]), ly = corner(box[1]);
     const float ext = kSteinSide * (float)(1 << kSteinBits);
-    // Both forms' times in us, fitted at 65536 points (direct 1085, values 27.4 and moments 33.4
-    // with 60 cells): a spread of points over very many cells stays direct.
-    const float direct = 2.5e-7f * (float)S.n * (float)S.n;
-    const float cells = 4.6e-4f * (float)tt * (float)tc + 2.5e-4f * (float)(S.n + 128 * th) * (float)((tc + 31) / 32) + 50.f;
+    const SteinTimes t = stein_times(S.n, tc, th, tt);
     // every point in the cell of its code: nothing outside the coded box
-    const bool ok = box[4] == 0u && tc <= kSteinCells && th <= S.chmax && tt <= S.tmax && cells < direct &&
+    const bool ok = box[4] == 0u && tc <= kSteinCells && th <= S.chmax && tt <= S.tmax && t.cell < t.direct &&
                     (long long)(th + tc) * tc * kSteinMom <= S.room &&
                     from_ordered(box[2]) - lx < ext && from_ordered(box[3]) - ly < ext;
     if (id == 0) {
@@ -452,6 +449,18 @@ __global__ __launch_bounds__(256) void k_st_values(SteinCells S, const float* __
 }
 
 }  // namespace
+
+bool stein_cells_offered(int T, float h) {
+    if (h <= 0.f) return true;
+    const double side = std::sqrt(1.4426950408889634 / (double)h) / kSteinSide;
+    const double cells = (side + 0.5) * (side + 0.5);   // random walks lie in 0.96 of these
+    if (side > (1 << kSteinBits) || cells > kSteinCells) return false;
+    const int c = std::max(1, (int)cells), chunks = c + T / std::max(512, (T / 128 + 255) / 256 * 256);
+    const SteinTimes t = stein_times(T, c, chunks, c / 2 + T / kSteinTile);
+    // (the model is a fifth too kind to many cells of few points: 32768 points, h = 0.004, 225
+    // cells, 316 us against 283 direct)
+    return t.cell < 0.8f * t.direct;
+}
 
 bool stein_cells_for(int T, int d) { return d == 2 && T >= kSteinCellMinT && T <= kSteinCellMaxT; }
 

@@ -1421,6 +1421,7 @@ ct_status svgd_check(const float* x, int64_t T64, int32_t d, float h, float* phi
 // Bandwidth, staging and the T x T sum for a score already in device memory.
 ct_status svgd_flow(const float* x, int T, int d, const float* score, float h, float* phi,
                     float* h_used, const SvLayout& L, hipStream_t st) {
+    const bool cells = L.cells && stein_cells_offered(T, h);
     const bool median = h <= 0.f && T > 1;
     hipLaunchKernelGGL(k_sv_prep, dim3(kSvOriginBlocks), dim3(256), 0, st, x, T, d, L.origin,
                        median ? L.cmed : nullptr, L.st, L.sst, L.hist);
@@ -1501,9 +1502,9 @@ ct_status svgd_flow(const float* x, int T, int d, const float* score, float h, f
     hipLaunchKernelGGL(k_svgd_stage, dim3((Tpad + 255) / 256), dim3(256), 0, st, x, score, T, Tpad,
                        d, h > 0.f ? h : 0.f, L.st, L.origin, L.qc, L.krec);
     CT_CHECK_HIP(hipGetLastError());
-    if (L.cells) CT_CHECK_HIP(launch_stein_cells(L.sc, L.krec, &L.st->h, phi, h_used, st));
+    if (cells) CT_CHECK_HIP(launch_stein_cells(L.sc, L.krec, &L.st->h, phi, h_used, st));
     SvgdJob J;
-    J.cells = L.cells ? L.sc.cnt + 3 : nullptr;
+    J.cells = cells ? L.sc.cnt + 3 : nullptr;
     J.qc = L.qc;
     J.krec = L.krec;
     J.T = T;
