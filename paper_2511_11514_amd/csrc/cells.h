@@ -35,15 +35,23 @@ struct CellDim<2> {
     static constexpr int N = 64;     // products kept
     static constexpr int F = 9;      // one-dimensional functions n = 0..8
     static constexpr int bits = 5;   // cells per axis: at most 2^bits
-    static constexpr double lambda = 1.0;
+    static constexpr double side = 435.0 / 256;
+    static constexpr double lambda = 1.00067730;
 };
 template <>
 struct CellDim<3> {
     static constexpr int N = 192;
     static constexpr int F = 8;
     static constexpr int bits = 4;
-    static constexpr double lambda = 0.46;
+    static constexpr double side = 295.0 / 256;
+    static constexpr double lambda = 0.46021373;
 };
+template <int D>
+constexpr bool lambda_is_of_side() {
+    const double e = CellDim<D>::lambda - 0.34657359027997264 * CellDim<D>::side * CellDim<D>::side;
+    return e < 1e-7 && e > -1e-7;
+}
+static_assert(lambda_is_of_side<2>() && lambda_is_of_side<3>(), "lambda = ln2 w^2 / 2");
 constexpr int kCellIds = 4096;       // most cell codes of either dimension (1024 in 2-D)
 constexpr int kCellTile = 32;        // queries per evaluation tile, cells per moment tile
 constexpr int kCellChunkMax = 1024;  // most keys of one chunk
@@ -111,8 +119,8 @@ struct CellLaunch {
     float inv_cell;        // 1 / w
 };
 
-// Side of a cell in scaled coordinates: lambda = ln2 w^2 / 2.
-double cell_side(int d);
+// Side w of a cell in scaled coordinates.
+inline double cell_side(int d) { return d == 2 ? CellDim<2>::side : CellDim<3>::side; }
 
 // What a sweep's time in the cell form depends on, of one point set.
 struct CellCounts {

@@ -38,7 +38,7 @@ def _grad64(x, y, eps, iters):
     return 2.0 / len(x) * (_offsets(x, x, la + p / eps, pp, eps) - _offsets(x, y, lb + g / eps, fp, eps))
 
 
-@pytest.mark.parametrize("eps", [0.005])
+@pytest.mark.parametrize("eps", [0.005, 0.02])
 def test_batch_errors_no_larger_than_the_direct_sweeps(ct, monkeypatch, eps):
     monkeypatch.setenv("CT_CELL_MIN_PAIRS", "1.5e7")   # these sizes take the form
     rng = np.random.default_rng(41)
