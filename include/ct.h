@@ -124,7 +124,7 @@ const char* ct_version(void);
                            pairs in all on, those launches take the cell form of a sweep
                            where it pays (a grid of cells over each point set, sums
                            over pairs of cells by truncated expansions that leave out less
-                           than 1e-7 of any pair's term; offered where eps gives a unit box
+                           than 1.4e-7 of any pair's term (2.2e-8 in 3-D); offered where eps gives a unit box
                            few enough cells for the points, then decided on the device), unless
                            CT_UNFUSED, CT_DIFFERENCE or CT_SAFE_LSE is given or the
                            workspace lacks its arrays. */
@@ -339,7 +339,7 @@ typedef struct ct_gmm {
  * candidates): 245 MB in all at T = 65536 (d = 3), 458 MB at T = 92681.  For d = 2 and 32768 <=
  * T <= 92681 also some 45 bytes per point for the cell form of the sum, whose moments take the
  * candidates' place (sums over pairs of grid cells by truncated expansions that leave out less
- * than 1e-8 of any pair's term; taken where it pays, decided on the device, for a given
+ * than 1.2e-8 of any pair's term; taken where it pays, decided on the device, for a given
  * bandwidth where a unit box has few cells for it); a smaller
  * workspace that holds the rest is accepted and sums directly. */
 size_t ct_svgd_workspace_size(int64_t T, int32_t d);

@@ -10,8 +10,9 @@
 //     e^(lambda s u) = I_0(lambda s) + 2 sum_n I_n(lambda s) T_n(u)
 // (T_n Chebyshev polynomials, I_n modified Bessel functions).  The products over the
 // axes with the largest coefficients, 64 of them in 2-D at lambda = 1 and 192 in 3-D at
-// lambda = 0.46, leave out terms that add up to less than 9e-8 of the factor's largest
-// possible value, whatever the points: the rounding of float32.  A sweep becomes
+// lambda = 0.46, leave out terms that add up to less than 9e-8, whatever the points: of the
+// factor, which is smallest at opposite corners of the cells, at most 1.4e-7 (2.2e-8 in 3-D),
+// about the rounding of float32.  A sweep becomes
 //     moments   M[a][c][n] = sum_{j in c} 2^(h_j - |u_j|^2 + 2 d.u_j - mu_ac) T_n(u_j)
 //     values    sum_c 2^(mu_ac - |d|^2 - 2 d.s_i - |s_i|^2 - sh_i) sum_n phi_n(s_i) M[a][c][n]
 // for every pair (a, c) of query and key cell, two matrix products of float32 in the
@@ -20,8 +21,8 @@
 // the potentials vary.  Per point and cell it costs 64 (192) multiply-adds; per point
 // pair the direct sweep costs 5 (6) instructions, one of them an exponential.  Measured on
 // an MI355X, d = 2, T = 65536, M = 262144, eps = 0.002, 200 iterations: 1142 ms with direct
-// sweeps (94 % of their issue roof), 84.3 ms in this form; T = 4096, M = 16384, eps = 0.005,
-// 200 iterations: 16.0 against 8.9 ms.
+// sweeps (94 % of their issue roof), 83 to 84 ms in this form; T = 4096, M = 16384, eps = 0.005,
+// 200 iterations: 16.0 against 8.7 to 9.4 ms, by the points' spread.
 #pragma once
 
 #include "ct_internal.h"
@@ -177,8 +178,9 @@ struct CellLimits {
     // Pairs of all iterations below which splitting the points (0.1 ms) costs more than it
     // saves: 40 iterations at T = 3174, M = 12915 (3.7e9 pairs) 1.69 against 1.54 ms.
     double work = 1e10;
-    // Pairs of a 3-D sweep below which it stays direct: cells of so few points are too sparse
-    // to pay (40 iterations at T = 16355, M = 22674 lose 2 %, at T = 10246, M = 35898 win 26 %).
+    // Pairs of a 3-D sweep below which it stays direct, from whole calls at eps = 0.01 (40
+    // iterations at T = 16355, M = 22674 lose 2 %, at T = 10246, M = 35898 win 26 %).  The points
+    // per cell would be the truer rule; the model that knows them is fitted to larger sweeps.
     double pairs3 = 1.2e9;
     bool expect = true;   // ask CellOffer
 };

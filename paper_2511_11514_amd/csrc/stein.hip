@@ -8,7 +8,7 @@
 // holds exactly, and on each axis, in units of half a cell, 2^(2 s u) is e^(lambda s u) with
 // lambda = ln2 w^2 / 2 = 0.597, expanded as in the cell form of the soft-min sweep:
 // I_0(lambda s) + 2 sum_n I_n(lambda s) T_n(u).  Eight functions per axis leave out
-// 2 I_8(lambda) < 4e-9.  The moments of a cell's keys, for query cell a,
+// 2 I_8(lambda) < 4e-9 per axis, of a pair's term at most 1.2e-8 (at opposite corners).  The moments of a cell's keys, for query cell a,
 //     M[a][c][r][n] = sum_{j in c} 2^(2 d.u - |u|^2) v_rj T_nx(u_x) T_ny(u_y)
 // with v = (1, score_x - cb u_x, score_y - cb u_y), are a product of two matrices over the keys
 // (float32 in the matrix cores, v_mfma_f32_32x32x2); a query then costs 192 multiply-adds per
