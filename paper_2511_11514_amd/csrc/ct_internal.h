@@ -266,7 +266,7 @@ bool mesh_plan(int T, int M, int d, bool debias, bool ref_iter, size_t lds_cap, 
 // the solves of four hardware queues stay resident side by side), two 512-thread blocks to a
 // compute unit where LDS allows; from 32 rows on 1024 threads; kMeshRows rows otherwise.
 // Measured on an MI355X, us per iteration with 8 / 16 / 32 / 64 rows (and one block), cached
-// reference: d = 3, T = M = 100: 4.9 / 5.1 / 4.8 / 5.1 (3.8); 300: 5.3 / 5.4 / 6.0 / 7.1; 500:
+// reference: d = 3, T = M = 100: 4.9 / 5.1 / 4.8 / 5.1 (3.5); 300: 5.3 / 5.4 / 6.0 / 7.1; 500:
 // 5.6 / 5.9 / 6.8 / 8.9; 2000 (1024 threads): 8.8 / 10.7 / 14.9 / 23.4; before rows were swept
 // two per thread over key subsets and self sweeps ran during the exchanges, with 64 rows:
 // 4.9 (one-workgroup solve), 7.9, 10.0 and 24.9.

@@ -26,7 +26,7 @@
 // by two waves that do not wait for each other.  That costs 0.06 us an iteration of 3.39 at
 // T = M = 100; two copies of the self records by the iteration's parity cost 0.65 (their
 // addresses are no longer the same in every iteration), one wave for all self rows 0.27.  Measured, us per iteration (d = 3, cached reference; before: 64 rows
-// per block, one row per lane, f and p published together): T = M = 100 3.8 (4.9 in
+// per block, one row per lane, f and p published together): T = M = 100 3.5 (4.9 in
 // the one-workgroup solve), 300 5.3 (7.9), 500 5.6 (10.0), 1000 8.0 (14.5), 2000 12.1
 // (24.9).  Launching a block per compute unit at 1024 threads (no two resident) was
 // 0.3 us faster at 8 rows, but leaves room for one solve less on each hardware queue.
