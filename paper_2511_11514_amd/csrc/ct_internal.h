@@ -118,7 +118,7 @@ struct TabLaunch {
     const int* mrg_end;
     int njobs;
     int nblocks, nmerge;
-    const struct CellJob* cell; // not null: jobs whose cell form is on (cells.h) leave at once
+    const struct CellJob* cell; // not null (d = 3): jobs whose cell form is on leave at once
     int expanded;          // 1: lagged sweeps without offsets use the expanded pair form
     float kappa, inv_kappa, inv_sqrt_kappa;
 };
